@@ -138,7 +138,7 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
                     for (int reduce : {DFK_REDUCE_ATOMIC, DFK_REDUCE_TICKET})
                         push(make_cfg(DFK_VARIANT_FUSED, DFK_PATH_MFMA, clamp_splits(splits, d_ff), waves,
                                       depth, 0, 0, a2dt, reduce));
-        const int nblk = d_model / 128;
+        const int nblk = (d_model + 127) / 128;   // (a partial last column block: the 64-token pair in bf16 only)
         // the single launch on the k-major stage one of the 64-token pair (a slice of at most 64 rows per workgroup)
         for (int splits : {256, 512, d_ff > 512 * 64 ? ((d_ff + 63) / 64 + 255) / 256 * 256 : 512})
             for (int reduce : {DFK_REDUCE_ATOMIC, DFK_REDUCE_TICKET})
@@ -692,7 +692,7 @@ dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const 
     auto carries = [&](const dfk_config_t& k) {
         if (wd_t) return k.path == DFK_PATH_MFMA && k.kmajor == 5 && mfma_km_t_config_valid(k, M, d_model, d_ff, dtype);
         return k.path == DFK_PATH_MFMA &&
-               ((k.kmajor == 1 && mfma_km_config_valid(k, M, d_model, d_ff, dtype)) ||
+               ((k.kmajor == 1 && d_model % 128 == 0 && mfma_km_config_valid(k, M, d_model, d_ff, dtype)) ||
                 (k.kmajor == 2 && mfma_big_config_valid(k, M, d_model, d_ff, dtype)));
     };
     dfk_config_t c;

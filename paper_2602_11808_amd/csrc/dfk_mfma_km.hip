@@ -68,13 +68,18 @@ __host__ __device__ inline int km_norm_stride(int d_model, int waves) {
 }
 
 // ---------------------------------------------------------------- gate/up kernel
-template <int NW, int TT>
+// TAIL: the rows' length is no whole number of chunks (kdim any multiple of 8).  The last chunk's 16-byte pieces past
+// the row's end are fetched from its last 16 bytes instead and the operands zeroed at use.  A form of its own,
+// because the clamps cost a few VALU instructions per tile: with it a 2888 x 7688 layer takes the matrix cores, 428 ->
+// 43 us at 12 tokens in bf16 against the plain-FMA pair, which re-reads X for every weight row.
+template <int NW, int TT, bool TAIL>
 struct KmStream1 {
     const char *Wg, *Wu, *X;
     size_t row_bytes;          // d_model * 2
     size_t w_base;             // byte offset of (row j0, this wavefront's first k)
     size_t x_base;             // byte offset of (token m_base, this wavefront's first k)
     int nt, nkc, m_count;
+    unsigned k_last;           // TAIL: byte offset from this wavefront's first k to the row's last 16 bytes
     int tile_rows;             // weight rows between consecutive row tiles (8: gate and up rows side by side; 16: one matrix)
     int q, g;
     unsigned off1[4];
@@ -89,8 +94,19 @@ struct KmStream1 {
             for (int u = 0; u < 4; ++u) {
                 const int i = 4 * u + g;
                 const int token = min(p_idx * 16 + i, m_count - 1);
-                const char* src = X + x_base + (size_t)token * row_bytes + (size_t)p_kc * (kKC * 2) + ((q ^ i) * 16);
+                unsigned ko = (unsigned)p_kc * (kKC * 2) + (q ^ i) * 16;
+                if (TAIL) ko = min(ko, k_last);
+                const char* src = X + x_base + (size_t)token * row_bytes + ko;
                 __builtin_amdgcn_global_load_lds(src, DFK_LDS_PTR(slot + u * 1024), 16, 0, 0);
+            }
+        } else if (TAIL) {     // (below, with the offset into the row clamped)
+            const size_t tb = w_base + (size_t)(p_idx - TT) * tile_rows * row_bytes;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = 4 * u + g;
+                const unsigned ko = min((unsigned)p_kc * (kKC * 2) + (q ^ i) * 16, k_last);
+                __builtin_amdgcn_global_load_lds((u < 2 ? Wg : Wu) + tb + (size_t)(i & 7) * row_bytes + ko, DFK_LDS_PTR(slot + u * 1024), 16, 0,
+                                                 kAuxNonTemporal);
             }
         } else {               // weight tile of row tile p_idx - TT: 8 rows of W_gate, the same 8 of W_up
             const size_t tb = w_base + (size_t)(p_idx - TT) * tile_rows * row_bytes + (size_t)p_kc * (kKC * 2);
@@ -146,7 +162,7 @@ struct KmStream1 {
 // (a linear layer's own [out, in] layout): Y^T = W_down^T A_2^T has the shape of stage one, with d_ff as the k
 // range, a row tile = 16 rows of one matrix, A_2 in X's place, and workgroup s owning a slice of d_model whole:
 // nothing is summed across workgroups, the end just adds the wavefronts' k-partial sums and stores Y.
-template <int NW, int TT, typename E, bool NORM, bool PUBLISH, bool DOWN_T = false>
+template <int NW, int TT, typename E, bool NORM, bool PUBLISH, bool DOWN_T = false, bool TAIL = false>
 __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds) {
     constexpr int TOK = 16 * TT;
     constexpr int NTHREADS = NW * 64;
@@ -167,11 +183,12 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     // The 128-k chunks of a row are dealt out to the wavefronts in contiguous runs, as evenly as
     // their number allows (equal runs when the k range is a multiple of 128 * NW).
     const int kdim = DOWN_T ? a.d_ff : a.d_model;
-    const int nchunks = kdim / kKC;
+    static_assert(!TAIL || (!NORM && !DOWN_T), "a partial last chunk is built for the plain gate/up kernel");
+    const int nchunks = TAIL ? (kdim + kKC - 1) / kKC : kdim / kKC;
     const int c0 = wave * nchunks / NW, c1 = (wave + 1) * nchunks / NW;
     const size_t kbase = (size_t)c0 * (kKC * 2);          // bytes into a row
 
-    KmStream1<NW, TT> ts;
+    KmStream1<NW, TT, TAIL> ts;
     ts.row_bytes = (size_t)kdim * 2;
     if (DOWN_T) {
         ts.Wg = (const char*)a.Wd; ts.Wu = (const char*)a.Wd + 8 * ts.row_bytes; ts.X = (const char*)a.a2;
@@ -184,6 +201,7 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     ts.x_base = (size_t)a.m_base * ts.row_bytes + kbase;
     ts.nt = nt; ts.nkc = c1 - c0; ts.m_count = a.m_count;
     ts.q = q; ts.g = g;
+    ts.k_last = (unsigned)(ts.row_bytes - 16 - kbase);
     ts.ring = lds + wave * geo.depth * kTileBytes;
     ts.depth = geo.depth;
     DFK_STAMP(DOWN_T ? 3 : 0);
@@ -212,12 +230,20 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     for (int kc = 0; kc < ts.nkc; ++kc) {
+        // TAIL: this lane's k groups 4c + g of the chunk that hold real k (both operands of the others are zeroed: a
+        // weight that is not finite must not meet a zero)
+        const int kgroups = TAIL ? (kdim - (c0 + kc) * kKC) >> 3 : 16;
         u32x4 xk[TT][4];       // B operand of this chunk: token q of each token tile, k group g of step c
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
             const unsigned char* slot = ts.acquire();
 #pragma unroll
             for (int c = 0; c < 4; ++c) xk[tt][c] = *(const u32x4*)(slot + (q * 16 + ((4 * c + g) ^ q)) * 16);
+            if (TAIL && kgroups < 16) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (4 * c + g >= kgroups) xk[tt][c] = u32x4{0, 0, 0, 0};
+            }
             if (NORM) {   // one token tile at a time, the weight re-read from LDS: few registers live
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
@@ -245,7 +271,8 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
                 const unsigned char* slot = ts.acquire();
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const u32x4 av = *(const u32x4*)(slot + (q * 16 + ((4 * c + g) ^ q)) * 16);
+                    u32x4 av = *(const u32x4*)(slot + (q * 16 + ((4 * c + g) ^ q)) * 16);
+                    if (TAIL && kgroups < 16 && 4 * c + g >= kgroups) av = u32x4{0, 0, 0, 0};
 #pragma unroll
                     for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma16<E>(av, xk[tt][c], acc[rt][tt]);
                 }
@@ -342,10 +369,10 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     }
 }
 
-template <int NW, int TT, typename E, bool NORM>
+template <int NW, int TT, typename E, bool NORM, bool TAIL = false>
 __global__ __launch_bounds__(NW * 64) void k_gateup_km(MlpArgs a, KmGeom geo) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    gateup_km_body<NW, TT, E, NORM, false>(a, geo, blockIdx.x, lds);
+    gateup_km_body<NW, TT, E, NORM, false, false, TAIL>(a, geo, blockIdx.x, lds);
 }
 
 // Down projection from W_down given as [d_model, d_ff]: k2_splits workgroups, a slice of d_model each.
@@ -356,7 +383,9 @@ __global__ __launch_bounds__(NW * 64) void k_down_t_km(MlpArgs a, KmGeom geo) {
 }
 
 // ---------------------------------------------------------------- down kernel
-template <int NW, int TT>
+// TAIL: d_model is no multiple of 128 (any multiple of 8).  The last column block's 16-byte pieces past the row's end
+// are fetched from its last 16 bytes: columns are independent of each other, and those are never stored.
+template <int NW, int TT, bool TAIL>
 struct KmStream2 {
     // A_2 travels in tiles of 64 d_ff rows x 32 tokens: per token 128 contiguous bytes, one whole cache line per
     // request (a 32-row tile would be 64-byte pieces, twice the requests for the same bytes).  One tile serves
@@ -401,7 +430,14 @@ struct KmStream2 {
             const int b = wj >> 1, h = wj & 1;
             const int row0 = j0 + jb * 32 + 4 * h;           // lane adds 8g + u
             const size_t colb = (size_t)(blk_first + b) * 256;
-            if (row0 + 28 <= d_ff) {
+            if (TAIL) {
+                const size_t co = min(colb + 16 * q, row_bytes - 16);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int row = min(row0 + 8 * g + u, d_ff - 1);
+                    __builtin_amdgcn_global_load_lds(Wd + (size_t)row * row_bytes + co, DFK_LDS_PTR(slot + u * 1024), 16, 0, kAuxNonTemporal);
+                }
+            } else if (row0 + 28 <= d_ff) {
                 const char* base = Wd + (size_t)row0 * row_bytes + colb;
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
@@ -453,7 +489,7 @@ __host__ __device__ constexpr int km_col_blocks(int tt) { return tt >= 3 ? 1 : 2
 // WAIT (the single launch of both kernels' workgroups): the stream carries the A tile of a 32-row block behind the
 // first column block's weight tiles and starts with those alone; then the workgroup waits until every gate/up
 // workgroup has counted itself done, drops what its caches hold of A_2's lines, and goes on as the kernel does.
-template <int NW, int TT, typename E, bool WAIT>
+template <int NW, int TT, typename E, bool WAIT, bool TAIL = false>
 __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds) {
     __shared__ int flag;
     constexpr int NTHREADS = NW * 64;
@@ -467,13 +503,13 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
     int j0, j1;
     slice_rows(a.d_ff, a.k2_splits, js, j0, j1);
     const int rows = j1 - j0;
-    const int CB = a.d_model / 128 / a.k2_col_blocks;      // <= CBM, checked on the host
+    const int CB = (TAIL ? (a.d_model + 127) / 128 : a.d_model / 128) / a.k2_col_blocks;      // <= CBM, checked on the host
     const int blk_lo = cb * CB;
     const int njb_all = (rows + 31) / 32;
     const int jb_lo = (int)((long long)njb_all * wave / NW);
     const int njb = (int)((long long)njb_all * (wave + 1) / NW) - jb_lo;
 
-    KmStream2<NW, TT> ts;
+    KmStream2<NW, TT, TAIL> ts;
     ts.Wd = (const char*)a.Wd; ts.A2 = (const char*)a.a2;
     ts.row_bytes = (size_t)a.d_model * 2;
     ts.a2_row_bytes = (size_t)a.d_ff * 2;
@@ -535,7 +571,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
         u32x4 av[2][TT];       // A operands of the pair's two blocks: A_2[token q of tile tt][rows 8g .. 8g+7 of the block]
         auto take_a = [&]() {
 #pragma unroll
-            for (int half = 0; half < KmStream2<NW, TT>::NA; ++half) {
+            for (int half = 0; half < KmStream2<NW, TT, TAIL>::NA; ++half) {
                 const unsigned char* slot = ts.acquire();
 #pragma unroll
                 for (int t2 = 0; t2 < 2; ++t2) {
@@ -651,7 +687,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
                             float v = 0.f;
 #pragma unroll
                             for (int w = 0; w < NW; ++w) v += stage[w * 16 * 128 + idx];
-                            acc_add(a.yacc + (size_t)(tt * 16 + (idx >> 7)) * a.d_model + nb + (idx & 127), v);
+                            if (!TAIL || nb + (idx & 127) < a.d_model) acc_add(a.yacc + (size_t)(tt * 16 + (idx >> 7)) * a.d_model + nb + (idx & 127), v);
                         }
                     } else {
                         for (int idx = tid; idx < mt * 32; idx += NTHREADS) {
@@ -659,7 +695,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
 #pragma unroll
                             for (int w = 0; w < NW; ++w) v += *(const f32x4*)(stage + w * 16 * 128 + 4 * idx);
                             const int m = tt * 16 + (idx >> 5), c4 = idx & 31;
-                            store4_device(a.P + ((size_t)js * a.m_count + m) * a.d_model + nb + 4 * c4, v[0], v[1], v[2], v[3]);
+                            if (!TAIL || nb + 4 * c4 < a.d_model) store4_device(a.P + ((size_t)js * a.m_count + m) * a.d_model + nb + 4 * c4, v[0], v[1], v[2], v[3]);
                         }
                     }
                     __syncthreads();
@@ -667,7 +703,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
             }
         }
     }
-    const int width = CB * 128;
+    const int width = TAIL ? min(CB * 128, a.d_model - blk_lo * 128) : CB * 128;
     if (WAIT && geo.role_wait > 0 && tid == 0) {
         // every down workgroup is past its wait once the last one has said so: that one clears the counters for the next launch
         const unsigned n_down = (unsigned)(a.k2_splits * a.k2_col_blocks);
@@ -700,10 +736,10 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
     reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid);
 }
 
-template <int NW, int TT, typename E>
+template <int NW, int TT, typename E, bool TAIL = false>
 __global__ __launch_bounds__(NW * 64) void k_down_km(MlpArgs a, KmGeom geo) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    down_km_body<NW, TT, E, false>(a, geo, blockIdx.x, lds);
+    down_km_body<NW, TT, E, false, TAIL>(a, geo, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------- both kernels' workgroups in one launch
@@ -758,6 +794,27 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
     return std::max(ring, (size_t)geo->pass * per_tile);
 }
 
+// The pair for a d_model that is no multiple of 128 (bf16, plain block).
+template <int NW, int TT>
+hipError_t launch_km_tail(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    static LdsAllowance allowed1, allowed2;
+    if (a.norm_w || a.dtype != DFK_BF16 || c.kmajor != 1) return hipErrorInvalidValue;
+    KmGeom geo{};
+    if (g_stage_mask & 1) {
+        const size_t lds = km_lds_gateup(c, TT, a.d_model, a.d_ff, false, &geo);
+        if (hipError_t e = allow_lds(allowed1, (const void*)k_gateup_km<NW, TT, BF16, false, true>, lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_gateup_km<NW, TT, BF16, false, true>), dim3(a.splits), dim3(NW * 64), lds, st, a, geo);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    if (g_stage_mask & 2) {
+        const size_t lds = km_lds_down(c, &geo);
+        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NW, TT, BF16, true>, lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_down_km<NW, TT, BF16, true>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NW * 64), lds, st, a, geo);
+        return hipGetLastError();
+    }
+    return hipSuccess;
+}
+
 template <int NW, int TT, typename E>
 hipError_t launch_km_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     static LdsAllowance allowed1, allowed1n, allowed2;   // of the three kernels of this instantiation, per device
@@ -797,6 +854,7 @@ hipError_t launch_km_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st)
 
 template <int NW, int TT>
 hipError_t launch_km_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    if (a.d_model % kKC) return launch_km_tail<NW, TT>(a, c, st);
     return a.dtype == DFK_FP16 ? launch_km_te<NW, TT, FP16>(a, c, st) : launch_km_te<NW, TT, BF16>(a, c, st);
 }
 
@@ -839,12 +897,14 @@ bool mfma_km_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, d
     if (c.reduce != DFK_REDUCE_TICKET && c.reduce != DFK_REDUCE_ATOMIC) return false;
     if ((c.waves != 4 && c.waves != 8) || c.depth < 2 || c.depth > 16) return false;
     if (M < 1 || d_model < 8 || d_ff < 8 || d_ff % 8 || d_model > kMaxDModel) return false;
-    if (d_model % kKC || d_model / kKC < c.waves) return false;   // each wavefront owns whole 128-k chunks, at least one
+    // Each wavefront owns whole 128-k chunks, at least one.  A last chunk that is partly past the row's end is built for
+    // bf16 only: with half inputs the plain-FMA pair that such widths have keeps A_2 in fp32, this one would round it.
+    if (d_model % 8 || (d_model % kKC && dtype != DFK_BF16) || (d_model + kKC - 1) / kKC < c.waves) return false;
     const int ng = d_ff / 8;
     if (c.splits < 1 || c.splits > ng || c.splits > 65535) return false;
     if (max_slice_rows(d_ff, c.splits) / 8 > kKmMaxRowTiles) return false;   // accumulators of the row tiles
     if (c.k2_splits < 1 || c.k2_splits > ng) return false;
-    const int nblk = d_model / 128;
+    const int nblk = (d_model + 127) / 128;
     if (c.k2_col_blocks < 1 || nblk % c.k2_col_blocks) return false;
     if ((long long)c.k2_splits * c.k2_col_blocks > 65535 || c.k2_col_blocks > kTicketLevel2) return false;
     const int tokens = std::min(M, kKmTokensPerLaunch);
@@ -878,6 +938,7 @@ bool mfma_km_t_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff,
 // The pre-norm residual form runs on this kernel pair only; its gate/up kernel needs a
 // little more LDS (weight of the normalisation, sums of squares).
 bool mfma_km_block_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    if (d_model % kKC) return false;
     if (c.kmajor == 5 ? !mfma_km_t_config_valid(c, M, d_model, d_ff, dtype) : !mfma_km_config_valid(c, M, d_model, d_ff, dtype)) return false;
     KmGeom geo{};
     return km_lds_gateup(c, km_token_tiles(std::min(M, kKmTokensPerLaunch)), d_model, d_ff, true, &geo) <= (size_t)kLdsLimit;
@@ -887,7 +948,7 @@ bool mfma_km_block_config_valid(const dfk_config_t& c, int M, int d_model, int d
 // configuration, and a grid small enough that its 16-bit-safe index arithmetic holds.
 static dfk_config_t roles_as_pair(const dfk_config_t& c) { dfk_config_t p = c; p.variant = DFK_VARIANT_TWO_KERNEL; p.kmajor = 1; return p; }
 bool mfma_km_roles_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
-    if (c.variant != DFK_VARIANT_FUSED || c.kmajor != 4 || c.waves != 8) return false;
+    if (c.variant != DFK_VARIANT_FUSED || c.kmajor != 4 || c.waves != 8 || d_model % kKC) return false;
     if ((long long)c.splits + (long long)c.k2_splits * c.k2_col_blocks > 65535) return false;
     if (c.k2_splits > kRoleCountEnd - kRoleCount0) return false;   // one counter per d_ff split of the down projection
     return mfma_km_config_valid(roles_as_pair(c), M, d_model, d_ff, dtype);
