@@ -117,8 +117,8 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  2 = the pair that takes up to 256 tokens per launch (offered beyond 64
  *                  tokens, and at any token count where d_model rules out pair 1): the wavefronts
  *                  share every weight tile through LDS and own a share of the tokens each;
- *                  waves = 4 or 8 (wavefronts of the gate/up kernel; the down kernel always runs
- *                  8), depth = 3 or 4 (buffers of shared tiles), k2_col_blocks = d_model / 128;
+ *                  waves = 4 or 8, depth = 3 or 4 (both kernels run eight wavefronts and size their
+ *                  buffers themselves whatever these say), k2_col_blocks = d_model / 128;
  *                  with DFK_REDUCE_TICKET the splits' partial sums are added by a third, small
  *                  launch;
  *                  5 = gate/up kernel of pair 1, then a down kernel that takes W_down as
@@ -128,7 +128,7 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  is deterministic), up to 64 tokens per launch.  With path = DFK_PATH_VALU the
  *                  same pair in plain fp32 FMAs (any shape and type; k2_splits = workgroups of
  *                  the down kernel, whose wavefronts own output columns whole);
- *                  3 = gate/up kernel of pair 2 with four wavefronts of one token tile each,
+ *                  3 = gate/up kernel of pair 2 with one token tile per token group,
  *                  down kernel of pair 1 (offered for 33..64 tokens; waves = 8, depth = 3 or 4,
  *                  the constraints of both pairs).
  *                  fused variant:

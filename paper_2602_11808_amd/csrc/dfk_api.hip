@@ -214,11 +214,9 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             const int k2c = nblk;
             for (int splits : {256, 512, more_splits})
                 for (int grid : {256, 512})
-                    for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})
-                        for (int depth : {3, 4})
-                            for (int waves : {8, 4})   // of the gate/up kernel
-                                push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), waves, depth,
-                                              clamp_splits(std::max(1, grid / k2c), d_ff), k2c, (int)dtype, reduce, 0, 2));
+                    for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})   // (waves and depth no longer change its kernels)
+                        push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), 8, 3,
+                                      clamp_splits(std::max(1, grid / k2c), d_ff), k2c, (int)dtype, reduce, 0, 2));
         }
     }
     for (int splits : {256, 512, 1024})

@@ -773,9 +773,9 @@ hipError_t launch_nt(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
 
 }  // namespace
 
-// The mixed pair for 33..64 tokens (kmajor = 3): gate/up kernel with workgroup-shared weight tiles (four
-// wavefronts, one token tile each), down kernel of the 64-token pair.
-dfk_config_t mixed_gateup_cfg(const dfk_config_t& c) { dfk_config_t g = c; g.waves = 4; g.kmajor = 2; return g; }
+// The mixed pair for 33..64 tokens (kmajor = 3): gate/up kernel with workgroup-shared weight tiles (one
+// token tile per group), down kernel of the 64-token pair.
+dfk_config_t mixed_gateup_cfg(const dfk_config_t& c) { dfk_config_t g = c; g.kmajor = 2; return g; }
 dfk_config_t mixed_down_cfg(const dfk_config_t& c) { dfk_config_t d = c; d.kmajor = 1; return d; }
 
 bool mfma_mixed_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {

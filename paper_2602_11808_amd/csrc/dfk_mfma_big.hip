@@ -3,60 +3,57 @@
 // With more than 64 tokens the block stops being a matrix-vector stream: per weight tile
 // there are 8..16 token tiles of MFMA work, too many accumulators for one wavefront and too
 // much operand traffic if every wavefront fetched its own copy of the weights.  These
-// kernels are the "row-major" end of the Method section's tiling choice carried through:
-// the wavefronts of a workgroup (four or eight in the gate/up kernel, eight in the down kernel) share
-// every weight tile through LDS, each wavefront owns its share of the launch's tokens (1, 2
-// or 4 token tiles of 16) and keeps the whole reduction for them, so there is no
-// cross-wavefront sum at the end.
+// kernels are the "row-major" end of the Method section's tiling choice carried through: a
+// workgroup's eight wavefronts share weight and activation tiles through LDS.  Wavefront
+// (tg, kh) owns token group tg of four (1..4 tiles of 16 tokens) and half kh of every step's k
+// range: the eight read each weight tile four times per step in all, where eight wavefronts that
+// each own tokens over the whole k range read it eight times.  Those operand reads were the
+// bound (66 of 70 us of the gate/up kernel at 256 tokens of the 4096 x 14336 layer, the
+// loads alone taking less): LDS moves 134 KB per 64 k where it moved 190 KB.  Measured: 61 us there, whole
+// call 129 -> 116 us; 8192 x 28672 at 150 tokens (three tiles per group, where 150 tokens had taken the form for
+// 256) gate/up 280 -> 205, down 171 -> 122, whole call 443 -> 328 us.
 //
-// Data movement is the same asynchronous global->LDS tile load as in the other MFMA kernels,
-// organised as a workgroup pipeline instead of per-wavefront rings:
-//   * shared tiles (weights): 4 KB tiles of the usual layout; the 1 KB load instructions of a
-//     step's tiles are dealt out evenly, so the wavefronts fill the tiles together and issue
-//     the same number of loads.  `nb` buffers of one pipeline step each.
-//   * private tiles (activations of the wavefront's own tokens): loaded and read by one
-//     wavefront only, `pl` buffers per wavefront.
-//   * one LDS-only barrier per step: before it every wavefront waits, by count, for its own
-//     loads of the step (loads complete in issue order; the kernel keeps the running count of
-//     issued loads and the count at which each step's loads were complete); after it the
-//     step's shared tiles are whole and the buffer of the step before is free to refill.
+// Data movement is the asynchronous global->LDS tile load of the other MFMA kernels,
+// organised as a workgroup pipeline:
+//   * a step is 64 k: tiles of 16 rows x 128 bytes (one cache line per row), 2 KB.  In LDS the eight
+//     16-byte pieces of row i sit XOR-swizzled by i / 2, so that the operand reads of 16 rows
+//     cover all banks once.
+//   * wavefronts 0..3 request the weights, 4..7 the activations.  Loads complete in issue order
+//     per wavefront, so a wavefront that requested both would have to wait for its newest
+//     activations (one or two steps ahead, out of L2) and with them for every older weight load (several
+//     steps ahead, out of HBM): the weights in flight would shrink to what the activations' look-ahead allows.
+//   * one LDS-only barrier per step: before it every requesting wavefront waits, by count, for its own
+//     loads of the step; after it the step's tiles are whole and the buffers of the step before are free to refill.
 //
 // Gate/up kernel: workgroup s owns a d_ff slice of at most 8 row tiles (8 rows of W_gate and
-// the same 8 of W_up per tile); a step is one 128-k chunk: the slice's weight tiles (shared)
-// and the wavefront's token tiles of X (private, read into registers as MFMA B operands at
-// the start of the step).  The D tile of a row tile holds gate rows in lanes 0..31 and up
-// rows in lanes 32..63 of the same token: one cross-lane exchange, SiLU(G)*U, store of A_2.
-//
-// Down kernel: workgroup (js, cb) owns one 128-column block over d_ff split js; a step is
-// two 32-row blocks of W_down (shared, regrouped per lane with v_perm_b32 as in the other
-// down kernels) and the wavefront's A_2 tiles for those rows (private).  Each wavefront
-// publishes its finished [tokens x 128] sums itself (partial block of the split, or the
-// fp32 accumulator); the cross-workgroup reduction is that of the other kernels.
+// the same 8 of W_up per tile).  Down kernel: workgroup (js, cb) owns one 128-column block over
+// d_ff split js; W_down is regrouped per lane with v_perm_b32 as in the other down kernels.
+// In both the two halves of the k range meet in LDS at the end, each wavefront finishing half of the
+// outputs.  The down kernel's sums over the splits are plain stores of partial blocks and a small third launch.
 #include <atomic>
 #include <algorithm>
+#include <type_traits>
 
 #include "dfk_mfma_common.h"
 
 namespace dfk {
 namespace {
 
-constexpr int kBigWaves = 4;          // gate/up kernel: 4 or 8; token tiles per wavefront are counted for 4
-constexpr int kBigDownWaves = 8;      // down kernel: two wavefronts per SIMD, so that one's operand shuffles
-                                      // (v_perm_b32) run under the other's MFMAs
+constexpr int kBigWaves = 8;          // 4 token groups x 2 halves of the k range
 constexpr int kBigMaxRowTiles = 8;
 constexpr int kBigTokensPerLaunch = 256;
-constexpr int kBigSB = 2;            // 32-row blocks of W_down per step of the down kernel (the A_2 tile layout assumes 2)
+constexpr int kBigStepK = 64;         // k (d_ff rows in the down kernel) of one pipeline step
+constexpr int kBigTile = 2048;        // 16 rows x 128 bytes
 
 constexpr size_t kL2BytesPerXcd = (size_t)4 << 20;
 
-struct BigGeom {
-    int nb;          // buffers of shared tiles (steps)
-    int pl;          // private buffers per wavefront (1 or 2)
-    int shared_step; // bytes of one shared buffer
-    int priv_off;    // byte offset of the private region
-    int priv_step;   // bytes of one private buffer
-    int by_xcd;      // down kernel: place the workgroups of a d_ff split on one XCD (see down_tile_of)
-};
+// Buffers (pipeline steps) of the activations, which come out of L2: two steps ahead is enough (with one: 72 -> 83 us for
+// the gate/up kernel at 256 tokens of the 4096 x 14336 layer, 49 -> 66 at 128).  The weights, out of HBM, get what LDS is left,
+// up to 8.  Compile-time constants of a kernel, so that the wait of a step is one instruction with a constant count.
+constexpr int kBigXBufs = 3;
+constexpr int big_w_bufs(int TT, int w_step) {
+    return (kLdsLimit - kBigXBufs * 4 * TT * kBigTile) / w_step < 8 ? (kLdsLimit - kBigXBufs * 4 * TT * kBigTile) / w_step : 8;
+}
 
 // s_waitcnt vmcnt(n) for a run-time n (uniform); more than 63 waits for 63.
 __device__ __forceinline__ void wait_vm_exact(int n) {
@@ -74,172 +71,143 @@ __device__ __forceinline__ void wait_vm_exact(int n) {
     asm volatile("" ::: "memory");
 }
 
-// Bookkeeping of the workgroup pipeline, plain wave-uniform ints in the kernels (kept out of
-// any struct that is passed around: that ended up in scratch memory, whose loads drain the
-// tile loads): `issued` counts this wavefront's tile-load instructions; p_mark<i> / s_mark<i> is
-// that count right after the loads of the private / shared tiles of step (current + i) were
-// issued (0: none issued, nothing to wait for).
-#define DFK_PIPE_DECL() int issued = 0, p_mark0 = 0, p_mark1 = 0, s_mark0 = 0, s_mark1 = 0, s_mark2 = 0
-#define DFK_PIPE_SET_P(ahead) do { if ((ahead) == 0) p_mark0 = issued; else p_mark1 = issued; } while (0)
-#define DFK_PIPE_SET_S(ahead) do { if ((ahead) == 0) s_mark0 = issued; else if ((ahead) == 1) s_mark1 = issued; else s_mark2 = issued; } while (0)
-// Wait for this wavefront's loads of the current step, meet the other wavefronts, move on one step.
-#define DFK_PIPE_ENTER_STEP() do {                                             \
-        wait_vm_exact(issued - max(p_mark0, s_mark0));                          \
-        lds_barrier();                                                          \
-        p_mark0 = p_mark1; p_mark1 = 0;                                         \
-        s_mark0 = s_mark1; s_mark1 = s_mark2; s_mark2 = 0;                      \
-    } while (0)
-
-// ---------------------------------------------------------------- gate/up kernel
-template <int TT, int NW>
-struct BigLoads1 {
-    const char* wsrc;          // this lane's address in the slice's first weight tile, chunk 0
-    const char* xsrc[TT][4];   // this lane's addresses in the wavefront's X tiles, chunk 0
-    size_t row_bytes;
-    int nt, wave;
-    unsigned char *lds, *xpriv;
-    int shared_step, priv_step;
-
-    __device__ __forceinline__ int issue_x(int kc, int buf) {
-        unsigned char* dst = xpriv + (size_t)buf * priv_step;
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                __builtin_amdgcn_global_load_lds(xsrc[tt][u] + (size_t)kc * (kKC * 2), DFK_LDS_PTR(dst + tt * kTileBytes + u * 1024), 16, 0, 0);
-        return 4 * TT;
-    }
-    // 4 wavefronts: each issues its instruction (wave) of every tile; 8: instruction wave % 4 of
-    // the tiles of parity wave / 4
-    __device__ __forceinline__ int issue_w(int kc, int buf) {
-        unsigned char* dst = lds + (size_t)buf * shared_step + (wave & 3) * 1024;
-        int n = 0;
-        for (int rt = NW == 8 ? (wave >> 2) : 0; rt < nt; rt += NW == 8 ? 2 : 1) {
-            __builtin_amdgcn_global_load_lds(wsrc + (size_t)rt * 8 * row_bytes + (size_t)kc * (kKC * 2), DFK_LDS_PTR(dst + rt * kTileBytes), 16, 0,
-                                             kAuxNonTemporal);
-            ++n;
-        }
-        return n;
-    }
-};
-
-// MFMAs of one 128-k chunk for NTC row tiles: the A operands (weight tile rows) are read from
-// LDS one row tile ahead of their use, so that the read latency hides behind the MFMAs of the
-// tile before.  wt points at this lane's row (q) of the chunk's first weight tile.
-template <int NTC, int TT, typename E>
-__device__ __forceinline__ void gateup_chunk(f32x4 (&acc)[NTC][TT], const u32x4 (&xk)[TT][4], const unsigned char* wt, int q, int g,
-                                             bool last_present) {
-    u32x4 av[2][4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) av[0][c] = *(const u32x4*)(wt + (((4 * c + g) ^ q)) * 16);
-#pragma unroll
-    for (int rt = 0; rt < NTC; ++rt) {
-        if (rt + 1 < NTC) {   // (the last tile's buffer exists in every workgroup; its data is used only where present)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) av[(rt + 1) & 1][c] = *(const u32x4*)(wt + (rt + 1) * kTileBytes + (((4 * c + g) ^ q)) * 16);
-        }
-        // keep the four reads above ahead of this tile's MFMAs (the scheduler otherwise moves each
-        // read next to its use, two MFMAs before a full LDS wait)
-        __builtin_amdgcn_sched_barrier(0);
-        if (rt + 1 < NTC || last_present) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma16<E>(av[rt & 1][c], xk[tt][c], acc[rt][tt]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
+template <int N>
+__device__ __forceinline__ void wait_vm_const() {
+    DFK_WAIT_VM(N < 63 ? N : 63);
+    asm volatile("" ::: "memory");
 }
 
+// This lane's byte offset of its MFMA operand within a tile: row q, the 16-byte piece of k group g of half kh.
+__device__ __forceinline__ int big_operand_off(int q, int g, int kh) { return q * 128 + (((4 * kh + g) ^ (q >> 1)) & 7) * 16; }
+
+// ---------------------------------------------------------------- gate/up kernel
 // NTC: the largest row-tile count of a d_ff slice of the launch (a compile-time constant so that
-// the chunk body is straight-line code); every slice has NTC or NTC - 1 row tiles.
-template <int TT, typename E, int NTC, int NW>
-__global__ __launch_bounds__(NW * 64) void k_gateup_big(MlpArgs a, BigGeom geo) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    constexpr int NT = NTC;
+// a step is straight-line code); every slice has NTC or NTC - 1 row tiles (the missing one's sums are never stored).
+template <int TT, typename E, int NTC>
+__device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char* lds) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane & 15, g = lane >> 4;
+    const int tg = wave & 3, kh = wave >> 2;
     int j0, j1;
     slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
     const int nt = (j1 - j0) / 8;                  // NTC or NTC - 1 (slices differ by at most one 8-row group)
-    const int nkc = a.d_model / kKC;
+    const int nsteps = a.d_model / kBigStepK;
     const size_t row_bytes = (size_t)a.d_model * 2;
-    const int tile0 = wave * TT;                   // this wavefront's first token tile
+    const int tile0 = tg * TT;                     // first token tile of this wavefront's group
 
-    BigLoads1<TT, NW> ld;
-    ld.row_bytes = row_bytes; ld.nt = nt; ld.wave = wave; ld.lds = lds;
-    ld.shared_step = geo.shared_step; ld.priv_step = geo.priv_step;
-    // this wavefront's instruction of a weight tile: tile row i = 4*wave + g, 16-byte chunk q ^ i
-    const int iw = 4 * (wave & 3) + g;
-    ld.wsrc = (const char*)((wave & 3) < 2 ? a.Wg : a.Wu) + (size_t)j0 * row_bytes + (size_t)(iw & 7) * row_bytes + ((q ^ iw) * 16);
-    // X tile: instruction u covers tile rows (tokens) 4u + g
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = 4 * u + g;
-            const int token = min((tile0 + tt) * 16 + i, a.m_count - 1);
-            ld.xsrc[tt][u] = (const char*)a.X + (size_t)(a.m_base + token) * row_bytes + ((q ^ i) * 16);
-        }
-    unsigned char* xpriv = lds + geo.priv_off + (size_t)wave * geo.pl * geo.priv_step;
-    ld.xpriv = xpriv;
-
-    DFK_PIPE_DECL();
-    DFK_STAMP(0);
-    // Every workgroup walks the k chunks in its own rotation: all of them read the same X, and in
+    // Every workgroup walks the k range in its own rotation: all of them read the same X, and in
     // lock-step they would ask the same few L2 channels for the same lines at the same moment.
-    const int rot = (int)((blockIdx.x * 7u) % (unsigned)nkc);
-#define DFK_KC(step) (((step) + rot) < nkc ? (step) + rot : (step) + rot - nkc)
-    // prologue: X of the first pl steps, weights of the first nb - 1, earliest needs first
-    {
-        int xs = 0, ws = 0;
-        for (int s = 0; s < 3; ++s) {
-            if (xs < geo.pl && xs < nkc && xs <= s) { issued += ld.issue_x(DFK_KC(xs), xs); DFK_PIPE_SET_P(xs); ++xs; }
-            if (ws < geo.nb - 1 && ws < nkc && ws <= s) { issued += ld.issue_w(DFK_KC(ws), ws); DFK_PIPE_SET_S(ws); ++ws; }
-        }
-    }
+    const int rot = (int)((blockIdx.x * 7u) % (unsigned)nsteps);
+    const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
+    const int lo = big_operand_off(q, g, kh);
 
-    f32x4 acc[NT][TT];
+    f32x4 acc[NTC][TT];
 #pragma unroll
-    for (int rt = 0; rt < NT; ++rt)
+    for (int rt = 0; rt < NTC; ++rt)
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    int xbuf = 0, wbuf = 0;                        // buffers of the current step
-    int wfree = geo.nb - 1;                        // shared buffer the step nb-1 ahead goes to
-    for (int kc = 0; kc < nkc; ++kc) {
-        DFK_PIPE_ENTER_STEP();
-        u32x4 xk[TT][4];       // B operands of the chunk: token q of each of the wavefront's token tiles
-        {
-            const unsigned char* xs = xpriv + (size_t)xbuf * geo.priv_step;
+    DFK_STAMP(0);
+    constexpr int x_step = 4 * TT * kBigTile, w_step = NTC * kBigTile;
+    constexpr int nbx = kBigXBufs, nbw = big_w_bufs(TT, w_step), w_off = nbx * x_step;
+    // The steps of a wavefront that requests N weight loads per step or (N = -1) activations: of the slice's 2 nt weight loads
+    // (half n & 1 of row tile n / 2: the gate rows or the up rows) n = wave, wave + 4, ...; or the two loads of each token tile
+    // of its group.
+    auto steps = [&](auto n_) {
+        constexpr int N = decltype(n_)::value;
+        constexpr bool W = N >= 0;
+        constexpr int SLOTS = W ? N : 2 * TT;
+        constexpr int nb = W ? nbw : nbx;
+        const char* const src = W ? (const char*)(wave & 1 ? a.Wu : a.Wg) + (size_t)(j0 + (wave >> 1) * 8) * row_bytes
+                                  : (const char*)a.X + (size_t)a.m_base * row_bytes;
+        // Byte offset of load i: row 16 i (weights) or 8 i (tokens, the last one for those that do not exist) further on than
+        // load 0's; the piece's place changes by half a row (64 bytes) from a tile's rows 0..7 to its rows 8..15.
+        const unsigned rb = (unsigned)row_bytes;
+        const unsigned off = (unsigned)(W ? prow : tile0 * 16 + prow) * rb, off_last = (unsigned)(a.m_count - 1) * rb;
+        const unsigned place = (unsigned)(((piece ^ (prow >> 1)) & 7) * 16) ^ (W && (wave & 1) ? 64u : 0u);
+        unsigned char* const dst0 = W ? lds + w_off + (wave >> 1) * kBigTile + (wave & 1) * 1024 : lds + tile0 * kBigTile;
+        constexpr int buf_bytes = W ? w_step : x_step;
+        auto source = [&](int step) { return src + (size_t)(step + rot < nsteps ? step + rot : step + rot - nsteps) * (kBigStepK * 2); };
+        auto load = [&](const char* p, unsigned char* dst, int i) {
+            const unsigned o = W ? off + 16u * i * rb + place : min(off + 8u * i * rb, off_last) + (place ^ (i & 1 ? 64u : 0u));
+            __builtin_amdgcn_global_load_lds(p + o, DFK_LDS_PTR(dst + i * (W ? 2 * kBigTile : 1024)), 16, 0, W ? kAuxNonTemporal : 0);
+        };
+        for (int s = 0; s < nb && s < nsteps; ++s)
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
+            for (int i = 0; i < SLOTS; ++i) load(source(s), dst0 + s * buf_bytes, i);
+
+        u32x4 xk[2][TT], wv[2][NTC];               // operands of this step and of the next
+        int xbuf = 0, wbuf = 0, freebuf = 0;
+        wait_vm_exact(SLOTS * (min(nb, nsteps) - 1));
+        lds_barrier();
 #pragma unroll
-                for (int c = 0; c < 4; ++c) xk[tt][c] = *(const u32x4*)(xs + tt * kTileBytes + (q * 16 + ((4 * c + g) ^ q)) * 16);
+        for (int tt = 0; tt < TT; ++tt) xk[0][tt] = *(const u32x4*)(lds + tile0 * kBigTile + lo + tt * kBigTile);
+#pragma unroll
+        for (int rt = 0; rt < NTC; ++rt) wv[0][rt] = *(const u32x4*)(lds + w_off + lo + rt * kBigTile);
+        auto step = [&](int s, auto cur_) {
+            constexpr int cur = decltype(cur_)::value, nxt = cur ^ 1;
+            // The loads of step s + 1 have landed (later ones may be in flight), and every wavefront has read step s:
+            // its buffers are free for the loads of step s + nb.
+            if (s + nb <= nsteps) wait_vm_const<SLOTS * (nb - 2)>();
+            else if (s + 1 < nsteps) wait_vm_exact(SLOTS * (nsteps - s - 2));
+            lds_barrier();
+            if (++xbuf == nbx) xbuf = 0;
+            if (++wbuf == nbw) wbuf = 0;
+            const unsigned char* xs = lds + xbuf * x_step + tile0 * kBigTile + lo;
+            const unsigned char* ws = lds + w_off + wbuf * w_step + lo;
+            const char* p = source(s + nb < nsteps ? s + nb : 0);
+            unsigned char* dst = dst0 + freebuf * buf_bytes;
+            const bool more = s + nb < nsteps;
+            // Loads, operand reads of step s + 1 and MFMAs of step s in turn: in three blocks one after the other, each of the
+            // three units idles while the eight wavefronts queue for another (75 us at 256 tokens of the 4096 x 14336 layer).
+#pragma unroll
+            for (int rt = 0; rt < NTC; ++rt) {
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma16<E>(wv[cur][rt], xk[cur][tt], acc[rt][tt]);
+                wv[nxt][rt] = *(const u32x4*)(ws + rt * kBigTile);
+#pragma unroll
+                for (int tt = rt * TT / NTC; tt < (rt + 1) * TT / NTC; ++tt) xk[nxt][tt] = *(const u32x4*)(xs + tt * kBigTile);
+                if (more) {
+#pragma unroll
+                    for (int i = rt * SLOTS / NTC; i < (rt + 1) * SLOTS / NTC; ++i) load(p, dst, i);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (++freebuf == nb) freebuf = 0;
+        };
+        for (int s = 0; s < nsteps; s += 2) {      // (an even number: d_model is a multiple of 128)
+            step(s, std::integral_constant<int, 0>{});
+            step(s + 1, std::integral_constant<int, 1>{});
         }
-        DFK_WAIT_LGKM0();      // the X buffer has been read: it may be refilled
-        asm volatile("" ::: "memory");
-        if (kc + geo.pl < nkc) { issued += ld.issue_x(DFK_KC(kc + geo.pl), xbuf); DFK_PIPE_SET_P(geo.pl - 1); }
-        if (kc + geo.nb - 1 < nkc) { issued += ld.issue_w(DFK_KC(kc + geo.nb - 1), wfree); DFK_PIPE_SET_S(geo.nb - 2); }
-        const unsigned char* wt = lds + (size_t)wbuf * geo.shared_step + (q * 16) * 16;
-        gateup_chunk<NTC, TT, E>(acc, xk, wt, q, g, nt == NTC);
-        if (++xbuf == geo.pl) xbuf = 0;
-        if (++wbuf == geo.nb) wbuf = 0;
-        if (++wfree == geo.nb) wfree = 0;
-    }
-#undef DFK_KC
+    };
+    constexpr int NMAX = (2 * NTC + 3) / 4;        // a weight wavefront has NMAX loads per step or one less
+    if (kh == 1) steps(std::integral_constant<int, -1>{});
+    else if ((2 * nt - wave + 3) >> 2 == NMAX) steps(std::integral_constant<int, NMAX>{});
+    else steps(std::integral_constant<int, NMAX - 1>{});
     DFK_STAMP(2);
 
+    // The halves of the k range meet: wavefront (tg, 0) finishes row tiles [0, H), (tg, 1) the others.
+    constexpr int H = (NTC + 1) / 2;
+    lds_barrier();                                 // nothing in flight and nothing read any more: the buffers are free
+    f32x4* mine = (f32x4*)lds + (size_t)wave * (H * TT * 64) + lane;
+    const f32x4* theirs = (const f32x4*)lds + (size_t)(wave ^ 4) * (H * TT * 64) + lane;
+#pragma unroll
+    for (int rt = 0; rt < NTC; ++rt)
+        if ((rt < H) == (kh == 1)) {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) mine[((rt < H ? rt : rt - H) * TT + tt) * 64] = acc[rt][tt];
+        }
+    __syncthreads();
     // D tile of (row tile, token tile): lane (q, g) holds token q, tile rows 4g .. 4g+3; rows 0..7
     // are the gate rows, 8..15 the up rows of the same 8 d_ff rows: lanes 32 apart pair up.
 #pragma unroll
-    for (int rt = 0; rt < NT; ++rt) {
-        if (rt < nt) {
+    for (int rt = 0; rt < NTC; ++rt) {
+        if ((rt < H) == (kh == 0) && rt < nt) {
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
-                const f32x4 v = acc[rt][tt];
+                const f32x4 v = acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64];
                 float o[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) o[i] = __shfl_xor(v[i], 32);
@@ -256,55 +224,13 @@ __global__ __launch_bounds__(NW * 64) void k_gateup_big(MlpArgs a, BigGeom geo) 
     DFK_STAMP(1);
 }
 
+template <int TT, typename E, int NTC>
+__global__ __launch_bounds__(kBigWaves * 64) void k_gateup_big(MlpArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    gateup_big_body<TT, E, NTC>(a, lds);
+}
+
 // ---------------------------------------------------------------- down kernel
-template <int TT, int NW>
-struct BigLoads2 {
-    const char* asrc[TT][2];   // this lane's token rows of A_2 at the split's first row (per load instruction)
-    const char* Wd;
-    size_t row_bytes, colb;
-    int j0, rows, njb, d_ff, wave, q, g, lane;
-    unsigned char *lds, *apriv;
-    int shared_step, priv_step;
-
-    // A_2 of a step (64 rows = 128 contiguous bytes per token), 2 KB per token tile: instruction h
-    // covers tokens 8h .. 8h+7 of the tile, 8 consecutive lanes one token's 128 bytes (a whole
-    // cache line per token); within a token the eight 16-byte chunks sit XOR-swizzled by the
-    // token so that the operand reads below spread over the LDS banks.
-    __device__ __forceinline__ int issue_a(int s, int buf) {
-        unsigned char* dst = apriv + (size_t)buf * priv_step;
-        const int chunk = (lane & 7) ^ ((lane >> 3) & 7);
-        const int j = min(s * 64 + 8 * chunk, rows - 8);   // past the split: any valid address (masked at use)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                __builtin_amdgcn_global_load_lds(asrc[tt][h] + (size_t)j * 2, DFK_LDS_PTR(dst + tt * 2048 + h * 1024), 16, 0, 0);
-        return 2 * TT;
-    }
-    // W_down tiles of a 32-row block: tile h (0, 1) holds rows 4h + 8g + u for instruction u.  The
-    // 8 instructions of a block are dealt out evenly: with 4 wavefronts each issues instruction
-    // u = wave of both tiles, with 8 wavefronts instruction wave % 4 of tile wave / 4.
-    __device__ __forceinline__ int issue_w(int s, int buf) {
-        const int u = wave & 3;
-        unsigned char* dst = lds + (size_t)buf * shared_step + u * 1024;
-        int n = 0;
-        for (int b = 0; b < kBigSB; ++b) {
-            const int jb = s * kBigSB + b;
-            if (jb < njb) {
-#pragma unroll
-                for (int hh = 0; hh < (NW == 8 ? 1 : 2); ++hh) {
-                    const int h = NW == 8 ? (wave >> 2) : hh;
-                    const int row = min(j0 + jb * 32 + 4 * h + 8 * g + u, d_ff - 1);   // past d_ff: masked at use
-                    __builtin_amdgcn_global_load_lds(Wd + (size_t)row * row_bytes + colb + 16 * q,
-                                                     DFK_LDS_PTR(dst + (b * 2 + h) * kTileBytes), 16, 0, kAuxNonTemporal);
-                }
-                n += NW == 8 ? 1 : 2;
-            }
-        }
-        return n;
-    }
-};
-
 // Which (d_ff split, column block) a workgroup of the down kernel takes.  Workgroups are handed to
 // the 8 XCDs in turn (workgroup b runs on XCD b % 8) and each XCD has its own L2; all column blocks
 // of a split read the same A_2 rows, so a split's workgroups are placed on one XCD (or, with fewer
@@ -331,55 +257,28 @@ __device__ __forceinline__ void down_tile_of(int b, int S, int C, bool by_xcd, i
     }
 }
 
-template <int TT, typename E, int NW>
-__global__ __launch_bounds__(NW * 64) void k_down_big(MlpArgs a, BigGeom geo) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+template <int TT, typename E>
+__device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xcd, unsigned char* lds) {
     __shared__ int flag;
-    static_assert(NW == 4 || NW == 8, "shared tiles are dealt out to 4 or 8 wavefronts");
-    constexpr int NTHREADS = NW * 64;
-    constexpr int SB = kBigSB;
+    constexpr int NTHREADS = kBigWaves * 64;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane & 15, g = lane >> 4;
+    const int tg = wave & 3, kh = wave >> 2;
     int js, cb;   // d_ff split and 128-column block of this workgroup (one column block each: checked on the host)
-    down_tile_of((int)blockIdx.x, a.k2_splits, a.k2_col_blocks, geo.by_xcd != 0, js, cb);
+    down_tile_of((int)blockIdx.x, a.k2_splits, a.k2_col_blocks, by_xcd, js, cb);
     int j0, j1;
     slice_rows(a.d_ff, a.k2_splits, js, j0, j1);
     const int rows = j1 - j0;
-    const int njb = (rows + 31) / 32;
-    const int nsteps = (njb + SB - 1) / SB;
+    const int nsteps = (rows + kBigStepK - 1) / kBigStepK;
     const size_t row_bytes = (size_t)a.d_model * 2;
-    const int tile0 = wave * TT;
-    const size_t colb = (size_t)cb * 256;
+    const int tile0 = tg * TT;
 
-    BigLoads2<TT, NW> ld;
-    ld.Wd = (const char*)a.Wd; ld.row_bytes = row_bytes; ld.colb = colb;
-    ld.j0 = j0; ld.rows = rows; ld.njb = njb; ld.d_ff = a.d_ff; ld.wave = wave; ld.q = q; ld.g = g;
-    ld.lds = lds; ld.shared_step = geo.shared_step; ld.priv_step = geo.priv_step;
-    ld.lane = lane;
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int token = min((tile0 + tt) * 16 + 8 * h + (lane >> 3), a.m_count - 1);
-            ld.asrc[tt][h] = (const char*)a.a2 + ((size_t)(a.m_base + token) * a.d_ff + j0) * 2;
-        }
-    unsigned char* apriv = lds + geo.priv_off + (size_t)wave * geo.pl * geo.priv_step;
-    ld.apriv = apriv;
-
-    DFK_PIPE_DECL();
-    DFK_STAMP(3);
     // The workgroups of one split read the same A_2 rows: each walks the steps in its own rotation.
     const int rot = (int)((cb * 5u) % (unsigned)nsteps);
-#define DFK_ST(step) (((step) + rot) < nsteps ? (step) + rot : (step) + rot - nsteps)
-    {
-        int as = 0, ws = 0;
-        for (int s = 0; s < 3; ++s) {
-            if (as < geo.pl && as < nsteps && as <= s) { issued += ld.issue_a(DFK_ST(as), as); DFK_PIPE_SET_P(as); ++as; }
-            if (ws < geo.nb - 1 && ws < nsteps && ws <= s) { issued += ld.issue_w(DFK_ST(ws), ws); DFK_PIPE_SET_S(ws); ++ws; }
-        }
-    }
+    const int prow = lane >> 3, piece = lane & 7;
+    const int lo = big_operand_off(q, g, kh);
 
     f32x4 acc2[8][TT];
 #pragma unroll
@@ -387,85 +286,135 @@ __global__ __launch_bounds__(NW * 64) void k_down_big(MlpArgs a, BigGeom geo) {
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc2[c][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    int abuf = 0, wbuf = 0, wfree = geo.nb - 1;
-    for (int s = 0; s < nsteps; ++s) {
-        const int se = DFK_ST(s);   // the rows this step covers: 64 se .. 64 se + 63 of the split
-        DFK_PIPE_ENTER_STEP();
-        u32x4 av[SB][TT];      // A operands: A_2[token q of tile tt][rows 8g .. 8g+7 of block b]
-        {
-            // token q of the tile sits in instruction q / 8 at lanes 8 (q % 8) .. +7, chunk k at (k ^ (q % 8))
-            const unsigned char* as = apriv + (size_t)abuf * geo.priv_step + (q >> 3) * 1024 + (q & 7) * 128;
-#pragma unroll
-            for (int b = 0; b < SB; ++b) {
-                const int k = 4 * b + g;
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt) av[b][tt] = *(const u32x4*)(as + tt * 2048 + ((k ^ (q & 7)) * 16));
+    DFK_STAMP(3);
+    constexpr int x_step = 4 * TT * kBigTile, w_step = 4 * kTileBytes;
+    constexpr int nbx = kBigXBufs, nbw = big_w_bufs(TT, w_step), w_off = nbx * x_step;
+    // Loads per step: wavefronts 0..3 take row u = wave of the four 4 KB tiles (32-row block b, half h) of W_down: rows
+    // 32 b + 4 h + 8 g + u of the step, 256 bytes each; 4..7 the two loads of each token tile of their group
+    // (A_2: 64 rows = one cache line per token).  Rows past the split are any valid address (zeroed at use).
+    auto steps = [&](auto is_w) {
+        constexpr bool W = decltype(is_w)::value;
+        constexpr int SLOTS = W ? 4 : 2 * TT;
+        constexpr int nb = W ? nbw : nbx;
+        const char* const src = W ? (const char*)a.Wd + (size_t)cb * 256 + 16 * q : (const char*)a.a2 + ((size_t)a.m_base * a.d_ff + j0) * 2;
+        // A_2: byte offsets of the first token's row and of the last that exists (256 tokens x 2 d_ff bytes: below 4 GiB)
+        const unsigned a2_row = (unsigned)a.d_ff * 2u;
+        const unsigned off = (unsigned)(tile0 * 16 + prow) * a2_row, off_last = (unsigned)(a.m_count - 1) * a2_row;
+        unsigned char* const dst0 = W ? lds + w_off + wave * 1024 : lds + tile0 * kBigTile;
+        constexpr int buf_bytes = W ? w_step : x_step;
+        auto first_row = [&](int step) { return (step + rot < nsteps ? step + rot : step + rot - nsteps) * kBigStepK; };
+        auto load = [&](int r0, unsigned char* dst, int i) {
+            if (W) {
+                const int row = min(j0 + r0 + (i >> 1) * 32 + (i & 1) * 4 + 8 * g + wave, a.d_ff - 1);
+                __builtin_amdgcn_global_load_lds(src + (size_t)row * row_bytes, DFK_LDS_PTR(dst + i * kTileBytes), 16, 0, kAuxNonTemporal);
+            } else {
+                const int j = min(r0 + 8 * ((piece ^ (((i & 1) * 8 + prow) >> 1)) & 7), rows - 8);
+                __builtin_amdgcn_global_load_lds(src + (min(off + (unsigned)(8 * i) * a2_row, off_last) + (unsigned)j * 2u), DFK_LDS_PTR(dst + i * 1024), 16, 0, 0);
             }
-            if ((se + 1) * SB * 32 > rows) {   // only the split's last 64 rows can reach past it
+        };
+        for (int s = 0; s < nb && s < nsteps; ++s)
 #pragma unroll
-                for (int b = 0; b < SB; ++b) {
-                    const bool past = (se * SB + b) * 32 + 8 * g >= rows;
+            for (int i = 0; i < SLOTS; ++i) load(first_row(s), dst0 + s * buf_bytes, i);
+
+        u32x4 av[2][TT], w[2][8];    // A_2[token q of tile tt][rows 8g .. 8g+7 of block kh]; the same rows of W_down, 8 columns
+        const unsigned char* const xs0 = lds + tile0 * kBigTile + lo;
+        const unsigned char* const ws0 = lds + w_off + kh * 2 * kTileBytes + lane * 16;
+        int xbuf = 0, wbuf = 0, freebuf = 0;
+        wait_vm_exact(SLOTS * (min(nb, nsteps) - 1));
+        lds_barrier();
 #pragma unroll
-                    for (int tt = 0; tt < TT; ++tt)
-                        if (past) av[b][tt] = u32x4{0, 0, 0, 0};
-                }
+        for (int r = 0; r < 8; ++r) w[0][r] = *(const u32x4*)(ws0 + (r >> 2) * kTileBytes + (r & 3) * 1024);
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) av[0][tt] = *(const u32x4*)(xs0 + tt * kBigTile);
+        auto step = [&](int s, auto cur_) {
+            constexpr int cur = decltype(cur_)::value, nxt = cur ^ 1;
+            if (s + nb <= nsteps) wait_vm_const<SLOTS * (nb - 2)>();
+            else if (s + 1 < nsteps) wait_vm_exact(SLOTS * (nsteps - s - 2));
+            lds_barrier();
+            if (++xbuf == nbx) xbuf = 0;
+            if (++wbuf == nbw) wbuf = 0;
+            const unsigned char* xs = xs0 + xbuf * x_step;
+            const unsigned char* ws = ws0 + wbuf * w_step;
+            const bool more = s + nb < nsteps;
+            const int r0 = first_row(more ? s + nb : 0);
+            unsigned char* dst = dst0 + freebuf * buf_bytes;
+            const int here = first_row(s);
+            if (here + kBigStepK > rows && here + kh * 32 + 8 * g >= rows) {   // this lane's eight rows are past the split: they contribute nothing
+#pragma unroll
+                for (int r = 0; r < 8; ++r) w[cur][r] = u32x4{0, 0, 0, 0};
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) av[cur][tt] = u32x4{0, 0, 0, 0};
             }
-        }
-        DFK_WAIT_LGKM0();
-        asm volatile("" ::: "memory");
-        if (s + geo.pl < nsteps) { issued += ld.issue_a(DFK_ST(s + geo.pl), abuf); DFK_PIPE_SET_P(geo.pl - 1); }
-        if (s + geo.nb - 1 < nsteps) { issued += ld.issue_w(DFK_ST(s + geo.nb - 1), wfree); DFK_PIPE_SET_S(geo.nb - 2); }
-        // Both blocks of the step are read and multiplied unconditionally: a block past the split
-        // has every row masked to zero below and its A operands zeroed above.
-        const unsigned char* wt = lds + (size_t)wbuf * geo.shared_step + lane * 16;
-        u32x4 w[SB][8];
-#pragma unroll
-        for (int b = 0; b < SB; ++b)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) w[b][r] = *(const u32x4*)(wt + (b * 2 + (r >> 2)) * kTileBytes + (r & 3) * 1024);
-#pragma unroll
-        for (int b = 0; b < SB; ++b) {
-            const int jb = se * SB + b;
-            if (jb * 32 + 32 > rows) {   // rows past the split contribute nothing
-#pragma unroll
-                for (int r = 0; r < 8; ++r)
-                    if (jb * 32 + 8 * g + r >= rows) w[b][r] = u32x4{0, 0, 0, 0};
-            }
+            // operand reads of step s + 1, loads and MFMAs of step s in turn, as in the gate/up kernel
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
                 u32x4 bb;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) bb[p] = __builtin_amdgcn_perm(w[b][2 * p + 1][c >> 1], w[b][2 * p][c >> 1], sel);
+                for (int p = 0; p < 4; ++p) bb[p] = __builtin_amdgcn_perm(w[cur][2 * p + 1][c >> 1], w[cur][2 * p][c >> 1], sel);
 #pragma unroll
-                for (int tt = 0; tt < TT; ++tt) acc2[c][tt] = mfma16<E>(av[b][tt], bb, acc2[c][tt]);
+                for (int tt = 0; tt < TT; ++tt) acc2[c][tt] = mfma16<E>(av[cur][tt], bb, acc2[c][tt]);
+                w[nxt][c] = *(const u32x4*)(ws + (c >> 2) * kTileBytes + (c & 3) * 1024);
+#pragma unroll
+                for (int tt = c * TT / 8; tt < (c + 1) * TT / 8; ++tt) av[nxt][tt] = *(const u32x4*)(xs + tt * kBigTile);
+                if (more) {
+#pragma unroll
+                    for (int i = c * SLOTS / 8; i < (c + 1) * SLOTS / 8; ++i) load(r0, dst, i);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
+            if (++freebuf == nb) freebuf = 0;
+        };
+        int s = 0;
+        for (; s + 1 < nsteps; s += 2) {
+            step(s, std::integral_constant<int, 0>{});
+            step(s + 1, std::integral_constant<int, 1>{});
         }
-        if (++abuf == geo.pl) abuf = 0;
-        if (++wbuf == geo.nb) wbuf = 0;
-        if (++wfree == geo.nb) wfree = 0;
-    }
-#undef DFK_ST
+        if (s < nsteps) step(s, std::integral_constant<int, 0>{});
+    };
+    if (kh == 0) steps(std::true_type{});
+    else steps(std::false_type{});
     DFK_STAMP(4);
 
     // D tile (column tile c, token tile tt): lane (q, g) holds tokens 4g .. 4g+3 of the tile, column
-    // 8q + c of the block: the lane's 8 column tiles are 8 consecutive columns.
+    // 8q + c of the block: the lane's 8 column tiles are 8 consecutive columns.  The halves of the k range meet:
+    // wavefront (tg, 0) finishes tokens 4g and 4g+1, (tg, 1) tokens 4g+2 and 4g+3.
+    lds_barrier();
+    f32x4* mine = (f32x4*)lds + (size_t)wave * (TT * 4 * 64) + lane;
+    const f32x4* theirs = (const f32x4*)lds + (size_t)(wave ^ 4) * (TT * 4 * 64) + lane;
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {              // token i = x / 2 of the partner's two, columns 4 (x & 1) ..
+            const int c = 4 * (x & 1);
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = kh == 0 ? acc2[c + e][tt][2 + (x >> 1)] : acc2[c + e][tt][x >> 1];
+            mine[(tt * 4 + x) * 64] = v;
+        }
+    __syncthreads();
     const bool atomic_mode = a.reduce_mode == DFK_REDUCE_ATOMIC;
     const int nb0 = cb * 128;
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = (tile0 + tt) * 16 + 4 * g + i;
+        for (int i = 0; i < 2; ++i) {
+            f32x4 v0 = theirs[(tt * 4 + 2 * i) * 64], v1 = theirs[(tt * 4 + 2 * i + 1) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v0[e] += kh == 0 ? acc2[e][tt][i] : acc2[e][tt][2 + i];
+                v1[e] += kh == 0 ? acc2[4 + e][tt][i] : acc2[4 + e][tt][2 + i];
+            }
+            const int m = (tile0 + tt) * 16 + 4 * g + 2 * kh + i;
             if (m < a.m_count) {
                 if (atomic_mode) {
                     float* dst = a.yacc + (size_t)m * a.d_model + nb0 + 8 * q;
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) acc_add(dst + c, acc2[c][tt][i]);
+                    for (int e = 0; e < 4; ++e) { acc_add(dst + e, v0[e]); acc_add(dst + 4 + e, v1[e]); }
                 } else {       // partial block of the split: plain stores, summed by the launch that follows
                     float* dst = a.P + ((size_t)js * a.m_count + m) * a.d_model + nb0 + 8 * q;
-                    *(f32x4*)dst = f32x4{acc2[0][tt][i], acc2[1][tt][i], acc2[2][tt][i], acc2[3][tt][i]};
-                    *(f32x4*)(dst + 4) = f32x4{acc2[4][tt][i], acc2[5][tt][i], acc2[6][tt][i], acc2[7][tt][i]};
+                    *(f32x4*)dst = v0;
+                    *(f32x4*)(dst + 4) = v1;
                 }
             }
         }
@@ -489,6 +438,12 @@ __global__ __launch_bounds__(NW * 64) void k_down_big(MlpArgs a, BigGeom geo) {
             *(uint32_t*)((uint16_t*)a.Y + o) = E::pack2(v0, v1);
         }
     }
+}
+
+template <int TT, typename E>
+__global__ __launch_bounds__(kBigWaves * 64) void k_down_big(MlpArgs a, int by_xcd) {   // by_xcd: place the workgroups of a d_ff split on one XCD (see down_tile_of)
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    down_big_body<TT, E>(a, by_xcd != 0, lds);
 }
 
 // Sum of the splits' partial blocks (counter reduction mode of the down kernel above): with
@@ -517,91 +472,75 @@ __global__ __launch_bounds__(256) void k_sum_partials_big(MlpArgs a) {
 
 // Every instantiation the launcher uses, spelled out (the host pass otherwise emitted the launch
 // stub of only one element type per token-tile count).
-#define DFK_INST_GATEUP(NTC)                                                     \
-    template __global__ void k_gateup_big<1, BF16, NTC, 8>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<1, FP16, NTC, 8>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<2, BF16, NTC, 8>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<2, FP16, NTC, 8>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<2, BF16, NTC, 4>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<2, FP16, NTC, 4>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<4, BF16, NTC, 4>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<4, FP16, NTC, 4>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<1, BF16, NTC, 4>(MlpArgs, BigGeom);    \
-    template __global__ void k_gateup_big<1, FP16, NTC, 4>(MlpArgs, BigGeom);
+#define DFK_INST_GATEUP(NTC)                                                  \
+    template __global__ void k_gateup_big<1, BF16, NTC>(MlpArgs);    \
+    template __global__ void k_gateup_big<1, FP16, NTC>(MlpArgs);    \
+    template __global__ void k_gateup_big<2, BF16, NTC>(MlpArgs);    \
+    template __global__ void k_gateup_big<2, FP16, NTC>(MlpArgs);    \
+    template __global__ void k_gateup_big<3, BF16, NTC>(MlpArgs);    \
+    template __global__ void k_gateup_big<3, FP16, NTC>(MlpArgs);    \
+    template __global__ void k_gateup_big<4, BF16, NTC>(MlpArgs);    \
+    template __global__ void k_gateup_big<4, FP16, NTC>(MlpArgs);
 DFK_INST_GATEUP(1) DFK_INST_GATEUP(2) DFK_INST_GATEUP(3) DFK_INST_GATEUP(4)
 DFK_INST_GATEUP(5) DFK_INST_GATEUP(6) DFK_INST_GATEUP(7) DFK_INST_GATEUP(8)
 #undef DFK_INST_GATEUP
 template __global__ void k_sum_partials_big<BF16>(MlpArgs);
 template __global__ void k_sum_partials_big<FP16>(MlpArgs);
-template __global__ void k_down_big<1, BF16, kBigDownWaves>(MlpArgs, BigGeom);
-template __global__ void k_down_big<1, FP16, kBigDownWaves>(MlpArgs, BigGeom);
-template __global__ void k_down_big<2, BF16, kBigDownWaves>(MlpArgs, BigGeom);
-template __global__ void k_down_big<2, FP16, kBigDownWaves>(MlpArgs, BigGeom);
+#define DFK_INST_DOWN(TT)                                              \
+    template __global__ void k_down_big<TT, BF16>(MlpArgs, int);   \
+    template __global__ void k_down_big<TT, FP16>(MlpArgs, int);
+DFK_INST_DOWN(1) DFK_INST_DOWN(2) DFK_INST_DOWN(3) DFK_INST_DOWN(4)
+#undef DFK_INST_DOWN
 
 // ---------------------------------------------------------------- host side
-int big_token_tiles(int m_count) { return m_count <= 128 ? 2 : 4; }   // per wavefront
+int big_token_tiles(int m_count) { return (m_count + 63) / 64; }   // per token group
 
-// LDS of the gate/up kernel: nb shared buffers of the slice's weight tiles, then pl X buffers per wavefront.
-size_t big_lds_gateup(const dfk_config_t& c, int TT, int d_ff, BigGeom* geo) {
+// LDS of the kernels: activation and weight buffers, or what the two halves of the k range exchange at the end.
+size_t big_lds(int TT, int w_step, size_t end) {
+    const size_t bufs = (size_t)kBigXBufs * 4 * TT * kBigTile + (size_t)big_w_bufs(TT, w_step) * w_step;
+    return std::max(bufs, end);
+}
+size_t big_lds_gateup(const dfk_config_t& c, int TT, int d_ff) {
     const int nt_max = max_slice_rows(d_ff, c.splits) / 8;
-    geo->nb = c.depth;
-    geo->shared_step = nt_max * kTileBytes;
-    geo->priv_off = geo->nb * geo->shared_step;
-    geo->priv_step = TT * kTileBytes * kBigWaves / c.waves;   // TT counts token tiles per wavefront of the 4-wavefront form
-    const size_t one = (size_t)c.waves * geo->priv_step;
-    geo->pl = (size_t)geo->priv_off + 2 * one <= (size_t)kLdsLimit ? 2 : 1;
-    return (size_t)geo->priv_off + geo->pl * one;
+    return big_lds(TT, nt_max * kBigTile, (size_t)kBigWaves * ((nt_max + 1) / 2) * TT * 1024);
 }
-size_t big_lds_down(const dfk_config_t& c, BigGeom* geo) {
-    geo->nb = c.depth;
-    geo->shared_step = kBigSB * 2 * kTileBytes;
-    geo->priv_off = geo->nb * geo->shared_step;
-    geo->priv_step = 2 * 2048;                 // 2 KB per token tile of the wavefront (up to 2)
-    const size_t one = (size_t)kBigDownWaves * geo->priv_step;
-    geo->pl = (size_t)geo->priv_off + 2 * one <= (size_t)kLdsLimit ? 2 : 1;
-    return (size_t)geo->priv_off + geo->pl * one;
-}
+size_t big_lds_down(int TT) { return big_lds(TT, 4 * kTileBytes, (size_t)kBigWaves * TT * 4 * 1024); }
+static_assert(big_w_bufs(4, kBigMaxRowTiles * kBigTile) >= 3 && big_w_bufs(4, 4 * kTileBytes) >= 3, "weights at least two steps ahead");
 
 template <int TT, typename E, int NTC>
 hipError_t launch_big_gateup(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    static LdsAllowance allowed4, allowed8;   // of the two kernels of this instantiation, per device
-    BigGeom geo{};
-    const size_t lds = big_lds_gateup(c, TT, a.d_ff, &geo);
-    if (c.waves == 8) {
-        if (hipError_t e = allow_lds(allowed8, (const void*)k_gateup_big<TT / 2, E, NTC, 8>, lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_gateup_big<TT / 2, E, NTC, 8>), dim3(a.splits), dim3(512), lds, st, a, geo);
-    } else {
-        if (hipError_t e = allow_lds(allowed4, (const void*)k_gateup_big<TT, E, NTC, 4>, lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_gateup_big<TT, E, NTC, 4>), dim3(a.splits), dim3(256), lds, st, a, geo);
-    }
+    static LdsAllowance allowed;   // of this instantiation, per device
+    const size_t lds = big_lds_gateup(c, TT, a.d_ff);
+    if (hipError_t e = allow_lds(allowed, (const void*)k_gateup_big<TT, E, NTC>, lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_gateup_big<TT, E, NTC>), dim3(a.splits), dim3(kBigWaves * 64), lds, st, a);
     return hipGetLastError();
+}
+template <int TT, typename E>
+hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    switch (max_slice_rows(a.d_ff, c.splits) / 8) {
+        case 1: return launch_big_gateup<TT, E, 1>(a, c, st);
+        case 2: return launch_big_gateup<TT, E, 2>(a, c, st);
+        case 3: return launch_big_gateup<TT, E, 3>(a, c, st);
+        case 4: return launch_big_gateup<TT, E, 4>(a, c, st);
+        case 5: return launch_big_gateup<TT, E, 5>(a, c, st);
+        case 6: return launch_big_gateup<TT, E, 6>(a, c, st);
+        case 7: return launch_big_gateup<TT, E, 7>(a, c, st);
+        case 8: return launch_big_gateup<TT, E, 8>(a, c, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int TT, typename E>
 hipError_t launch_big_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     static LdsAllowance allowed2;   // of the down kernel of this instantiation, per device
     if (g_stage_mask & 1) {
-        hipError_t e;
-        switch (max_slice_rows(a.d_ff, c.splits) / 8) {
-            case 1: e = launch_big_gateup<TT, E, 1>(a, c, st); break;
-            case 2: e = launch_big_gateup<TT, E, 2>(a, c, st); break;
-            case 3: e = launch_big_gateup<TT, E, 3>(a, c, st); break;
-            case 4: e = launch_big_gateup<TT, E, 4>(a, c, st); break;
-            case 5: e = launch_big_gateup<TT, E, 5>(a, c, st); break;
-            case 6: e = launch_big_gateup<TT, E, 6>(a, c, st); break;
-            case 7: e = launch_big_gateup<TT, E, 7>(a, c, st); break;
-            case 8: e = launch_big_gateup<TT, E, 8>(a, c, st); break;
-            default: e = hipErrorInvalidValue; break;
-        }
-        if (e != hipSuccess) return e;
+        if (hipError_t e = launch_big_gateup_n<TT, E>(a, c, st); e != hipSuccess) return e;
     }
     if (g_stage_mask & 2) {
-        BigGeom geo{};
-        const size_t lds = big_lds_down(c, &geo);
-        geo.by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
-        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_big<TT / 2, E, kBigDownWaves>, lds); e != hipSuccess) return e;
-        // (TT token tiles per wavefront of the 4-wavefront gate/up kernel are TT / 2 in the 8 of this one)
-        hipLaunchKernelGGL((k_down_big<TT / 2, E, kBigDownWaves>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigDownWaves * 64), lds, st, a, geo);
+        const size_t lds = big_lds_down(TT);
+        const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
+        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_big<TT, E>, lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigWaves * 64), lds, st, a, by_xcd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || a.reduce_mode == DFK_REDUCE_ATOMIC) return e;
         const size_t n4 = (size_t)a.m_count * (a.d_model / 4);
@@ -620,47 +559,19 @@ hipError_t launch_big_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st)
 
 int mfma_big_tokens_per_launch() { return kBigTokensPerLaunch; }
 
-// The gate/up kernel alone with four wavefronts of one token tile each: up to 64 tokens per launch.  Paired with
+// The gate/up kernel alone with one token tile per group: up to 64 tokens per launch.  Paired with
 // the down kernel of the 64-token pair for 33..64 tokens (config field kmajor = 3): with three or four token
 // tiles the shared weight tiles (read from L2 once per workgroup instead of once per wavefront) pay, while the
 // down kernel of this family does not yet.
-namespace {
-template <typename E, int NTC>
-hipError_t launch_gateup_64_n(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    static LdsAllowance allowed;
-    BigGeom geo{};
-    const size_t lds = big_lds_gateup(c, 1, a.d_ff, &geo);
-    if (hipError_t e = allow_lds(allowed, (const void*)k_gateup_big<1, E, NTC, 4>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_gateup_big<1, E, NTC, 4>), dim3(a.splits), dim3(256), lds, st, a, geo);
-    return hipGetLastError();
-}
-template <typename E>
-hipError_t launch_gateup_64_e(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    switch (max_slice_rows(a.d_ff, c.splits) / 8) {
-        case 1: return launch_gateup_64_n<E, 1>(a, c, st);
-        case 2: return launch_gateup_64_n<E, 2>(a, c, st);
-        case 3: return launch_gateup_64_n<E, 3>(a, c, st);
-        case 4: return launch_gateup_64_n<E, 4>(a, c, st);
-        case 5: return launch_gateup_64_n<E, 5>(a, c, st);
-        case 6: return launch_gateup_64_n<E, 6>(a, c, st);
-        case 7: return launch_gateup_64_n<E, 7>(a, c, st);
-        case 8: return launch_gateup_64_n<E, 8>(a, c, st);
-        default: return hipErrorInvalidValue;
-    }
-}
-}  // namespace
-
-// c.waves must be 4 here (the caller passes a copy of its configuration with the gate/up kernel's wavefront count)
 hipError_t launch_big_gateup_64(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     if (a.norm_w || a.m_count > 64) return hipErrorInvalidValue;
-    return a.dtype == DFK_FP16 ? launch_gateup_64_e<FP16>(a, c, st) : launch_gateup_64_e<BF16>(a, c, st);
+    return a.dtype == DFK_FP16 ? launch_big_gateup_n<1, FP16>(a, c, st) : launch_big_gateup_n<1, BF16>(a, c, st);
 }
 bool big_gateup_64_fits(const dfk_config_t& c, int d_model, int d_ff) {
     if (d_model < 128 || d_model % kKC || d_model > kMaxDModel) return false;
     if (c.depth < 3 || c.depth > 4) return false;
     if (max_slice_rows(d_ff, c.splits) / 8 > kBigMaxRowTiles) return false;
-    BigGeom geo{};
-    return big_lds_gateup(c, 1, d_ff, &geo) <= (size_t)kLdsLimit;
+    return big_lds_gateup(c, 1, d_ff) <= (size_t)kLdsLimit;
 }
 
 bool mfma_big_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
@@ -679,13 +590,18 @@ bool mfma_big_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, 
     if (c.reduce == DFK_REDUCE_ATOMIC && (size_t)tokens * d_model * 4 > kYaccBytes) return false;   // fp32 accumulator of one launch
     // (this pair's counter mode keeps one partial block per split and no group sums)
     if (c.reduce == DFK_REDUCE_TICKET && (size_t)c.k2_splits * tokens * d_model * 4 > partial_bytes(M, d_model)) return false;
-    BigGeom geo{};
-    return big_lds_gateup(c, big_token_tiles(tokens), d_ff, &geo) <= (size_t)kLdsLimit && big_lds_down(c, &geo) <= (size_t)kLdsLimit;
+    return big_lds_gateup(c, big_token_tiles(tokens), d_ff) <= (size_t)kLdsLimit && big_lds_down(big_token_tiles(tokens)) <= (size_t)kLdsLimit;
 }
 
 hipError_t launch_mfma_big(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     if (a.norm_w) return hipErrorInvalidValue;   // the normalisation is folded into the 64-token pair only
-    return big_token_tiles(a.m_count) == 2 ? launch_big_t<2>(a, c, st) : launch_big_t<4>(a, c, st);
+    switch (big_token_tiles(a.m_count)) {
+        case 1: return launch_big_t<1>(a, c, st);
+        case 2: return launch_big_t<2>(a, c, st);
+        case 3: return launch_big_t<3>(a, c, st);
+        case 4: return launch_big_t<4>(a, c, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace dfk
