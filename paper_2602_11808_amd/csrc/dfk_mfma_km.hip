@@ -80,6 +80,7 @@ struct KmStream1 {
     size_t x_base;             // byte offset of (token m_base, this wavefront's first k)
     int nt, nkc, m_count;
     unsigned k_last;           // TAIL: byte offset from this wavefront's first k to the row's last 16 bytes
+    int rot;                   // chunk the stream starts at (it runs to the end of the wavefront's run and on from its beginning)
     int tile_rows;             // weight rows between consecutive row tiles (8: gate and up rows side by side; 16: one matrix)
     int q, g;
     unsigned off1[4];
@@ -117,7 +118,7 @@ struct KmStream1 {
                 __builtin_amdgcn_global_load_lds((u < 2 ? gb : ub) + off1[u], DFK_LDS_PTR(slot + u * 1024), 16, 0,
                                                  kAuxNonTemporal);
         }
-        if (++p_idx == TT + nt) { p_idx = 0; ++p_kc; }
+        if (++p_idx == TT + nt) { p_idx = 0; if (++p_kc == nkc) p_kc = 0; }
         ++issued;
         if (++issue_slot == depth) issue_slot = 0;
     }
@@ -128,7 +129,7 @@ struct KmStream1 {
             off1[u] = (unsigned)((i & 7) * row_bytes + (q ^ i) * 16);
         }
         T = nkc * (TT + nt);
-        issued = 0; issue_slot = 0; take_slot = 0; p_kc = 0; p_idx = 0;
+        issued = 0; issue_slot = 0; take_slot = 0; p_kc = rot; p_idx = 0;
         const int ahead = min(depth - 1, T);
         for (int i = 0; i < ahead; ++i) issue();
     }
@@ -200,6 +201,13 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     ts.w_base = (size_t)j0 * ts.row_bytes + kbase;
     ts.x_base = (size_t)a.m_base * ts.row_bytes + kbase;
     ts.nt = nt; ts.nkc = c1 - c0; ts.m_count = a.m_count;
+    // Where all workgroups start at the same k, those of an XCD ask for the same X lines at once and, with rows of 32 KB and
+    // more, for weights in the same few memory channels whenever a second or third workgroup per CU starts in step with the
+    // others: gate/up kernel of 16384 x 53248 at 2 tokens 583 -> 515 us, 18432 x 16384 187 -> 179, 32768 x 8192 164 -> 158 with
+    // a start of its own per workgroup (of an XCD: workgroups b, b + 8, ...).  With three or four token tiles it is the X
+    // tiles: 46.3 -> 44.6 us at 64 tokens of 4096 x 14336, 166 -> 160 of 8192 x 28672.  At 32 tokens or less and rows below
+    // 32 KB nothing or 1 to 2 % worse (8192 x 28672 at 1 token 139 -> 141 us).
+    ts.rot = !DOWN_T && ts.nkc > 1 && (TT >= 3 || a.d_model >= 16384) ? (int)(((unsigned)wg >> 3) % (unsigned)ts.nkc) : 0;
     ts.q = q; ts.g = g;
     ts.k_last = (unsigned)(ts.row_bytes - 16 - kbase);
     ts.ring = lds + wave * geo.depth * kTileBytes;
@@ -229,7 +237,8 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    for (int kc = 0; kc < ts.nkc; ++kc) {
+    for (int step = 0; step < ts.nkc; ++step) {
+        const int kc = ts.rot + step < ts.nkc ? ts.rot + step : ts.rot + step - ts.nkc;
         // TAIL: this lane's k groups 4c + g of the chunk that hold real k (both operands of the others are zeroed: a
         // weight that is not finite must not meet a zero)
         const int kgroups = TAIL ? (kdim - (c0 + kc) * kKC) >> 3 : 16;
