@@ -99,6 +99,10 @@ dfk_status_t check(const void* X, const void* Wg, const void* Wu, const void* Wd
 // the single launch that holds both kernels' workgroups: variant FUSED, but partial sums and stages of the pair
 bool roles_launch(const dfk_config_t& c) { return c.variant == DFK_VARIANT_FUSED && c.path == DFK_PATH_MFMA && c.kmajor == 4; }
 
+// Down kernels of the 64-token pair, untuned: d_ff splits beyond 16 cost more than the workgroups they add are worth, because
+// the end of the kernel is a chain of round trips plus the sum of the splits' blocks (one token, counter reduction:
+// 512 x 1536 with 64 splits 16.2 us per call, with 12 to 16 10.4; 896 x 4864 with 36 splits 18.6 us, with 16 15.6).
+constexpr int kFewSplits = 16;
 int clamp_splits(int want, int d_ff) { return std::max(1, std::min(want, d_ff / 8)); }
 
 dfk_config_t make_cfg(int variant, int path, int splits, int waves, int depth, int k2s, int k2c,
@@ -178,11 +182,11 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             for (int cbw : {1, 2}) {
                 if (nblk < cbw || nblk % cbw) continue;
                 const int k2c = nblk / cbw;
-                for (int grid : {256, 512})
+                for (int k2s : {std::min(kFewSplits, 256 / k2c), 256 / k2c, 512 / k2c})
                     for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})
                         for (int wd : {83, 84, 46, 48})   // wavefronts, ring depth
                             push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,
-                                          clamp_splits(std::max(1, grid / k2c), d_ff), k2c, (int)dtype, reduce, 0, 1));
+                                          clamp_splits(std::max(1, k2s), d_ff), k2c, (int)dtype, reduce, 0, 1));
             }
         // both kernels of that pair in one launch (gate/up workgroups at the head of the grid, down workgroups
         // behind them)
@@ -190,11 +194,11 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             for (int cbw : {1, 2}) {
                 if (nblk < cbw || nblk % cbw) continue;
                 const int k2c = nblk / cbw;
-                for (int grid : {256, 512})
+                for (int k2s : {std::min(kFewSplits, 256 / k2c), 256 / k2c, 512 / k2c})
                     for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})
                         for (int depth : {3, 4})
                             push(make_cfg(DFK_VARIANT_FUSED, DFK_PATH_MFMA, clamp_splits(splits, d_ff), 8, depth,
-                                          clamp_splits(std::max(1, grid / k2c), d_ff), k2c, (int)dtype, reduce, 0, 4));
+                                          clamp_splits(std::max(1, k2s), d_ff), k2c, (int)dtype, reduce, 0, 4));
             }
         // two-kernel for 33..64 tokens: gate/up kernel with workgroup-shared weight tiles and one token tile per
         // wavefront, down kernel of the pair above
@@ -213,10 +217,13 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
         if ((M > 64 || !have_km) && nblk >= 1) {
             const int k2c = nblk;
             for (int splits : {256, 512, more_splits})
-                for (int grid : {256, 512})
-                    for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})   // (waves and depth no longer change its kernels)
+                // Untuned (first in the list): at most 12 d_ff splits; more of them only add partial blocks (down kernel and
+                // sum launch, us: 1920 x 3072 at 253 tokens 26.2 with 17 splits, 23.2 with 12; 1024 x 2816 at 80 tokens
+                // 15.8 with 32, 11.9 with 12; 2304 x 9216 at 256 tokens 34.4 with 14, 31.1 with 12).
+                for (int k2s : {std::min(12, 256 / k2c), 256 / k2c, 512 / k2c})
+                    for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})   // (waves and depth do not change its kernels)
                         push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), 8, 3,
-                                      clamp_splits(std::max(1, grid / k2c), d_ff), k2c, (int)dtype, reduce, 0, 2));
+                                      clamp_splits(std::max(1, k2s), d_ff), k2c, (int)dtype, reduce, 0, 2));
         }
     }
     for (int splits : {256, 512, 1024})
@@ -275,7 +282,12 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
 // atomic reduction (no boundary between two kernels, and its 256 full-width partial sums are still cheap).  Up to
 // 64 tokens: the single launch that holds both kernels' workgroups (atomic reduction), which saves the launch
 // boundary at every token count.  Of the two-kernel forms: beyond 64 tokens the pair that takes up to 256 per
-// launch, else the pair for up to 64 tokens, then the rows-split down kernel, then the rest.
+// launch, else the pair for up to 64 tokens, then the rows-split down kernel, then the rest.  Within a form of the
+// 64-token pair: at most 16 d_ff splits of the down projection, and workgroups of two 128-column blocks from a d_model of
+// 5120 on, where that still leaves a workgroup per CU (512-byte pieces of W_down's rows, A_2 read half as often; us per
+// call with one and two blocks: 5120 x 27648 at 4 tokens 138.6 / 137.1, 8192 x 28672 at 1 token 219.4 / 215.6 and at 16
+// 222.8 / 219.0, 12288 x 49152 553 / 537, 16384 x 53248 815 / 793; below, 4096 x 14336 at 16 tokens 62.6 / 63.4 and
+// 2304 x 9216 at 8 29.0 / 30.2).
 bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out) {
     auto cands = candidates(M, d_model, d_ff, dtype);
     auto rank = [&](const dfk_config_t& c) {
@@ -289,10 +301,18 @@ bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant
             return c.reduce == DFK_REDUCE_ATOMIC && c.waves == 8 ? (M == 1 ? -3 : 3) : 4;
         return 5;
     };
+    const int nblk = (d_model + 127) / 128;
+    auto split_rank = [&](const dfk_config_t& c) {         // among configurations of one rank
+        if (c.path != DFK_PATH_MFMA || c.k2_col_blocks < 1 || (c.kmajor != 1 && c.kmajor != 4)) return 0;
+        const int width = nblk / c.k2_col_blocks, want = d_model >= 5120 ? 2 : 1;
+        return (c.k2_splits > kFewSplits ? 2 : 0) + (width != want ? 1 : 0);
+    };
     const dfk_config_t* best = nullptr;
+    std::pair<int, int> best_rank;
     for (const auto& c : cands) {
         if (want_variant != DFK_VARIANT_AUTO && c.variant != want_variant) continue;
-        if (!best || rank(c) < rank(*best)) best = &c;
+        const std::pair<int, int> r(rank(c), split_rank(c));
+        if (!best || r < best_rank) { best = &c; best_rank = r; }
     }
     if (!best) return false;
     *out = *best;

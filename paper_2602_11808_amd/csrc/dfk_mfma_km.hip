@@ -742,7 +742,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
         }
         return;
     }
-    reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid);
+    reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid, (float4*)lds);
 }
 
 template <int NW, int TT, typename E, bool TAIL = false>
