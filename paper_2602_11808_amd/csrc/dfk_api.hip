@@ -288,7 +288,7 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
 // call with one and two blocks: 5120 x 27648 at 4 tokens 138.6 / 137.1, 8192 x 28672 at 1 token 219.4 / 215.6 and at 16
 // 222.8 / 219.0, 12288 x 49152 553 / 537, 16384 x 53248 815 / 793; below, 4096 x 14336 at 16 tokens 62.6 / 63.4 and
 // 2304 x 9216 at 8 29.0 / 30.2).
-bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out) {
+bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out) {
     auto cands = candidates(M, d_model, d_ff, dtype);
     auto rank = [&](const dfk_config_t& c) {
         if (c.variant == DFK_VARIANT_TWO_KERNEL) {
@@ -316,6 +316,31 @@ bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant
     }
     if (!best) return false;
     *out = *best;
+    return true;
+}
+
+// The default is a pure function of the problem, and finding it lists and validates every candidate (5 to 25 us of host
+// time per call; a 512 x 1536 layer, whose kernels take 9 us: 18.1 us per call from Python, 10.8 without it).  Each thread
+// remembers the last ones it found, a fixed number of slots by hash of the problem.
+constexpr int kWdtVariant = -1;        // in place of a variant: W_down given as [d_model, d_ff]
+bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out) {
+    struct Slot { int M, d_model, d_ff, dtype, variant; dfk_config_t cfg; };
+    constexpr unsigned kSlots = 64;
+    static thread_local Slot slots[kSlots];          // M = 0: empty
+    const unsigned h = ((((unsigned)M * 31u + (unsigned)d_model) * 31u + (unsigned)d_ff) * 31u + (unsigned)dtype) * 31u + (unsigned)want_variant;
+    Slot& s = slots[(h ^ h >> 6 ^ h >> 12) % kSlots];
+    if (s.M != M || s.d_model != d_model || s.d_ff != d_ff || s.dtype != (int)dtype || s.variant != want_variant) {
+        dfk_config_t c;
+        if (want_variant == kWdtVariant) {
+            const auto cands = candidates_wdt(M, d_model, d_ff, dtype);
+            if (cands.empty()) return false;
+            c = cands[0];
+        } else if (!enumerate_default(M, d_model, d_ff, dtype, want_variant, &c)) {
+            return false;
+        }
+        s.M = M; s.d_model = d_model; s.d_ff = d_ff; s.dtype = (int)dtype; s.variant = want_variant; s.cfg = c;
+    }
+    *out = s.cfg;
     return true;
 }
 
@@ -363,10 +388,7 @@ bool choose_wdt(int M, int d_model, int d_ff, dfk_dtype_t dtype, dfk_config_t* o
         return true;
     }
     if (tuned) *tuned = 0;
-    auto cands = candidates_wdt(M, d_model, d_ff, dtype);
-    if (cands.empty()) return false;
-    *out = cands[0];
-    return true;
+    return heuristic(M, d_model, d_ff, dtype, kWdtVariant, out);
 }
 
 bool choose(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out,
