@@ -174,6 +174,11 @@ __device__ __forceinline__ float acc_take(float* p) {
     return __hip_atomic_exchange(p, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Two adjacent floats (p a multiple of 8 bytes) in one exchange.
+__device__ __forceinline__ unsigned long long acc_take2(float* p) {
+    return __hip_atomic_exchange((unsigned long long*)p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Arrival counter: returns true for the last of `expected` arrivals, and resets
 // the counter for the next call.  The caller orders its published stores before
 // it (drain_own_memory_ops in every wavefront, then a workgroup barrier).
@@ -271,6 +276,50 @@ __device__ __forceinline__ void store4_plus(void* Y, const void* resid, size_t i
     float r[4];
     E::load4(resid, i, r);
     E::store4(Y, i, v.x + r[0], v.y + r[1], v.z + r[2], v.w + r[3]);
+}
+
+// End of the atomic reduction: the last workgroup to arrive takes columns [c_lo, c_lo + width) (even numbers) of the
+// launch's tokens out of the accumulator, leaving zero, and stores them as Y.  An exchange is a round trip to the
+// memory side; every thread issues eight of them, two floats each, before it looks at the first.  One at a time, as the
+// plain loop did it, 64 tokens of a 128-column block were sixteen of these one after the other for
+// each thread: single launch of both kernels' workgroups, 4096 x 14336 at 64 tokens 78.6 -> 75.8 us, 8192 x 7168 at 33 tokens
+// 72.7 -> 70.8, and of the one with A_2 in LDS at one token 59.9 -> 59.3.  Up to 16 tokens two do, in a form of few
+// instructions (they are met out of a cold instruction cache).
+template <typename E, int NTHREADS, int BATCH>
+__device__ __forceinline__ void drain_accumulator_by(const MlpArgs& a, int c_lo, int width) {
+    const int half = width / 2, total = a.m_count * half;
+    for (int base = threadIdx.x; base < total; base += BATCH * NTHREADS) {
+        unsigned long long v[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int idx = base + u * NTHREADS;
+            if (idx < total) {
+                const int m = idx / half, c2 = idx - m * half;
+                v[u] = acc_take2(a.yacc + (size_t)m * a.d_model + c_lo + 2 * c2);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int idx = base + u * NTHREADS;
+            if (idx < total) {
+                const int m = idx / half, c2 = idx - m * half;
+                const size_t o = (size_t)(a.m_base + m) * a.d_model + c_lo + 2 * c2;
+                float v0 = __uint_as_float((uint32_t)v[u]), v1 = __uint_as_float((uint32_t)(v[u] >> 32));
+                if (a.resid) {
+                    float r0, r1;
+                    E::widen2(*(const uint32_t*)((const uint16_t*)a.resid + o), r0, r1);
+                    v0 += r0; v1 += r1;
+                }
+                *(uint32_t*)((uint16_t*)a.Y + o) = E::pack2(v0, v1);
+            }
+        }
+    }
+}
+
+template <typename E, int NTHREADS>
+__device__ __forceinline__ void drain_accumulator(const MlpArgs& a, int c_lo, int width) {
+    if (a.m_count * (width / 2) <= 2 * NTHREADS) drain_accumulator_by<E, NTHREADS, 2>(a, c_lo, width);
+    else drain_accumulator_by<E, NTHREADS, 8>(a, c_lo, width);
 }
 
 // Last step of a one-level reduction with at most half as many outputs (float4s) as threads: the blocks are divided among

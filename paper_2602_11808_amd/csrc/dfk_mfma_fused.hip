@@ -296,12 +296,7 @@ __global__ __launch_bounds__(NW * 64) void k_fused_local(MlpArgs a, LocalGeom ge
     __syncthreads();
     DFK_STAMP(6);
     if (!flag) return;
-    for (int idx = tid; idx < a.m_count * (a.d_model / 2); idx += NTHREADS) {
-        const int m = idx / (a.d_model / 2), c2 = idx - m * (a.d_model / 2);
-        float* src = a.yacc + (size_t)m * a.d_model + 2 * c2;
-        const float v0 = acc_take(src), v1 = acc_take(src + 1);
-        *(uint32_t*)((uint16_t*)a.Y + (size_t)(a.m_base + m) * a.d_model + 2 * c2) = E::pack2(v0, v1);
-    }
+    drain_accumulator<E, NTHREADS>(a, 0, a.d_model);
     DFK_STAMP(7);
 }
 

@@ -728,18 +728,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
         if (tid == 0) flag = arrive_last(a.tickets + cb, (unsigned)a.k2_splits) ? 1 : 0;
         __syncthreads();
         if (!flag) return;
-        for (int idx = tid; idx < a.m_count * (width / 2); idx += NTHREADS) {
-            const int m = idx / (width / 2), c2 = idx - m * (width / 2);
-            float* src = a.yacc + (size_t)m * a.d_model + blk_lo * 128 + 2 * c2;
-            float v0 = acc_take(src), v1 = acc_take(src + 1);
-            const size_t o = (size_t)(a.m_base + m) * a.d_model + blk_lo * 128 + 2 * c2;
-            if (a.resid) {
-                float r0, r1;
-                E::widen2(*(const uint32_t*)((const uint16_t*)a.resid + o), r0, r1);
-                v0 += r0; v1 += r1;
-            }
-            *(uint32_t*)((uint16_t*)a.Y + o) = E::pack2(v0, v1);
-        }
+        drain_accumulator<E, NTHREADS>(a, blk_lo * 128, width);
         return;
     }
     reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid, (float4*)lds);
