@@ -77,6 +77,13 @@ __device__ __forceinline__ void wait_vm_const() {
     asm volatile("" ::: "memory");
 }
 
+// A lane's offset from a scalar base, kept as the 32 bits it is: hoisted out of the loop as a 64-bit value it takes twice the
+// registers and a 64-bit add per load instead of the load's own scalar base.
+__device__ __forceinline__ unsigned keep32(unsigned o) {
+    asm("" : "+v"(o));
+    return o;
+}
+
 // This lane's byte offset of its MFMA operand within a tile: row q, the 16-byte piece of k group g of half kh.
 __device__ __forceinline__ int big_operand_off(int q, int g, int kh) { return q * 128 + (((4 * kh + g) ^ (q >> 1)) & 7) * 16; }
 
@@ -132,7 +139,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         auto source = [&](int step) { return src + (size_t)(step + rot < nsteps ? step + rot : step + rot - nsteps) * (kBigStepK * 2); };
         auto load = [&](const char* p, unsigned char* dst, int i) {
             const unsigned o = W ? off + 16u * i * rb + place : min(off + 8u * i * rb, off_last) + (place ^ (i & 1 ? 64u : 0u));
-            __builtin_amdgcn_global_load_lds(p + o, DFK_LDS_PTR(dst + i * (W ? 2 * kBigTile : 1024)), 16, 0, W ? kAuxNonTemporal : 0);
+            __builtin_amdgcn_global_load_lds(p + keep32(o), DFK_LDS_PTR(dst + i * (W ? 2 * kBigTile : 1024)), 16, 0, W ? kAuxNonTemporal : 0);
         };
         for (int s = 0; s < nb && s < nsteps; ++s)
 #pragma unroll
@@ -292,24 +299,32 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
     // Loads per step: wavefronts 0..3 take row u = wave of the four 4 KB tiles (32-row block b, half h) of W_down: rows
     // 32 b + 4 h + 8 g + u of the step, 256 bytes each; 4..7 the two loads of each token tile of their group
     // (A_2: 64 rows = one cache line per token).  Rows past the split are any valid address (zeroed at use).
-    auto steps = [&](auto is_w) {
-        constexpr bool W = decltype(is_w)::value;
+    auto steps = [&](auto is_w, auto ragged_) {
+        constexpr bool W = decltype(is_w)::value, RAGGED = decltype(ragged_)::value;
         constexpr int SLOTS = W ? 4 : 2 * TT;
         constexpr int nb = W ? nbw : nbx;
-        const char* const src = W ? (const char*)a.Wd + (size_t)cb * 256 + 16 * q : (const char*)a.a2 + ((size_t)a.m_base * a.d_ff + j0) * 2;
+        const char* const src = W ? (const char*)a.Wd + (size_t)cb * 256 : (const char*)a.a2 + ((size_t)a.m_base * a.d_ff + j0) * 2;
         // A_2: byte offsets of the first token's row and of the last that exists (256 tokens x 2 d_ff bytes: below 4 GiB)
         const unsigned a2_row = (unsigned)a.d_ff * 2u;
         const unsigned off = (unsigned)(tile0 * 16 + prow) * a2_row, off_last = (unsigned)(a.m_count - 1) * a2_row;
         unsigned char* const dst0 = W ? lds + w_off + wave * 1024 : lds + tile0 * kBigTile;
         constexpr int buf_bytes = W ? w_step : x_step;
         auto first_row = [&](int step) { return (step + rot < nsteps ? step + rot : step + rot - nsteps) * kBigStepK; };
+        // A step's address is scalar but for offsets that do not change, unless the split's last step is partial.
+        unsigned lane_off[SLOTS];
+#pragma unroll
+        for (int i = 0; i < SLOTS; ++i)
+            lane_off[i] = W ? (unsigned)(((i >> 1) * 32 + (i & 1) * 4 + 8 * g + wave) * row_bytes) + 16u * q
+                            : min(off + (unsigned)(8 * i) * a2_row, off_last) + (unsigned)(((piece ^ (((i & 1) * 8 + prow) >> 1)) & 7) * 16);
         auto load = [&](int r0, unsigned char* dst, int i) {
             if (W) {
-                const int row = min(j0 + r0 + (i >> 1) * 32 + (i & 1) * 4 + 8 * g + wave, a.d_ff - 1);
-                __builtin_amdgcn_global_load_lds(src + (size_t)row * row_bytes, DFK_LDS_PTR(dst + i * kTileBytes), 16, 0, kAuxNonTemporal);
+                const char* p = RAGGED ? src + (size_t)min(j0 + r0 + (i >> 1) * 32 + (i & 1) * 4 + 8 * g + wave, a.d_ff - 1) * row_bytes + 16 * q
+                                       : src + (size_t)(j0 + r0) * row_bytes + keep32(lane_off[i]);
+                __builtin_amdgcn_global_load_lds(p, DFK_LDS_PTR(dst + i * kTileBytes), 16, 0, kAuxNonTemporal);
             } else {
-                const int j = min(r0 + 8 * ((piece ^ (((i & 1) * 8 + prow) >> 1)) & 7), rows - 8);
-                __builtin_amdgcn_global_load_lds(src + (min(off + (unsigned)(8 * i) * a2_row, off_last) + (unsigned)j * 2u), DFK_LDS_PTR(dst + i * 1024), 16, 0, 0);
+                const char* p = RAGGED ? src + min(off + (unsigned)(8 * i) * a2_row, off_last) + (size_t)min(r0 + 8 * ((piece ^ (((i & 1) * 8 + prow) >> 1)) & 7), rows - 8) * 2
+                                       : src + (size_t)r0 * 2 + keep32(lane_off[i]);
+                __builtin_amdgcn_global_load_lds(p, DFK_LDS_PTR(dst + i * 1024), 16, 0, 0);
             }
         };
         for (int s = 0; s < nb && s < nsteps; ++s)
@@ -339,7 +354,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
             const int r0 = first_row(more ? s + nb : 0);
             unsigned char* dst = dst0 + freebuf * buf_bytes;
             const int here = first_row(s);
-            if (here + kBigStepK > rows && here + kh * 32 + 8 * g >= rows) {   // this lane's eight rows are past the split: they contribute nothing
+            if (RAGGED && here + kBigStepK > rows && here + kh * 32 + 8 * g >= rows) {   // this lane's eight rows are past the split: they contribute nothing
 #pragma unroll
                 for (int r = 0; r < 8; ++r) w[cur][r] = u32x4{0, 0, 0, 0};
 #pragma unroll
@@ -372,8 +387,13 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
         }
         if (s < nsteps) step(s, std::integral_constant<int, 0>{});
     };
-    if (kh == 0) steps(std::true_type{});
-    else steps(std::false_type{});
+    if (rows % kBigStepK == 0) {       // whole steps only: no clamped addresses, nothing to zero
+        if (kh == 0) steps(std::true_type{}, std::false_type{});
+        else steps(std::false_type{}, std::false_type{});
+    } else {
+        if (kh == 0) steps(std::true_type{}, std::true_type{});
+        else steps(std::false_type{}, std::true_type{});
+    }
     DFK_STAMP(4);
 
     // D tile (column tile c, token tile tt): lane (q, g) holds tokens 4g .. 4g+3 of the tile, column
