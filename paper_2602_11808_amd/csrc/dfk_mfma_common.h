@@ -16,6 +16,7 @@ constexpr int kTileBytes = 4096;   // one ring slot = 4 global->LDS instructions
 constexpr int kKC = 128;           // k extent of a stage-one tile
 constexpr int kLdsLimit = 160 * 1024 - 256;   // dynamic part; a few static words (flags) come on top
 constexpr int kAuxNonTemporal = 2;  // cache-policy bit "nt": the weight stream is read once
+constexpr int kAuxDeviceScope = 16; // cache-policy bit "sc1": a load of device scope, which reads past lines this XCD's caches hold
 
 
 

@@ -394,7 +394,8 @@ __global__ __launch_bounds__(NW * 64) void k_down_t_km(MlpArgs a, KmGeom geo) {
 // ---------------------------------------------------------------- down kernel
 // TAIL: d_model is no multiple of 128 (any multiple of 8).  The last column block's 16-byte pieces past the row's end
 // are fetched from its last 16 bytes: columns are independent of each other, and those are never stored.
-template <int NW, int TT, bool TAIL>
+// COHERENT: A_2 is being written by workgroups of the same launch, on any XCD, while this one runs.
+template <int NW, int TT, bool TAIL, bool COHERENT>
 struct KmStream2 {
     // A_2 travels in tiles of 64 d_ff rows x 32 tokens: per token 128 contiguous bytes, one whole cache line per
     // request (a 32-row tile would be 64-byte pieces, twice the requests for the same bytes).  One tile serves
@@ -430,7 +431,7 @@ struct KmStream2 {
                 const int token = min(min(tl, 16 * TT - 1), m_count - 1);
                 const int j = min(jb0 * 32 + 8 * chunk, rows - 8);   // past the split: any valid address (masked at use)
                 const char* src = A2 + a2_base + (size_t)token * a2_row_bytes + (size_t)j * 2;
-                __builtin_amdgcn_global_load_lds(src, DFK_LDS_PTR(slot + u * 1024), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds(src, DFK_LDS_PTR(slot + u * 1024), 16, 0, COHERENT ? kAuxDeviceScope : 0);
             }
         } else {
             const int wi = p_idx - (p_idx > a_pos ? NA : 0);   // index among the pair's weight tiles
@@ -497,7 +498,11 @@ __host__ __device__ constexpr int km_col_blocks(int tt) { return tt >= 3 ? 1 : 2
 //
 // WAIT (the single launch of both kernels' workgroups): the stream carries the A tile of a 32-row block behind the
 // first column block's weight tiles and starts with those alone; then the workgroup waits until every gate/up
-// workgroup has counted itself done, drops what its caches hold of A_2's lines, and goes on as the kernel does.
+// workgroup of its rows has counted itself done, and goes on as the kernel does, but with A_2 loads of device scope:
+// workgroups of other XCDs wrote parts of the lines this XCD's caches may hold.  (The writers store with device scope and
+// count themselves once the stores are acknowledged.)  With one invalidation of the caches per workgroup after the wait
+// instead, and plain loads: 60.7 us where this takes 60.0 at one token of 4096 x 14336, 28.9 / 28.3 at 8 of 2304 x 9216, 71.1 /
+// 70.3 at 33 of 8192 x 7168; equal at 64 tokens of 8192 x 28672, where the 64 column blocks re-read the most.
 template <int NW, int TT, typename E, bool WAIT, bool TAIL = false>
 __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds) {
     __shared__ int flag;
@@ -518,7 +523,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
     const int jb_lo = (int)((long long)njb_all * wave / NW);
     const int njb = (int)((long long)njb_all * (wave + 1) / NW) - jb_lo;
 
-    KmStream2<NW, TT, TAIL> ts;
+    KmStream2<NW, TT, TAIL, WAIT> ts;
     ts.Wd = (const char*)a.Wd; ts.A2 = (const char*)a.a2;
     ts.row_bytes = (size_t)a.d_model * 2;
     ts.a2_row_bytes = (size_t)a.d_ff * 2;
@@ -550,8 +555,6 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
                     if (++polls > geo.role_spin_limit) { ok = 0; break; }
                     __builtin_amdgcn_s_sleep(8);
                 }
-                // gate/up workgroups of other XCDs wrote parts of lines this XCD's L2 may hold: drop them
-                acquire_device();
                 flag = ok;
             }
             __syncthreads();
@@ -580,7 +583,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
         u32x4 av[2][TT];       // A operands of the pair's two blocks: A_2[token q of tile tt][rows 8g .. 8g+7 of the block]
         auto take_a = [&]() {
 #pragma unroll
-            for (int half = 0; half < KmStream2<NW, TT, TAIL>::NA; ++half) {
+            for (int half = 0; half < KmStream2<NW, TT, TAIL, WAIT>::NA; ++half) {
                 const unsigned char* slot = ts.acquire();
 #pragma unroll
                 for (int t2 = 0; t2 < 2; ++t2) {
