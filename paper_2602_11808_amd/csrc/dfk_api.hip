@@ -231,10 +231,16 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             push(make_cfg(DFK_VARIANT_FUSED, DFK_PATH_VALU, clamp_splits(splits, d_ff), waves, 0, 0, 0,
                           a2dt));
     const int nchunk = d_model / (dtype == DFK_FP32 ? 4 : 8);
+    // The first of these is the untuned two-kernel form: the fewest d_ff splits whose down kernel has at least 160
+    // workgroups.  A workgroup's loads in flight are what paces it, so too few leave most of the chip waiting (half inputs, 8
+    // tokens of 2888 x 7688, five column blocks: 197 us with 8 splits, 103 with 16, 62 with 32; fp32, eleven: 128, 71, 75).
+    const int max_cb = std::max(1, nchunk / 64);
+    int k2_first = 8;
+    while (k2_first < 64 && k2_first * std::min(max_cb, 512 / k2_first) < 160) k2_first *= 2;
     for (int splits : {512, 1024})
-        for (int k2s : {8, 16, 32}) {
+        for (int k2s : {k2_first, 8, 16, 32}) {
             const int k2 = clamp_splits(k2s, d_ff);
-            const int cb = std::max(1, std::min(nchunk / 64 > 0 ? nchunk / 64 : 1, std::max(1, 512 / k2)));
+            const int cb = std::max(1, std::min(max_cb, std::max(1, 512 / k2)));
             push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_VALU, clamp_splits(splits, d_ff), 8, 0, k2,
                           cb, a2dt));
         }
