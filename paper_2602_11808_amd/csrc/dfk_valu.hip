@@ -10,6 +10,8 @@
 // W_down and accumulates A_2[m,j] * W_down[j, chunk] over the slice's rows.
 // The slice's fp32 partial Y is published to the workspace and is
 // combined by the two-level arrival-counter reduction (reduce_store).
+#include <algorithm>
+
 #include "dfk_device.h"
 #include "dfk_internal.h"
 
@@ -99,6 +101,60 @@ __device__ __forceinline__ void stage2_valu(const MlpArgs& a, int j0, int rows, 
     }
 }
 
+// The same where the columns are at most half as many chunks as the workgroup has threads: the rows are divided among
+// `groups` threads per chunk, whose sums meet in LDS one token at a time (the space of A_2, free by then) and are
+// added in order.  With one thread per chunk the down kernel's narrow column blocks left most of the workgroup idle (72 of 512
+// threads on a 2888-wide layer): it waits on loads, 62 -> 46 us at 8 tokens of 2888 x 7688 in half (240 rows per split), call
+// in fp32 at 4 of 4096 x 14336 224 -> 181.  Below about 100 rows the sums in LDS cost more than that saves (24 rows of 520 x 1536,
+// 4 tokens: 23 us per call without, 26 with).
+constexpr int kRowGroupRows = 96;
+template <typename E, int MT>
+__device__ __forceinline__ void stage2_valu_rows(const MlpArgs& a, int j0, int rows, int mt, int p,
+                                                 float* a2s, int a2_stride, int c_lo, int c_hi) {
+    constexpr int VEC = E::VEC;
+    const int nchunk = a.d_model / VEC, ncol = c_hi - c_lo;
+    const int groups = (int)blockDim.x / ncol;
+    const int group = threadIdx.x / ncol, col = threadIdx.x - group * ncol, c = c_lo + col;
+    float acc[MT][VEC];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[m][v] = 0.f;
+    if (group < groups) {
+#pragma unroll 4
+        for (int j = group; j < rows; j += groups) {
+            float w[VEC];
+            E::widen(ld16_stream(a.Wd, (size_t)(j0 + j) * nchunk + c), w);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const float s = a2s[m * a2_stride + j];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[m][v] = fmaf(s, w[v], acc[m][v]);
+            }
+        }
+    }
+    float4* red = (float4*)a2s;          // [group][col][VEC / 4]
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        if (m < mt) {
+            __syncthreads();             // A_2, or the token before, has been read
+            if (group < groups) {
+#pragma unroll
+                for (int v = 0; v < VEC; v += 4) red[(size_t)threadIdx.x * (VEC / 4) + v / 4] = make_float4(acc[m][v], acc[m][v + 1], acc[m][v + 2], acc[m][v + 3]);
+            }
+            __syncthreads();
+            for (int x = threadIdx.x; x < ncol * (VEC / 4); x += blockDim.x) {
+                float4 s = red[x];
+                for (int g = 1; g < groups; ++g) {
+                    const float4 t = red[(size_t)g * ncol * (VEC / 4) + x];
+                    s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+                }
+                store4_device(a.P + ((size_t)p * a.m_count + m) * a.d_model + (size_t)c_lo * VEC + 4 * x, s.x, s.y, s.z, s.w);
+            }
+        }
+    }
+}
+
 template <typename E, int MT>
 __global__ __launch_bounds__(512) void k_fused_valu(MlpArgs a, int a2_stride) {
     extern __shared__ float a2s[];
@@ -155,7 +211,8 @@ __global__ __launch_bounds__(512) void k_down_valu(MlpArgs a, int a2_stride) {
         a2s[m * a2_stride + r] = v;
     }
     __syncthreads();
-    stage2_valu<E, MT>(a, j0, rows, a.m_count, js, a2s, a2_stride, c_lo, c_hi);
+    if (2 * (c_hi - c_lo) <= (int)blockDim.x && rows >= kRowGroupRows) stage2_valu_rows<E, MT>(a, j0, rows, a.m_count, js, a2s, a2_stride, c_lo, c_hi);
+    else stage2_valu<E, MT>(a, j0, rows, a.m_count, js, a2s, a2_stride, c_lo, c_hi);
     reduce_store<E>(plan_column_block(a, cb, c_lo * E::VEC, c_hi * E::VEC), a.Y, a.m_base, &flag);
 }
 
@@ -235,8 +292,9 @@ hipError_t launch_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
         return hipGetLastError();
     }
     const int s2 = max_slice_rows(a.d_ff, a.k2_splits);
-    hipLaunchKernelGGL((k_down_valu<E, MT>), dim3(a.k2_splits * a.k2_col_blocks), dim3(threads),
-                       (size_t)MT * s2 * sizeof(float), st, a, s2);
+    // A_2 of the split's rows, then the row groups' sums of one token (16 bytes per thread and four columns of a chunk)
+    const size_t lds = std::max((size_t)MT * s2 * sizeof(float), (size_t)threads * E::VEC * sizeof(float));
+    hipLaunchKernelGGL((k_down_valu<E, MT>), dim3(a.k2_splits * a.k2_col_blocks), dim3(threads), lds, st, a, s2);
     return hipGetLastError();
 }
 
