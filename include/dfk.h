@@ -112,7 +112,8 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  travel through the same LDS rings as the weight tiles instead of sitting in
  *                  registers; gate/up kernel k-major with all its row tiles accumulating in
  *                  registers); needs k2_rows_by_wave = 0 and d_model a multiple of 128 with at
- *                  least `waves` 128-k chunks (512 and up);
+ *                  least `waves` 128-k chunks (512 and up; in bf16 also any
+ *                  other multiple of 8 from 392 on, the last chunk counting as one);
  *                  0 = the first pair (activations in registers, row-tile-major);
  *                  2 = the pair that takes up to 256 tokens per launch (offered beyond 64
  *                  tokens, and at any token count where d_model rules out pair 1): the wavefronts

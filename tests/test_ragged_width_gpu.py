@@ -20,7 +20,7 @@ def _pair(M, d, ff):
 
 # one 8-wide piece in the last chunk, all but one, a few; one to four token tiles and two launches; ragged d_ff; chunk
 # counts that do and do not divide among the wavefronts; column blocks paired (an even number of them) or not
-@pytest.mark.parametrize("shape", [(1, 520, 1000), (16, 632, 1536), (17, 1016, 2056), (33, 904, 520), (48, 1032, 1000), (64, 2296, 4104),
+@pytest.mark.parametrize("shape", [(2, 392, 520), (20, 504, 1000), (1, 520, 1000), (16, 632, 1536), (17, 1016, 2056), (33, 904, 520), (48, 1032, 1000), (64, 2296, 4104),
                                    (70, 888, 2816), (12, 2888, 7688)], ids=lambda s: "M%d_d%d_ff%d" % s)
 def test_partial_last_chunk_and_column_block(shape):
     M, d, ff = shape

@@ -1,0 +1,78 @@
+"""Which kernels a problem is given to, on the host: widths that are no multiple of 128, the split counts of the untuned choice,
+and that the remembered choice is the one a fresh search finds.  No HIP call is made."""
+import threading
+
+import pytest
+
+import paper_2602_11808_amd as dfk
+
+A = 1 << 30     # fake device addresses: every call here ends before the first HIP call, or is a query
+MFMA, VALU = dfk.DFK_PATH_MFMA, dfk.DFK_PATH_VALU
+TWO, FUSED = dfk.DFK_VARIANT_TWO_KERNEL, dfk.DFK_VARIANT_FUSED
+
+
+def cands(M, d, ff, dt):
+    return [dfk.dfk_get_candidate(M, d, ff, dt, i) for i in range(dfk.dfk_num_candidates(M, d, ff, dt))]
+
+
+@pytest.mark.parametrize("d", [392, 504, 520, 632, 1000, 2888, 8200, 32760])
+@pytest.mark.parametrize("M", [1, 16, 64, 65, 256])
+def test_widths_off_128_run_on_the_matrix_cores_in_bf16_only(M, d):
+    ff = 1000
+    pick, _ = dfk.dfk_get_choice(M, d, ff, dfk.DFK_BF16)
+    assert (pick.path, pick.variant, pick.kmajor, pick.a2_dtype) == (MFMA, TWO, 1, dfk.DFK_BF16)
+    assert {c.kmajor for c in cands(M, d, ff, dfk.DFK_BF16) if c.path == MFMA} == {1}
+    for c in cands(M, d, ff, dfk.DFK_BF16):
+        assert dfk.dfk_config_valid(c, M, d, ff, dfk.DFK_BF16)
+        if c.path == MFMA:      # A_2 would be rounded to half there, which the plain-FMA pair keeps in fp32
+            h = dfk.dfk_config_t(**dict(c.as_dict(), a2_dtype=dfk.DFK_FP16))
+            assert not dfk.dfk_config_valid(h, M, d, ff, dfk.DFK_FP16)
+    for dt in (dfk.DFK_FP16, dfk.DFK_FP32):
+        assert all(c.path == VALU for c in cands(M, d, ff, dt))
+    # the plain-FMA candidates stay on offer, and so does the single launch among them
+    assert any(c.path == VALU and c.variant == FUSED for c in cands(M, d, ff, dfk.DFK_BF16))
+
+
+@pytest.mark.parametrize("d", [8, 264, 376])
+def test_narrow_widths_off_128_stay_on_the_plain_fma_kernels(d):
+    assert all(c.path == VALU for c in cands(4, d, 1000, dfk.DFK_BF16))
+
+
+def test_the_block_and_the_other_layout_refuse_what_they_refused():
+    import ctypes
+    L = dfk.lib()
+    M, d, ff = 4, 2888, 7688
+    wsb = dfk.dfk_workspace_bytes(M, d, ff)
+    p = [A + (i << 28) for i in range(7)]
+    km = next(c for c in cands(M, d, ff, dfk.DFK_BF16) if c.path == MFMA)
+    for cfg in (None, ctypes.byref(km)):
+        assert L.dfk_mlp_block(p[0], p[1], 1e-5, p[2], p[3], p[4], p[5], M, d, ff, dfk.DFK_BF16, cfg, p[6], wsb, None) == dfk.DFK_ERR_UNSUPPORTED_SHAPE
+    n = dfk.dfk_num_candidates_wdt(M, d, ff, dfk.DFK_BF16)
+    assert n and all(dfk.dfk_get_candidate_wdt(M, d, ff, dfk.DFK_BF16, i).path == VALU for i in range(n))
+
+
+@pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
+def test_split_counts_and_widths_of_the_untuned_choice(dt):
+    for M in (1, 4, 16, 32, 33, 64):
+        for d in (512, 896, 1024, 2304, 4096, 5120, 8192, 16384):
+            for ff in (1536, 9216, 28672):
+                pick, _ = dfk.dfk_get_choice(M, d, ff, dt)
+                if pick.k2_splits == 0:
+                    continue
+                assert pick.k2_splits <= 16, (M, d, ff, pick)
+                assert d // 128 // pick.k2_col_blocks == (2 if d >= 5120 and M <= 32 else 1), (M, d, ff, pick)
+    for d in (512, 1024, 2304, 4096):
+        assert dfk.dfk_get_choice(200, d, 9216, dt)[0].k2_splits <= 12
+
+
+def test_the_remembered_choice_is_what_a_new_thread_finds():
+    """More problems than a thread remembers, asked for twice in different orders, against a thread that starts from nothing."""
+    probs = [(M, d, ff, dt) for M in (1, 7, 64, 65, 256) for d in (512, 520, 896, 4096, 5120) for ff in (1536, 14336)
+             for dt in (dfk.DFK_BF16, dfk.DFK_FP16, dfk.DFK_FP32)]
+    ask = lambda q: [(dfk.dfk_get_choice(*x)[0].as_dict(), dfk.dfk_get_choice_wdt(*x)[0].as_dict()) for x in q]
+    first, again = ask(probs), ask(probs[::-1])[::-1]
+    got = []
+    t = threading.Thread(target=lambda: got.extend(ask(probs)))
+    t.start()
+    t.join()
+    assert first == again == got
