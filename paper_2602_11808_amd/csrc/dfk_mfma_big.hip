@@ -15,7 +15,7 @@
 //
 // Data movement is the asynchronous global->LDS tile load of the other MFMA kernels,
 // organised as a workgroup pipeline:
-//   * a step is 64 k: tiles of 16 rows x 128 bytes (one cache line per row), 2 KB.  In LDS the eight
+//   * a step is 64 k (or two such pieces in the gate/up kernel): tiles of 16 rows x 128 bytes (one cache line per row), 2 KB.  In LDS the eight
 //     16-byte pieces of row i sit XOR-swizzled by i / 2, so that the operand reads of 16 rows
 //     cover all banks once.
 //   * wavefronts 0..3 request the weights, 4..7 the activations.  Loads complete in issue order
@@ -51,9 +51,14 @@ constexpr size_t kL2BytesPerXcd = (size_t)4 << 20;
 // the gate/up kernel at 256 tokens of the 4096 x 14336 layer, 49 -> 66 at 128).  The weights, out of HBM, get what LDS is left,
 // up to 8.  Compile-time constants of a kernel, so that the wait of a step is one instruction with a constant count.
 constexpr int kBigXBufs = 3;
-constexpr int big_w_bufs(int TT, int w_step) {
-    return (kLdsLimit - kBigXBufs * 4 * TT * kBigTile) / w_step < 8 ? (kLdsLimit - kBigXBufs * 4 * TT * kBigTile) / w_step : 8;
+constexpr int big_w_bufs(int x_step, int w_step) {
+    return (kLdsLimit - kBigXBufs * x_step) / w_step < 8 ? (kLdsLimit - kBigXBufs * x_step) / w_step : 8;
 }
+// 64-k pieces per step of the gate/up kernel.  A step costs about 0.4 us before any multiplication; with few row tiles per slice
+// and few token tiles per group that is most of it, so two pieces share one, where LDS still holds three buffers of it (whole
+// call: 2432 x 3968 at 65 tokens 36.6 -> 32.8 us, 2560 x 3712 at 107 39.6 -> 37.0, 2304 x 8192 at 104 45.9 -> 43.1).  With one token
+// tile per group it gained 10 % at five row tiles (2304 x 9216) and lost 5 % at four (8192 x 7168), so not beyond three.
+constexpr int big_gateup_pieces(int TT, int NTC) { return (TT == 1 && NTC <= 3) || (TT == 2 && NTC <= 5) ? 2 : 1; }
 
 // s_waitcnt vmcnt(n) for a run-time n (uniform); more than 63 waits for 63.
 __device__ __forceinline__ void wait_vm_exact(int n) {
@@ -100,7 +105,8 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     int j0, j1;
     slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
     const int nt = (j1 - j0) / 8;                  // NTC or NTC - 1 (slices differ by at most one 8-row group)
-    const int nsteps = a.d_model / kBigStepK;
+    constexpr int KS = big_gateup_pieces(TT, NTC);
+    const int nsteps = a.d_model / (kBigStepK * KS);
     const size_t row_bytes = (size_t)a.d_model * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
 
@@ -117,15 +123,15 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     DFK_STAMP(0);
-    constexpr int x_step = 4 * TT * kBigTile, w_step = NTC * kBigTile;
-    constexpr int nbx = kBigXBufs, nbw = big_w_bufs(TT, w_step), w_off = nbx * x_step;
-    // The steps of a wavefront that requests N weight loads per step or (N = -1) activations: of the slice's 2 nt weight loads
+    constexpr int x_piece = 4 * TT * kBigTile, w_piece = NTC * kBigTile, x_step = KS * x_piece, w_step = KS * w_piece;
+    constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
+    // The steps of a wavefront that requests N weight loads per 64-k piece or (N = -1) activations: of the slice's 2 nt weight loads
     // (half n & 1 of row tile n / 2: the gate rows or the up rows) n = wave, wave + 4, ...; or the two loads of each token tile
     // of its group.
     auto steps = [&](auto n_) {
         constexpr int N = decltype(n_)::value;
         constexpr bool W = N >= 0;
-        constexpr int SLOTS = W ? N : 2 * TT;
+        constexpr int PER = W ? N : 2 * TT, SLOTS = KS * PER;
         constexpr int nb = W ? nbw : nbx;
         const char* const src = W ? (const char*)(wave & 1 ? a.Wu : a.Wg) + (size_t)(j0 + (wave >> 1) * 8) * row_bytes
                                   : (const char*)a.X + (size_t)a.m_base * row_bytes;
@@ -136,23 +142,28 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         const unsigned place = (unsigned)(((piece ^ (prow >> 1)) & 7) * 16) ^ (W && (wave & 1) ? 64u : 0u);
         unsigned char* const dst0 = W ? lds + w_off + (wave >> 1) * kBigTile + (wave & 1) * 1024 : lds + tile0 * kBigTile;
         constexpr int buf_bytes = W ? w_step : x_step;
-        auto source = [&](int step) { return src + (size_t)(step + rot < nsteps ? step + rot : step + rot - nsteps) * (kBigStepK * 2); };
-        auto load = [&](const char* p, unsigned char* dst, int i) {
+        auto source = [&](int step) { return src + (size_t)(step + rot < nsteps ? step + rot : step + rot - nsteps) * (KS * kBigStepK * 2); };
+        auto load = [&](const char* p, unsigned char* dst, int slot) {
+            const int u = PER ? slot / PER : 0, i = slot - u * PER;   // (constants)
             const unsigned o = W ? off + 16u * i * rb + place : min(off + 8u * i * rb, off_last) + (place ^ (i & 1 ? 64u : 0u));
-            __builtin_amdgcn_global_load_lds(p + keep32(o), DFK_LDS_PTR(dst + i * (W ? 2 * kBigTile : 1024)), 16, 0, W ? kAuxNonTemporal : 0);
+            __builtin_amdgcn_global_load_lds(p + u * (kBigStepK * 2) + keep32(o), DFK_LDS_PTR(dst + u * (W ? w_piece : x_piece) + i * (W ? 2 * kBigTile : 1024)), 16, 0,
+                                             W ? kAuxNonTemporal : 0);
         };
         for (int s = 0; s < nb && s < nsteps; ++s)
 #pragma unroll
             for (int i = 0; i < SLOTS; ++i) load(source(s), dst0 + s * buf_bytes, i);
 
-        u32x4 xk[2][TT], wv[2][NTC];               // operands of this step and of the next
+        u32x4 xk[2][KS][TT], wv[2][KS][NTC];       // operands of this step and of the next
         int xbuf = 0, wbuf = 0, freebuf = 0;
         wait_vm_exact(SLOTS * (min(nb, nsteps) - 1));
         lds_barrier();
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) xk[0][tt] = *(const u32x4*)(lds + tile0 * kBigTile + lo + tt * kBigTile);
+        for (int u = 0; u < KS; ++u) {
 #pragma unroll
-        for (int rt = 0; rt < NTC; ++rt) wv[0][rt] = *(const u32x4*)(lds + w_off + lo + rt * kBigTile);
+            for (int tt = 0; tt < TT; ++tt) xk[0][u][tt] = *(const u32x4*)(lds + u * x_piece + (tile0 + tt) * kBigTile + lo);
+#pragma unroll
+            for (int rt = 0; rt < NTC; ++rt) wv[0][u][rt] = *(const u32x4*)(lds + w_off + u * w_piece + rt * kBigTile + lo);
+        }
         auto step = [&](int s, auto cur_) {
             constexpr int cur = decltype(cur_)::value, nxt = cur ^ 1;
             // The loads of step s + 1 have landed (later ones may be in flight), and every wavefront has read step s:
@@ -170,24 +181,27 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
             // Loads, operand reads of step s + 1 and MFMAs of step s in turn: in three blocks one after the other, each of the
             // three units idles while the eight wavefronts queue for another (75 us at 256 tokens of the 4096 x 14336 layer).
 #pragma unroll
-            for (int rt = 0; rt < NTC; ++rt) {
+            for (int x = 0; x < KS * NTC; ++x) {
+                const int u = x / NTC, rt = x - u * NTC;
 #pragma unroll
-                for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma16<E>(wv[cur][rt], xk[cur][tt], acc[rt][tt]);
-                wv[nxt][rt] = *(const u32x4*)(ws + rt * kBigTile);
+                for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma16<E>(wv[cur][u][rt], xk[cur][u][tt], acc[rt][tt]);
+                wv[nxt][u][rt] = *(const u32x4*)(ws + u * w_piece + rt * kBigTile);
 #pragma unroll
-                for (int tt = rt * TT / NTC; tt < (rt + 1) * TT / NTC; ++tt) xk[nxt][tt] = *(const u32x4*)(xs + tt * kBigTile);
+                for (int tt = rt * TT / NTC; tt < (rt + 1) * TT / NTC; ++tt) xk[nxt][u][tt] = *(const u32x4*)(xs + u * x_piece + tt * kBigTile);
                 if (more) {
 #pragma unroll
-                    for (int i = rt * SLOTS / NTC; i < (rt + 1) * SLOTS / NTC; ++i) load(p, dst, i);
+                    for (int i = x * SLOTS / (KS * NTC); i < (x + 1) * SLOTS / (KS * NTC); ++i) load(p, dst, i);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (++freebuf == nb) freebuf = 0;
         };
-        for (int s = 0; s < nsteps; s += 2) {      // (an even number: d_model is a multiple of 128)
+        int s = 0;
+        for (; s + 1 < nsteps; s += 2) {
             step(s, std::integral_constant<int, 0>{});
             step(s + 1, std::integral_constant<int, 1>{});
         }
+        if (s < nsteps) step(s, std::integral_constant<int, 0>{});
     };
     constexpr int NMAX = (2 * NTC + 3) / 4;        // a weight wavefront has NMAX loads per step or one less
     if (kh == 1) steps(std::integral_constant<int, -1>{});
@@ -295,7 +309,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
 
     DFK_STAMP(3);
     constexpr int x_step = 4 * TT * kBigTile, w_step = 4 * kTileBytes;
-    constexpr int nbx = kBigXBufs, nbw = big_w_bufs(TT, w_step), w_off = nbx * x_step;
+    constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
     // Loads per step: wavefronts 0..3 take row u = wave of the four 4 KB tiles (32-row block b, half h) of W_down: rows
     // 32 b + 4 h + 8 g + u of the step, 256 bytes each; 4..7 the two loads of each token tile of their group
     // (A_2: 64 rows = one cache line per token).  Rows past the split are any valid address (zeroed at use).
@@ -505,16 +519,25 @@ DFK_INST_DOWN(1) DFK_INST_DOWN(2) DFK_INST_DOWN(3) DFK_INST_DOWN(4)
 int big_token_tiles(int m_count) { return (m_count + 63) / 64; }   // per token group
 
 // LDS of the kernels: activation and weight buffers, or what the two halves of the k range exchange at the end.
-size_t big_lds(int TT, int w_step, size_t end) {
-    const size_t bufs = (size_t)kBigXBufs * 4 * TT * kBigTile + (size_t)big_w_bufs(TT, w_step) * w_step;
-    return std::max(bufs, end);
+size_t big_lds(int x_step, int w_step, size_t end) {
+    return std::max((size_t)kBigXBufs * x_step + (size_t)big_w_bufs(x_step, w_step) * w_step, end);
 }
 size_t big_lds_gateup(const dfk_config_t& c, int TT, int d_ff) {
-    const int nt_max = max_slice_rows(d_ff, c.splits) / 8;
-    return big_lds(TT, nt_max * kBigTile, (size_t)kBigWaves * ((nt_max + 1) / 2) * TT * 1024);
+    const int nt_max = max_slice_rows(d_ff, c.splits) / 8, ks = big_gateup_pieces(TT, nt_max);
+    return big_lds(ks * 4 * TT * kBigTile, ks * nt_max * kBigTile, (size_t)kBigWaves * ((nt_max + 1) / 2) * TT * 1024);
 }
-size_t big_lds_down(int TT) { return big_lds(TT, 4 * kTileBytes, (size_t)kBigWaves * TT * 4 * 1024); }
-static_assert(big_w_bufs(4, kBigMaxRowTiles * kBigTile) >= 3 && big_w_bufs(4, 4 * kTileBytes) >= 3, "weights at least two steps ahead");
+size_t big_lds_down(int TT) { return big_lds(4 * TT * kBigTile, 4 * kTileBytes, (size_t)kBigWaves * TT * 4 * 1024); }
+constexpr bool big_buffers_fit() {
+    for (int tt = 1; tt <= 4; ++tt) {
+        if (big_w_bufs(4 * tt * kBigTile, 4 * kTileBytes) < 3) return false;
+        for (int n = 1; n <= kBigMaxRowTiles; ++n) {
+            const int ks = big_gateup_pieces(tt, n);
+            if (big_w_bufs(ks * 4 * tt * kBigTile, ks * n * kBigTile) < 3) return false;
+        }
+    }
+    return true;
+}
+static_assert(big_buffers_fit(), "weights at least two steps ahead");
 
 template <int TT, typename E, int NTC>
 hipError_t launch_big_gateup(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
