@@ -104,9 +104,10 @@ __device__ __forceinline__ void stage2_valu(const MlpArgs& a, int j0, int rows, 
 // The same where the columns are at most half as many chunks as the workgroup has threads: the rows are divided among
 // `groups` threads per chunk, whose sums meet in LDS one token at a time (the space of A_2, free by then) and are
 // added in order.  With one thread per chunk the down kernel's narrow column blocks left most of the workgroup idle (72 of 512
-// threads on a 2888-wide layer): it waits on loads, 62 -> 46 us at 8 tokens of 2888 x 7688 in half (240 rows per split), call
-// in fp32 at 4 of 4096 x 14336 224 -> 181.  Below about 100 rows the sums in LDS cost more than that saves (24 rows of 520 x 1536,
-// 4 tokens: 23 us per call without, 26 with).
+// threads on a 2888-wide layer): it waits on loads.  Down kernel: 61.5 -> 41.4 us at 8 tokens of 2888 x 7688 in half (240 rows per
+// split), 91.4 -> 45.1 in fp32 at 4 of 4096 x 14336 (whole call 225 -> 178).  With few rows the sums in LDS cost more than that
+// saves: 4 tokens of 520 x 1536 take 24.1 us per call without and 25.2 with at 24 rows, 22.5 and 21.0 at 48, 25.2 and 20.8 at 76,
+// 26.2 and 19.6 at 96.  The line stands above the break-even: with fewer rows the form has been measured on this width only.
 constexpr int kRowGroupRows = 96;
 template <typename E, int MT>
 __device__ __forceinline__ void stage2_valu_rows(const MlpArgs& a, int j0, int rows, int mt, int p,
@@ -133,7 +134,7 @@ __device__ __forceinline__ void stage2_valu_rows(const MlpArgs& a, int j0, int r
             }
         }
     }
-    float4* red = (float4*)a2s;          // [group][col][VEC / 4]
+    float4* red = (float4*)a2s;          // [group][col][VEC / 4]; the kernels declare the array with a float4's alignment
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         if (m < mt) {
@@ -157,7 +158,7 @@ __device__ __forceinline__ void stage2_valu_rows(const MlpArgs& a, int j0, int r
 
 template <typename E, int MT>
 __global__ __launch_bounds__(512) void k_fused_valu(MlpArgs a, int a2_stride) {
-    extern __shared__ float a2s[];
+    extern __shared__ __attribute__((aligned(16))) float a2s[];
     __shared__ int flag;
     int j0, j1;
     slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(512) void k_fused_valu(MlpArgs a, int a2_stride) {
 // First kernel of the two-kernel variant: A_2 slice -> workspace.
 template <typename E, int MT>
 __global__ __launch_bounds__(512) void k_gateup_valu(MlpArgs a, int a2_stride) {
-    extern __shared__ float a2s[];
+    extern __shared__ __attribute__((aligned(16))) float a2s[];
     int j0, j1;
     slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
     const int rows = j1 - j0;
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(512) void k_gateup_valu(MlpArgs a, int a2_stride) {
 // Second kernel: Y = A_2 W_down over a (d_ff split) x (column block) grid.
 template <typename E, int MT>
 __global__ __launch_bounds__(512) void k_down_valu(MlpArgs a, int a2_stride) {
-    extern __shared__ float a2s[];
+    extern __shared__ __attribute__((aligned(16))) float a2s[];
     __shared__ int flag;
     const int js = blockIdx.x / a.k2_col_blocks;
     const int cb = blockIdx.x - js * a.k2_col_blocks;
