@@ -231,9 +231,11 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             push(make_cfg(DFK_VARIANT_FUSED, DFK_PATH_VALU, clamp_splits(splits, d_ff), waves, 0, 0, 0,
                           a2dt));
     const int nchunk = d_model / (dtype == DFK_FP32 ? 4 : 8);
-    // The first of these is the untuned two-kernel form: the fewest d_ff splits whose down kernel has at least 160
-    // workgroups.  A workgroup's loads in flight are what paces it, so too few leave most of the chip waiting (half inputs, 8
-    // tokens of 2888 x 7688, five column blocks: 197 us with 8 splits, 103 with 16, 62 with 32; fp32, eleven: 128, 71, 75).
+    // The first of these is the untuned two-kernel form: the fewest d_ff splits (a power of two, 8 to 64) whose down kernel has at
+    // least 160 workgroups, or 64 splits where no count up to that has: with one or two column blocks (half inputs below a d_model of
+    // 1536, fp32 below 768).  A workgroup's loads in flight are what paces it, so too few leave most of the chip waiting; beyond, the
+    // sum of the splits' blocks costs more (down kernel, us, with 8, 16, 32 and 64 splits: half inputs, 8 tokens of 2888 x 7688, five column
+    // blocks: 105, 60.6, 41.4, 56.1; fp32, 4 tokens, eleven: 37.6, 26.8, 35.1, 40.2).
     const int max_cb = std::max(1, nchunk / 64);
     int k2_first = 8;
     while (k2_first < 64 && k2_first * std::min(max_cb, 512 / k2_first) < 160) k2_first *= 2;
