@@ -36,9 +36,10 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 }
 
 // Same with the hardware's exp2 and reciprocal (about 1 ulp each): for results that
-// are rounded to bf16 next.  exp2(+inf) -> rcp gives 0 for g << 0; no division.
+// are rounded to bf16 next.  exp2(+inf) -> rcp gives 0 for g << 0; no division.  SiLU(g) first: u * g may overflow where
+// the result does not, and an infinite product times that 0 would be NaN.
 __device__ __forceinline__ float silu_mul_fast(float g, float u) {
-    return u * g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896341f * g));
+    return u * (g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896341f * g)));
 }
 
 // ---- element traits: 16-byte vectors of the storage type -------------------
