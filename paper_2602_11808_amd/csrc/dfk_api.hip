@@ -99,10 +99,20 @@ dfk_status_t check(const void* X, const void* Wg, const void* Wu, const void* Wd
 // the single launch that holds both kernels' workgroups: variant FUSED, but partial sums and stages of the pair
 bool roles_launch(const dfk_config_t& c) { return c.variant == DFK_VARIANT_FUSED && c.path == DFK_PATH_MFMA && c.kmajor == 4; }
 
-// Down kernels of the 64-token pair, untuned: d_ff splits beyond 16 cost more than the workgroups they add are worth, because
-// the end of the kernel is a chain of round trips plus the sum of the splits' blocks (one token, counter reduction:
-// 512 x 1536 with 64 splits 16.2 us per call, with 12 to 16 10.4; 896 x 4864 with 36 splits 18.6 us, with 16 15.6).
+// d_ff splits of the 64-token pair's down kernels, untuned, with `k2c` column blocks: as a rule 16 at most, because the end of the
+// kernel is a chain of round trips plus the sum of the splits' blocks (one token, counter reduction: 512 x 1536 with 64 splits 16.2 us
+// per call, with 12 to 16 10.4; 896 x 4864 with 36 splits 18.6 us, with 16 15.6; 64 tokens: 512 x 2816 with 64 45.8, with 16 25.1; atomic
+// reduction, 1024 x 5632 at 64 tokens with 32 27.3, with 16 23.0).  Where d_ff is many times d_model, 16 splits are long and their
+// few workgroups leave most of the chip's bandwidth unused: more of them, of as many rows as the layer is wide (of twice as
+// many for the counter reduction of more than 16 tokens, whose blocks cost the most, of three quarters for the atomic one,
+// whose cost the least).  512 x 28672, counter reduction: 1 token 33.8 us with 16, 27.0 with 48, 27.5 with 64; 16 tokens 36.4, 32.6, 34.5; 64 tokens 60.2 with 16, 59.1 with 24, 70.1 with 64; 512 x 14336 at 1 token 20.7
+// with 16, 19.3 with 24, 19.8 with 64, at 64 tokens 39.7, 41.6, 55.5; atomic, at 16 tokens, 1024 x 28672 42.2 with 16, 40.0
+// with 32, 1536 x 28672 53.9 with 16, 54.4 with 18, 53.1 with 21.
 constexpr int kFewSplits = 16;
+int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
+    const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
+    return std::max(1, std::min(256 / k2c, std::max(kFewSplits, d_ff / rows)));
+}
 int clamp_splits(int want, int d_ff) { return std::max(1, std::min(want, d_ff / 8)); }
 
 dfk_config_t make_cfg(int variant, int path, int splits, int waves, int depth, int k2s, int k2c,
@@ -182,11 +192,12 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             for (int cbw : {1, 2}) {
                 if (nblk < cbw || nblk % cbw) continue;
                 const int k2c = nblk / cbw;
-                for (int k2s : {std::min(kFewSplits, 256 / k2c), 256 / k2c, 512 / k2c})
+                for (int k2s : {0, std::min(kFewSplits, 256 / k2c), 256 / k2c, 512 / k2c})     // 0: the untuned count
                     for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})
                         for (int wd : {83, 84, 46, 48})   // wavefronts, ring depth
                             push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,
-                                          clamp_splits(std::max(1, k2s), d_ff), k2c, (int)dtype, reduce, 0, 1));
+                                          clamp_splits(k2s ? k2s : few_splits(M, d_model, d_ff, k2c, reduce), d_ff), k2c, (int)dtype,
+                                          reduce, 0, 1));
             }
         // both kernels of that pair in one launch (gate/up workgroups at the head of the grid, down workgroups
         // behind them)
@@ -194,11 +205,12 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             for (int cbw : {1, 2}) {
                 if (nblk < cbw || nblk % cbw) continue;
                 const int k2c = nblk / cbw;
-                for (int k2s : {std::min(kFewSplits, 256 / k2c), 256 / k2c, 512 / k2c})
+                for (int k2s : {0, std::min(kFewSplits, 256 / k2c), 256 / k2c, 512 / k2c})
                     for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})
                         for (int depth : {3, 4})
                             push(make_cfg(DFK_VARIANT_FUSED, DFK_PATH_MFMA, clamp_splits(splits, d_ff), 8, depth,
-                                          clamp_splits(std::max(1, k2s), d_ff), k2c, (int)dtype, reduce, 0, 4));
+                                          clamp_splits(k2s ? k2s : few_splits(M, d_model, d_ff, k2c, reduce), d_ff), k2c, (int)dtype,
+                                          reduce, 0, 4));
             }
         // two-kernel for 33..64 tokens: gate/up kernel with workgroup-shared weight tiles and one token tile per
         // wavefront, down kernel of the pair above
@@ -291,7 +303,7 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
 // 64 tokens: the single launch that holds both kernels' workgroups (atomic reduction), which saves the launch
 // boundary at every token count.  Of the two-kernel forms: beyond 64 tokens the pair that takes up to 256 per
 // launch, else the pair for up to 64 tokens, then the rows-split down kernel, then the rest.  Within a form of the
-// 64-token pair: at most 16 d_ff splits of the down projection, and workgroups of two 128-column blocks from a d_model of
+// 64-token pair: as many d_ff splits of the down projection as few_splits says, and workgroups of two 128-column blocks from a d_model of
 // 5120 on, where that still leaves a workgroup per CU (512-byte pieces of W_down's rows, A_2 read half as often; us per
 // call with one and two blocks: 5120 x 27648 at 4 tokens 138.6 / 137.1, 8192 x 28672 at 1 token 219.4 / 215.6 and at 16
 // 222.8 / 219.0, 12288 x 49152 553 / 537, 16384 x 53248 815 / 793; below, 4096 x 14336 at 16 tokens 62.6 / 63.4 and
@@ -313,7 +325,8 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
     auto split_rank = [&](const dfk_config_t& c) {         // among configurations of one rank
         if (c.path != DFK_PATH_MFMA || c.k2_col_blocks < 1 || (c.kmajor != 1 && c.kmajor != 4)) return 0;
         const int width = nblk / c.k2_col_blocks, want = d_model >= 5120 ? 2 : 1;
-        return (c.k2_splits > kFewSplits ? 2 : 0) + (width != want ? 1 : 0);
+        const int few = clamp_splits(few_splits(M, d_model, d_ff, c.k2_col_blocks, c.reduce), d_ff);
+        return (c.k2_splits > few ? 4 : c.k2_splits < few ? 2 : 0) + (width != want ? 1 : 0);
     };
     const dfk_config_t* best = nullptr;
     std::pair<int, int> best_rank;

@@ -59,10 +59,27 @@ def test_split_counts_and_widths_of_the_untuned_choice(dt):
                 pick, _ = dfk.dfk_get_choice(M, d, ff, dt)
                 if pick.k2_splits == 0:
                     continue
-                assert pick.k2_splits <= 16, (M, d, ff, pick)
+                if ff <= 12 * d:
+                    assert pick.k2_splits <= 16, (M, d, ff, pick)
                 assert d // 128 // pick.k2_col_blocks == (2 if d >= 5120 and M <= 32 else 1), (M, d, ff, pick)
     for d in (512, 1024, 2304, 4096):
         assert dfk.dfk_get_choice(200, d, 9216, dt)[0].k2_splits <= 12
+
+
+@pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
+@pytest.mark.parametrize("d,ff", [(512, 14336), (512, 28672), (640, 28672), (896, 28672), (1024, 28672), (1280, 28672)])
+@pytest.mark.parametrize("M", [2, 16, 17, 64])
+def test_a_long_d_ff_over_a_narrow_layer_is_cut_into_more_splits(M, d, ff, dt):
+    """16 splits of such a layer are 900 to 1800 rows long and a quarter to a half of the CUs' worth of workgroups: up to 28 % slower than
+    more of them (512 x 28672).  No split is longer than the layer is wide (counter reduction; twice that where it adds the blocks of
+    more than 16 tokens) or three quarters of that (atomic reduction), and there are never more workgroups of the down kernel than CUs."""
+    pick, _ = dfk.dfk_get_choice(M, d, ff, dt)
+    rows = d * 3 // 4 if pick.reduce == dfk.DFK_REDUCE_ATOMIC else d * (2 if M > 16 else 1)
+    blocks = d // 128
+    assert pick.k2_splits == min(256 // blocks, max(16, ff // rows)), pick
+    block_pick = next(c for c in cands(M, d, ff, dt) if c.kmajor == 1 and c.variant == TWO and c.k2_col_blocks == blocks)
+    assert block_pick.reduce == dfk.DFK_REDUCE_TICKET      # what dfk_mlp_block takes
+    assert block_pick.k2_splits == min(256 // blocks, max(16, ff // (d * (2 if M > 16 else 1))))
 
 
 def test_the_remembered_choice_is_what_a_new_thread_finds():
