@@ -113,6 +113,24 @@ int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
     const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
     return std::max(1, std::min(256 / k2c, std::max(kFewSplits, d_ff / rows)));
 }
+// The same for the 256-token pair: 12, one per 640 rows of a longer d_ff (512 with fewer than 8 column blocks), with fewer than 10
+// and more than 128 tokens up to 16 of 320 rows and more; or the next smaller count that cuts d_ff into whole 64-row steps of the down kernel, if there is one that is not
+// much smaller (five eighths; where that makes splits of more than 1024 rows three quarters, up to 128 tokens seven eighths).  More
+// splits only add partial blocks; fewer leave CUs without a workgroup; a split with a partial last step takes the form with clamped
+// addresses and a step more, which costs the most with three or four token tiles per group.
+// Whole call, us: 1920 x 3072 at 253 tokens 44.8 with 17 splits, 41.4 with 12, 40.6 with 8; 1024 x 2816 at 80 24.2 with 32, 20.5 with 12,
+// 20.0 with 11; 2304 x 9216 at 256 68.7 with 14, 64.8 with 12; 2432 x 6656 at 256 60.6 with 12, 58.5 with 8; 1536 x 8960 at 256 53.4 with 12,
+// 49.9 with 14, 52.1 with 20; 3584 x 18944 at 256 170 with 9, 147 with 8; 6912 x 20352 at 212 266 with 4, 273 with 3; 4480 x 23040 at 68 139.9
+// with 7, 142.5 with 6; a long d_ff: 512 x 28672 at 256 83.9 with 12, 59.4 with 32, 60.0 with 64; 256 x 8192 at 1 18.8 with 8, 17.4 with 12; 1024 x 14336 at 256 57.4 with 12, 50.3 with
+// 16, 52.3 with 32; no whole steps: 1920 x 10496 at 96 46.5 with 12 or 17, 45.5 with 16; few column blocks: 1152 x 5504 at 200 38.8 with 12,
+// 37.6 with 16, 38.3 with 28, and at 128 30.7 with 12, 30.8 with 16; 2048 x 5504 at 200 46.9 with 12, 47.7 with 16.
+int big_splits(int M, int d_ff, int k2c) {
+    const int most = 256 / k2c, narrow = M > 128 && k2c < 10 ? std::min(16, d_ff / 320) : 0;
+    const int want = std::min(most, std::max({12, d_ff / (k2c < 8 ? 512 : 640), narrow}));
+    for (int k = want; 8 * k >= 5 * want; --k)
+        if (d_ff % (64 * k) == 0 && (d_ff <= 1024 * k || (M > 128 ? 4 * k > 3 * want : 8 * k >= 7 * want))) return k;
+    return want;
+}
 int clamp_splits(int want, int d_ff) { return std::max(1, std::min(want, d_ff / 8)); }
 
 dfk_config_t make_cfg(int variant, int path, int splits, int waves, int depth, int k2s, int k2c,
@@ -229,10 +247,7 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
         if ((M > 64 || !have_km) && nblk >= 1) {
             const int k2c = nblk;
             for (int splits : {256, 512, more_splits})
-                // Untuned (first in the list): at most 12 d_ff splits; more of them only add partial blocks (down kernel and
-                // sum launch, us: 1920 x 3072 at 253 tokens 26.2 with 17 splits, 23.2 with 12; 1024 x 2816 at 80 tokens
-                // 15.8 with 32, 11.9 with 12; 2304 x 9216 at 256 tokens 34.4 with 14, 31.1 with 12).
-                for (int k2s : {std::min(12, 256 / k2c), 256 / k2c, 512 / k2c})
+                for (int k2s : {big_splits(M, d_ff, k2c), std::min(12, 256 / k2c), 256 / k2c, 512 / k2c})   // the untuned count first
                     for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})   // (waves and depth do not change its kernels)
                         push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), 8, 3,
                                       clamp_splits(std::max(1, k2s), d_ff), k2c, (int)dtype, reduce, 0, 2));
@@ -308,7 +323,9 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
 // call with one and two blocks: 5120 x 27648 at 4 tokens 138.6 / 137.1, 8192 x 28672 at 1 token 219.4 / 215.6 and at 16
 // 222.8 / 219.0, 12288 x 49152 553 / 537, 16384 x 53248 815 / 793; below, 4096 x 14336 at 16 tokens 62.6 / 63.4 and
 // 2304 x 9216 at 8 29.0 / 30.2).
-bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out) {
+// `fits`: which candidates the caller can run (all of them, or those within its scratch).
+template <typename F>
+bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out, F fits) {
     auto cands = candidates(M, d_model, d_ff, dtype);
     auto rank = [&](const dfk_config_t& c) {
         if (c.variant == DFK_VARIANT_TWO_KERNEL) {
@@ -323,6 +340,10 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
     };
     const int nblk = (d_model + 127) / 128;
     auto split_rank = [&](const dfk_config_t& c) {         // among configurations of one rank
+        if (c.kmajor == 2) {
+            const int few = clamp_splits(big_splits(M, d_ff, c.k2_col_blocks), d_ff);
+            return (c.reduce == DFK_REDUCE_TICKET ? 0 : 4) + (c.k2_splits > few ? 2 : c.k2_splits < few ? 1 : 0);
+        }
         if (c.path != DFK_PATH_MFMA || c.k2_col_blocks < 1 || (c.kmajor != 1 && c.kmajor != 4)) return 0;
         const int width = nblk / c.k2_col_blocks, want = d_model >= 5120 ? 2 : 1;
         const int few = clamp_splits(few_splits(M, d_model, d_ff, c.k2_col_blocks, c.reduce), d_ff);
@@ -331,7 +352,7 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
     const dfk_config_t* best = nullptr;
     std::pair<int, int> best_rank;
     for (const auto& c : cands) {
-        if (want_variant != DFK_VARIANT_AUTO && c.variant != want_variant) continue;
+        if ((want_variant != DFK_VARIANT_AUTO && c.variant != want_variant) || !fits(c)) continue;
         const std::pair<int, int> r(rank(c), split_rank(c));
         if (!best || r < best_rank) { best = &c; best_rank = r; }
     }
@@ -356,7 +377,7 @@ bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant
             const auto cands = candidates_wdt(M, d_model, d_ff, dtype);
             if (cands.empty()) return false;
             c = cands[0];
-        } else if (!enumerate_default(M, d_model, d_ff, dtype, want_variant, &c)) {
+        } else if (!enumerate_default(M, d_model, d_ff, dtype, want_variant, &c, [](const dfk_config_t&) { return true; })) {
             return false;
         }
         s.M = M; s.d_model = d_model; s.d_ff = d_ff; s.dtype = (int)dtype; s.variant = want_variant; s.cfg = c;
@@ -710,12 +731,8 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* Wg, const void* Wu
         if (!partials_fit_static(c, M, d_model, p_bytes, q_bytes)) return DFK_ERR_WORKSPACE;
     } else {
         if (!choose(M, d_model, d_ff, dtype, DFK_VARIANT_AUTO, &c, nullptr)) return DFK_ERR_UNSUPPORTED_SHAPE;
-        if (!partials_fit_static(c, M, d_model, p_bytes, q_bytes)) {   // the first candidate that fits instead
-            bool found = false;
-            for (const auto& k : candidates(M, d_model, d_ff, dtype))
-                if (partials_fit_static(k, M, d_model, p_bytes, q_bytes)) { c = k; found = true; break; }
-            if (!found) return DFK_ERR_WORKSPACE;
-        }
+        auto fits = [&](const dfk_config_t& k) { return partials_fit_static(k, M, d_model, p_bytes, q_bytes); };
+        if (!fits(c) && !enumerate_default(M, d_model, d_ff, dtype, DFK_VARIANT_AUTO, &c, fits)) return DFK_ERR_WORKSPACE;
     }
     void* ws = nullptr;
     bool first = false;

@@ -63,7 +63,7 @@ def test_split_counts_and_widths_of_the_untuned_choice(dt):
                     assert pick.k2_splits <= 16, (M, d, ff, pick)
                 assert d // 128 // pick.k2_col_blocks == (2 if d >= 5120 and M <= 32 else 1), (M, d, ff, pick)
     for d in (512, 1024, 2304, 4096):
-        assert dfk.dfk_get_choice(200, d, 9216, dt)[0].k2_splits <= 12
+        assert dfk.dfk_get_choice(200, d, 6144, dt)[0].k2_splits <= (16 if d < 1280 else 12)
 
 
 @pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
@@ -80,6 +80,19 @@ def test_a_long_d_ff_over_a_narrow_layer_is_cut_into_more_splits(M, d, ff, dt):
     block_pick = next(c for c in cands(M, d, ff, dt) if c.kmajor == 1 and c.variant == TWO and c.k2_col_blocks == blocks)
     assert block_pick.reduce == dfk.DFK_REDUCE_TICKET      # what dfk_mlp_block takes
     assert block_pick.k2_splits == min(256 // blocks, max(16, ff // (d * (2 if M > 16 else 1))))
+
+
+@pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
+@pytest.mark.parametrize("M,d,ff,splits", [
+    (256, 512, 28672, 56), (256, 128, 28672, 56), (1, 256, 28672, 56), (1, 256, 8192, 16), (100, 1024, 14336, 16), (200, 1024, 14336, 16), (256, 2048, 11264, 16),  # a long d_ff
+    (96, 1920, 10496, 16), (128, 1152, 5504, 12), (205, 1152, 5504, 16), (200, 2048, 5504, 12), (200, 1024, 5376, 14),  # no whole steps; few column blocks
+    (256, 2304, 9216, 12), (212, 2048, 4096, 8), (231, 2304, 3456, 9), (256, 3072, 8192, 8), (256, 3584, 18944, 8), (85, 2048, 9984, 13),   # whole steps
+    (256, 1536, 8960, 14), (256, 2432, 6656, 8),
+    (128, 3200, 13312, 10), (68, 4480, 23040, 7), (212, 6912, 20352, 4),            # whole steps would leave too few workgroups
+    (239, 2816, 3712, 11), (80, 896, 2816, 11), (200, 1024, 1000, 12), (256, 4096, 14336, 8), (150, 8192, 28672, 4), (256, 32768, 8192, 1), (65, 512, 64, 8)])
+def test_split_counts_of_the_256_token_pair(M, d, ff, splits, dt):
+    pick, _ = dfk.dfk_get_choice(M, d, ff, dt)
+    assert (pick.kmajor, pick.reduce, pick.k2_splits) == (2, dfk.DFK_REDUCE_TICKET, splits)
 
 
 def test_the_remembered_choice_is_what_a_new_thread_finds():
