@@ -113,17 +113,37 @@ int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
     const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
     return std::max(1, std::min(256 / k2c, std::max(kFewSplits, d_ff / rows)));
 }
-// The same for the 256-token pair: 12, one per 640 rows of a longer d_ff (512 with fewer than 8 column blocks), with fewer than 10
-// and more than 128 tokens up to 16 of 320 rows and more; or the next smaller count that cuts d_ff into whole 64-row steps of the down kernel, if there is one that is not
-// much smaller (five eighths; where that makes splits of more than 1024 rows three quarters, up to 128 tokens seven eighths).  More
-// splits only add partial blocks; fewer leave CUs without a workgroup; a split with a partial last step takes the form with clamped
-// addresses and a step more, which costs the most with three or four token tiles per group.
-// Whole call, us: 1920 x 3072 at 253 tokens 44.8 with 17 splits, 41.4 with 12, 40.6 with 8; 1024 x 2816 at 80 24.2 with 32, 20.5 with 12,
-// 20.0 with 11; 2304 x 9216 at 256 68.7 with 14, 64.8 with 12; 2432 x 6656 at 256 60.6 with 12, 58.5 with 8; 1536 x 8960 at 256 53.4 with 12,
-// 49.9 with 14, 52.1 with 20; 3584 x 18944 at 256 170 with 9, 147 with 8; 6912 x 20352 at 212 266 with 4, 273 with 3; 4480 x 23040 at 68 139.9
-// with 7, 142.5 with 6; a long d_ff: 512 x 28672 at 256 83.9 with 12, 59.4 with 32, 60.0 with 64; 256 x 8192 at 1 18.8 with 8, 17.4 with 12; 1024 x 14336 at 256 57.4 with 12, 50.3 with
-// 16, 52.3 with 32; no whole steps: 1920 x 10496 at 96 46.5 with 12 or 17, 45.5 with 16; few column blocks: 1152 x 5504 at 200 38.8 with 12,
-// 37.6 with 16, 38.3 with 28, and at 128 30.7 with 12, 30.8 with 16; 2048 x 5504 at 200 46.9 with 12, 47.7 with 16.
+// Workgroups of the 64-token pair's down kernels, untuned, own two 128-column blocks instead of one (512-byte pieces of W_down's
+// rows, A_2 read half as often) where the layer is wide and a split then still has many rows: two blocks mean twice as many
+// splits, whose sum has to be paid for by the reading.  Time with two blocks over time with one, atomic reduction (single launch),
+// 2 to 16 tokens: 298 rows (5120 x 3584) 1.07 to 1.10, 614 (6144 x 6144) 1.00 to 1.02, 796 (7168 x 7168) 0.99 to 1.00, 930 (5888 x
+// 10240) 1.00 to 1.02, 938 (5120 x 11264) 0.96 to 0.98, 1109 (7168 x 9984) 0.98 to 0.99, 2201 (11008 x 11008) 0.96; 32 tokens: 938
+// 1.01, 1109 1.01, 1194 (10240 x 7168) 1.00, 1424 (8192 x 11392) 1.00, 2201 0.96.  Counter reduction (pair of launches, the
+// block), 1 to 16 tokens: 938 1.00 to 1.03, 1175 (5888 x 12928) 1.00 to 1.02, 1393 (7168 x 12544) 0.98 to 1.00, 2201 0.98 to 0.99,
+// 2304 (5120 x 27648, 4 tokens, whole call) 138.6 -> 137.1 us; 32 tokens: 1424 1.02, 1792 (8192 x 14336) 1.02, 2389 (10240 x
+// 14336) 1.00, 2848 (16384 x 11392) 1.00, 3584 (8192 x 28672, whole call) 235.3 -> 238.5 us, 4096 (16384 x 16384) 0.99, and where
+// splits of one block each make few workgroups 1536 (11008 x 7680, 172 of them) 0.99, 2457 (12288 x 12288, 192) 0.99.  Below a
+// d_model of 5120 it gained at most 2 % and lost as much (4608 x 10112, 722 rows: 0.99 to 1.02).
+bool two_blocks(int M, int d_model, int d_ff, int reduce) {
+    if (d_model < 5120) return false;
+    const int nblk = (d_model + 127) / 128, rows = d_ff / few_splits(M, d_model, d_ff, nblk / 2, reduce);
+    if (reduce == DFK_REDUCE_ATOMIC) return rows >= (M > 16 ? 1152 : 896);
+    const bool few = nblk * few_splits(M, d_model, d_ff, nblk, reduce) < 208;   // workgroups with one block each
+    return rows >= (M > 16 && !few ? 4096 : 1280);
+}
+// d_ff splits of the 256-token pair's down kernel, untuned: 12, one per 640 rows of a longer d_ff (512 with fewer than 8 column
+// blocks), with fewer than 10 and more than 128 tokens up to 16 of 320 rows and more; or the next smaller count that cuts d_ff
+// into whole 64-row steps of the down kernel, if there is one that is not much smaller (five eighths; where that makes splits of
+// more than 1024 rows three quarters, up to 128 tokens seven eighths).  More splits only add partial blocks; fewer leave CUs
+// without a workgroup; a split with a partial last step takes the form with clamped addresses and a step more, which costs the
+// most with three or four token tiles per group. Whole call, us: 1920 x 3072 at 253 tokens 44.8 with 17 splits, 41.4 with 12, 40.6
+// with 8; 1024 x 2816 at 80 24.2 with 32, 20.5 with 12, 20.0 with 11; 2304 x 9216 at 256 68.7 with 14, 64.8 with 12; 2432 x 6656
+// at 256 60.6 with 12, 58.5 with 8; 1536 x 8960 at 256 53.4 with 12, 49.9 with 14, 52.1 with 20; 3584 x 18944 at 256 170 with 9,
+// 147 with 8; 6912 x 20352 at 212 266 with 4, 273 with 3; 4480 x 23040 at 68 139.9 with 7, 142.5 with 6; a long d_ff: 512 x 28672
+// at 256 83.9 with 12, 59.4 with 32, 60.0 with 64; 256 x 8192 at 1 18.8 with 8, 17.4 with 12; 1024 x 14336 at 256 57.4 with 12,
+// 50.3 with 16, 52.3 with 32; no whole steps: 1920 x 10496 at 96 46.5 with 12 or 17, 45.5 with 16; few column blocks: 1152 x 5504
+// at 200 38.8 with 12, 37.6 with 16, 38.3 with 28, and at 128 30.7 with 12, 30.8 with 16; 2048 x 5504 at 200 46.9 with 12, 47.7
+// with 16.
 int big_splits(int M, int d_ff, int k2c) {
     const int most = 256 / k2c, narrow = M > 128 && k2c < 10 ? std::min(16, d_ff / 320) : 0;
     const int want = std::min(most, std::max({12, d_ff / (k2c < 8 ? 512 : 640), narrow}));
@@ -318,11 +338,7 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
 // 64 tokens: the single launch that holds both kernels' workgroups (atomic reduction), which saves the launch
 // boundary at every token count.  Of the two-kernel forms: beyond 64 tokens the pair that takes up to 256 per
 // launch, else the pair for up to 64 tokens, then the rows-split down kernel, then the rest.  Within a form of the
-// 64-token pair: as many d_ff splits of the down projection as few_splits says, and workgroups of two 128-column blocks from a d_model of
-// 5120 on, where that still leaves a workgroup per CU (512-byte pieces of W_down's rows, A_2 read half as often; us per
-// call with one and two blocks: 5120 x 27648 at 4 tokens 138.6 / 137.1, 8192 x 28672 at 1 token 219.4 / 215.6 and at 16
-// 222.8 / 219.0, 12288 x 49152 553 / 537, 16384 x 53248 815 / 793; below, 4096 x 14336 at 16 tokens 62.6 / 63.4 and
-// 2304 x 9216 at 8 29.0 / 30.2).
+// 64-token pair: splits and column blocks as few_splits and two_blocks say.
 // `fits`: which candidates the caller can run (all of them, or those within its scratch).
 template <typename F>
 bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out, F fits) {
@@ -345,7 +361,7 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
             return (c.reduce == DFK_REDUCE_TICKET ? 0 : 4) + (c.k2_splits > few ? 2 : c.k2_splits < few ? 1 : 0);
         }
         if (c.path != DFK_PATH_MFMA || c.k2_col_blocks < 1 || (c.kmajor != 1 && c.kmajor != 4)) return 0;
-        const int width = nblk / c.k2_col_blocks, want = d_model >= 5120 ? 2 : 1;
+        const int width = nblk / c.k2_col_blocks, want = two_blocks(M, d_model, d_ff, c.reduce) ? 2 : 1;
         const int few = clamp_splits(few_splits(M, d_model, d_ff, c.k2_col_blocks, c.reduce), d_ff);
         return (c.k2_splits > few ? 4 : c.k2_splits < few ? 2 : 0) + (width != want ? 1 : 0);
     };

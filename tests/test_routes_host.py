@@ -51,6 +51,19 @@ def test_the_block_and_the_other_layout_refuse_what_they_refused():
     assert n and all(dfk.dfk_get_candidate_wdt(M, d, ff, dfk.DFK_BF16, i).path == VALU for i in range(n))
 
 
+def _rows_of_two_blocks(d, ff):
+    """Rows of a d_ff split where workgroups of the down kernel own two column blocks."""
+    return ff // min(16, 256 // (d // 256))
+
+
+def _two_from(M, d, c):
+    """Rows from which on two blocks win."""
+    if c.reduce == dfk.DFK_REDUCE_ATOMIC:
+        return 1152 if M > 16 else 896
+    blocks = d // 128
+    return 4096 if M > 16 and blocks * min(16, 256 // blocks) >= 208 else 1280
+
+
 @pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
 def test_split_counts_and_widths_of_the_untuned_choice(dt):
     for M in (1, 4, 16, 32, 33, 64):
@@ -61,9 +74,23 @@ def test_split_counts_and_widths_of_the_untuned_choice(dt):
                     continue
                 if ff <= 12 * d:
                     assert pick.k2_splits <= 16, (M, d, ff, pick)
-                assert d // 128 // pick.k2_col_blocks == (2 if d >= 5120 and M <= 32 else 1), (M, d, ff, pick)
+                assert d // 128 // pick.k2_col_blocks == (2 if d >= 5120 and M <= 32 and _rows_of_two_blocks(d, ff) >= _two_from(M, d, pick) else 1), (M, d, ff, pick)
+    for M, d, ff, width in ((32, 8192, 40960, 2), (32, 5120, 40960, 1), (16, 5120, 40960, 2), (32, 11008, 40960, 2), (32, 16384, 53248, 2)):
+        pick, _ = dfk.dfk_get_choice(M, d, ff, dt)     # (slices too long for the single launch: the pair, counter reduction)
+        assert (pick.variant, pick.kmajor, pick.reduce, d // 128 // pick.k2_col_blocks) == (TWO, 1, dfk.DFK_REDUCE_TICKET, width), pick
     for d in (512, 1024, 2304, 4096):
         assert dfk.dfk_get_choice(200, d, 6144, dt)[0].k2_splits <= (16 if d < 1280 else 12)
+
+
+@pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
+@pytest.mark.parametrize("M,d,ff,width", [
+    (8, 5888, 5760, 1), (20, 5376, 7680, 1), (27, 5120, 8192, 1),       # short splits: one block
+    (16, 5120, 11264, 2), (32, 5120, 11264, 1), (16, 7168, 12544, 2), (32, 7168, 12544, 2), (4, 5120, 27648, 2), (32, 16384, 16384, 2),
+    (2, 11008, 11008, 2), (33, 16384, 16384, 1), (4, 4096, 28672, 1)])
+def test_column_blocks_of_a_workgroup(M, d, ff, width, dt):
+    """Two 128-column blocks where a split keeps enough rows (single launch, atomic reduction)."""
+    c, _ = dfk.dfk_get_choice(M, d, ff, dt)
+    assert (c.variant, c.kmajor, c.reduce, d // 128 // c.k2_col_blocks) == (FUSED, 4, dfk.DFK_REDUCE_ATOMIC, width), c
 
 
 @pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
