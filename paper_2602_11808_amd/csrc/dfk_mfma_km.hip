@@ -72,7 +72,7 @@ __host__ __device__ inline int km_norm_stride(int d_model, int waves) {
 // the row's end are fetched from its last 16 bytes instead and the operands zeroed at use.  A form of its own,
 // because the clamps cost a few VALU instructions per tile: with it a 2888 x 7688 layer takes the matrix cores, 428 ->
 // 43 us at 12 tokens in bf16 against the plain-FMA pair, which re-reads X for every weight row.
-template <int NW, int TT, bool TAIL>
+template <int NW, int TT, bool TAIL, bool ROT>
 struct KmStream1 {
     const char *Wg, *Wu, *X;
     size_t row_bytes;          // d_model * 2
@@ -95,9 +95,9 @@ struct KmStream1 {
             for (int u = 0; u < 4; ++u) {
                 const int i = 4 * u + g;
                 const int token = min(p_idx * 16 + i, m_count - 1);
-                unsigned ko = (unsigned)p_kc * (kKC * 2) + (q ^ i) * 16;
-                if (TAIL) ko = min(ko, k_last);
-                const char* src = X + x_base + (size_t)token * row_bytes + ko;
+                const char* src = X + x_base + (size_t)token * row_bytes;
+                if (TAIL) src += min((unsigned)p_kc * (kKC * 2) + (q ^ i) * 16, k_last);
+                else src += (size_t)p_kc * (kKC * 2) + ((q ^ i) * 16);
                 __builtin_amdgcn_global_load_lds(src, DFK_LDS_PTR(slot + u * 1024), 16, 0, 0);
             }
         } else if (TAIL) {     // (below, with the offset into the row clamped)
@@ -118,7 +118,7 @@ struct KmStream1 {
                 __builtin_amdgcn_global_load_lds((u < 2 ? gb : ub) + off1[u], DFK_LDS_PTR(slot + u * 1024), 16, 0,
                                                  kAuxNonTemporal);
         }
-        if (++p_idx == TT + nt) { p_idx = 0; if (++p_kc == nkc) p_kc = 0; }
+        if (++p_idx == TT + nt) { p_idx = 0; ++p_kc; if (ROT && p_kc == nkc) p_kc = 0; }
         ++issued;
         if (++issue_slot == depth) issue_slot = 0;
     }
@@ -129,7 +129,7 @@ struct KmStream1 {
             off1[u] = (unsigned)((i & 7) * row_bytes + (q ^ i) * 16);
         }
         T = nkc * (TT + nt);
-        issued = 0; issue_slot = 0; take_slot = 0; p_kc = rot; p_idx = 0;
+        issued = 0; issue_slot = 0; take_slot = 0; p_kc = ROT ? rot : 0; p_idx = 0;
         const int ahead = min(depth - 1, T);
         for (int i = 0; i < ahead; ++i) issue();
     }
@@ -189,7 +189,7 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     const int c0 = wave * nchunks / NW, c1 = (wave + 1) * nchunks / NW;
     const size_t kbase = (size_t)c0 * (kKC * 2);          // bytes into a row
 
-    KmStream1<NW, TT, TAIL> ts;
+    KmStream1<NW, TT, TAIL, !DOWN_T> ts;
     ts.row_bytes = (size_t)kdim * 2;
     if (DOWN_T) {
         ts.Wg = (const char*)a.Wd; ts.Wu = (const char*)a.Wd + 8 * ts.row_bytes; ts.X = (const char*)a.a2;
@@ -238,7 +238,7 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     for (int step = 0; step < ts.nkc; ++step) {
-        const int kc = ts.rot + step < ts.nkc ? ts.rot + step : ts.rot + step - ts.nkc;
+        const int kc = DOWN_T ? step : ts.rot + step < ts.nkc ? ts.rot + step : ts.rot + step - ts.nkc;
         // TAIL: this lane's k groups 4c + g of the chunk that hold real k (both operands of the others are zeroed: a
         // weight that is not finite must not meet a zero)
         const int kgroups = TAIL ? (kdim - (c0 + kc) * kKC) >> 3 : 16;
