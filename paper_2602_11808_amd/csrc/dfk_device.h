@@ -292,11 +292,11 @@ __device__ __forceinline__ void store4_plus(void* Y, const void* resid, size_t i
 
 // End of the atomic reduction: the last workgroup to arrive takes columns [c_lo, c_lo + width) (even numbers) of the
 // launch's tokens out of the accumulator, leaving zero, and stores them as Y.  An exchange is a round trip to the
-// memory side; every thread issues eight of them, two floats each, before it looks at the first.  One at a time, as the
-// plain loop did it, 64 tokens of a 128-column block were sixteen of these one after the other for
-// each thread: single launch of both kernels' workgroups, 4096 x 14336 at 64 tokens 78.6 -> 75.8 us, 8192 x 7168 at 33 tokens
-// 72.7 -> 70.8, and of the one with A_2 in LDS at one token 59.9 -> 59.3.  Up to 16 tokens two do, in a form of few
-// instructions (they are met out of a cold instruction cache).
+// memory side, of two floats: a thread issues BATCH of them before it looks at the first.  One at a time, as the plain loop did
+// it, 64 tokens of a 128-column block were sixteen of these one after the other for each thread: single launch of both kernels'
+// workgroups, 4096 x 14336 at 64 tokens 78.6 -> 75.8 us, 8192 x 7168 at 33 tokens 72.7 -> 70.8, and of the one with A_2 in LDS at one
+// token 59.9 -> 59.3.  Eight of them, or two in a form of few instructions (they are met out of a cold instruction cache) where
+// that covers the block: tokens x columns at most four per thread, so up to 16 tokens of 128 columns with 512 threads, 8 of 256.
 template <typename E, int NTHREADS, int BATCH>
 __device__ __forceinline__ void drain_accumulator_by(const MlpArgs& a, int c_lo, int width) {
     const int half = width / 2, total = a.m_count * half;
@@ -328,9 +328,10 @@ __device__ __forceinline__ void drain_accumulator_by(const MlpArgs& a, int c_lo,
     }
 }
 
+__host__ __device__ inline bool drain_is_small(const MlpArgs& a, int width, int nthreads) { return a.m_count * (width / 2) <= 2 * nthreads; }
 template <typename E, int NTHREADS>
 __device__ __forceinline__ void drain_accumulator(const MlpArgs& a, int c_lo, int width) {
-    if (a.m_count * (width / 2) <= 2 * NTHREADS) drain_accumulator_by<E, NTHREADS, 2>(a, c_lo, width);
+    if (drain_is_small(a, width, NTHREADS)) drain_accumulator_by<E, NTHREADS, 2>(a, c_lo, width);
     else drain_accumulator_by<E, NTHREADS, 8>(a, c_lo, width);
 }
 
