@@ -230,7 +230,7 @@ dfk_status_t dfk_transpose_w_down(const void* W_down, void* W_down_t, int d_mode
  * in an array that is part of the library's code object: 48 MiB per device, held from the moment
  * the library is loaded on that device until the process ends.  No call allocates or frees anything.
  * Arguments as dfk_swiglu_mlp_ex without the workspace; cfg == NULL takes the scheduler's choice, or,
- * if its partial sums do not fit the array, the first candidate that fits.
+ * if its partial sums do not fit the array, the best-ranked candidate that fits.
  * Limits: M * d_ff * 4 (A_2) at most 16 MiB, and the partial-sum blocks of the configuration within
  * what is left (about 21 MiB; the atomic reduction needs none).  Beyond them: DFK_ERR_WORKSPACE,
  * before any launch.  The first call on a device resolves the array's address and enqueues a fill

@@ -70,8 +70,8 @@ __host__ __device__ inline int km_norm_stride(int d_model, int waves) {
 // ---------------------------------------------------------------- gate/up kernel
 // TAIL: the rows' length is no whole number of chunks (kdim any multiple of 8).  The last chunk's 16-byte pieces past
 // the row's end are fetched from its last 16 bytes instead and the operands zeroed at use.  A form of its own,
-// because the clamps cost a few VALU instructions per tile: with it a 2888 x 7688 layer takes the matrix cores, 428 ->
-// 43 us at 12 tokens in bf16 against the plain-FMA pair, which re-reads X for every weight row.
+// because the clamps cost a few VALU instructions per tile, in every chunk although only the last needs them: with it a 2888 x 7688
+// layer takes the matrix cores, 429 -> 39.7 us at 12 tokens in bf16 against the plain-FMA pair, which re-reads X for every weight row.
 template <int NW, int TT, bool TAIL, bool ROT>
 struct KmStream1 {
     const char *Wg, *Wu, *X;
@@ -203,10 +203,14 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     ts.nt = nt; ts.nkc = c1 - c0; ts.m_count = a.m_count;
     // Where all workgroups start at the same k, those of an XCD ask for the same X lines at once and, with rows of 32 KB and
     // more, for weights in the same few memory channels whenever a second or third workgroup per CU starts in step with the
-    // others: gate/up kernel of 16384 x 53248 at 2 tokens 583 -> 515 us, 18432 x 16384 187 -> 179, 32768 x 8192 164 -> 158 with
-    // a start of its own per workgroup (of an XCD: workgroups b, b + 8, ...).  With three or four token tiles it is the X
-    // tiles: 46.3 -> 44.6 us at 64 tokens of 4096 x 14336, 166 -> 160 of 8192 x 28672.  At 32 tokens or less and rows below
-    // 32 KB nothing or 1 to 2 % worse (8192 x 28672 at 1 token 139 -> 141 us).
+    // others.  A start of its own per workgroup (of an XCD: workgroups b, b + 8, ...), gate/up kernel, us: 16384 x 53248 at 2
+    // tokens 583 -> 515, 16512 x 16384 246 -> 185, 18432 x 16384 188 -> 180, 24576 x 16384 242 -> 239, 32640 x 8192 158 -> 156;
+    // 17408 to 30720 otherwise equal to 1 % worse.  With three or four token tiles it is the X tiles: 46.3 -> 44.6 at 64 tokens
+    // of 4096 x 14336, 166 -> 160 of 8192 x 28672.  At 32 tokens or less and rows below 32 KB it depends on the width with no
+    // order that a line could follow, time with over time without, 2 to 32 tokens: 6144 x 16384 0.93 to 0.94, 8192 x 28672 1.01
+    // to 1.03, 9216 x 24576 1.00, 10240 x 30720 1.01 to 1.02, 11008 x 22016 0.96 to 0.97, 12288 x 28672 0.98 to 1.00, 13312 x
+    // 20480 1.02 to 1.03, 14336 x 24576 0.98 to 1.00, 15360 x 24576 1.00, 16256 x 24576 0.76 to 0.78; there all start at the
+    // same k.
     ts.rot = !DOWN_T && ts.nkc > 1 && (TT >= 3 || a.d_model >= 16384) ? (int)(((unsigned)wg >> 3) % (unsigned)ts.nkc) : 0;
     ts.q = q; ts.g = g;
     ts.k_last = (unsigned)(ts.row_bytes - 16 - kbase);
