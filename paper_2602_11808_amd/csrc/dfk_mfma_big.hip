@@ -92,6 +92,23 @@ __device__ __forceinline__ unsigned keep32(unsigned o) {
 // This lane's byte offset of its MFMA operand within a tile: row q, the 16-byte piece of k group g of half kh.
 __device__ __forceinline__ int big_operand_off(int q, int g, int kh) { return q * 128 + (((4 * kh + g) ^ (q >> 1)) & 7) * 16; }
 
+// Step at which a workgroup of the gate/up kernel starts its walk through the k range.  All of them read the same X: in
+// lock-step they would ask the same few L2 channels for the same lines at the same moment, so starts differ, as a rule over the whole
+// range.  But what is live of X is what lies between the first and the last of an XCD's workgroups (b, b + 8, ...), and that has
+// to stay in its 4 MB L2 beside the weights passing through.  Where X is larger than 3 MB the starts are spread over a window of 64
+// steps (2 MB at 256 tokens and 64 k a step) instead: otherwise X came from beyond the L2 again for every workgroup.  The same
+// where rows are a multiple of 16 KB apart: there a step's rows lie in the same memory channels, and XCDs that walk in step spread the
+// weights better.  Whole call, us, whole range / window / all at step 0: 16384 x 8192 at 256 tokens 455 / 269 / 274, 16384 x 16384 at 128
+// 364 / 319 / 352, 12288 x 12288 at 200 285 / 261 / 267, 12288 x 20480 at 200 482 / 444, 8192 x 28672 at 256 387 / 376, 8192 x 14336
+// at 100 148 / 142 / 150, 8192 x 28672 at 80 267 / 264.  On the other side of the line: 9856 x 28032 at 111 (2.2 MB) 326 / 332, 5504 x
+// 25216 at 105 193 / 196, 5760 x 29568 at 227 (2.6 MB) 305 / 305, 4096 x 14336 at 128 85.5 / 86.2 / 90.1.
+__device__ __forceinline__ int big_k_start(const MlpArgs& a, int nsteps) {
+    const unsigned b = blockIdx.x;
+    const size_t row = (size_t)a.d_model * 2;
+    const bool window = nsteps > 64 && (a.m_count * row > ((size_t)3 << 20) || row % 16384 == 0);
+    return window ? (int)((b >> 3) * 7u & 63u) : (int)(b * 7u % (unsigned)nsteps);
+}
+
 // ---------------------------------------------------------------- gate/up kernel
 // NTC: the largest row-tile count of a d_ff slice of the launch (a compile-time constant so that
 // a step is straight-line code); every slice has NTC or NTC - 1 row tiles (the missing one's sums are never stored).
@@ -110,9 +127,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     const size_t row_bytes = (size_t)a.d_model * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
 
-    // Every workgroup walks the k range in its own rotation: all of them read the same X, and in
-    // lock-step they would ask the same few L2 channels for the same lines at the same moment.
-    const int rot = (int)((blockIdx.x * 7u) % (unsigned)nsteps);
+    const int rot = big_k_start(a, nsteps);
     const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
     const int lo = big_operand_off(q, g, kh);
 
@@ -296,8 +311,6 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
     const size_t row_bytes = (size_t)a.d_model * 2;
     const int tile0 = tg * TT;
 
-    // The workgroups of one split read the same A_2 rows: each walks the steps in its own rotation.
-    const int rot = (int)((cb * 5u) % (unsigned)nsteps);
     const int prow = lane >> 3, piece = lane & 7;
     const int lo = big_operand_off(q, g, kh);
 
@@ -323,7 +336,10 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
         const unsigned off = (unsigned)(tile0 * 16 + prow) * a2_row, off_last = (unsigned)(a.m_count - 1) * a2_row;
         unsigned char* const dst0 = W ? lds + w_off + wave * 1024 : lds + tile0 * kBigTile;
         constexpr int buf_bytes = W ? w_step : x_step;
-        auto first_row = [&](int step) { return (step + rot < nsteps ? step + rot : step + rot - nsteps) * kBigStepK; };
+        // The workgroups of a split walk it in step, so that what is live of their A_2 rows stays small: with a start of its own for
+        // each column block 16384 x 16384 at 128 tokens took 142 us instead of 116 (8 MB of A_2), 2304 x 9216 at 200 28.1 / 27.4, 4096 x
+        // 14336 at 128 and 256 the same within 2 %.
+        auto first_row = [&](int step) { return step * kBigStepK; };
         // A step's address is scalar but for offsets that do not change, unless the split's last step is partial.
         unsigned lane_off[SLOTS];
 #pragma unroll
