@@ -126,7 +126,12 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  [d_model, d_ff] (dfk_swiglu_mlp_wdt only): k2_splits workgroups own a slice of
  *                  d_model each (whole 16-row tiles, at most 8 per workgroup), k2_col_blocks = 1,
  *                  reduce = DFK_REDUCE_TICKET (nothing is reduced across workgroups; the result
- *                  is deterministic), up to 64 tokens per launch.  With path = DFK_PATH_VALU the
+ *                  is deterministic), up to 64 tokens per launch.  With k2_col_blocks = d_model / 128
+                  (at least 2) the down projection is split over d_ff instead: k2_splits times that many
+                  workgroups own 128 rows of W_down_t over a split of whole 64-row steps, a third,
+                  small launch adds the splits' partial sums in a fixed order (deterministic too),
+                  and a launch takes up to 256 tokens; beyond 64 tokens its gate/up kernel is
+                  pair 2's (d_model and d_ff multiples of 128).  With path = DFK_PATH_VALU the
  *                  same pair in plain fp32 FMAs (any shape and type; k2_splits = workgroups of
  *                  the down kernel, whose wavefronts own output columns whole);
  *                  3 = gate/up kernel of pair 2 with one token tile per token group,
@@ -204,8 +209,9 @@ dfk_status_t dfk_swiglu_mlp_ex(const void* X, const void* W_gate, const void* W_
 /*
  * dfk_swiglu_mlp_ex with the down projection's weights given as W_down_t [d_model, d_ff], row n = column n of
  * the paper's W_down (Background, SwiGLU equations: Y = A_2 W_down): the [out, in] layout a linear layer's
- * weights are stored in, and the layout W_gate and W_up already have here.  Same result.  In this layout a
- * workgroup of the down kernel owns a slice of d_model over all of d_ff, so nothing is summed across workgroups
+ * weights are stored in, and the layout W_gate and W_up already have here.  Same result.  In this layout, up to
+ * 64 tokens, a workgroup of the down kernel can own a slice of d_model over all of d_ff, so that nothing is summed
+ * across workgroups
  * (config field kmajor = 5: on the MFMA path for the 16-bit types with d_model a multiple of 128 and d_ff a
  * multiple of 128 with at least `waves` 128-k chunks each; on the VALU path for every supported shape and type).
  * cfg == NULL: the scheduler's choice for this layout (dfk_get_choice_wdt); else cfg must be a kmajor = 5
@@ -278,7 +284,8 @@ dfk_status_t dfk_mlp_block(const void* H, const void* norm_weight, float eps,
 
 /* The same with the down projection's weights given as W_down_t [d_model, d_ff] (see dfk_swiglu_mlp_wdt):
  * cfg == NULL or a kmajor = 5 configuration; the normalisation is folded into the gate/up kernel as with
- * kmajor = 1, the residual is added where the down kernel stores Y. */
+ * kmajor = 1 (beyond 64 tokens with k2_col_blocks > 1 a small launch of its own, as with kmajor = 2), the residual is added
+ * where Y is stored. */
 dfk_status_t dfk_mlp_block_wdt(const void* H, const void* norm_weight, float eps,
                                const void* W_gate, const void* W_up, const void* W_down_t,
                                void* H_out, int M, int d_model, int d_ff, dfk_dtype_t dtype,

@@ -296,8 +296,24 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
     return out;
 }
 
-// W_down given as [d_model, d_ff]: the 64-token pair's gate/up kernel, then the down kernel whose workgroups own
-// slices of d_model (no sum across workgroups).  First in the list = the untuned default.
+// W_down given as [d_model, d_ff]: whether the down projection is split over d_ff (kmajor = 5 with column blocks) or its
+// workgroups own rows of W_down^T whole, with nothing to sum across them.  Beyond 64 tokens always: whole rows take 64 tokens per
+// launch and stream the weights again for each (256 tokens, us: 4096 x 14336 345 whole rows, 108 split; 896 x 4864 136, 34; 12288 x
+// 12288 665, 265).  Up to 64, whole rows read all of A_2 in every workgroup; that costs more than a split's sum where it is at least
+// twice the workgroup's weights (tokens against rows) and at least 450 KB, or 180 KB where narrow widths leave four wavefronts.
+// Whole rows / split, us: 4096 x 14336 at 20 tokens 66.5 / 65.4, at 32 70.8 / 67.3, at 64 87.5 / 75.1; 2304 x 9216 at 32 38.7 / 37.4;
+// 6144 x 8064 at 48 67.5 / 65.3; 8192 x 7168 at 64 78.5 / 77.3; 896 x 4864 at 20 22.8 / 18.6; 512 x 2048 at 48 14.9 / 13.7.  On the
+// other side: 8192 x 7168 at 48 71.9 / 73.1; 6144 x 8064 at 32 62.5 / 62.7; 12288 x 12288 at 64 166 / 179; 1024 x 2816 at 32 13.8 /
+// 15.1, at 64 18.3 / 18.3; 512 x 2048 at 32 12.1 / 12.5.
+bool wdt_split_pays(int M, int d_model, int d_ff) {
+    if (M > 64) return true;
+    const int tokens = (M + 15) / 16 * 16, rows = d_model / std::max(1, std::min(256, d_model / 16));
+    const size_t a2 = (size_t)tokens * d_ff * 2;
+    return M > 16 && tokens >= 2 * rows && a2 >= (size_t)(d_model < 1024 ? 180 : 450) << 10;
+}
+
+// The candidates of that layout: the 64-token pair's gate/up kernel, then the down kernel whose workgroups own slices of d_model; and
+// the form that splits d_ff.  First in the list = the untuned default.
 std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     std::vector<dfk_config_t> out;
     // plain fp32-FMA kernels for every shape and type (after the MFMA pair in the list, where there is one)
@@ -319,16 +335,30 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     }
     const int more_splits = d_ff > 512 * 64 ? ((d_ff + 63) / 64 + 255) / 256 * 256 : 512;
     const int t16 = d_model / 16;
+    auto push = [&](const dfk_config_t& c) {
+        if (!config_valid(c, M, d_model, d_ff, dtype)) return;
+        for (const auto& o : out)
+            if (same_cfg(o, c)) return;
+        out.push_back(c);
+    };
+    // the form that splits the down projection over d_ff
+    auto split_form = [&]() {
+        const int nblk = d_model / 128;
+        if (nblk < 2) return;
+        for (int wd : {84, 83, 48})
+            for (int splits : {256, more_splits})
+                for (int k2s : {big_splits(M, d_ff, nblk), 256 / nblk, std::min(12, 256 / nblk)})
+                    push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,
+                                  std::max(1, std::min(k2s, d_ff / 64)), nblk, (int)dtype, DFK_REDUCE_TICKET, 0, 5));
+    };
+    if (wdt_split_pays(M, d_model, d_ff)) split_form();
     for (int wd : {82, 83, 84, 46})          // wavefronts, ring depth
         for (int splits : {256, 512, more_splits})
             for (int k2s : {256, 512, 128}) {
-                dfk_config_t c = make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,
-                                          std::max(1, std::min(k2s, t16)), 1, (int)dtype, DFK_REDUCE_TICKET, 0, 5);
-                if (!config_valid(c, M, d_model, d_ff, dtype)) continue;
-                bool dup = false;
-                for (const auto& o : out) dup = dup || same_cfg(o, c);
-                if (!dup) out.push_back(c);
+                push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,
+                              std::max(1, std::min(k2s, t16)), 1, (int)dtype, DFK_REDUCE_TICKET, 0, 5));
             }
+    if (M > 16) split_form();   // (again: nothing is listed twice)
     valu();
     return out;
 }
@@ -479,7 +509,7 @@ dfk_status_t run_in(const WsLayout& l, const void* X, const void* Wg, const void
     a.Q = (float*)((char*)ws + l.q_off);
     a.a2 = (char*)ws + l.a2_off;
     a.norm_w = norm_w; a.eps = eps; a.resid = resid;
-    if (norm_w && (c.kmajor == 2 || !mfma_km_block_config_valid(c, M, d_model, d_ff, dtype))) {   // (kmajor 1 and 5 fold it)
+    if (norm_w && (c.kmajor == 2 || !mfma_km_block_config_valid(c, M, d_model, d_ff, dtype))) {   // (kmajor 1 and, up to 64 tokens, 5 fold it)
         // The 256-token pair is paced by its MFMA and LDS work, so scaling X inside every workgroup
         // costs more there than one small launch that writes the normalised input once.  The
         // 64-token pair folds the normalisation into its gate/up kernel unless the slices of the
@@ -784,7 +814,7 @@ dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const 
             return DFK_ERR_ALIAS;
     }
     auto carries = [&](const dfk_config_t& k) {
-        if (wd_t) return k.path == DFK_PATH_MFMA && k.kmajor == 5 && mfma_km_t_config_valid(k, M, d_model, d_ff, dtype);
+        if (wd_t) return k.path == DFK_PATH_MFMA && k.kmajor == 5 && mfma_config_valid(k, M, d_model, d_ff, dtype);
         return k.path == DFK_PATH_MFMA &&
                ((k.kmajor == 1 && d_model % 128 == 0 && mfma_km_config_valid(k, M, d_model, d_ff, dtype)) ||
                 (k.kmajor == 2 && mfma_big_config_valid(k, M, d_model, d_ff, dtype)));

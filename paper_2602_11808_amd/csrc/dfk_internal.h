@@ -155,6 +155,10 @@ bool mfma_km_block_config_valid(const dfk_config_t& c, int M, int d_model, int d
 int mfma_km_tokens_per_launch();
 // the pair whose down kernel takes W_down as [d_model, d_ff] (kmajor = 5)
 bool mfma_km_t_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);
+// the form of that layout that splits the down projection over d_ff (kmajor = 5 with more than one column block)
+inline bool wdt_split(const dfk_config_t& c) { return c.kmajor == 5 && c.path == DFK_PATH_MFMA && c.k2_col_blocks > 1; }
+hipError_t launch_wdt_split(const MlpArgs& a, const dfk_config_t& c, hipStream_t st);
+bool mfma_wdt_split_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);
 // both kernels' workgroups in one launch (variant FUSED, kmajor = 4)
 hipError_t launch_mfma_km_roles(const MlpArgs& a, const dfk_config_t& c, hipStream_t st);
 bool mfma_km_roles_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);

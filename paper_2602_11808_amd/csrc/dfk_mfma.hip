@@ -796,6 +796,7 @@ hipError_t launch_mfma_mixed(const MlpArgs& a, const dfk_config_t& c, hipStream_
 }
 
 int mfma_max_tokens_per_launch(const dfk_config_t& c, int d_model) {
+    if (wdt_split(c)) return mfma_big_tokens_per_launch();
     if (c.kmajor == 4 || c.kmajor == 5) return mfma_km_tokens_per_launch();
     if (c.kmajor == 3) return mfma_km_tokens_per_launch();
     if (c.kmajor == 2) return mfma_big_tokens_per_launch();
@@ -805,6 +806,7 @@ int mfma_max_tokens_per_launch(const dfk_config_t& c, int d_model) {
 
 bool mfma_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     if (c.kmajor == 4) return mfma_km_roles_config_valid(c, M, d_model, d_ff, dtype);
+    if (wdt_split(c)) return mfma_wdt_split_valid(c, M, d_model, d_ff, dtype);
     if (c.kmajor == 5) return mfma_km_t_config_valid(c, M, d_model, d_ff, dtype);
     if (c.kmajor == 3) return mfma_mixed_config_valid(c, M, d_model, d_ff, dtype);
     if (c.kmajor == 2) return mfma_big_config_valid(c, M, d_model, d_ff, dtype);
@@ -848,6 +850,7 @@ bool mfma_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_
 
 hipError_t launch_mfma(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     if (c.kmajor == 4) return launch_mfma_km_roles(a, c, st);
+    if (wdt_split(c)) return launch_wdt_split(a, c, st);
     if (c.kmajor == 3) return launch_mfma_mixed(a, c, st);
     if (c.kmajor == 2) return launch_mfma_big(a, c, st);
     if (c.kmajor == 1 && c.variant == DFK_VARIANT_FUSED) return launch_mfma_fused_km(a, c, st);

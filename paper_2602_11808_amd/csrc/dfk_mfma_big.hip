@@ -109,25 +109,65 @@ __device__ __forceinline__ int big_k_start(const MlpArgs& a, int nsteps) {
     return window ? (int)((b >> 3) * 7u & 63u) : (int)(b * 7u % (unsigned)nsteps);
 }
 
+// Which (d_ff split, column block) a workgroup of the down kernel takes.  Workgroups are handed to
+// the 8 XCDs in turn (workgroup b runs on XCD b % 8) and each XCD has its own L2; all column blocks
+// of a split read the same A_2 rows, so a split's workgroups are placed on one XCD (or, with fewer
+// than 8 splits, on 8 / splits of them) and those rows are fetched into that L2 once.  Any other
+// split count keeps the plain order, and so does a launch whose whole A_2 fits one L2 (the host
+// decides: there the plain order measured 2 us faster, at 128 tokens of the 8B shape; beyond,
+// the placement gains 1 to 4 us of 60 at 256 tokens of that shape and 13 of 200 on the 70B
+// shape).  A bijection from
+// [0, S * C) onto S x C in every case.
+__device__ __forceinline__ void down_tile_of(int b, int S, int C, bool by_xcd, int& js, int& cb) {
+    const int x = b & 7, r = b >> 3;
+    if (!by_xcd) {
+        js = b / C;
+        cb = b - js * C;
+    } else if ((S & 7) == 0) {
+        js = x + 8 * (r / C);
+        cb = r % C;
+    } else if ((S == 1 || S == 2 || S == 4) && ((C * S) & 7) == 0) {
+        js = x % S;
+        cb = (x / S) * (C * S / 8) + r;
+    } else {
+        js = b / C;
+        cb = b - js * C;
+    }
+}
+
 // ---------------------------------------------------------------- gate/up kernel
 // NTC: the largest row-tile count of a d_ff slice of the launch (a compile-time constant so that
 // a step is straight-line code); every slice has NTC or NTC - 1 row tiles (the missing one's sums are never stored).
-template <int TT, typename E, int NTC>
-__device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char* lds) {
+//
+// DOWN_T: the same pipeline computes the down projection from W_down given as [d_model, d_ff]: Y^T = W_down^T A_2^T has the
+// shape of stage one with d_ff as the k range and A_2 in X's place.  Workgroup (js, cb) owns 128 rows of W_down^T (NTC = 8 tiles of
+// 16 rows of the one matrix) over d_ff split js in whole 64-row steps; the end stores the partial block of the split.
+template <int TT, typename E, int NTC, bool DOWN_T = false>
+__device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char* lds, const bool by_xcd = false) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane & 15, g = lane >> 4;
     const int tg = wave & 3, kh = wave >> 2;
-    int j0, j1;
-    slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
-    const int nt = (j1 - j0) / 8;                  // NTC or NTC - 1 (slices differ by at most one 8-row group)
-    constexpr int KS = big_gateup_pieces(TT, NTC);
-    const int nsteps = a.d_model / (kBigStepK * KS);
-    const size_t row_bytes = (size_t)a.d_model * 2;
+    int j0, j1, js = 0, cb = 0, k0 = 0;            // rows of the weights; d_ff split, column block and first k (DOWN_T)
+    constexpr int KS = DOWN_T ? 1 : big_gateup_pieces(TT, NTC);
+    int nsteps;
+    if (DOWN_T) {
+        down_tile_of((int)blockIdx.x, a.k2_splits, a.k2_col_blocks, by_xcd, js, cb);
+        const int steps = a.d_ff / kBigStepK;
+        k0 = (int)((long long)steps * js / a.k2_splits);
+        nsteps = (int)((long long)steps * (js + 1) / a.k2_splits) - k0;
+        k0 *= kBigStepK;
+        j0 = cb * 128; j1 = j0 + 128;
+    } else {
+        slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
+        nsteps = a.d_model / (kBigStepK * KS);
+    }
+    const int nt = DOWN_T ? NTC : (j1 - j0) / 8;   // NTC or NTC - 1 (slices differ by at most one 8-row group)
+    const size_t row_bytes = (size_t)(DOWN_T ? a.d_ff : a.d_model) * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
 
-    const int rot = big_k_start(a, nsteps);
+    const int rot = DOWN_T ? 0 : big_k_start(a, nsteps);   // (a split's column blocks walk it in step, as in the other down kernel)
     const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
     const int lo = big_operand_off(q, g, kh);
 
@@ -137,7 +177,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    DFK_STAMP(0);
+    DFK_STAMP(DOWN_T ? 3 : 0);
     constexpr int x_piece = 4 * TT * kBigTile, w_piece = NTC * kBigTile, x_step = KS * x_piece, w_step = KS * w_piece;
     constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
     // The steps of a wavefront that requests N weight loads per 64-k piece or (N = -1) activations: of the slice's 2 nt weight loads
@@ -148,10 +188,11 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         constexpr bool W = N >= 0;
         constexpr int PER = W ? N : 2 * TT, SLOTS = KS * PER;
         constexpr int nb = W ? nbw : nbx;
-        const char* const src = W ? (const char*)(wave & 1 ? a.Wu : a.Wg) + (size_t)(j0 + (wave >> 1) * 8) * row_bytes
-                                  : (const char*)a.X + (size_t)a.m_base * row_bytes;
-        // Byte offset of load i: row 16 i (weights) or 8 i (tokens, the last one for those that do not exist) further on than
-        // load 0's; the piece's place changes by half a row (64 bytes) from a tile's rows 0..7 to its rows 8..15.
+        const char* const src = (W && DOWN_T ? (const char*)a.Wd + (size_t)(j0 + wave * 8) * row_bytes
+                                 : W         ? (const char*)(wave & 1 ? a.Wu : a.Wg) + (size_t)(j0 + (wave >> 1) * 8) * row_bytes
+                                             : (const char*)(DOWN_T ? a.a2 : a.X) + (size_t)a.m_base * row_bytes) + (size_t)k0 * 2;
+        // Byte offset of load i: row 16 i (gate and up rows; 32 i of the one matrix) or 8 i (tokens, the last one for those that do not
+        // exist) further on than load 0's; the piece's place changes by half a row (64 bytes) from a tile's rows 0..7 to its rows 8..15.
         const unsigned rb = (unsigned)row_bytes;
         const unsigned off = (unsigned)(W ? prow : tile0 * 16 + prow) * rb, off_last = (unsigned)(a.m_count - 1) * rb;
         const unsigned place = (unsigned)(((piece ^ (prow >> 1)) & 7) * 16) ^ (W && (wave & 1) ? 64u : 0u);
@@ -160,7 +201,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         auto source = [&](int step) { return src + (size_t)(step + rot < nsteps ? step + rot : step + rot - nsteps) * (KS * kBigStepK * 2); };
         auto load = [&](const char* p, unsigned char* dst, int slot) {
             const int u = PER ? slot / PER : 0, i = slot - u * PER;   // (constants)
-            const unsigned o = W ? off + 16u * i * rb + place : min(off + 8u * i * rb, off_last) + (place ^ (i & 1 ? 64u : 0u));
+            const unsigned o = W ? off + (DOWN_T ? 32u : 16u) * i * rb + place : min(off + 8u * i * rb, off_last) + (place ^ (i & 1 ? 64u : 0u));
             __builtin_amdgcn_global_load_lds(p + u * (kBigStepK * 2) + keep32(o), DFK_LDS_PTR(dst + u * (W ? w_piece : x_piece) + i * (W ? 2 * kBigTile : 1024)), 16, 0,
                                              W ? kAuxNonTemporal : 0);
         };
@@ -222,7 +263,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     if (kh == 1) steps(std::integral_constant<int, -1>{});
     else if ((2 * nt - wave + 3) >> 2 == NMAX) steps(std::integral_constant<int, NMAX>{});
     else steps(std::integral_constant<int, NMAX - 1>{});
-    DFK_STAMP(2);
+    DFK_STAMP(DOWN_T ? 4 : 2);
 
     // The halves of the k range meet: wavefront (tg, 0) finishes row tiles [0, H), (tg, 1) the others.
     constexpr int H = (NTC + 1) / 2;
@@ -236,6 +277,21 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
             for (int tt = 0; tt < TT; ++tt) mine[((rt < H ? rt : rt - H) * TT + tt) * 64] = acc[rt][tt];
         }
     __syncthreads();
+    if (DOWN_T) {              // four adjacent columns of the split's partial block, summed by the launch that follows
+#pragma unroll
+        for (int rt = 0; rt < NTC; ++rt) {
+            if ((rt < H) == (kh == 0)) {
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) {
+                    const f32x4 v = acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64];
+                    const int m = (tile0 + tt) * 16 + q;
+                    if (m < a.m_count) *(f32x4*)(a.P + ((size_t)js * a.m_count + m) * a.d_model + j0 + rt * 16 + 4 * g) = v;
+                }
+            }
+        }
+        DFK_STAMP(6);
+        return;
+    }
     // D tile of (row tile, token tile): lane (q, g) holds token q, tile rows 4g .. 4g+3; rows 0..7
     // are the gate rows, 8..15 the up rows of the same 8 d_ff rows: lanes 32 apart pair up.
 #pragma unroll
@@ -267,32 +323,6 @@ __global__ __launch_bounds__(kBigWaves * 64) void k_gateup_big(MlpArgs a) {
 }
 
 // ---------------------------------------------------------------- down kernel
-// Which (d_ff split, column block) a workgroup of the down kernel takes.  Workgroups are handed to
-// the 8 XCDs in turn (workgroup b runs on XCD b % 8) and each XCD has its own L2; all column blocks
-// of a split read the same A_2 rows, so a split's workgroups are placed on one XCD (or, with fewer
-// than 8 splits, on 8 / splits of them) and those rows are fetched into that L2 once.  Any other
-// split count keeps the plain order, and so does a launch whose whole A_2 fits one L2 (the host
-// decides: there the plain order measured 2 us faster, at 128 tokens of the 8B shape; beyond,
-// the placement gains 1 to 4 us of 60 at 256 tokens of that shape and 13 of 200 on the 70B
-// shape).  A bijection from
-// [0, S * C) onto S x C in every case.
-__device__ __forceinline__ void down_tile_of(int b, int S, int C, bool by_xcd, int& js, int& cb) {
-    const int x = b & 7, r = b >> 3;
-    if (!by_xcd) {
-        js = b / C;
-        cb = b - js * C;
-    } else if ((S & 7) == 0) {
-        js = x + 8 * (r / C);
-        cb = r % C;
-    } else if ((S == 1 || S == 2 || S == 4) && ((C * S) & 7) == 0) {
-        js = x % S;
-        cb = (x / S) * (C * S / 8) + r;
-    } else {
-        js = b / C;
-        cb = b - js * C;
-    }
-}
-
 template <int TT, typename E>
 __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xcd, unsigned char* lds) {
     __shared__ int flag;
@@ -485,6 +515,17 @@ __global__ __launch_bounds__(kBigWaves * 64) void k_down_big(MlpArgs a, int by_x
     down_big_body<TT, E>(a, by_xcd != 0, lds);
 }
 
+// Down projection from W_down given as [d_model, d_ff], 65 tokens and more (and fewer, see wdt_split_pays): the pipeline of
+// the gate/up kernel over (d_ff splits) x (blocks of 128 rows of W_down^T).  Its sibling for a few tokens, whose workgroups own rows
+// whole so that nothing is summed across them, takes 64 tokens per launch and streams all three weights again for each 64: that, not
+// its own pace, bounded it.  Whole call, 4096 x 14336, us: 80 tokens 149 -> 77, 128 173 -> 85, 256 345 -> 108 (the other layout,
+// whose weights are regrouped in registers, 115).
+template <int TT, typename E>
+__global__ __launch_bounds__(kBigWaves * 64) void k_down_t_big(MlpArgs a, int by_xcd) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    gateup_big_body<TT, E, 8, true>(a, lds, by_xcd != 0);
+}
+
 // Sum of the splits' partial blocks (counter reduction mode of the down kernel above): with
 // hundreds of tokens the blocks are tens of MB, too much for the last workgroup of a column
 // block to add up alone, so a launch of its own spreads the sum over the whole chip.  Fixed
@@ -530,6 +571,11 @@ template __global__ void k_sum_partials_big<FP16>(MlpArgs);
     template __global__ void k_down_big<TT, FP16>(MlpArgs, int);
 DFK_INST_DOWN(1) DFK_INST_DOWN(2) DFK_INST_DOWN(3) DFK_INST_DOWN(4)
 #undef DFK_INST_DOWN
+#define DFK_INST_DOWN_T(TT)                                            \
+    template __global__ void k_down_t_big<TT, BF16>(MlpArgs, int); \
+    template __global__ void k_down_t_big<TT, FP16>(MlpArgs, int);
+DFK_INST_DOWN_T(1) DFK_INST_DOWN_T(2) DFK_INST_DOWN_T(3) DFK_INST_DOWN_T(4)
+#undef DFK_INST_DOWN_T
 
 // ---------------------------------------------------------------- host side
 int big_token_tiles(int m_count) { return (m_count + 63) / 64; }   // per token group
@@ -542,6 +588,7 @@ size_t big_lds_gateup(const dfk_config_t& c, int TT, int d_ff) {
     const int nt_max = max_slice_rows(d_ff, c.splits) / 8, ks = big_gateup_pieces(TT, nt_max);
     return big_lds(ks * 4 * TT * kBigTile, ks * nt_max * kBigTile, (size_t)kBigWaves * ((nt_max + 1) / 2) * TT * 1024);
 }
+size_t big_lds_down_t(int TT) { return big_lds(4 * TT * kBigTile, 8 * kBigTile, (size_t)kBigWaves * 4 * TT * 1024); }
 size_t big_lds_down(int TT) { return big_lds(4 * TT * kBigTile, 4 * kTileBytes, (size_t)kBigWaves * TT * 4 * 1024); }
 constexpr bool big_buffers_fit() {
     for (int tt = 1; tt <= 4; ++tt) {
@@ -578,6 +625,13 @@ hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStrea
     }
 }
 
+hipError_t launch_sum_partials(const MlpArgs& a, hipStream_t st) {
+    const size_t n4 = (size_t)a.m_count * (a.d_model / 4);
+    if (a.dtype == DFK_FP16) hipLaunchKernelGGL((k_sum_partials_big<FP16>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_sum_partials_big<BF16>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 template <int TT, typename E>
 hipError_t launch_big_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     static LdsAllowance allowed2;   // of the down kernel of this instantiation, per device
@@ -591,11 +645,24 @@ hipError_t launch_big_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st
         hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigWaves * 64), lds, st, a, by_xcd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || a.reduce_mode == DFK_REDUCE_ATOMIC) return e;
-        const size_t n4 = (size_t)a.m_count * (a.d_model / 4);
-        hipLaunchKernelGGL((k_sum_partials_big<E>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, a);
-        return hipGetLastError();
+        return launch_sum_partials(a, st);
     }
     return hipSuccess;
+}
+
+template <int TT, typename E>
+hipError_t launch_down_t_te(const MlpArgs& a, hipStream_t st) {
+    static LdsAllowance allowed;
+    const size_t lds = big_lds_down_t(TT);
+    const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
+    if (hipError_t e = allow_lds(allowed, (const void*)k_down_t_big<TT, E>, lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_down_t_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigWaves * 64), lds, st, a, by_xcd);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    return launch_sum_partials(a, st);
+}
+template <int TT>
+hipError_t launch_down_t(const MlpArgs& a, hipStream_t st) {
+    return a.dtype == DFK_FP16 ? launch_down_t_te<TT, FP16>(a, st) : launch_down_t_te<TT, BF16>(a, st);
 }
 
 template <int TT>
@@ -648,6 +715,44 @@ hipError_t launch_mfma_big(const MlpArgs& a, const dfk_config_t& c, hipStream_t 
         case 2: return launch_big_t<2>(a, c, st);
         case 3: return launch_big_t<3>(a, c, st);
         case 4: return launch_big_t<4>(a, c, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// W_down as [d_model, d_ff] with the down projection split over d_ff (kmajor = 5, k2_col_blocks = d_model / 128 > 1): up to 64
+// tokens the 64-token pair's gate/up kernel, which folds a normalisation, beyond them this file's; then the down kernel above.
+bool mfma_wdt_split_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    if (c.path != DFK_PATH_MFMA || (dtype != DFK_BF16 && dtype != DFK_FP16) || c.variant != DFK_VARIANT_TWO_KERNEL) return false;
+    if (c.kmajor != 5 || c.k2_rows_by_wave != 0 || c.a2_dtype != (int)dtype || c.reduce != DFK_REDUCE_TICKET) return false;
+    if (M < 1 || d_model < 256 || d_model % 128 || d_model > kMaxDModel || d_ff < 128 || d_ff % 128) return false;
+    if (c.k2_col_blocks != d_model / 128 || c.k2_splits < 1 || c.k2_splits > d_ff / kBigStepK) return false;
+    if ((long long)c.k2_splits * c.k2_col_blocks > 65535) return false;
+    const int tokens = std::min(M, kBigTokensPerLaunch);
+    if ((size_t)c.k2_splits * tokens * d_model * 4 > partial_bytes(M, d_model)) return false;
+    dfk_config_t g = c;            // its gate/up kernel, as that kernel's own pair asks for it
+    g.k2_splits = 1;
+    if (M <= mfma_km_tokens_per_launch()) {
+        g.kmajor = 1;
+        return mfma_km_config_valid(g, M, d_model, d_ff, dtype);
+    }
+    if ((c.waves != 4 && c.waves != 8) || c.depth < 2 || c.depth > 16) return false;
+    g.kmajor = 2; g.waves = 8; g.depth = 3;
+    return mfma_big_config_valid(g, M, d_model, d_ff, dtype);
+}
+
+hipError_t launch_wdt_split(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    const int saved = g_stage_mask;
+    dfk_config_t g = c;
+    g.kmajor = a.M <= mfma_km_tokens_per_launch() ? 1 : 2;
+    g_stage_mask = saved & 1;                          // the gate/up kernel only
+    hipError_t e = g.kmajor == 1 ? launch_mfma_km(a, g, st) : launch_mfma_big(a, g, st);
+    g_stage_mask = saved;
+    if (e != hipSuccess || !(saved & 2)) return e;
+    switch (big_token_tiles(a.m_count)) {
+        case 1: return launch_down_t<1>(a, st);
+        case 2: return launch_down_t<2>(a, st);
+        case 3: return launch_down_t<3>(a, st);
+        case 4: return launch_down_t<4>(a, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -944,7 +944,8 @@ bool mfma_km_t_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff,
 // little more LDS (weight of the normalisation, sums of squares).
 bool mfma_km_block_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     if (d_model % kKC) return false;
-    if (c.kmajor == 5 ? !mfma_km_t_config_valid(c, M, d_model, d_ff, dtype) : !mfma_km_config_valid(c, M, d_model, d_ff, dtype)) return false;
+    if (wdt_split(c) ? M > kKmTokensPerLaunch || !mfma_wdt_split_valid(c, M, d_model, d_ff, dtype)
+        : c.kmajor == 5 ? !mfma_km_t_config_valid(c, M, d_model, d_ff, dtype) : !mfma_km_config_valid(c, M, d_model, d_ff, dtype)) return false;
     KmGeom geo{};
     return km_lds_gateup(c, km_token_tiles(std::min(M, kKmTokensPerLaunch)), d_model, d_ff, true, &geo) <= (size_t)kLdsLimit;
 }

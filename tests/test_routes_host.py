@@ -133,3 +133,14 @@ def test_the_remembered_choice_is_what_a_new_thread_finds():
     t.start()
     t.join()
     assert first == again == got
+
+
+@pytest.mark.parametrize("M,d,ff,split", [(16, 4096, 14336, False), (17, 4096, 14336, True), (64, 4096, 14336, True), (65, 12288, 12288, True),
+                                          (64, 12288, 12288, False), (48, 8192, 7168, False), (64, 8192, 7168, True), (64, 1024, 2816, False),
+                                          (32, 896, 4864, True), (32, 512, 2048, False), (48, 512, 2048, True), (256, 512, 1024, True)])
+def test_which_down_kernel_the_transposed_layout_gets(M, d, ff, split):
+    for dt in (dfk.DFK_BF16, dfk.DFK_FP16):
+        pick, tuned = dfk.dfk_get_choice_wdt(M, d, ff, dt)
+        assert not tuned and (pick.path, pick.kmajor) == (MFMA, 5)
+        assert pick.k2_col_blocks == (d // 128 if split else 1), pick
+        assert dfk.dfk_config_valid(pick, M, d, ff, dt)
