@@ -135,6 +135,15 @@ __device__ __forceinline__ void down_tile_of(int b, int S, int C, bool by_xcd, i
     }
 }
 
+// Step at which a workgroup of the down kernels starts its split.  In step with the split's other column blocks, so that what
+// is live of their A_2 rows stays small and XCDs spread W_down over the memory channels; only where a whole split sits on one XCD
+// (down_tile_of, a multiple of 8 splits), in a start of its own, against the lock-step on the L2 channels.  Down kernel with
+// its sum, us, own start / in step: 16384 x 16384 at 128 tokens 142 / 117, 9856 x 28032 at 111 148 / 110, 5760 x 29568 at 227 146 /
+// 126, 2304 x 9216 at 200 28.1 / 27.4, 4096 x 14336 at 128 (not placed by XCD) 37.8 / 36.3; at 256 (placed) 51.9 / 53.0.
+__device__ __forceinline__ int big_down_start(const MlpArgs& a, bool by_xcd, int cb, int nsteps) {
+    return by_xcd && (a.k2_splits & 7) == 0 ? (int)(cb * 5u % (unsigned)nsteps) : 0;
+}
+
 // ---------------------------------------------------------------- gate/up kernel
 // NTC: the largest row-tile count of a d_ff slice of the launch (a compile-time constant so that
 // a step is straight-line code); every slice has NTC or NTC - 1 row tiles (the missing one's sums are never stored).
@@ -167,7 +176,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     const size_t row_bytes = (size_t)(DOWN_T ? a.d_ff : a.d_model) * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
 
-    const int rot = DOWN_T ? 0 : big_k_start(a, nsteps);   // (a split's column blocks walk it in step, as in the other down kernel)
+    const int rot = DOWN_T ? big_down_start(a, by_xcd, cb, nsteps) : big_k_start(a, nsteps);
     const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
     const int lo = big_operand_off(q, g, kh);
 
@@ -341,6 +350,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
     const size_t row_bytes = (size_t)a.d_model * 2;
     const int tile0 = tg * TT;
 
+    const int rot = big_down_start(a, by_xcd, cb, nsteps);
     const int prow = lane >> 3, piece = lane & 7;
     const int lo = big_operand_off(q, g, kh);
 
@@ -366,10 +376,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
         const unsigned off = (unsigned)(tile0 * 16 + prow) * a2_row, off_last = (unsigned)(a.m_count - 1) * a2_row;
         unsigned char* const dst0 = W ? lds + w_off + wave * 1024 : lds + tile0 * kBigTile;
         constexpr int buf_bytes = W ? w_step : x_step;
-        // The workgroups of a split walk it in step, so that what is live of their A_2 rows stays small: with a start of its own for
-        // each column block 16384 x 16384 at 128 tokens took 142 us instead of 116 (8 MB of A_2), 2304 x 9216 at 200 28.1 / 27.4, 4096 x
-        // 14336 at 128 and 256 the same within 2 %.
-        auto first_row = [&](int step) { return step * kBigStepK; };
+        auto first_row = [&](int step) { return (step + rot < nsteps ? step + rot : step + rot - nsteps) * kBigStepK; };
         // A step's address is scalar but for offsets that do not change, unless the split's last step is partial.
         unsigned lane_off[SLOTS];
 #pragma unroll
