@@ -273,8 +273,9 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* W_gate, const void
  * cfg->kmajor == 2 (up to 256 tokens; there the normalisation is one small launch of its own
  * ahead of the pair, into the workspace: that pair is paced by its arithmetic, and scaling X
  * inside every workgroup measured slower; the residual add stays in the final store).
- * cfg == NULL picks the scheduler's choice among those.  Any other configuration, and shapes
- * those pairs do not cover, give DFK_ERR_UNSUPPORTED_SHAPE.  Workspace as for dfk_swiglu_mlp_ex.
+ * cfg == NULL picks the scheduler's choice among those; without a tuned entry a kmajor = 1 choice
+ * may run as one launch that holds both kernels' workgroups (kmajor = 4 of the fused variant: same
+ * splits, same counter reduction).  Any other configuration, and shapes those pairs do not cover, give DFK_ERR_UNSUPPORTED_SHAPE.  Workspace as for dfk_swiglu_mlp_ex.
  */
 dfk_status_t dfk_mlp_block(const void* H, const void* norm_weight, float eps,
                            const void* W_gate, const void* W_up, const void* W_down,

@@ -795,6 +795,20 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* Wg, const void* Wu
 }
 
 namespace {
+// The untuned pair of a block, up to 64 tokens, as the single launch of both kernels' workgroups: same splits, same counter reduction
+// (the result stays reproducible bit for bit), no boundary between two launches.  Up to 16 tokens only from 48 MB of weights on: below,
+// the down workgroups' wait costs what the boundary does.  Layers replayed from a graph, us per layer, pair / single launch: 2304 x 9216
+// at 1, 8 and 33 tokens 32.2 / 30.5, 33.3 / 31.7, 44.3 / 42.0; 4096 x 14336 at 1 and 64 65.1 / 63.5, 83.8 / 82.4; 5120 x 27648 at 64 186.9
+// / 180.0; 1792 x 4864 (52 MB) at 12 22.5 / 21.6; 1024 x 2816 at 40 22.8 / 22.3; 12288 x 12288 at 33 167.4 / 168.1.  On the other side:
+// 1024 x 5632 (35 MB) at 1 16.0 / 16.5, 1152 x 4096 at 8 16.7 / 17.1, 1536 x 4096 (38 MB) at 8 18.2 / 18.5.
+void single_launch_of(dfk_config_t* c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    dfk_config_t r = *c;
+    if (M > 64 || c->kmajor != 1 || c->variant != DFK_VARIANT_TWO_KERNEL) return;
+    if (M <= 16 && (size_t)6 * d_model * d_ff < (size_t)48000000) return;
+    r.variant = DFK_VARIANT_FUSED; r.kmajor = 4; r.depth = 4;
+    if (mfma_km_block_config_valid(r, M, d_model, d_ff, dtype)) *c = r;
+}
+
 dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const void* Wg,
                        const void* Wu, const void* Wd, void* H_out, int M, int d_model, int d_ff,
                        dfk_dtype_t dtype, const dfk_config_t* cfg, void* workspace,
@@ -820,10 +834,11 @@ dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const 
                 (k.kmajor == 2 && mfma_big_config_valid(k, M, d_model, d_ff, dtype)));
     };
     dfk_config_t c;
+    int tuned = 0;
     if (cfg) c = *cfg;
     else {
-        if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, nullptr)
-                 : !choose(M, d_model, d_ff, dtype, DFK_VARIANT_TWO_KERNEL, &c, nullptr)) return DFK_ERR_UNSUPPORTED_SHAPE;
+        if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, &tuned)
+                 : !choose(M, d_model, d_ff, dtype, DFK_VARIANT_TWO_KERNEL, &c, &tuned)) return DFK_ERR_UNSUPPORTED_SHAPE;
         if (!carries(c)) {   // the scheduler's pick is another kernel family: first candidate that carries this form
             bool found = false;
             for (const auto& k : wd_t ? candidates_wdt(M, d_model, d_ff, dtype) : candidates(M, d_model, d_ff, dtype))
@@ -832,6 +847,7 @@ dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const 
         }
     }
     if (!carries(c)) return DFK_ERR_UNSUPPORTED_SHAPE;
+    if (!cfg && !wd_t && !tuned) single_launch_of(&c, M, d_model, d_ff, dtype);
     return run(H, Wg, Wu, Wd, H_out, M, d_model, d_ff, dtype, c, workspace, (hipStream_t)stream, norm_weight, eps, H);
 }
 }  // namespace

@@ -754,10 +754,12 @@ __global__ __launch_bounds__(NW * 64) void k_down_km(MlpArgs a, KmGeom geo) {
 // two: no launch boundary (drain, dispatch and ramp with HBM idle), and the down workgroups request their first
 // W_down tiles while the last gate/up workgroups are still streaming.  A_2 crosses between workgroups through
 // device memory (2 bytes per token and d_ff row), as between the two kernels.
-template <int NW, int TT, typename E>
+// NORM: with the normalisation in front and the residual added (dfk_mlp_block).  The output may be the input there: a column
+// block is stored once every d_ff split has arrived, so after every gate/up workgroup has read the input and published.
+template <int NW, int TT, typename E, bool NORM = false>
 __global__ __launch_bounds__(NW * 64) void k_roles_km(MlpArgs a, KmGeom geo) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    if ((int)blockIdx.x < geo.n_gateup) gateup_km_body<NW, TT, E, false, true>(a, geo, blockIdx.x, lds);
+    if ((int)blockIdx.x < geo.n_gateup) gateup_km_body<NW, TT, E, NORM, true>(a, geo, blockIdx.x, lds);
     else down_km_body<NW, TT, E, true>(a, geo, blockIdx.x - geo.n_gateup, lds);
 }
 
@@ -865,12 +867,11 @@ hipError_t launch_km_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) 
 
 // Both kernels' workgroups in one launch.  The stage mask of the per-kernel timer maps to the head of the grid
 // alone (gate/up workgroups, nothing counted) and to the tail alone (down workgroups that wait for nobody).
-template <int NW, int TT, typename E>
+template <int NW, int TT, typename E, bool NORM>
 hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     static LdsAllowance allowed;
-    if (a.norm_w) return hipErrorInvalidValue;
     KmGeom geo{}, gd{};
-    size_t lds = std::max(km_lds_gateup(c, TT, a.d_model, a.d_ff, false, &geo), km_lds_down(c, &gd));
+    size_t lds = std::max(km_lds_gateup(c, TT, a.d_model, a.d_ff, NORM, &geo), km_lds_down(c, &gd));
     const bool head = g_stage_mask & 1, tail = g_stage_mask & 2;
     geo.n_gateup = head ? a.splits : 0;
     geo.role_publish = head && tail;
@@ -883,13 +884,14 @@ hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream
     if (const char* e = std::getenv("DFK_DEBUG_SPIN_LIMIT")) geo.role_spin_limit = std::atoi(e);
     const int grid = geo.n_gateup + (tail ? a.k2_splits * a.k2_col_blocks : 0);
     if (grid == 0) return hipSuccess;
-    if (hipError_t e = allow_lds(allowed, (const void*)k_roles_km<NW, TT, E>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_roles_km<NW, TT, E>), dim3(grid), dim3(NW * 64), lds, st, a, geo);
+    if (hipError_t e = allow_lds(allowed, (const void*)k_roles_km<NW, TT, E, NORM>, lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_roles_km<NW, TT, E, NORM>), dim3(grid), dim3(NW * 64), lds, st, a, geo);
     return hipGetLastError();
 }
 template <int NW, int TT>
 hipError_t launch_km_roles_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    return a.dtype == DFK_FP16 ? launch_km_roles_te<NW, TT, FP16>(a, c, st) : launch_km_roles_te<NW, TT, BF16>(a, c, st);
+    if (a.norm_w) return a.dtype == DFK_FP16 ? launch_km_roles_te<NW, TT, FP16, true>(a, c, st) : launch_km_roles_te<NW, TT, BF16, true>(a, c, st);
+    return a.dtype == DFK_FP16 ? launch_km_roles_te<NW, TT, FP16, false>(a, c, st) : launch_km_roles_te<NW, TT, BF16, false>(a, c, st);
 }
 
 }  // namespace
@@ -944,7 +946,9 @@ bool mfma_km_t_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff,
 // little more LDS (weight of the normalisation, sums of squares).
 bool mfma_km_block_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     if (d_model % kKC) return false;
-    if (wdt_split(c) ? M > kKmTokensPerLaunch || !mfma_wdt_split_valid(c, M, d_model, d_ff, dtype)
+    if (c.variant == DFK_VARIANT_FUSED) {
+        if (!mfma_km_roles_config_valid(c, M, d_model, d_ff, dtype)) return false;
+    } else if (wdt_split(c) ? M > kKmTokensPerLaunch || !mfma_wdt_split_valid(c, M, d_model, d_ff, dtype)
         : c.kmajor == 5 ? !mfma_km_t_config_valid(c, M, d_model, d_ff, dtype) : !mfma_km_config_valid(c, M, d_model, d_ff, dtype)) return false;
     KmGeom geo{};
     return km_lds_gateup(c, km_token_tiles(std::min(M, kKmTokensPerLaunch)), d_model, d_ff, true, &geo) <= (size_t)kLdsLimit;
