@@ -72,6 +72,10 @@ __host__ __device__ inline int km_norm_stride(int d_model, int waves) {
 // the row's end are fetched from its last 16 bytes instead and the operands zeroed at use.  A form of its own,
 // because the clamps cost a few VALU instructions per tile, in every chunk although only the last needs them: with it a 2888 x 7688
 // layer takes the matrix cores, 429 -> 39.7 us at 12 tokens in bf16 against the plain-FMA pair, which re-reads X for every weight row.
+// Rows then start anywhere in a cache line, and a 256-byte piece shares its first or last line with its neighbours: no
+// non-temporal hint here and in the down kernel of these widths, so that such a line is still in the L2 when the
+// neighbour asks for it: 2888 x 7688 at 1, 12 and 64 tokens 38.1 -> 37.1, 40.0 -> 38.9, 55.5 -> 54.4 us, 1000 x 3000 at 4 14.7 -> 14.0.
+// (Clamping only in the last chunk and column block, a branch per tile: 40.1 -> 40.4.)
 template <int NW, int TT, bool TAIL, bool ROT>
 struct KmStream1 {
     const char *Wg, *Wu, *X;
@@ -106,8 +110,7 @@ struct KmStream1 {
             for (int u = 0; u < 4; ++u) {
                 const int i = 4 * u + g;
                 const unsigned ko = min((unsigned)p_kc * (kKC * 2) + (q ^ i) * 16, k_last);
-                __builtin_amdgcn_global_load_lds((u < 2 ? Wg : Wu) + tb + (size_t)(i & 7) * row_bytes + ko, DFK_LDS_PTR(slot + u * 1024), 16, 0,
-                                                 kAuxNonTemporal);
+                __builtin_amdgcn_global_load_lds((u < 2 ? Wg : Wu) + tb + (size_t)(i & 7) * row_bytes + ko, DFK_LDS_PTR(slot + u * 1024), 16, 0, 0);
             }
         } else {               // weight tile of row tile p_idx - TT: 8 rows of W_gate, the same 8 of W_up
             const size_t tb = w_base + (size_t)(p_idx - TT) * tile_rows * row_bytes + (size_t)p_kc * (kKC * 2);
@@ -449,7 +452,7 @@ struct KmStream2 {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int row = min(row0 + 8 * g + u, d_ff - 1);
-                    __builtin_amdgcn_global_load_lds(Wd + (size_t)row * row_bytes + co, DFK_LDS_PTR(slot + u * 1024), 16, 0, kAuxNonTemporal);
+                    __builtin_amdgcn_global_load_lds(Wd + (size_t)row * row_bytes + co, DFK_LDS_PTR(slot + u * 1024), 16, 0, 0);
                 }
             } else if (row0 + 28 <= d_ff) {
                 const char* base = Wd + (size_t)row0 * row_bytes + colb;
