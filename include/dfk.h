@@ -92,7 +92,7 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  shape constraints, see dfk_config_valid)
  *   splits         number of d_ff slices = workgroups of the fused kernel, or of
  *                  the first kernel of the two-kernel variant
- *   waves          wavefronts (64 lanes) per workgroup
+ *   waves          wavefronts (64 lanes) per workgroup (kmajor = 1 pair with 4: the down kernel runs 8 beyond 16 tokens)
  *   depth          software pipeline depth of the weight stream (tiles or loads in flight)
  *   reduce         dfk_reduce_t
  *   k2_splits      two-kernel variant: d_ff splits of the down projection

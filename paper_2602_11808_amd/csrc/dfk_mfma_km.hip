@@ -804,6 +804,19 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
     return std::max(ring, (size_t)geo->pass * per_tile);
 }
 
+// Wavefronts of the pair's down kernel: as configured, but eight where the gate/up kernel runs four (narrow widths: few 128-k chunks
+// of d_model, which say nothing about the down kernel's d_ff rows) and there is more than one token tile.  Four there had twice the
+// tiles each and the same stages to add at the end: 896 x 4864 at 40 tokens 26.8 -> 24.4 us per call, 640 x 2560 at 64 27.5 -> 24.9, 512 x 1536 at 24
+// 15.2 -> 14.6; up to 16 tokens equal or worse (7.5 ->
+// 8.1 at one token of 1024 x 2816).
+constexpr int km_down_waves(int waves, int tt) { return waves == 4 && tt >= 2 ? 8 : waves; }
+inline dfk_config_t km_down_cfg(const dfk_config_t& c, int tt) {
+    dfk_config_t d = c;
+    d.waves = km_down_waves(c.waves, tt);
+    d.depth = std::min(c.depth, (int)((size_t)kLdsLimit / ((size_t)d.waves * kTileBytes)));
+    return d;
+}
+
 // The pair for a d_model that is no multiple of 128 (bf16, plain block).
 template <int NW, int TT>
 hipError_t launch_km_tail(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
@@ -817,9 +830,10 @@ hipError_t launch_km_tail(const MlpArgs& a, const dfk_config_t& c, hipStream_t s
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     if (g_stage_mask & 2) {
-        const size_t lds = km_lds_down(c, &geo);
-        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NW, TT, BF16, true>, lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_down_km<NW, TT, BF16, true>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NW * 64), lds, st, a, geo);
+        constexpr int NWD = km_down_waves(NW, TT);
+        const size_t lds = km_lds_down(km_down_cfg(c, TT), &geo);
+        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NWD, TT, BF16, true>, lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_down_km<NWD, TT, BF16, true>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NWD * 64), lds, st, a, geo);
         return hipGetLastError();
     }
     return hipSuccess;
@@ -854,9 +868,10 @@ hipError_t launch_km_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st)
     }
     if (g_stage_mask & 2) {
         KmGeom geo{};
-        const size_t lds = km_lds_down(c, &geo);
-        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NW, TT, E>, lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_down_km<NW, TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NW * 64), lds, st, a, geo);
+        constexpr int NWD = km_down_waves(NW, TT);
+        const size_t lds = km_lds_down(km_down_cfg(c, TT), &geo);
+        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NWD, TT, E>, lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_down_km<NWD, TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NWD * 64), lds, st, a, geo);
         return hipGetLastError();
     }
     return hipSuccess;
