@@ -363,8 +363,19 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     return out;
 }
 
-// Untuned default, from measurements on MI355X.  One token: the single launch that keeps A_2 in LDS, with the
-// atomic reduction (no boundary between two kernels, and its 256 full-width partial sums are still cheap).  Up to
+// One token: whether the single launch that keeps A_2 in LDS is the untuned choice, or the one that holds both kernels' workgroups.
+// The former has nothing to wait for, but 256 partial sums of all of Y, a second round of workgroups from d_ff = 16384 on (a
+// slice is at most 64 rows), and wavefronts that each own an eighth of the chunks and column blocks, which only widths that are
+// multiples of 1024 divide evenly.  us, A_2 in LDS / both kernels' workgroups: 2048 x 5504 20.2 / 21.1, 3072 x 12288 43.1 / 43.7, 4096 x
+// 8192 40.4 / 41.1, 4096 x 14336 59.4 / 60.1, 4096 x 16384 66.6 / 67.8.  On the other side: 4096 x 20480 88.5 / 83.2, 4096 x 4096 30.1 /
+// 23.7, 1024 x 2816 13.2 / 11.4, 1536 x 4096 20.2 / 15.1, 2304 x 9216 31.1 / 27.9, 3584 x 9216 40.8 / 37.1, 7168 x 20480 146 / 135,
+// 8192 x 14336 113 / 111, 8192 x 28672 222 / 213, 16384 x 16384 277 / 246; 3072 x 8192 30.8 / 30.7.
+bool local_pays(int d_model, int d_ff) {
+    return d_model % 1024 == 0 && d_model >= 2048 && d_model <= 4096 && d_ff >= 2 * d_model && d_ff <= 16384;
+}
+
+// Untuned default, from measurements on MI355X.  One token of some sizes (local_pays): the single launch that keeps A_2 in LDS, with
+// the atomic reduction (no boundary between two kernels, and its 256 full-width partial sums are still cheap).  Else, up to
 // 64 tokens: the single launch that holds both kernels' workgroups (atomic reduction), which saves the launch
 // boundary at every token count.  Of the two-kernel forms: beyond 64 tokens the pair that takes up to 256 per
 // launch, else the pair for up to 64 tokens, then the rows-split down kernel, then the rest.  Within a form of the
@@ -381,7 +392,7 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
         }
         if (roles_launch(c)) return M <= 64 && c.reduce == DFK_REDUCE_ATOMIC && c.depth == 4 ? -2 : 3;
         if (c.path == DFK_PATH_MFMA && c.kmajor == 1)      // the single launch with A_2 in LDS
-            return c.reduce == DFK_REDUCE_ATOMIC && c.waves == 8 ? (M == 1 ? -3 : 3) : 4;
+            return c.reduce == DFK_REDUCE_ATOMIC && c.waves == 8 ? (M == 1 && local_pays(d_model, d_ff) ? -3 : 3) : 4;
         return 5;
     };
     const int nblk = (d_model + 127) / 128;

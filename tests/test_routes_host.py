@@ -144,3 +144,11 @@ def test_which_down_kernel_the_transposed_layout_gets(M, d, ff, split):
         assert not tuned and (pick.path, pick.kmajor) == (MFMA, 5)
         assert pick.k2_col_blocks == (d // 128 if split else 1), pick
         assert dfk.dfk_config_valid(pick, M, d, ff, dt)
+
+
+@pytest.mark.parametrize("d,ff,kmajor", [(4096, 14336, 1), (4096, 16384, 1), (4096, 16392, 4), (4096, 8184, 4), (2048, 5504, 1), (3072, 8192, 1),
+                                         (1024, 5632, 4), (2304, 9216, 4), (5120, 13824, 4), (8192, 28672, 4)])
+def test_which_single_launch_one_token_gets(d, ff, kmajor):
+    for dt in (dfk.DFK_BF16, dfk.DFK_FP16):
+        pick, tuned = dfk.dfk_get_choice(1, d, ff, dt)
+        assert not tuned and (pick.variant, pick.path, pick.kmajor, pick.reduce) == (FUSED, MFMA, kmajor, dfk.DFK_REDUCE_ATOMIC), pick
