@@ -108,10 +108,16 @@ bool roles_launch(const dfk_config_t& c) { return c.variant == DFK_VARIANT_FUSED
 // whose cost the least).  512 x 28672, counter reduction: 1 token 33.8 us with 16, 27.0 with 48, 27.5 with 64; 16 tokens 36.4, 32.6, 34.5; 64 tokens 60.2 with 16, 59.1 with 24, 70.1 with 64; 512 x 14336 at 1 token 20.7
 // with 16, 19.3 with 24, 19.8 with 64, at 64 tokens 39.7, 41.6, 55.5; atomic, at 16 tokens, 1024 x 28672 42.2 with 16, 40.0
 // with 32, 1536 x 28672 53.9 with 16, 54.4 with 18, 53.1 with 21.
+// The counter reduction of more than two tokens takes 12 where d_ff is no such multiple: the last workgroup of a column block reads all its splits' blocks alone.
+// 16 / 12 splits, us: 512 x 1536 at 64 tokens 20.9 / 20.0, 896 x 4864 at 40 24.3 / 23.3, 1024 x 5632 at 16 18.5 / 18.0, 1536 x
+// 8960 at 64 39.9 / 37.8, 2048 x 5504 at 8 and 64 23.3 / 22.3, 36.7 / 33.7, 768 x 3072 at 4 13.5 / 13.0; at two tokens 896 x 4864 15.4 / 15.8,
+// 1536 x 8960 23.7 / 23.7; 896 x 4864 at 16 17.3 / 17.5, where a split has more than twelve 32-row blocks for four wavefronts.  (8: 2048 x 5504 at 64 33.6, 1024 x 5632 27.7 against 26.9.)
 constexpr int kFewSplits = 16;
 int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
     const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
-    return std::max(1, std::min(256 / k2c, std::max(kFewSplits, d_ff / rows)));
+    const bool four_waves = M <= 16 && d_model < 1024;
+    const int few = reduce == DFK_REDUCE_TICKET && M > 2 && d_ff <= 12 * d_model && !(four_waves && d_ff > 12 * 384) ? 12 : kFewSplits;
+    return std::max(1, std::min(256 / k2c, std::max(few, d_ff / rows)));
 }
 // Workgroups of the 64-token pair's down kernels, untuned, own two 128-column blocks instead of one (512-byte pieces of W_down's
 // rows, A_2 read half as often) where the layer is wide and a split then still has many rows: two blocks mean twice as many
@@ -352,7 +358,11 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
                                   std::max(1, std::min(k2s, d_ff / 64)), nblk, (int)dtype, DFK_REDUCE_TICKET, 0, 5));
     };
     if (wdt_split_pays(M, d_model, d_ff)) split_form();
-    for (int wd : {82, 83, 84, 46})          // wavefronts, ring depth
+    // Wavefronts, ring depth: the shortest ring (two slots) is the fastest, but where d_model has fewer 16-row tiles than there are CUs
+    // each workgroup needs more in flight (at 9 to 16 tokens of the narrower ones the A_2 tiles take that back).  Two / three slots, us: 2304 x 9216 at 1 and 8 tokens 30.3 / 29.7, 30.9 / 30.5, 1024 x 2816 at 1,
+    // 32 and 48 11.4 / 10.7, 14.1 / 13.5, 16.3 / 15.7; 4096 x 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3; at 12 and 16: 3584 x 9216 41.1 / 39.4, 2304 x 9216 32.3 / 32.5, 2048 x 5504 21.0 / 21.3.
+    const std::vector<int> rings = t16 < 256 && (M <= 8 || M > 16 || d_model > 2304) ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
+    for (int wd : rings)
         for (int splits : {256, 512, more_splits})
             for (int k2s : {256, 512, 128}) {
                 push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,

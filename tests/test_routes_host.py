@@ -152,3 +152,16 @@ def test_which_single_launch_one_token_gets(d, ff, kmajor):
     for dt in (dfk.DFK_BF16, dfk.DFK_FP16):
         pick, tuned = dfk.dfk_get_choice(1, d, ff, dt)
         assert not tuned and (pick.variant, pick.path, pick.kmajor, pick.reduce) == (FUSED, MFMA, kmajor, dfk.DFK_REDUCE_ATOMIC), pick
+
+
+@pytest.mark.parametrize("M,d,ff,splits", [(2, 896, 4864, 16), (3, 768, 3072, 12), (16, 896, 4864, 16), (17, 896, 4864, 12), (16, 896, 4608, 12), (64, 640, 2560, 12),
+                                           (16, 512, 6136, 16), (64, 512, 6144, 12), (64, 512, 6152, 16)])
+def test_splits_of_the_counter_reduction_on_narrow_layers(M, d, ff, splits):
+    pick, tuned = dfk.dfk_get_choice(M, d, ff, dfk.DFK_BF16)
+    assert not tuned and (pick.variant, pick.kmajor, pick.reduce, pick.k2_splits) == (TWO, 1, dfk.DFK_REDUCE_TICKET, splits), pick
+
+
+@pytest.mark.parametrize("M,d,ff,depth", [(1, 2304, 9216, 3), (8, 4096, 14336, 2), (16, 1024, 2816, 2), (8, 1024, 2816, 3), (24, 1024, 2816, 3), (16, 2432, 4096, 3), (1, 3968, 8192, 3), (4, 8192, 7168, 2)])
+def test_ring_of_the_transposed_layout(M, d, ff, depth):
+    pick, _ = dfk.dfk_get_choice_wdt(M, d, ff, dfk.DFK_BF16)
+    assert (pick.kmajor, pick.k2_col_blocks, pick.waves, pick.depth) == (5, 1, 8, depth), pick
