@@ -510,6 +510,21 @@ bool choose(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, d
     return heuristic(M, d_model, d_ff, dtype, want_variant, out);
 }
 
+// The untuned pair of a block, or of a width that is no multiple of 128, up to 64 tokens, as the single launch of both kernels' workgroups: same splits, same counter reduction
+// (the result stays reproducible bit for bit), no boundary between two launches.  Up to 16 tokens only from 48 MB of weights on: below,
+// the down workgroups' wait costs what the boundary does.  Layers replayed from a graph, us per layer, pair / single launch: 2304 x 9216
+// at 1, 8 and 33 tokens 32.2 / 30.5, 33.3 / 31.7, 44.3 / 42.0; 4096 x 14336 at 1 and 64 65.1 / 63.5, 83.8 / 82.4; 5120 x 27648 at 64 186.9
+// / 180.0; 1792 x 4864 (52 MB) at 12 22.5 / 21.6; 1024 x 2816 at 40 22.8 / 22.3; 12288 x 12288 at 33 167.4 / 168.1.  On the other side:
+// 1024 x 5632 (35 MB) at 1 16.0 / 16.5, 1152 x 4096 at 8 16.7 / 17.1, 1536 x 4096 (38 MB) at 8 18.2 / 18.5.
+// Widths off 128, whole call: 2888 x 7688 at 1, 12 and 64 tokens 37.1 / 35.3, 38.9 / 37.3, 54.4 / 53.8, 1800 x 5000 at 16 and 33 26.0 / 23.7, 32.0 / 29.5.
+void single_launch_of(dfk_config_t* c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    dfk_config_t r = *c;
+    if (M > 64 || c->kmajor != 1 || c->variant != DFK_VARIANT_TWO_KERNEL) return;
+    if (M <= 16 && (size_t)6 * d_model * d_ff < (size_t)48000000) return;
+    r.variant = DFK_VARIANT_FUSED; r.kmajor = 4; r.depth = 4;
+    if (d_model % 128 ? mfma_km_single_launch_fits(r, M, d_model, d_ff, dtype) : mfma_km_block_config_valid(r, M, d_model, d_ff, dtype)) *c = r;
+}
+
 // ---------------------------------------------------------------- dispatch
 // norm_w / eps / resid: the pre-norm residual form (kernel pair for up to 64 tokens only,
 // checked by the caller); NULL / 0 / NULL for the plain block.
@@ -573,9 +588,11 @@ dfk_status_t call(const void* X, const void* Wg, const void* Wu, const void* Wd,
     dfk_status_t s = check(X, Wg, Wu, Wd, Y, M, d_model, d_ff, dtype, cfg, ws, ws_bytes, true, false, wd_t);
     if (s != DFK_OK) return s;
     dfk_config_t c;
+    int tuned = 0;
     if (cfg) c = *cfg;
-    else if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, nullptr)
-                  : !choose(M, d_model, d_ff, dtype, want_variant, &c, nullptr)) return DFK_ERR_UNSUPPORTED_SHAPE;
+    else if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, &tuned)
+                  : !choose(M, d_model, d_ff, dtype, want_variant, &c, &tuned)) return DFK_ERR_UNSUPPORTED_SHAPE;
+    if (!cfg && !wd_t && !tuned && want_variant == DFK_VARIANT_AUTO && d_model % 128) single_launch_of(&c, M, d_model, d_ff, dtype);
     return run(X, Wg, Wu, Wd, Y, M, d_model, d_ff, dtype, c, ws, (hipStream_t)stream);
 }
 
@@ -816,20 +833,6 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* Wg, const void* Wu
 }
 
 namespace {
-// The untuned pair of a block, up to 64 tokens, as the single launch of both kernels' workgroups: same splits, same counter reduction
-// (the result stays reproducible bit for bit), no boundary between two launches.  Up to 16 tokens only from 48 MB of weights on: below,
-// the down workgroups' wait costs what the boundary does.  Layers replayed from a graph, us per layer, pair / single launch: 2304 x 9216
-// at 1, 8 and 33 tokens 32.2 / 30.5, 33.3 / 31.7, 44.3 / 42.0; 4096 x 14336 at 1 and 64 65.1 / 63.5, 83.8 / 82.4; 5120 x 27648 at 64 186.9
-// / 180.0; 1792 x 4864 (52 MB) at 12 22.5 / 21.6; 1024 x 2816 at 40 22.8 / 22.3; 12288 x 12288 at 33 167.4 / 168.1.  On the other side:
-// 1024 x 5632 (35 MB) at 1 16.0 / 16.5, 1152 x 4096 at 8 16.7 / 17.1, 1536 x 4096 (38 MB) at 8 18.2 / 18.5.
-void single_launch_of(dfk_config_t* c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
-    dfk_config_t r = *c;
-    if (M > 64 || c->kmajor != 1 || c->variant != DFK_VARIANT_TWO_KERNEL) return;
-    if (M <= 16 && (size_t)6 * d_model * d_ff < (size_t)48000000) return;
-    r.variant = DFK_VARIANT_FUSED; r.kmajor = 4; r.depth = 4;
-    if (mfma_km_block_config_valid(r, M, d_model, d_ff, dtype)) *c = r;
-}
-
 dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const void* Wg,
                        const void* Wu, const void* Wd, void* H_out, int M, int d_model, int d_ff,
                        dfk_dtype_t dtype, const dfk_config_t* cfg, void* workspace,

@@ -759,11 +759,11 @@ __global__ __launch_bounds__(NW * 64) void k_down_km(MlpArgs a, KmGeom geo) {
 // device memory (2 bytes per token and d_ff row), as between the two kernels.
 // NORM: with the normalisation in front and the residual added (dfk_mlp_block).  The output may be the input there: a column
 // block is stored once every d_ff split has arrived, so after every gate/up workgroup has read the input and published.
-template <int NW, int TT, typename E, bool NORM = false>
+template <int NW, int TT, typename E, bool NORM = false, bool TAIL = false>
 __global__ __launch_bounds__(NW * 64) void k_roles_km(MlpArgs a, KmGeom geo) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    if ((int)blockIdx.x < geo.n_gateup) gateup_km_body<NW, TT, E, NORM, true>(a, geo, blockIdx.x, lds);
-    else down_km_body<NW, TT, E, true>(a, geo, blockIdx.x - geo.n_gateup, lds);
+    if ((int)blockIdx.x < geo.n_gateup) gateup_km_body<NW, TT, E, NORM, true, false, TAIL>(a, geo, blockIdx.x, lds);
+    else down_km_body<NW, TT, E, true, TAIL>(a, geo, blockIdx.x - geo.n_gateup, lds);
 }
 
 // ---------------------------------------------------------------- host side
@@ -885,7 +885,7 @@ hipError_t launch_km_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) 
 
 // Both kernels' workgroups in one launch.  The stage mask of the per-kernel timer maps to the head of the grid
 // alone (gate/up workgroups, nothing counted) and to the tail alone (down workgroups that wait for nobody).
-template <int NW, int TT, typename E, bool NORM>
+template <int NW, int TT, typename E, bool NORM, bool TAIL = false>
 hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     static LdsAllowance allowed;
     KmGeom geo{}, gd{};
@@ -902,12 +902,13 @@ hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream
     if (const char* e = std::getenv("DFK_DEBUG_SPIN_LIMIT")) geo.role_spin_limit = std::atoi(e);
     const int grid = geo.n_gateup + (tail ? a.k2_splits * a.k2_col_blocks : 0);
     if (grid == 0) return hipSuccess;
-    if (hipError_t e = allow_lds(allowed, (const void*)k_roles_km<NW, TT, E, NORM>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_roles_km<NW, TT, E, NORM>), dim3(grid), dim3(NW * 64), lds, st, a, geo);
+    if (hipError_t e = allow_lds(allowed, (const void*)k_roles_km<NW, TT, E, NORM, TAIL>, lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_roles_km<NW, TT, E, NORM, TAIL>), dim3(grid), dim3(NW * 64), lds, st, a, geo);
     return hipGetLastError();
 }
 template <int NW, int TT>
 hipError_t launch_km_roles_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    if (a.d_model % kKC) return a.norm_w || a.dtype != DFK_BF16 ? hipErrorInvalidValue : launch_km_roles_te<NW, TT, BF16, false, true>(a, c, st);
     if (a.norm_w) return a.dtype == DFK_FP16 ? launch_km_roles_te<NW, TT, FP16, true>(a, c, st) : launch_km_roles_te<NW, TT, BF16, true>(a, c, st);
     return a.dtype == DFK_FP16 ? launch_km_roles_te<NW, TT, FP16, false>(a, c, st) : launch_km_roles_te<NW, TT, BF16, false>(a, c, st);
 }
@@ -976,7 +977,11 @@ bool mfma_km_block_config_valid(const dfk_config_t& c, int M, int d_model, int d
 // configuration, and a grid small enough that its 16-bit-safe index arithmetic holds.
 static dfk_config_t roles_as_pair(const dfk_config_t& c) { dfk_config_t p = c; p.variant = DFK_VARIANT_TWO_KERNEL; p.kmajor = 1; return p; }
 bool mfma_km_roles_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
-    if (c.variant != DFK_VARIANT_FUSED || c.kmajor != 4 || c.waves != 8 || d_model % kKC) return false;
+    return d_model % kKC == 0 && mfma_km_single_launch_fits(c, M, d_model, d_ff, dtype);
+}
+// Also for widths that are no multiple of 128 (bf16), where it is not offered as a configuration but stands in for the pair's untuned choice.
+bool mfma_km_single_launch_fits(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    if (c.variant != DFK_VARIANT_FUSED || c.kmajor != 4 || c.waves != 8) return false;
     if ((long long)c.splits + (long long)c.k2_splits * c.k2_col_blocks > 65535) return false;
     if (c.k2_splits > kRoleCountEnd - kRoleCount0) return false;   // one counter per d_ff split of the down projection
     return mfma_km_config_valid(roles_as_pair(c), M, d_model, d_ff, dtype);
