@@ -357,6 +357,9 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
                     push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,
                                   std::max(1, std::min(k2s, d_ff / 64)), nblk, (int)dtype, DFK_REDUCE_TICKET, 0, 5));
     };
+    // Half inputs where the whole-rows form does not exist (it needs four 128-wide chunks each way): the plain-FMA pair, which keeps A_2 in
+    // fp32, comes first at every token count.  The split form would round A_2 to half, and overflow beyond 65504: only for a caller who asks.
+    if (dtype == DFK_FP16 && (d_model < 512 || d_ff < 512)) valu();
     if (wdt_split_pays(M, d_model, d_ff)) split_form();
     // Wavefronts, ring depth: the shortest ring (two slots) is the fastest, but where d_model has fewer 16-row tiles than there are CUs
     // each workgroup needs more in flight (at 9 to 16 tokens of the narrower ones the A_2 tiles take that back).  Two / three slots, us: 2304 x 9216 at 1 and 8 tokens 30.3 / 29.7, 30.9 / 30.5, 1024 x 2816 at 1,
@@ -1037,7 +1040,9 @@ dfk_status_t dfk_tune(const int* M_list, int nM, int d_model, int d_ff, dfk_dtyp
         // the candidates for W_down as [d_model, d_ff] (timing does not depend on what the synthetic weights mean)
         Entry best_t;
         best_t.usec = -1.0;
-        for (const auto& c : candidates_wdt(M, d_model, d_ff, dtype)) {
+        const auto cands_t = candidates_wdt(M, d_model, d_ff, dtype);
+        for (const auto& c : cands_t) {
+            if (cands_t[0].a2_dtype == DFK_FP32 && c.a2_dtype != DFK_FP32) continue;   // being faster is no reason to round A_2
             double us = 0.0;
             dfk_status_t s = time_config(c, M, d_model, d_ff, dtype, scratch, sets, iters, (hipStream_t)stream, false, &us);
             if (s != DFK_OK) {

@@ -165,3 +165,14 @@ def test_splits_of_the_counter_reduction_on_narrow_layers(M, d, ff, splits):
 def test_ring_of_the_transposed_layout(M, d, ff, depth):
     pick, _ = dfk.dfk_get_choice_wdt(M, d, ff, dfk.DFK_BF16)
     assert (pick.kmajor, pick.k2_col_blocks, pick.waves, pick.depth) == (5, 1, 8, depth), pick
+
+
+@pytest.mark.parametrize("d,ff", [(256, 128), (256, 14336), (384, 640), (512, 128), (1024, 256), (4096, 384)])
+@pytest.mark.parametrize("M", [1, 16, 17, 33, 64, 65, 200, 256])
+def test_half_inputs_of_the_transposed_layout_keep_a_wide_a2_where_they_had_it(M, d, ff):
+    """Without four 128-wide chunks each way the plain-FMA pair is the choice for half inputs, at every token count alike: it keeps A_2 in
+    fp32.  The split form rounds it to half, so it is there for a caller who asks, and nobody else."""
+    pick, tuned = dfk.dfk_get_choice_wdt(M, d, ff, dfk.DFK_FP16)
+    assert not tuned and (pick.path, pick.a2_dtype) == (VALU, dfk.DFK_FP32), pick
+    pick, _ = dfk.dfk_get_choice_wdt(M, 512, 512, dfk.DFK_FP16)
+    assert pick.path == MFMA, pick
