@@ -148,10 +148,15 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  number of polls) until the gate/up workgroups of its d_ff rows have
  *                  published A_2, which crosses through device memory as between two kernels.
  *                  Up to 64 tokens per launch; waves = 8; otherwise the constraints of pair 1,
- *                  whose k2_splits, k2_col_blocks and reduce fields it uses.  The bound of the wait is
- *                  about two million polls (seconds); a workgroup whose wait runs out turns its
- *                  share of Y into NaN.  (Tests force that path from the host with the environment
- *                  variable DFK_DEBUG_SPIN_LIMIT = number of polls; leave it unset otherwise.);
+ *                  whose k2_splits, k2_col_blocks and reduce fields it uses.  Such launches may overlap
+ *                  on several streams (a workspace each): a down workgroup whose wait takes long makes
+ *                  room for others and is made up for later in the launch, so every wait ends as long as
+ *                  fewer such launches run at a time than an XCD has CUs.  The bound is a last
+ *                  resort, about two million polls (seconds); a workgroup whose wait runs out turns its
+ *                  share of Y into NaN (in place, dfk_mlp_block's input is lost with it), and the
+ *                  workspace has to be initialised again.  (Tests force these paths from the host with
+ *                  the environment variables DFK_DEBUG_SPIN_LIMIT = number of polls and
+ *                  DFK_DEBUG_DOWN_FIRST; leave them unset otherwise.);
  *                  0 = the first single-launch kernel (bf16 only).
  */
 typedef struct dfk_config_t {

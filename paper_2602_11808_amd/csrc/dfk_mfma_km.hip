@@ -31,6 +31,7 @@
 #include <atomic>
 #include <cstdlib>
 #include "dfk_mfma_common.h"
+#include "dfk_roles.h"
 
 namespace dfk {
 namespace {
@@ -43,19 +44,23 @@ struct KmGeom {
     int pass;    // gate/up kernel: row tiles whose partial sums LDS holds per pass at the end
     int norm_off;  // gate/up kernel with the normalisation: byte offset in LDS of the weight slices, past rings and stage
     // the single launch of both kernels' workgroups:
+    RoleShape role;
     int n_gateup;            // workgroups of the gate/up kernel at the head of the grid
     int role_publish;        // gate/up workgroups count themselves done
     int role_wait;           // down workgroups wait for the gate/up workgroups of their rows
-    int role_stride;         // words between the counters of adjacent d_ff splits
     int depth_down;          // ring slots per wavefront of the down workgroups
     int role_spin_limit;     // polls of the done counter before a down workgroup gives up (its outputs become NaN)
+    int down_first;          // tests: the down workgroups are at the head of the grid
 };
 
-// Counter words of the single launch of both kernels' workgroups, in the counter area of the workspace (column
-// block counters occupy [0, 512), the second reduction level word 512, the slice-local fused kernel word 1023).
-constexpr int kRolePassed = 1022;   // down workgroups that are past their wait: the last one clears the counters below
-constexpr int kRoleCount0 = 520;    // per d_ff split of the down projection: gate/up workgroups that have published
-constexpr int kRoleCountEnd = 1020; //   A_2 rows of that split; geo.role_stride words apart (spread over cache lines)
+static_assert(kRoleCount0 > kTicketLevel2 && kRolePassed < kMaxTickets - 1, "the words of the single launch lie between the reductions' counters");
+struct DeviceMem {
+    static __device__ __forceinline__ unsigned load(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    static __device__ __forceinline__ void store(unsigned* p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    static __device__ __forceinline__ unsigned fetch_add(unsigned* p, unsigned v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    static __device__ __forceinline__ void settle() { drain_own_memory_ops(); }
+    static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(8); }
+};
 
 // the slice (of S) that holds 8-row group gidx of ng: the inverse of slice_rows
 __device__ __forceinline__ int slice_of_group(int ng, int S, int gidx) { return (int)((((long long)gidx + 1) * S - 1) / ng); }
@@ -160,7 +165,7 @@ struct KmStream1 {
 // it has the whole sum of squares of every token by itself.
 //
 // PUBLISH (the single launch that holds both kernels' workgroups, further down): A_2 is stored
-// with device-scope stores and the workgroup ends by counting itself done on kRoleDone.
+// with device-scope stores and the workgroup ends by counting itself done on the d_ff splits of its rows.
 //
 // DOWN_T: the same stream and accumulation computes the down projection from W_down given as [d_model, d_ff]
 // (a linear layer's own [out, in] layout): Y^T = W_down^T A_2^T has the shape of stage one, with d_ff as the k
@@ -380,7 +385,7 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
             const int ng = a.d_ff / 8;
             const int lo = slice_of_group(ng, a.k2_splits, j0 / 8), hi = slice_of_group(ng, a.k2_splits, j1 / 8 - 1);
             for (int js = lo; js <= hi; ++js)
-                __hip_atomic_fetch_add(a.tickets + kRoleCount0 + js * geo.role_stride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(a.tickets + kRoleCount0 + js * geo.role.stride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -505,17 +510,21 @@ __host__ __device__ constexpr int km_col_blocks(int tt) { return tt >= 3 ? 1 : 2
 //
 // WAIT (the single launch of both kernels' workgroups): the stream carries the A tile of a 32-row block behind the
 // first column block's weight tiles and starts with those alone; then the workgroup waits until every gate/up
-// workgroup of its rows has counted itself done, and goes on as the kernel does, but with A_2 loads of device scope:
-// workgroups of other XCDs wrote parts of the lines this XCD's caches may hold.  (The writers store with device scope and
+// workgroup of its rows has counted itself done, or parks if that takes long (dfk_roles.h says why), and goes on as the kernel
+// does, but with A_2 loads of device scope: workgroups of other XCDs wrote parts of the lines this XCD's caches may hold.  (The writers store with device scope and
 // count themselves once the stores are acknowledged.)  With one invalidation of the caches per workgroup after the wait
 // instead, and plain loads: 60.7 us where this takes 60.0 at one token of 4096 x 14336, 28.9 / 28.3 at 8 of 2304 x 9216, 71.1 /
 // 70.3 at 33 of 8192 x 7168; equal at 64 tokens of 8192 x 28672, where the 64 column blocks re-read the most.
+//
+// stand_in: this workgroup does the work of a parked one.  Returns whether there are notes of parked workgroups for the caller to go through.
 template <int NW, int TT, typename E, bool WAIT, bool TAIL = false>
-__device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds) {
+__device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds, const bool stand_in = false) {
     __shared__ int flag;
+    __shared__ unsigned passed;
     constexpr int NTHREADS = NW * 64;
     constexpr int CBM = km_col_blocks(TT);
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    if (WAIT) asm volatile("" : "+v"(tid));    // (the caller's loop: nothing that depends on the thread is kept from one round to the next)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane & 15, g = lane >> 4;
@@ -554,22 +563,21 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
         ts.start(2 * pre);                 // weight tiles only: nothing of A_2 yet
         if (geo.role_wait > 0) {
             if (tid == 0) {
-                int polls = 0, ok = 1;
                 const int ng = a.d_ff / 8;
                 const unsigned expected = (unsigned)(slice_of_group(ng, a.splits, j1 / 8 - 1) - slice_of_group(ng, a.splits, j0 / 8) + 1);
-                const unsigned* cnt = a.tickets + kRoleCount0 + js * geo.role_stride;
-                while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < expected) {
-                    if (++polls > geo.role_spin_limit) { ok = 0; break; }
-                    __builtin_amdgcn_s_sleep(8);
-                }
-                flag = ok;
+                flag = role_wait<DeviceMem>(a.tickets, geo.role, js, expected, geo.role_spin_limit, stand_in ? nullptr : (unsigned*)a.Q, wg);
             }
             __syncthreads();
-            gave_up = flag == 0;
+            const int got = flag;
             __syncthreads();               // flag is used again by the reduction
+            if (got == kRoleParked) {
+                drain_own_memory_ops();    // the tiles requested ahead have landed
+                return false;
+            }
+            gave_up = got == kRoleGaveUp;
             DFK_STAMP(7);
             // this workgroup is past its wait; the answer is looked at when the stream has ended
-            if (tid == 0) passed_before = __hip_atomic_fetch_add(a.tickets + kRolePassed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0 && !stand_in) passed_before = role_pass<DeviceMem>(a.tickets);
         }
         ts.top_up();
     } else {
@@ -684,6 +692,7 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
     // at a time: per-wavefront stages [16 tokens][128] over the drained rings.
     const bool atomic_mode = a.reduce_mode == DFK_REDUCE_ATOMIC;
     float* stage = (float*)lds;                           // [NW][16][128]
+    if (WAIT && tid == 0) passed = passed_before;
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < CBM; ++b) {
@@ -723,13 +732,14 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
         }
     }
     const int width = TAIL ? min(CB * 128, a.d_model - blk_lo * 128) : CB * 128;
-    if (WAIT && geo.role_wait > 0 && tid == 0) {
-        // every down workgroup is past its wait once the last one has said so: that one clears the counters for the next launch
-        const unsigned n_down = (unsigned)(a.k2_splits * a.k2_col_blocks);
-        if (passed_before == n_down - 1u) {
-            __hip_atomic_store(a.tickets + kRolePassed, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (int x = 0; x < a.k2_splits; ++x)
-                __hip_atomic_store(a.tickets + kRoleCount0 + x * geo.role_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool notes = false;
+    if (WAIT && geo.role_wait > 0 && !stand_in) {
+        // every other down workgroup is past its wait, or parked, once the last one has said so: if none has parked, that one clears the
+        // words for the next launch here
+        const unsigned before = __builtin_amdgcn_readfirstlane(passed);
+        if (role_left(geo.role, before) == 1u) {
+            notes = before >> 16 != 0;
+            if (!notes && tid == 0) role_clear<DeviceMem>(a.tickets, geo.role);
         }
     }
     if (atomic_mode) {
@@ -737,11 +747,11 @@ __device__ __forceinline__ void down_km_body(const MlpArgs& a, const KmGeom& geo
         __syncthreads();
         if (tid == 0) flag = arrive_last(a.tickets + cb, (unsigned)a.k2_splits) ? 1 : 0;
         __syncthreads();
-        if (!flag) return;
-        drain_accumulator<E, NTHREADS>(a, blk_lo * 128, width);
-        return;
+        if (flag) drain_accumulator<E, NTHREADS>(a, blk_lo * 128, width);
+    } else {
+        reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid, (float4*)lds);
     }
-    reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid, (float4*)lds);
+    return notes;
 }
 
 template <int NW, int TT, typename E, bool TAIL = false>
@@ -751,19 +761,57 @@ __global__ __launch_bounds__(NW * 64) void k_down_km(MlpArgs a, KmGeom geo) {
 }
 
 // ---------------------------------------------------------------- both kernels' workgroups in one launch
-// Grid = the gate/up kernel's workgroups followed by the down kernel's.  Workgroups are dispatched in index
-// order, so no down workgroup starts before every gate/up workgroup (of its XCD's share of the grid) has, and a
-// gate/up workgroup waits for nothing: the down workgroups' wait always ends.  What the single launch buys over
+// Grid = the gate/up kernel's workgroups followed by the down kernel's.  Workgroups of a grid are dispatched in index
+// order on each XCD, so a down workgroup as a rule waits for workgroups that run; where launches of other streams hold their CUs it
+// may park (dfk_roles.h): the wait ends in any order of dispatch.  What the single launch buys over
 // two: no launch boundary (drain, dispatch and ramp with HBM idle), and the down workgroups request their first
 // W_down tiles while the last gate/up workgroups are still streaming.  A_2 crosses between workgroups through
 // device memory (2 bytes per token and d_ff row), as between the two kernels.
 // NORM: with the normalisation in front and the residual added (dfk_mlp_block).  The output may be the input there: a column
 // block is stored once every d_ff split has arrived, so after every gate/up workgroup has read the input and published.
+// The notes of parked workgroups are in the group sums' place in the workspace, which a reduction over column blocks does not use.
+struct RolesArgs { MlpArgs a; KmGeom geo; };
+// The launch's arguments, read again: to the compiler other values each time.
+__device__ __forceinline__ RolesArgs roles_args_again() {
+    typedef const __attribute__((address_space(4))) unsigned* ConstWords;
+    ConstWords p = (ConstWords)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    union { RolesArgs r; unsigned w[sizeof(RolesArgs) / 4]; } u;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(RolesArgs) / 4; ++i) u.w[i] = p[i];
+    return u.r;
+}
+
+// Place of this workgroup among the gate/up workgroups followed by the down workgroups.
+__device__ __forceinline__ int roles_place(const KmGeom& geo) {
+    const int b = (int)blockIdx.x;
+    return !geo.down_first ? b : b < geo.role.n_down ? geo.n_gateup + b : b - geo.role.n_down;
+}
+
 template <int NW, int TT, typename E, bool NORM = false, bool TAIL = false>
-__global__ __launch_bounds__(NW * 64) void k_roles_km(MlpArgs a, KmGeom geo) {
+__global__ __launch_bounds__(NW * 64) void k_roles_km(RolesArgs r) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    if ((int)blockIdx.x < geo.n_gateup) gateup_km_body<NW, TT, E, NORM, true, false, TAIL>(a, geo, blockIdx.x, lds);
-    else down_km_body<NW, TT, E, true, TAIL>(a, geo, blockIdx.x - geo.n_gateup, lds);
+    const int wg = roles_place(r.geo);
+    if (wg < r.geo.n_gateup) {
+        gateup_km_body<NW, TT, E, NORM, true, false, TAIL>(r.a, r.geo, wg, lds);
+        return;
+    }
+    if (__builtin_expect(!down_km_body<NW, TT, E, true, TAIL>(r.a, r.geo, wg - r.geo.n_gateup, lds), 1)) return;
+    // Others have parked: their work, one after the other.  Code apart from the call above and with arguments of its own for each round, so
+    // that nothing is kept in registers for it (as one loop around a single call it cost every launch 0.5 to 0.9 us).
+    const int n = __builtin_amdgcn_readfirstlane((int)DeviceMem::load(r.a.tickets + kRoleNotes));   // final, and by every wavefront read before it is cleared:
+    for (int i = 0; i < n; ++i) {                                                                   // at least one note is another's, whose work has barriers
+        RolesArgs k = roles_args_again();
+        k.a.trace = nullptr;               // (the stamps of this workgroup are those of its own work)
+        const int parked = __builtin_amdgcn_readfirstlane((int)DeviceMem::load((const unsigned*)k.a.Q + i));
+        if (parked == roles_place(k.geo) - k.geo.n_gateup) continue;       // (its own note, from when it was about to park)
+        __syncthreads();
+        down_km_body<NW, TT, E, true, TAIL>(k.a, k.geo, parked, lds, true);
+    }
+    if (threadIdx.x == 0) {
+        const RolesArgs k = roles_args_again();
+        role_clear<DeviceMem>(k.a.tickets, k.geo.role);
+    }
 }
 
 // ---------------------------------------------------------------- host side
@@ -894,16 +942,17 @@ hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream
     geo.n_gateup = head ? a.splits : 0;
     geo.role_publish = head && tail;
     geo.role_wait = head && tail ? a.splits : 0;
-    geo.role_stride = 1;
-    while (geo.role_stride < 32 && a.k2_splits * geo.role_stride * 2 <= kRoleCountEnd - kRoleCount0) geo.role_stride *= 2;
+    geo.role = RoleShape{tail ? a.k2_splits * a.k2_col_blocks : 0, a.k2_splits, 1};
+    while (geo.role.stride < 32 && a.k2_splits * geo.role.stride * 2 <= kRoleCountEnd - kRoleCount0) geo.role.stride *= 2;
     geo.depth_down = std::max(c.depth, std::min(c.depth + 1, (int)((size_t)kLdsLimit / ((size_t)NW * kTileBytes))));
     lds = std::max(lds, (size_t)NW * geo.depth_down * kTileBytes);
     geo.role_spin_limit = 1 << 21;          // seconds; a healthy launch needs a handful of polls
     if (const char* e = std::getenv("DFK_DEBUG_SPIN_LIMIT")) geo.role_spin_limit = std::atoi(e);
-    const int grid = geo.n_gateup + (tail ? a.k2_splits * a.k2_col_blocks : 0);
+    geo.down_first = head && tail && std::getenv("DFK_DEBUG_DOWN_FIRST");
+    const int grid = geo.n_gateup + geo.role.n_down;
     if (grid == 0) return hipSuccess;
     if (hipError_t e = allow_lds(allowed, (const void*)k_roles_km<NW, TT, E, NORM, TAIL>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_roles_km<NW, TT, E, NORM, TAIL>), dim3(grid), dim3(NW * 64), lds, st, a, geo);
+    hipLaunchKernelGGL((k_roles_km<NW, TT, E, NORM, TAIL>), dim3(grid), dim3(NW * 64), lds, st, RolesArgs{a, geo});
     return hipGetLastError();
 }
 template <int NW, int TT>
