@@ -148,7 +148,8 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  number of polls) until the gate/up workgroups of its d_ff rows have
  *                  published A_2, which crosses through device memory as between two kernels.
  *                  Up to 64 tokens per launch; waves = 8; otherwise the constraints of pair 1,
- *                  whose k2_splits, k2_col_blocks and reduce fields it uses.  Such launches may overlap
+ *                  (d_model off 128 in bf16 included) whose k2_splits, k2_col_blocks and reduce fields
+ *                  it uses.  Such launches may overlap
  *                  on several streams (a workspace each): a down workgroup whose wait takes long makes
  *                  room for others and is made up for later in the launch, so every wait ends as long as
  *                  fewer such launches run at a time than an XCD has CUs.  The bound is a last
@@ -278,9 +279,13 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* W_gate, const void
  * cfg->kmajor == 2 (up to 256 tokens; there the normalisation is one small launch of its own
  * ahead of the pair, into the workspace: that pair is paced by its arithmetic, and scaling X
  * inside every workgroup measured slower; the residual add stays in the final store).
- * cfg == NULL picks the scheduler's choice among those; without a tuned entry a kmajor = 1 choice
- * may run as one launch that holds both kernels' workgroups (kmajor = 4 of the fused variant: same
- * splits, same counter reduction).  Any other configuration, and shapes those pairs do not cover, give DFK_ERR_UNSUPPORTED_SHAPE.  Workspace as for dfk_swiglu_mlp_ex.
+ * or cfg->kmajor == 4 of the fused variant where the normalisation weight fits its LDS (the
+ * kmajor = 1 pair as one launch that holds both kernels' workgroups).
+ * cfg == NULL picks the scheduler's choice among those (dfk_get_choice_block): the pair tuned for
+ * the two-kernel variant, else the untuned one, and a kmajor = 1 pair of them as that one launch
+ * where it pays (same splits and reduction: with the counter reduction the same bits).  Any other
+ * configuration, and shapes those do not cover, give DFK_ERR_UNSUPPORTED_SHAPE.  Workspace as for
+ * dfk_swiglu_mlp_ex.
  */
 dfk_status_t dfk_mlp_block(const void* H, const void* norm_weight, float eps,
                            const void* W_gate, const void* W_up, const void* W_down,
@@ -376,9 +381,16 @@ dfk_status_t dfk_time_kernels(const dfk_config_t* cfg, int M, int d_model, int d
                               int sets, int iters, void* stream, double* usec_out);
 
 /* The configuration a call would use now (tuned entry, else heuristic).
- * *tuned_out (may be NULL) is set to 1 if it came from the table. */
+ * *tuned_out (may be NULL) is set to 1 if it came from the table.  For a d_model that is no multiple
+ * of 128 it may be the one launch of both kernels' workgroups (kmajor = 4 of the fused variant), which
+ * is a form of the listed kmajor = 1 pair and no candidate of its own; dfk_tune times it too. */
 dfk_status_t dfk_get_choice(int M, int d_model, int d_ff, dfk_dtype_t dtype,
                             dfk_config_t* out, int* tuned_out);
+
+/* The configuration a dfk_mlp_block call (w_down_t != 0: dfk_mlp_block_wdt) with cfg == NULL would use
+ * now; *tuned_out as above.  DFK_BF16 and DFK_FP16; DFK_ERR_UNSUPPORTED_SHAPE where the call gives it. */
+dfk_status_t dfk_get_choice_block(int M, int d_model, int d_ff, dfk_dtype_t dtype, int w_down_t,
+                                  dfk_config_t* out, int* tuned_out);
 
 /* The same three queries for W_down given as [d_model, d_ff] (dfk_swiglu_mlp_wdt): its candidates, and the
  * configuration a call would use now.  dfk_tune times these

@@ -82,6 +82,7 @@ SIGNATURES = [
     ("dfk_time_config", _ci, [_cfgp] + [_ci] * 4 + [_vp, _sz, _ci, _ci, _vp, ctypes.POINTER(ctypes.c_double)]),
     ("dfk_time_kernels", _ci, [_cfgp] + [_ci] * 4 + [_vp, _sz, _ci, _ci, _vp, ctypes.POINTER(ctypes.c_double)]),
     ("dfk_get_choice", _ci, [_ci] * 4 + [_cfgp, ctypes.POINTER(_ci)]),
+    ("dfk_get_choice_block", _ci, [_ci] * 5 + [_cfgp, ctypes.POINTER(_ci)]),
     ("dfk_set_choice", _ci, [_ci] * 4 + [_cfgp, ctypes.c_double]),
     ("dfk_clear_tuning", None, []),
     ("dfk_save_tuning", _ci, [ctypes.c_char_p]),
@@ -380,6 +381,15 @@ def dfk_get_choice(M, d_model, d_ff, dtype=DFK_BF16):
     tuned = ctypes.c_int(0)
     _check(lib().dfk_get_choice(M, d_model, d_ff, dtype, ctypes.byref(c), ctypes.byref(tuned)),
            "dfk_get_choice")
+    return c, bool(tuned.value)
+
+
+def dfk_get_choice_block(M, d_model, d_ff, dtype=DFK_BF16, w_down_t=False):
+    """What dfk_mlp_block (or dfk_mlp_block_wdt) without a configuration would use."""
+    c = dfk_config_t()
+    tuned = ctypes.c_int(0)
+    _check(lib().dfk_get_choice_block(M, d_model, d_ff, dtype, int(w_down_t), ctypes.byref(c), ctypes.byref(tuned)),
+           "dfk_get_choice_block")
     return c, bool(tuned.value)
 
 

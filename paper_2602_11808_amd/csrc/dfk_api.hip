@@ -244,10 +244,10 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
                                           reduce, 0, 1));
             }
         // both kernels of that pair in one launch (gate/up workgroups at the head of the grid, down workgroups
-        // behind them)
+        // behind them); off 128 it is a form of the listed pair that the scheduler takes by itself (single_launch_of)
         for (int splits : {256, 512})
             for (int cbw : {1, 2}) {
-                if (nblk < cbw || nblk % cbw) continue;
+                if (d_model % 128 || nblk < cbw || nblk % cbw) continue;
                 const int k2c = nblk / cbw;
                 for (int k2s : {0, std::min(kFewSplits, 256 / k2c), 256 / k2c, 512 / k2c})
                     for (int reduce : {DFK_REDUCE_TICKET, DFK_REDUCE_ATOMIC})
@@ -431,6 +431,36 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
     return true;
 }
 
+// The pair for up to 64 tokens as the single launch of both kernels' workgroups: same splits, same reduction, so the same bits with the
+// counter reduction, and no boundary between two launches.  What a block runs where it pays, and a width off 128 without a tuned
+// entry (whose candidates are the pair and not this form of it; dfk_tune times it beside them).  Up to 16 tokens from 48 MB of weights
+// on: below, the down workgroups' wait costs what the boundary does.  us, pair / single launch:
+//   blocks, layers replayed from a graph: 2304 x 9216 at 1, 8 and 33 tokens 32.0 / 30.2, 32.6 / 31.1, 43.6 / 41.5; 4096 x 14336 at 1 and 64
+//   62.3 / 61.2, 83.3 / 81.7; 5120 x 40960 at 64 271 / 257; 1792 x 4864 (52 MB) at 8 and 33 20.4 / 20.2, 29.9 / 28.6; 1536 x 8960 at 17 30.2 /
+//   29.4.  On the other side: 1024 x 4096 (25 MB) at 17 and 64 18.5 / 19.8, 27.3 / 28.2; 1536 x 4096 (38 MB) at 32 22.3 / 23.4;
+//   1280 x 5120 (39 MB) at 17 23.0 / 23.6.  A width that is a multiple of 1024 gives the eight wavefronts equal runs of k, so the gate/up
+//   kernel ends evenly and there is less to gain: from 100 MB on.  2048 x 5504 (68 MB) at 8 and 17 22.7 / 23.2, 25.9 / 26.3; 1024 x 8192
+//   (50 MB) at 8 20.1 / 20.8; 2048 x 8192 (101 MB) at 17 and 40 31.1 / 31.2, 37.5 / 36.9.
+//   off 128, whole call: 2888 x 7688 at 1, 12 and 64 tokens 37.5 / 35.1, 39.1 / 37.3, 54.5 / 53.5; 1800 x 5000 at 16 and 33 25.0 / 23.9,
+//   30.9 / 29.7.  Beyond 16 tokens at every size: 2008 x 2400 (29 MB) at 17 and 33 22.1 / 20.6, 26.6 / 24.5; 904 x 1024 (6 MB) at 33 18.2 /
+//   17.5; 1416 x 3776 at 17 22.2 / 22.6, at 64 31.1 / 31.0.  Not where d_ff is no larger than d_model: 8200 x 1000 at 1 and 17 22.8 / 24.7,
+//   30.9 / 31.9 (2888 x 2888 at 12 24.5 / 23.4).
+bool single_launch_pays(int M, int d_model, int d_ff) {
+    const size_t bytes = (size_t)6 * d_model * d_ff;
+    if (M > 64) return false;
+    if (d_model % 128) return d_ff > d_model && (M > 16 || bytes >= 48000000u);
+    return bytes >= (d_model % 1024 ? 48000000u : 100000000u);
+}
+// That form of a configuration, if it is of the pair and the form fits.
+bool single_launch_of(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype, bool block, dfk_config_t* out) {
+    if (M > 64 || c.kmajor != 1 || c.path != DFK_PATH_MFMA || c.variant != DFK_VARIANT_TWO_KERNEL) return false;
+    dfk_config_t r = c;
+    r.variant = DFK_VARIANT_FUSED; r.kmajor = 4; r.depth = 4;
+    if (block ? !mfma_km_block_config_valid(r, M, d_model, d_ff, dtype) : !mfma_km_roles_config_valid(r, M, d_model, d_ff, dtype)) return false;
+    *out = r;
+    return true;
+}
+
 // The default is a pure function of the problem, and finding it lists and validates every candidate (5 to 25 us of host
 // time per call; a 512 x 1536 layer, whose kernels take 9 us: 18.1 us per call from Python, 10.8 without it).  Each thread
 // remembers the last ones it found, a fixed number of slots by hash of the problem.
@@ -450,6 +480,7 @@ bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant
         } else if (!enumerate_default(M, d_model, d_ff, dtype, want_variant, &c, [](const dfk_config_t&) { return true; })) {
             return false;
         }
+        if (want_variant == DFK_VARIANT_AUTO && d_model % 128 && single_launch_pays(M, d_model, d_ff)) single_launch_of(c, M, d_model, d_ff, dtype, false, &c);
         s.M = M; s.d_model = d_model; s.d_ff = d_ff; s.dtype = (int)dtype; s.variant = want_variant; s.cfg = c;
     }
     *out = s.cfg;
@@ -471,7 +502,8 @@ void table_put(int M, int d_model, int d_ff, int dtype, const Entry& e, bool cho
         g_table[Key(M, d_model, d_ff, dtype, kSlotWdt)] = e;
         return;
     }
-    g_table[Key(M, d_model, d_ff, dtype, e.cfg.variant)] = e;
+    // off 128 the single launch of both kernels' workgroups is a form of the pair, not an entry of the fused variant (that one keeps A_2 in fp32)
+    if (!(d_model % 128 && roles_launch(e.cfg))) g_table[Key(M, d_model, d_ff, dtype, e.cfg.variant)] = e;
     if (chosen) g_table[Key(M, d_model, d_ff, dtype, 0)] = e;
 }
 
@@ -511,21 +543,6 @@ bool choose(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, d
     }
     if (tuned) *tuned = 0;
     return heuristic(M, d_model, d_ff, dtype, want_variant, out);
-}
-
-// The untuned pair of a block, or of a width that is no multiple of 128, up to 64 tokens, as the single launch of both kernels' workgroups: same splits, same counter reduction
-// (the result stays reproducible bit for bit), no boundary between two launches.  Up to 16 tokens only from 48 MB of weights on: below,
-// the down workgroups' wait costs what the boundary does.  Layers replayed from a graph, us per layer, pair / single launch: 2304 x 9216
-// at 1, 8 and 33 tokens 32.2 / 30.5, 33.3 / 31.7, 44.3 / 42.0; 4096 x 14336 at 1 and 64 65.1 / 63.5, 83.8 / 82.4; 5120 x 27648 at 64 186.9
-// / 180.0; 1792 x 4864 (52 MB) at 12 22.5 / 21.6; 1024 x 2816 at 40 22.8 / 22.3; 12288 x 12288 at 33 167.4 / 168.1.  On the other side:
-// 1024 x 5632 (35 MB) at 1 16.0 / 16.5, 1152 x 4096 at 8 16.7 / 17.1, 1536 x 4096 (38 MB) at 8 18.2 / 18.5.
-// Widths off 128, whole call: 2888 x 7688 at 1, 12 and 64 tokens 37.1 / 35.3, 38.9 / 37.3, 54.4 / 53.8, 1800 x 5000 at 16 and 33 26.0 / 23.7, 32.0 / 29.5.
-void single_launch_of(dfk_config_t* c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
-    dfk_config_t r = *c;
-    if (M > 64 || c->kmajor != 1 || c->variant != DFK_VARIANT_TWO_KERNEL) return;
-    if (M <= 16 && (size_t)6 * d_model * d_ff < (size_t)48000000) return;
-    r.variant = DFK_VARIANT_FUSED; r.kmajor = 4; r.depth = 4;
-    if (d_model % 128 ? mfma_km_single_launch_fits(r, M, d_model, d_ff, dtype) : mfma_km_block_config_valid(r, M, d_model, d_ff, dtype)) *c = r;
 }
 
 // ---------------------------------------------------------------- dispatch
@@ -591,11 +608,9 @@ dfk_status_t call(const void* X, const void* Wg, const void* Wu, const void* Wd,
     dfk_status_t s = check(X, Wg, Wu, Wd, Y, M, d_model, d_ff, dtype, cfg, ws, ws_bytes, true, false, wd_t);
     if (s != DFK_OK) return s;
     dfk_config_t c;
-    int tuned = 0;
     if (cfg) c = *cfg;
-    else if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, &tuned)
-                  : !choose(M, d_model, d_ff, dtype, want_variant, &c, &tuned)) return DFK_ERR_UNSUPPORTED_SHAPE;
-    if (!cfg && !wd_t && !tuned && want_variant == DFK_VARIANT_AUTO && d_model % 128) single_launch_of(&c, M, d_model, d_ff, dtype);
+    else if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, nullptr)
+                  : !choose(M, d_model, d_ff, dtype, want_variant, &c, nullptr)) return DFK_ERR_UNSUPPORTED_SHAPE;
     return run(X, Wg, Wu, Wd, Y, M, d_model, d_ff, dtype, c, ws, (hipStream_t)stream);
 }
 
@@ -836,6 +851,30 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* Wg, const void* Wu
 }
 
 namespace {
+// Whether a configuration (valid for the problem) runs the block too.
+bool block_carries(const dfk_config_t& k, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    if (k.path != DFK_PATH_MFMA) return false;
+    if (k.kmajor == 5 || k.kmajor == 2) return mfma_config_valid(k, M, d_model, d_ff, dtype);
+    if (k.variant == DFK_VARIANT_FUSED) return k.kmajor == 4 && mfma_km_block_config_valid(k, M, d_model, d_ff, dtype);
+    return k.kmajor == 1 && d_model % 128 == 0 && mfma_km_config_valid(k, M, d_model, d_ff, dtype);
+}
+// The block's configuration without one from the caller: the choice of its layout (of the two-kernel variant), else the first candidate that
+// carries it; the pair for up to 64 tokens, tuned or not, in the form of a single launch where that pays.
+bool choose_block(int M, int d_model, int d_ff, dfk_dtype_t dtype, bool wd_t, dfk_config_t* out, int* tuned) {
+    dfk_config_t c;
+    if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, tuned) : !choose(M, d_model, d_ff, dtype, DFK_VARIANT_TWO_KERNEL, &c, tuned)) return false;
+    if (!block_carries(c, M, d_model, d_ff, dtype)) {
+        if (tuned) *tuned = 0;
+        bool found = false;
+        for (const auto& k : wd_t ? candidates_wdt(M, d_model, d_ff, dtype) : candidates(M, d_model, d_ff, dtype))
+            if (k.variant == DFK_VARIANT_TWO_KERNEL && block_carries(k, M, d_model, d_ff, dtype)) { c = k; found = true; break; }
+        if (!found) return false;
+    }
+    if (!wd_t && single_launch_pays(M, d_model, d_ff)) single_launch_of(c, M, d_model, d_ff, dtype, true, &c);
+    *out = c;
+    return true;
+}
+
 dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const void* Wg,
                        const void* Wu, const void* Wd, void* H_out, int M, int d_model, int d_ff,
                        dfk_dtype_t dtype, const dfk_config_t* cfg, void* workspace,
@@ -854,27 +893,13 @@ dfk_status_t mlp_block(const void* H, const void* norm_weight, float eps, const 
         if (overlaps(H_out, nx, norm_weight, nv) || overlaps(workspace, workspace_bytes, norm_weight, nv))
             return DFK_ERR_ALIAS;
     }
-    auto carries = [&](const dfk_config_t& k) {
-        if (wd_t) return k.path == DFK_PATH_MFMA && k.kmajor == 5 && mfma_config_valid(k, M, d_model, d_ff, dtype);
-        return k.path == DFK_PATH_MFMA &&
-               ((k.kmajor == 1 && d_model % 128 == 0 && mfma_km_config_valid(k, M, d_model, d_ff, dtype)) ||
-                (k.kmajor == 2 && mfma_big_config_valid(k, M, d_model, d_ff, dtype)));
-    };
     dfk_config_t c;
-    int tuned = 0;
-    if (cfg) c = *cfg;
-    else {
-        if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, &tuned)
-                 : !choose(M, d_model, d_ff, dtype, DFK_VARIANT_TWO_KERNEL, &c, &tuned)) return DFK_ERR_UNSUPPORTED_SHAPE;
-        if (!carries(c)) {   // the scheduler's pick is another kernel family: first candidate that carries this form
-            bool found = false;
-            for (const auto& k : wd_t ? candidates_wdt(M, d_model, d_ff, dtype) : candidates(M, d_model, d_ff, dtype))
-                if (k.variant == DFK_VARIANT_TWO_KERNEL && carries(k)) { c = k; found = true; break; }
-            if (!found) return DFK_ERR_UNSUPPORTED_SHAPE;
-        }
+    if (cfg) {
+        if (!block_carries(*cfg, M, d_model, d_ff, dtype)) return DFK_ERR_UNSUPPORTED_SHAPE;
+        c = *cfg;
+    } else if (!choose_block(M, d_model, d_ff, dtype, wd_t, &c, nullptr)) {
+        return DFK_ERR_UNSUPPORTED_SHAPE;
     }
-    if (!carries(c)) return DFK_ERR_UNSUPPORTED_SHAPE;
-    if (!cfg && !wd_t && !tuned) single_launch_of(&c, M, d_model, d_ff, dtype);
     return run(H, Wg, Wu, Wd, H_out, M, d_model, d_ff, dtype, c, workspace, (hipStream_t)stream, norm_weight, eps, H);
 }
 }  // namespace
@@ -949,6 +974,14 @@ dfk_status_t dfk_get_choice_wdt(int M, int d_model, int d_ff, dfk_dtype_t dtype,
     return choose_wdt(M, d_model, d_ff, dtype, out, tuned_out) ? DFK_OK : DFK_ERR_UNSUPPORTED_SHAPE;
 }
 
+dfk_status_t dfk_get_choice_block(int M, int d_model, int d_ff, dfk_dtype_t dtype, int w_down_t, dfk_config_t* out, int* tuned_out) {
+    if (!out) return DFK_ERR_INVALID_ARG;
+    if (M < 1 || d_model < 1 || d_ff < 1) return DFK_ERR_INVALID_ARG;
+    if (dtype != DFK_BF16 && dtype != DFK_FP16) return dtype == DFK_FP32 ? DFK_ERR_UNSUPPORTED_SHAPE : DFK_ERR_INVALID_ARG;
+    if (!shape_supported(M, d_model, d_ff)) return DFK_ERR_UNSUPPORTED_SHAPE;
+    return choose_block(M, d_model, d_ff, dtype, w_down_t != 0, out, tuned_out) ? DFK_OK : DFK_ERR_UNSUPPORTED_SHAPE;
+}
+
 int dfk_num_candidates(int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     if (!shape_supported(M, d_model, d_ff)) return 0;
     return (int)candidates(M, d_model, d_ff, dtype).size();
@@ -1019,10 +1052,17 @@ dfk_status_t dfk_tune(const int* M_list, int nM, int d_model, int d_ff, dfk_dtyp
         const int M = M_list[i];
         auto cands = candidates(M, d_model, d_ff, dtype);
         if (cands.empty()) return DFK_ERR_UNSUPPORTED_SHAPE;
+        const size_t listed = cands.size();
+        for (size_t k = 0; d_model % 128 && k < listed; ++k) {   // the pair's other form, which is not listed there
+            dfk_config_t one;
+            if (!single_launch_of(cands[k], M, d_model, d_ff, dtype, false, &one)) continue;
+            if (std::none_of(cands.begin(), cands.end(), [&](const dfk_config_t& o) { return same_cfg(o, one); })) cands.push_back(one);
+        }
         Entry best, best_of[3];
         best.usec = best_of[1].usec = best_of[2].usec = -1.0;
         bool fill = true;  // scratch layout depends on M: refill once per M (until a candidate has run)
-        for (const auto& c : cands) {
+        for (size_t k = 0; k < cands.size(); ++k) {
+            const dfk_config_t& c = cands[k];
             double us = 0.0;
             dfk_status_t s = time_config(c, M, d_model, d_ff, dtype, scratch, sets, iters,
                                          (hipStream_t)stream, fill, &us);
@@ -1033,6 +1073,7 @@ dfk_status_t dfk_tune(const int* M_list, int nM, int d_model, int d_ff, dfk_dtyp
             }
             fill = false;
             if (best.usec < 0.0 || us < best.usec) { best.cfg = c; best.usec = us; }
+            if (k >= listed) continue;                            // (no entry of a variant, see table_put)
             Entry& bv = best_of[c.variant == DFK_VARIANT_FUSED ? 1 : 2];
             if (bv.usec < 0.0 || us < bv.usec) { bv.cfg = c; bv.usec = us; }
         }

@@ -1026,13 +1026,11 @@ bool mfma_km_block_config_valid(const dfk_config_t& c, int M, int d_model, int d
 // configuration, and a grid small enough that its 16-bit-safe index arithmetic holds.
 static dfk_config_t roles_as_pair(const dfk_config_t& c) { dfk_config_t p = c; p.variant = DFK_VARIANT_TWO_KERNEL; p.kmajor = 1; return p; }
 bool mfma_km_roles_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
-    return d_model % kKC == 0 && mfma_km_single_launch_fits(c, M, d_model, d_ff, dtype);
-}
-// Also for widths that are no multiple of 128 (bf16), where it is not offered as a configuration but stands in for the pair's untuned choice.
-bool mfma_km_single_launch_fits(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     if (c.variant != DFK_VARIANT_FUSED || c.kmajor != 4 || c.waves != 8) return false;
     if ((long long)c.splits + (long long)c.k2_splits * c.k2_col_blocks > 65535) return false;
     if (c.k2_splits > kRoleCountEnd - kRoleCount0) return false;   // one counter per d_ff split of the down projection
+    // (the notes of parked workgroups, a word each, fit the group sums: at least 512 bytes per column, and 8 wavefronts need 904 columns)
+    static_assert((size_t)512 * 904 >= (size_t)4 * 65535, "room for a note of every down workgroup");
     return mfma_km_config_valid(roles_as_pair(c), M, d_model, d_ff, dtype);
 }
 hipError_t launch_mfma_km_roles(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {

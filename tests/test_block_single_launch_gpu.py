@@ -1,5 +1,5 @@
-"""dfk_mlp_block without a configuration: the pair's untuned choice as one launch of both kernels' workgroups, on both sides of the
-rule (tokens, bytes of weights), one to four token tiles, out of place and in place."""
+"""dfk_mlp_block without a configuration, on both sides of the rule that says when the pair runs as one launch of both kernels' workgroups (bytes of
+weights), and both forms by name: one to four token tiles, out of place and in place, the same bits."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -13,11 +13,19 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("shape,dtype", [((1, 1536, 5632), "bf16"), ((16, 1536, 5632), "fp16"), ((16, 1536, 5120), "bf16"), ((17, 1024, 1536), "bf16"),
-                                         ((33, 1152, 2048), "fp16"), ((64, 1024, 2816), "bf16"), ((20, 896, 1024), "bf16")],
-                         ids=lambda s: "M%d_d%d_ff%d" % s if isinstance(s, tuple) else s)
-def test_untuned_block(shape, dtype):
+# the form the untuned block takes: one launch, the pair, or the pair because it is all there is
+@pytest.mark.parametrize("shape,dtype,single", [((1, 1536, 5632), "bf16", True), ((16, 1536, 5632), "fp16", True), ((16, 1536, 5120), "bf16", False),
+                                                ((17, 1024, 1536), "bf16", False), ((33, 1152, 2048), "fp16", False), ((64, 1024, 2816), "bf16", False),
+                                                ((40, 1536, 5632), "bf16", True), ((20, 896, 1024), "bf16", None)],
+                         ids=lambda s: "M%d_d%d_ff%d" % s if isinstance(s, tuple) else str(s))
+def test_untuned_block(shape, dtype, single):
     M, d, ff = shape
+    dt = dfk.DFK_BF16 if dtype == "bf16" else dfk.DFK_FP16
+    pick, _ = dfk.dfk_get_choice_block(M, d, ff, dt)
+    assert (pick.variant == dfk.DFK_VARIANT_FUSED) == bool(single), pick
+    pair = dfk.dfk_config_t(**dict(pick.as_dict(), variant=dfk.DFK_VARIANT_TWO_KERNEL, kmajor=1))
+    one = dfk.dfk_config_t(**dict(pick.as_dict(), variant=dfk.DFK_VARIANT_FUSED, kmajor=4, depth=4))
+    cfgs = [None, pair] + ([one] if single is not None else [])
     eps = 1e-5
     t = di.mlp_inputs(M, d, ff, seed=83, dtype=dtype)
     t["w"] = di.tensor(1083, (d,), 1.0, dtype)
@@ -29,7 +37,7 @@ def test_untuned_block(shape, dtype):
     for rep in range(20):
         out = g["X"].clone() if rep % 2 else torch.full_like(g["X"], float("nan"))
         src = out if rep % 2 else g["X"]
-        dfk.dfk_mlp_block(src, g["w"], eps, g["Wg"], g["Wu"], g["Wd"], out, None, ws)
+        dfk.dfk_mlp_block(src, g["w"], eps, g["Wg"], g["Wu"], g["Wd"], out, cfgs[rep // 2 % len(cfgs)], ws)
         torch.cuda.synchronize()
         if first is None:
             first = out.clone()

@@ -176,3 +176,93 @@ def test_half_inputs_of_the_transposed_layout_keep_a_wide_a2_where_they_had_it(M
     assert not tuned and (pick.path, pick.a2_dtype) == (VALU, dfk.DFK_FP32), pick
     pick, _ = dfk.dfk_get_choice_wdt(M, 512, 512, dfk.DFK_FP16)
     assert pick.path == MFMA, pick
+
+
+def _pair_of(M, d, ff, dt):
+    return next(c for c in cands(M, d, ff, dt) if c.variant == TWO and c.kmajor == 1)
+
+
+def _is_launch_form_of(c, pair):
+    return c.as_dict() == dict(pair.as_dict(), variant=FUSED, kmajor=4, depth=4)
+
+
+# 48 MB of weights, 100 MB where the width is a multiple of 1024, whatever the token count up to 64; eight wavefronts
+@pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
+@pytest.mark.parametrize("d,ff,single", [(1536, 5248, True), (1536, 5120, False), (2048, 8192, True), (2048, 8064, False), (1152, 8192, True), (1152, 4096, False),
+                                         (896, 28672, False), (2304, 9216, True), (4096, 14336, True), (5120, 40960, True)])
+def test_the_form_in_which_a_block_runs_the_pair(d, ff, single, dt):
+    for M in (1, 16, 17, 64):
+        c, tuned = dfk.dfk_get_choice_block(M, d, ff, dt)
+        pair = _pair_of(M, d, ff, dt) if d < 5120 else None       # (wide layers: not the first one listed)
+        assert not tuned and dfk.dfk_config_valid(c, M, d, ff, dt)
+        assert (c.variant, c.kmajor, c.reduce) == ((FUSED, 4) if single else (TWO, 1)) + (dfk.DFK_REDUCE_TICKET,), c
+        if pair is not None:
+            assert _is_launch_form_of(c, pair) if single else c.as_dict() == pair.as_dict(), (c, pair)
+    c, _ = dfk.dfk_get_choice_block(65, d, ff, dt)
+    assert (c.variant, c.kmajor) == (TWO, 2)
+
+
+@pytest.mark.parametrize("M,d,ff,single", [(1, 2888, 7688, True), (16, 2008, 4008, True), (16, 2008, 3960, False), (17, 2008, 3960, True), (64, 1000, 1008, True),
+                                           (64, 1000, 1000, False), (64, 8200, 1000, False), (17, 904, 2400, True), (64, 896 + 64, 2400, True), (64, 888, 2816, False),
+                                           (65, 2888, 7688, False)])
+def test_the_form_in_which_a_width_off_128_runs_the_pair(M, d, ff, single):
+    c, tuned = dfk.dfk_get_choice(M, d, ff, dfk.DFK_BF16)
+    pair = _pair_of(M, d, ff, dfk.DFK_BF16)
+    assert not tuned and dfk.dfk_config_valid(c, M, d, ff, dfk.DFK_BF16)
+    assert _is_launch_form_of(c, pair) if single else c.as_dict() == pair.as_dict(), (c, pair)
+    h = dfk.dfk_config_t(**dict(c.as_dict(), a2_dtype=dfk.DFK_FP16))
+    assert not dfk.dfk_config_valid(h, M, d, ff, dfk.DFK_FP16)
+
+
+def test_a_table_does_not_lose_the_single_launch(tmp_path):
+    """A tuned pair runs a block in the form that the untuned one would; off 128 that form can be the tuned choice, also through a file, and is
+    not taken for an entry of the fused variant."""
+    bf = dfk.DFK_BF16
+    try:
+        M, d, ff = 8, 2304, 9216
+        for reduce in (dfk.DFK_REDUCE_TICKET, dfk.DFK_REDUCE_ATOMIC):
+            pair = next(c for c in cands(M, d, ff, bf) if c.variant == TWO and c.kmajor == 1 and c.reduce == reduce and c.waves == 8)
+            dfk.dfk_set_choice(M, d, ff, bf, pair, 30.0)
+            c, tuned = dfk.dfk_get_choice_block(M, d, ff, bf)
+            assert tuned and _is_launch_form_of(c, pair), c
+        assert dfk.dfk_get_choice(M, d, ff, bf)[0].as_dict() == pair.as_dict()      # the plain call: as set
+        M, d, ff = 12, 2888, 7688
+        fused = next(c for c in cands(M, d, ff, bf) if c.variant == FUSED)
+        one, _ = dfk.dfk_get_choice(M, d, ff, bf)
+        pair = _pair_of(M, d, ff, bf)
+        for c, us in ((fused, 50.0), (pair, 39.0), (one, 37.0)):
+            dfk.dfk_set_choice(M, d, ff, bf, c, us)
+        path = str(tmp_path / "table.txt")
+        dfk.dfk_save_tuning(path)
+        for _ in range(2):
+            got, tuned = dfk.dfk_get_choice(M, d, ff, bf)
+            assert tuned and got.as_dict() == one.as_dict()
+            dfk.dfk_clear_tuning()
+            dfk.dfk_load_tuning(path)
+        lines = [l.split() for l in open(path) if not l.startswith("#") and l.split()[1] == "2888"]
+        assert [(l[4], l[14]) for l in lines] == [(str(fused.variant), str(fused.kmajor)), (str(TWO), "1"), (str(FUSED), "4")], lines
+        dfk.dfk_set_choice(M, d, ff, bf, pair, 36.0)
+        assert dfk.dfk_get_choice(M, d, ff, bf)[0].as_dict() == pair.as_dict()
+    finally:
+        dfk.dfk_clear_tuning()
+
+
+def test_a_block_takes_the_single_launch_by_name():
+    import ctypes
+    L = dfk.lib()
+    M, d, ff = 8, 2304, 9216
+    one, _ = dfk.dfk_get_choice_block(M, d, ff, dfk.DFK_BF16)
+    p, wsb = [A + (i << 28) for i in range(7)], dfk.dfk_workspace_bytes(M, d, ff)
+    call = lambda cfg, d=d: L.dfk_mlp_block(p[0], p[1], 1e-5, p[2], p[3], p[4], p[0] + 16, M, d, ff, dfk.DFK_BF16, ctypes.byref(cfg), p[6], wsb, None)
+    assert call(one) == dfk.DFK_ERR_ALIAS                       # accepted as far as that
+    local = next(c for c in cands(M, d, ff, dfk.DFK_BF16) if c.variant == FUSED and c.kmajor == 1)
+    ok = lambda cfg: L.dfk_mlp_block(p[0], p[1], 1e-5, p[2], p[3], p[4], p[5], M, d, ff, dfk.DFK_BF16, ctypes.byref(cfg), p[6], wsb, None)
+    assert ok(local) == dfk.DFK_ERR_UNSUPPORTED_SHAPE
+    out = dfk.dfk_config_t()
+    q = lambda *a: L.dfk_get_choice_block(*a, ctypes.byref(out), None)
+    assert q(8, 2888, 7688, dfk.DFK_BF16, 0) == dfk.DFK_ERR_UNSUPPORTED_SHAPE      # as the call
+    assert q(8, 2304, 9216, dfk.DFK_FP32, 0) == dfk.DFK_ERR_UNSUPPORTED_SHAPE
+    assert q(0, 2304, 9216, dfk.DFK_BF16, 0) == dfk.DFK_ERR_INVALID_ARG
+    assert q(8, 2304, 9216, 7, 0) == dfk.DFK_ERR_INVALID_ARG
+    assert q(8, 2304, 9216, dfk.DFK_FP16, 1) == dfk.DFK_OK and out.kmajor == 5
+    assert L.dfk_get_choice_block(8, 2304, 9216, dfk.DFK_BF16, 0, None, None) == dfk.DFK_ERR_INVALID_ARG
