@@ -108,15 +108,22 @@ bool roles_launch(const dfk_config_t& c) { return c.variant == DFK_VARIANT_FUSED
 // whose cost the least).  512 x 28672, counter reduction: 1 token 33.8 us with 16, 27.0 with 48, 27.5 with 64; 16 tokens 36.4, 32.6, 34.5; 64 tokens 60.2 with 16, 59.1 with 24, 70.1 with 64; 512 x 14336 at 1 token 20.7
 // with 16, 19.3 with 24, 19.8 with 64, at 64 tokens 39.7, 41.6, 55.5; atomic, at 16 tokens, 1024 x 28672 42.2 with 16, 40.0
 // with 32, 1536 x 28672 53.9 with 16, 54.4 with 18, 53.1 with 21.
-// The counter reduction of more than two tokens takes 12 where d_ff is no such multiple: the last workgroup of a column block reads all its splits' blocks alone.
-// 16 / 12 splits, us: 512 x 1536 at 64 tokens 20.9 / 20.0, 896 x 4864 at 40 24.3 / 23.3, 1024 x 5632 at 16 18.5 / 18.0, 1536 x
-// 8960 at 64 39.9 / 37.8, 2048 x 5504 at 8 and 64 23.3 / 22.3, 36.7 / 33.7, 768 x 3072 at 4 13.5 / 13.0; at two tokens 896 x 4864 15.4 / 15.8,
-// 1536 x 8960 23.7 / 23.7; 896 x 4864 at 16 17.3 / 17.5, where a split has more than twelve 32-row blocks for four wavefronts.  (8: 2048 x 5504 at 64 33.6, 1024 x 5632 27.7 against 26.9.)
+// The counter reduction of more than two tokens takes 12 where that gives the busiest wavefront no more 32-row blocks than 16 do: the last workgroup
+// of a column block reads all its splits' blocks alone.  16 / 12 splits, us: 512 x 1536 at 8 tokens 11.6 / 11.1, 768 x 4224 at 8 15.9 / 15.4, 896 x
+// 4864 at 33 23.4 / 22.8, 1024 x 5632 at 16 18.5 / 17.8, 2048 x 6144 at 64 38.5 / 36.1.  Where it gives more, the stream is longer by whole
+// blocks: 512 x 4096 at 8 (two blocks of four wavefronts, three) 13.3 / 13.9, 896 x 7168 at 33 25.1 / 26.2, 1024 x 8192 at 3 and 64 18.2 /
+// 19.2, 31.3 / 32.2, 896 x 4864 at 8 16.8 / 17.1.  From a width of 1536 on 16 splits are 192 workgroups and more, and up to four blocks
+// 12 are the better in any case: 1536 x 12288 at 8 and 64 29.6 / 29.4, 46.3 / 44.5, 2048 x 11264 34.4 / 33.6, 50.9 / 49.6; beyond, 1536 x 18176 at 8
+// 40.5 / 41.3, 2048 x 24320 60.2 / 61.5, 2048 x 16384 42.9 / 42.6, at 33 54.0 / 54.8.  At two tokens equal: 896 x 4864 15.4 / 15.8.
 constexpr int kFewSplits = 16;
 int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
     const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
-    const bool four_waves = M <= 16 && d_model < 1024;
-    const int few = reduce == DFK_REDUCE_TICKET && M > 2 && d_ff <= 12 * d_model && !(four_waves && d_ff > 12 * 384) ? 12 : kFewSplits;
+    int few = kFewSplits;
+    if (reduce == DFK_REDUCE_TICKET && M > 2) {
+        const int waves = M <= 16 && (d_model + 127) / 128 < 8 ? 4 : 8;                                  // of the down kernel
+        auto blocks = [&](int splits) { return ((max_slice_rows(d_ff, splits) + 31) / 32 + waves - 1) / waves; };   // of its busiest wavefront
+        if (blocks(12) == blocks(16) || (d_model >= 1536 && blocks(12) <= 4)) few = 12;
+    }
     return std::max(1, std::min(256 / k2c, std::max(few, d_ff / rows)));
 }
 // Workgroups of the 64-token pair's down kernels, untuned, own two 128-column blocks instead of one (512-byte pieces of W_down's

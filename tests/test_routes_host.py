@@ -266,3 +266,13 @@ def test_a_block_takes_the_single_launch_by_name():
     assert q(8, 2304, 9216, 7, 0) == dfk.DFK_ERR_INVALID_ARG
     assert q(8, 2304, 9216, dfk.DFK_FP16, 1) == dfk.DFK_OK and out.kmajor == 5
     assert L.dfk_get_choice_block(8, 2304, 9216, dfk.DFK_BF16, 0, None, None) == dfk.DFK_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("M,d,ff,splits", [(8, 512, 4096, 16), (17, 512, 3072, 12), (8, 768, 4224, 12), (33, 896, 7168, 16), (3, 1024, 5632, 12), (3, 1024, 8192, 16), (64, 1024, 8192, 16),
+                                           (3, 1536, 12288, 12), (8, 1536, 18176, 16), (64, 2048, 11264, 12), (33, 2048, 16384, 16), (2, 1024, 5632, 16), (8, 1000, 5000, 12), (8, 1000, 8000, 16)])
+def test_twelve_splits_where_they_cost_no_wavefront_another_block(M, d, ff, splits):
+    """Pair of launches, counter reduction: what a block takes, and a width off 128."""
+    c = _pair_of(M, d, ff, dfk.DFK_BF16)
+    assert (c.reduce, c.k2_splits) == (dfk.DFK_REDUCE_TICKET, splits), c
+    if d % 128 == 0:
+        assert dfk.dfk_get_choice_block(M, d, ff, dfk.DFK_BF16)[0].k2_splits == splits
