@@ -368,10 +368,12 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     // fp32, comes first at every token count.  The split form would round A_2 to half, and overflow beyond 65504: only for a caller who asks.
     if (dtype == DFK_FP16 && (d_model < 512 || d_ff < 512)) valu();
     if (wdt_split_pays(M, d_model, d_ff)) split_form();
-    // Wavefronts, ring depth: the shortest ring (two slots) is the fastest, but where d_model has fewer 16-row tiles than there are CUs
-    // each workgroup needs more in flight (at 9 to 16 tokens of the narrower ones the A_2 tiles take that back).  Two / three slots, us: 2304 x 9216 at 1 and 8 tokens 30.3 / 29.7, 30.9 / 30.5, 1024 x 2816 at 1,
-    // 32 and 48 11.4 / 10.7, 14.1 / 13.5, 16.3 / 15.7; 4096 x 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3; at 12 and 16: 3584 x 9216 41.1 / 39.4, 2304 x 9216 32.3 / 32.5, 2048 x 5504 21.0 / 21.3.
-    const std::vector<int> rings = t16 < 256 && (M <= 8 || M > 16 || d_model > 2304) ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
+    // Wavefronts, ring depth: three slots where the down kernel has workgroups (a 16-row tile each) for no more than three quarters of the CUs, so
+    // that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 32 tokens: 1536 x 4096 16.4 / 15.6, 17.2 / 16.8, 19.9 /
+    // 19.1; 2304 x 9216 30.3 / 29.5, 31.3 / 31.2, 36.9 / 36.5; 3072 x 8192 32.8 / 31.7, 34.3 / 33.9, 38.5 / 37.9; the most it loses there 1.3 %
+    // (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216 39.0 / 39.1, 40.0 / 40.2, 44.2 / 44.6, 3584 x 18944 67.9 /
+    // 69.4, 69.5 / 71.9, 77.0 / 77.8; 4096 x 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3.
+    const std::vector<int> rings = 4 * t16 <= 3 * 256 ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
     for (int wd : rings)
         for (int splits : {256, 512, more_splits})
             for (int k2s : {256, 512, 128}) {
