@@ -369,10 +369,10 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     if (dtype == DFK_FP16 && (d_model < 512 || d_ff < 512)) valu();
     if (wdt_split_pays(M, d_model, d_ff)) split_form();
     // Wavefronts, ring depth: three slots where the down kernel has workgroups (a 16-row tile each) for no more than three quarters of the CUs, so
-    // that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 32 tokens: 1536 x 4096 16.4 / 15.6, 17.2 / 16.8, 19.9 /
-    // 19.1; 2304 x 9216 30.3 / 29.5, 31.3 / 31.2, 36.9 / 36.5; 3072 x 8192 32.8 / 31.7, 34.3 / 33.9, 38.5 / 37.9; the most it loses there 1.3 %
-    // (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216 39.0 / 39.1, 40.0 / 40.2, 44.2 / 44.6, 3584 x 18944 67.9 /
-    // 69.4, 69.5 / 71.9, 77.0 / 77.8; 4096 x 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3.
+    // that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 32 tokens: 1536 x 4096 14.6 / 13.9, 15.2 / 14.8, 18.8 /
+    // 18.0; 2304 x 9216 30.3 / 29.5, 31.7 / 31.6, 38.9 / 38.4; 3072 x 8192 32.1 / 31.0, 32.5 / 32.0, 38.5 / 37.9; the most it loses there
+    // is 1.3 % (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216 37.7 / 37.9, 39.0 / 39.3, 46.5 / 46.9, 3584 x 18944 68.4 /
+    // 69.9, 72.0 / 74.4, 89.7 / 90.6; 4096 x 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3.
     const std::vector<int> rings = 4 * t16 <= 3 * 256 ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
     for (int wd : rings)
         for (int splits : {256, 512, more_splits})
