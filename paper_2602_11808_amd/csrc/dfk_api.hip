@@ -358,7 +358,7 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     auto split_form = [&]() {
         const int nblk = d_model / 128;
         if (nblk < 2) return;
-        for (int wd : {84, 83, 48})
+        for (int wd : M > 64 ? std::vector<int>{84} : std::vector<int>{84, 83, 48})   // (beyond 64 tokens waves and depth do not change its kernels)
             for (int splits : {256, more_splits})
                 for (int k2s : {big_splits(M, d_ff, nblk), 256 / nblk, std::min(12, 256 / nblk)})
                     push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,

@@ -278,3 +278,12 @@ def test_twelve_splits_where_they_cost_no_wavefront_another_block(M, d, ff, spli
     assert (c.reduce, c.k2_splits) == (dfk.DFK_REDUCE_TICKET, splits), c
     if d % 128 == 0:
         assert dfk.dfk_get_choice_block(M, d, ff, dfk.DFK_BF16)[0].k2_splits == splits
+
+
+@pytest.mark.parametrize("M,d,ff", [(65, 256, 128), (100, 4096, 14336), (256, 2304, 9216), (256, 1024, 40960)])
+def test_candidates_of_the_split_transposed_layout_are_different_launches(M, d, ff):
+    """Beyond 64 tokens its kernels take neither waves nor depth from the configuration, so no two candidates differ in those alone."""
+    for dt in (dfk.DFK_BF16, dfk.DFK_FP16):
+        cs = [dfk.dfk_get_candidate_wdt(M, d, ff, dt, i).as_dict() for i in range(dfk.dfk_num_candidates_wdt(M, d, ff, dt))]
+        split = [tuple(v for k, v in c.items() if k not in ("waves", "depth")) for c in cs if c["k2_col_blocks"] > 1]
+        assert split and len(set(split)) == len(split)
