@@ -391,14 +391,17 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
 // multiples of 1024 divide evenly.  us, A_2 in LDS / both kernels' workgroups: 2048 x 5504 20.2 / 21.1, 3072 x 12288 43.1 / 43.7, 4096 x
 // 8192 40.4 / 41.1, 4096 x 14336 59.4 / 60.1, 4096 x 16384 66.6 / 67.8.  On the other side: 4096 x 20480 88.5 / 83.2, 4096 x 4096 30.1 /
 // 23.7, 1024 x 2816 13.2 / 11.4, 1536 x 4096 20.2 / 15.1, 2304 x 9216 31.1 / 27.9, 3584 x 9216 40.8 / 37.1, 7168 x 20480 146 / 135,
-// 8192 x 14336 113 / 111, 8192 x 28672 222 / 213, 16384 x 16384 277 / 246; 3072 x 8192 30.8 / 30.7.
+// 8192 x 14336 113 / 111, 8192 x 28672 222 / 213, 16384 x 16384 277 / 246; 3072 x 8192 30.8 / 30.7.  Beyond a d_ff of 32768 the launch of both
+// kernels' workgroups is not listed (more than 512 slices of 64 rows), and what follows is the pair of launches with the counter reduction.  A_2 in
+// LDS / pair: 512 x 36864 37.1 / 33.6, 1024 x 33280 45.3 / 44.5, 4096 x 53248 215 / 209, 5120 x 40960 202 / 195, 8192 x 40960 321 / 307, 16384 x
+// 53248 923 / 789; 1024 x 53248 63.4 / 63.3, 3072 x 40960 124 / 124, 2048 x 40960 86.5 / 88.0.
 bool local_pays(int d_model, int d_ff) {
     return d_model % 1024 == 0 && d_model >= 2048 && d_model <= 4096 && d_ff >= 2 * d_model && d_ff <= 16384;
 }
 
 // Untuned default, from measurements on MI355X.  One token of some sizes (local_pays): the single launch that keeps A_2 in LDS, with
 // the atomic reduction (no boundary between two kernels, and its 256 full-width partial sums are still cheap).  Else, up to
-// 64 tokens: the single launch that holds both kernels' workgroups (atomic reduction), which saves the launch
+// 64 tokens and a d_ff of 32768: the single launch that holds both kernels' workgroups (atomic reduction), which saves the launch
 // boundary at every token count.  Of the two-kernel forms: beyond 64 tokens the pair that takes up to 256 per
 // launch, else the pair for up to 64 tokens, then the rows-split down kernel, then the rest.  Within a form of the
 // 64-token pair: splits and column blocks as few_splits and two_blocks say.

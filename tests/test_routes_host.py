@@ -287,3 +287,14 @@ def test_candidates_of_the_split_transposed_layout_are_different_launches(M, d, 
         cs = [dfk.dfk_get_candidate_wdt(M, d, ff, dt, i).as_dict() for i in range(dfk.dfk_num_candidates_wdt(M, d, ff, dt))]
         split = [tuple(v for k, v in c.items() if k not in ("waves", "depth")) for c in cs if c["k2_col_blocks"] > 1]
         assert split and len(set(split)) == len(split)
+
+
+@pytest.mark.parametrize("d,ff", [(512, 36864), (1024, 32776), (1024, 53248), (4096, 40960), (16384, 53248)])
+def test_one_token_of_a_d_ff_that_no_single_launch_takes(d, ff):
+    """Beyond 512 slices of 64 rows: the pair of launches, for every small token count alike; up to there the single launch."""
+    for dt in (dfk.DFK_BF16, dfk.DFK_FP16):
+        for M in (1, 2):
+            pick, _ = dfk.dfk_get_choice(M, d, ff, dt)
+            assert (pick.variant, pick.kmajor, pick.reduce) == (TWO, 1, dfk.DFK_REDUCE_TICKET), pick
+        if d >= 1024:
+            assert dfk.dfk_get_choice(1, d, 32768, dt)[0].kmajor == 4
