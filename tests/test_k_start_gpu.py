@@ -1,5 +1,7 @@
-"""Gate/up kernel of the 256-token pair: where a workgroup's walk through the k range starts, on both sides of the rule's lines (more
-than 64 steps; more than 3 MB of X, or rows a multiple of 16 KB apart)."""
+"""Gate/up kernel of the 256-token pair: where a workgroup's walk through the k range starts, on both sides of the rule's lines.  A window where
+there are more than 64 steps and either more than 3 MB of X (256 x 6272) or rows a multiple of 16 KB apart (129 x 8192: 2.1 MB, one
+64-k piece a step, 128 steps); else the whole range: rows 16 KB apart but 64 steps (65 x 8192: two pieces a step with one row tile per
+slice), just short of 3 MB (255 x 6144), few steps."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -13,7 +15,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("shape", [(65, 8192, 1024), (256, 6272, 1024), (255, 6144, 1024), (200, 4096, 640)], ids=lambda s: "M%d_d%d_ff%d" % s)
+@pytest.mark.parametrize("shape", [(65, 8192, 1024), (129, 8192, 1024), (256, 6272, 1024), (255, 6144, 1024), (200, 4096, 640)], ids=lambda s: "M%d_d%d_ff%d" % s)
 def test_every_start_of_the_k_walk(shape):
     M, d, ff = shape
     t = di.mlp_inputs(M, d, ff, seed=73)
