@@ -92,7 +92,8 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  shape constraints, see dfk_config_valid)
  *   splits         number of d_ff slices = workgroups of the fused kernel, or of
  *                  the first kernel of the two-kernel variant
- *   waves          wavefronts (64 lanes) per workgroup (kmajor = 1 pair with 4: the down kernel runs 8 beyond 16 tokens)
+ *   waves          wavefronts (64 lanes) per workgroup (kmajor = 1 pair with 4: the down kernel runs 8
+ *                  beyond 16 tokens)
  *   depth          software pipeline depth of the weight stream (tiles or loads in flight)
  *   reduce         dfk_reduce_t
  *   k2_splits      two-kernel variant: d_ff splits of the down projection
@@ -127,11 +128,11 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  d_model each (whole 16-row tiles, at most 8 per workgroup), k2_col_blocks = 1,
  *                  reduce = DFK_REDUCE_TICKET (nothing is reduced across workgroups; the result
  *                  is deterministic), up to 64 tokens per launch.  With k2_col_blocks = d_model / 128
-                  (at least 2) the down projection is split over d_ff instead: k2_splits times that many
-                  workgroups own 128 rows of W_down_t over a split of whole 64-row steps, a third,
-                  small launch adds the splits' partial sums in a fixed order (deterministic too),
-                  and a launch takes up to 256 tokens; beyond 64 tokens its gate/up kernel is
-                  pair 2's (d_model and d_ff multiples of 128).  With path = DFK_PATH_VALU the
+ *                  (at least 2) the down projection is split over d_ff instead: k2_splits times that many
+ *                  workgroups own 128 rows of W_down_t over a split of whole 64-row steps, a third,
+ *                  small launch adds the splits' partial sums in a fixed order (deterministic too),
+ *                  and a launch takes up to 256 tokens; beyond 64 tokens its gate/up kernel is
+ *                  pair 2's (d_model and d_ff multiples of 128).  With path = DFK_PATH_VALU the
  *                  same pair in plain fp32 FMAs (any shape and type; k2_splits = workgroups of
  *                  the down kernel, whose wavefronts own output columns whole);
  *                  3 = gate/up kernel of pair 2 with one token tile per token group,
@@ -147,12 +148,12 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  a down workgroup requests its first W_down tiles, then waits (a bounded
  *                  number of polls) until the gate/up workgroups of its d_ff rows have
  *                  published A_2, which crosses through device memory as between two kernels.
- *                  Up to 64 tokens per launch; waves = 8; otherwise the constraints of pair 1,
- *                  (d_model off 128 in bf16 included) whose k2_splits, k2_col_blocks and reduce fields
- *                  it uses.  Such launches may overlap
- *                  on several streams (a workspace each): a down workgroup whose wait takes long makes
- *                  room for others and is made up for later in the launch, so every wait ends as long as
- *                  fewer such launches run at a time than an XCD has CUs.  The bound is a last
+ *                  Up to 64 tokens per launch; waves = 8; otherwise the constraints of pair 1
+ *                  (d_model off 128 in bf16 included), whose k2_splits, k2_col_blocks and reduce
+ *                  fields it uses.  Such launches may overlap on several streams (a workspace each): a
+ *                  down workgroup whose wait takes long makes room for others and is made up for later
+ *                  in the launch, so every wait ends as long as fewer such launches run at a time than
+ *                  an XCD has CUs.  The bound is a last
  *                  resort, about two million polls (seconds); a workgroup whose wait runs out turns its
  *                  share of Y into NaN (in place, dfk_mlp_block's input is lost with it), and the
  *                  workspace has to be initialised again.  (Tests force these paths from the host with
@@ -217,9 +218,9 @@ dfk_status_t dfk_swiglu_mlp_ex(const void* X, const void* W_gate, const void* W_
  * the paper's W_down (Background, SwiGLU equations: Y = A_2 W_down): the [out, in] layout a linear layer's
  * weights are stored in, and the layout W_gate and W_up already have here.  Same result.  In this layout, up to
  * 64 tokens, a workgroup of the down kernel can own a slice of d_model over all of d_ff, so that nothing is summed
- * across workgroups
- * (config field kmajor = 5: on the MFMA path for the 16-bit types with d_model a multiple of 128 and d_ff a
+ * across workgroups (config field kmajor = 5: on the MFMA path for the 16-bit types with d_model a multiple of 128 and d_ff a
  * multiple of 128 with at least `waves` 128-k chunks each; on the VALU path for every supported shape and type).
+ * With half inputs and d_model or d_ff below 512 the scheduler's choice is the VALU pair, which keeps A_2 in fp32.
  * cfg == NULL: the scheduler's choice for this layout (dfk_get_choice_wdt); else cfg must be a kmajor = 5
  * configuration (the other entry points reject those, and this one rejects the others, with
  * DFK_ERR_INVALID_ARG: a configuration belongs to one layout).
@@ -263,7 +264,7 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* W_gate, const void
  *     H_out = H + SwiGLU_MLP( RMSNorm(H; norm_weight, eps) )
  *     RMSNorm(H; w, eps)[m,k] = H[m,k] * w[k] / sqrt( mean_k H[m,k]^2 + eps )
  *
- * in the same two launches as the plain block: the gate/up kernel scales its X operand by
+ * in the same launches as the plain block: the gate/up kernel scales its X operand by
  * norm_weight, sums the squares of the H values it streams anyway and applies the
  * per-token factor to its fp32 sums; the down kernel adds H at its final store.
  *
@@ -295,8 +296,9 @@ dfk_status_t dfk_mlp_block(const void* H, const void* norm_weight, float eps,
 
 /* The same with the down projection's weights given as W_down_t [d_model, d_ff] (see dfk_swiglu_mlp_wdt):
  * cfg == NULL or a kmajor = 5 configuration; the normalisation is folded into the gate/up kernel as with
- * kmajor = 1 (beyond 64 tokens with k2_col_blocks > 1 a small launch of its own, as with kmajor = 2), the residual is added
- * where Y is stored. */
+ * kmajor = 1 (beyond 64 tokens with k2_col_blocks > 1 a small launch of its own, as with kmajor = 2:
+ * the normalised input is rounded to dtype there, instead of the product H[m,k] * w[k]), the
+ * residual is added where Y is stored. */
 dfk_status_t dfk_mlp_block_wdt(const void* H, const void* norm_weight, float eps,
                                const void* W_gate, const void* W_up, const void* W_down_t,
                                void* H_out, int M, int d_model, int d_ff, dfk_dtype_t dtype,
@@ -446,7 +448,8 @@ dfk_status_t dfk_rms_normalize(const void* in, void* out, int M, int d_model, vo
  * of at least 64 bytes per workgroup of the launch is registered, each workgroup
  * writes up to 8 wall-clock stamps (100 MHz counter): [0] start, [1] first tile
  * landed, [2] stage one streamed, [3] A_2 ready, [4] stage two streamed,
- * [5] partial published, [6] end of first reduction level (or exit), [7] Y written by the last group.  NULL unregisters.  Off by default. */
+ * [5] partial published, [6] end of first reduction level (or exit), [7] Y written by the last group.
+ * NULL unregisters.  Off by default. */
 dfk_status_t dfk_set_trace_buffer(void* buffer, size_t bytes);
 
 /* ---------------------------------------------------------------- misc */

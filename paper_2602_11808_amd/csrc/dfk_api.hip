@@ -99,44 +99,49 @@ dfk_status_t check(const void* X, const void* Wg, const void* Wu, const void* Wd
 // the single launch that holds both kernels' workgroups: variant FUSED, but partial sums and stages of the pair
 bool roles_launch(const dfk_config_t& c) { return c.variant == DFK_VARIANT_FUSED && c.path == DFK_PATH_MFMA && c.kmajor == 4; }
 
-// d_ff splits of the 64-token pair's down kernels, untuned, with `k2c` column blocks: as a rule 16 at most, because the end of the
-// kernel is a chain of round trips plus the sum of the splits' blocks (one token, counter reduction: 512 x 1536 with 64 splits 16.2 us
-// per call, with 12 to 16 10.4; 896 x 4864 with 36 splits 18.6 us, with 16 15.6; 64 tokens: 512 x 2816 with 64 45.8, with 16 25.1; atomic
-// reduction, 1024 x 5632 at 64 tokens with 32 27.3, with 16 23.0).  Where d_ff is many times d_model, 16 splits are long and their
-// few workgroups leave most of the chip's bandwidth unused: more of them, of as many rows as the layer is wide (of twice as
-// many for the counter reduction of more than 16 tokens, whose blocks cost the most, of three quarters for the atomic one,
-// whose cost the least).  512 x 28672, counter reduction: 1 token 33.8 us with 16, 27.0 with 48, 27.5 with 64; 16 tokens 36.4, 32.6, 34.5; 64 tokens 60.2 with 16, 59.1 with 24, 70.1 with 64; 512 x 14336 at 1 token 20.7
-// with 16, 19.3 with 24, 19.8 with 64, at 64 tokens 39.7, 41.6, 55.5; atomic, at 16 tokens, 1024 x 28672 42.2 with 16, 40.0
-// with 32, 1536 x 28672 53.9 with 16, 54.4 with 18, 53.1 with 21.
-// The counter reduction of more than two tokens takes 12 where that gives the busiest wavefront no more 32-row blocks than 16 do: the last workgroup
-// of a column block reads all its splits' blocks alone.  16 / 12 splits, us: 512 x 1536 at 8 tokens 11.6 / 11.1, 768 x 4224 at 8 15.9 / 15.4, 896 x
-// 4864 at 33 23.4 / 22.8, 1024 x 5632 at 16 18.5 / 17.8, 2048 x 6144 at 64 38.5 / 36.1.  Where it gives more, the stream is longer by whole
-// blocks: 512 x 4096 at 8 (two blocks of four wavefronts, three) 13.3 / 13.9, 896 x 7168 at 33 25.1 / 26.2, 1024 x 8192 at 3 and 64 18.2 /
-// 19.2, 31.3 / 32.2, 896 x 4864 at 8 16.8 / 17.1.  From a width of 1536 on 16 splits are 192 workgroups and more, and up to four blocks
-// 12 are the better in any case: 1536 x 12288 at 8 and 64 29.6 / 29.4, 46.3 / 44.5, 2048 x 11264 34.4 / 33.6, 50.9 / 49.6; beyond, 1536 x 18176 at 8
-// 40.5 / 41.3, 2048 x 24320 60.2 / 61.5, 2048 x 16384 42.9 / 42.6, at 33 54.0 / 54.8.  At two tokens equal: 896 x 4864 15.4 / 15.8.
+// d_ff splits of the 64-token pair's down kernels, untuned, with `k2c` column blocks: as a rule 16 at most, because the end of
+// the kernel is a chain of round trips plus the sum of the splits' blocks (one token, counter reduction: 512 x 1536 with 64
+// splits 16.2 us per call, with 12 to 16 10.4; 896 x 4864 with 36 splits 18.6 us, with 16 15.6; 64 tokens: 512 x 2816 with 64
+// 45.8, with 16 25.1; atomic reduction, 1024 x 5632 at 64 tokens with 32 27.3, with 16 23.0).  Where d_ff is many times d_model,
+// 16 splits are long and their few workgroups leave most of the chip's bandwidth unused: more of them, of as many rows as the
+// layer is wide (of twice as many for the counter reduction of more than 16 tokens, whose blocks cost the most, of three quarters
+// for the atomic one, whose cost the least).  512 x 28672, counter reduction: 1 token 33.8 us with 16, 27.0 with 48, 27.5 with
+// 64; 16 tokens 36.4, 32.6, 34.5; 64 tokens 60.2 with 16, 59.1 with 24, 70.1 with 64; 512 x 14336 at 1 token 20.7 with 16, 19.3
+// with 24, 19.8 with 64, at 64 tokens 39.7, 41.6, 55.5; atomic, at 16 tokens, 1024 x 28672 42.2 with 16, 40.0 with 32, 1536 x
+// 28672 53.9 with 16, 54.4 with 18, 53.1 with 21.
+// The counter reduction of more than two tokens takes 12 where that gives the busiest wavefront no more 32-row blocks than 16 do:
+// the last workgroup of a column block reads all its splits' blocks alone.  16 / 12 splits, us: 512 x 1536 at 8 tokens 11.6 /
+// 11.1, 768 x 4224 at 8 15.9 / 15.4, 896 x 4864 at 33 23.4 / 22.8, 1024 x 5632 at 16 18.5 / 17.8, 2048 x 6144 at 64 38.5 / 36.1.
+// Where it gives more, the stream is longer by whole blocks: 512 x 4096 at 8 (two blocks of four wavefronts, three) 13.3 / 13.9,
+// 896 x 7168 at 33 25.1 / 26.2, 1024 x 8192 at 3 and 64 18.2 /
+// 19.2, 31.3 / 32.2, 896 x 4864 at 8 16.8 / 17.1.  From a width of 1536 on 16 splits are 192 workgroups and more, and up to four
+// blocks 12 are the better in any case: 1536 x 12288 at 8 and 64 29.6 / 29.4, 46.3 / 44.5, 2048 x 11264 34.4 / 33.6, 50.9 / 49.6;
+// beyond, 1536 x 18176 at 8
+// 40.5 / 41.3, 2048 x 24320 60.2 / 61.5, 2048 x 16384 42.9 / 42.6, at 33 54.0 / 54.8.  At two tokens equal: 896 x 4864 15.4 /
+// 15.8.
 constexpr int kFewSplits = 16;
 int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
     const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
     int few = kFewSplits;
     if (reduce == DFK_REDUCE_TICKET && M > 2) {
         const int waves = M <= 16 && (d_model + 127) / 128 < 8 ? 4 : 8;                                  // of the down kernel
-        auto blocks = [&](int splits) { return ((max_slice_rows(d_ff, splits) + 31) / 32 + waves - 1) / waves; };   // of its busiest wavefront
+        auto blocks = [&](int splits) { return ((max_slice_rows(d_ff, splits) + 31) / 32 + waves - 1) / waves; };   // of its busiest one
         if (blocks(12) == blocks(16) || (d_model >= 1536 && blocks(12) <= 4)) few = 12;
     }
     return std::max(1, std::min(256 / k2c, std::max(few, d_ff / rows)));
 }
 // Workgroups of the 64-token pair's down kernels, untuned, own two 128-column blocks instead of one (512-byte pieces of W_down's
 // rows, A_2 read half as often) where the layer is wide and a split then still has many rows: two blocks mean twice as many
-// splits, whose sum has to be paid for by the reading.  Time with two blocks over time with one, atomic reduction (single launch),
-// 2 to 16 tokens: 298 rows (5120 x 3584) 1.07 to 1.10, 614 (6144 x 6144) 1.00 to 1.02, 796 (7168 x 7168) 0.99 to 1.00, 930 (5888 x
-// 10240) 1.00 to 1.02, 938 (5120 x 11264) 0.96 to 0.98, 1109 (7168 x 9984) 0.98 to 0.99, 2201 (11008 x 11008) 0.96; 32 tokens: 938
+// splits, whose sum has to be paid for by the reading.  Time with two blocks over time with one, atomic reduction (single
+// launch), 2 to 16 tokens: 298 rows (5120 x 3584) 1.07 to 1.10, 614 (6144 x 6144) 1.00 to 1.02, 796 (7168 x 7168) 0.99 to 1.00,
+// 930 (5888 x 10240) 1.00 to 1.02, 938 (5120 x 11264) 0.96 to 0.98, 1109 (7168 x 9984) 0.98 to 0.99, 2201 (11008 x 11008) 0.96;
+// 32 tokens: 938
 // 1.01, 1109 1.01, 1194 (10240 x 7168) 1.00, 1424 (8192 x 11392) 1.00, 2201 0.96.  Counter reduction (pair of launches, the
-// block), 1 to 16 tokens: 938 1.00 to 1.03, 1175 (5888 x 12928) 1.00 to 1.02, 1393 (7168 x 12544) 0.98 to 1.00, 2201 0.98 to 0.99,
-// 2304 (5120 x 27648, 4 tokens, whole call) 138.6 -> 137.1 us; 32 tokens: 1424 1.02, 1792 (8192 x 14336) 1.02, 2389 (10240 x
-// 14336) 1.00, 2848 (16384 x 11392) 1.00, 3584 (8192 x 28672, whole call) 235.3 -> 238.5 us, 4096 (16384 x 16384) 0.99, and where
-// splits of one block each make few workgroups 1536 (11008 x 7680, 172 of them) 0.99, 2457 (12288 x 12288, 192) 0.99.  Below a
-// d_model of 5120 it gained at most 2 % and lost as much (4608 x 10112, 722 rows: 0.99 to 1.02).
+// block), 1 to 16 tokens: 938 1.00 to 1.03, 1175 (5888 x 12928) 1.00 to 1.02, 1393 (7168 x 12544) 0.98 to 1.00, 2201 0.98 to
+// 0.99, 2304 (5120 x 27648, 4 tokens, whole call) 138.6 -> 137.1 us; 32 tokens: 1424 1.02, 1792 (8192 x 14336) 1.02, 2389 (10240
+// x 14336) 1.00, 2848 (16384 x 11392) 1.00, 3584 (8192 x 28672, whole call) 235.3 -> 238.5 us, 4096 (16384 x 16384) 0.99, and
+// where splits of one block each make few workgroups 1536 (11008 x 7680, 172 of them) 0.99, 2457 (12288 x 12288, 192) 0.99.
+// Below a d_model of 5120 it gained at most 2 % and lost as much (4608 x 10112, 722 rows: 0.99 to 1.02).
 bool two_blocks(int M, int d_model, int d_ff, int reduce) {
     if (d_model < 5120) return false;
     const int nblk = (d_model + 127) / 128, rows = d_ff / few_splits(M, d_model, d_ff, nblk / 2, reduce);
@@ -149,11 +154,12 @@ bool two_blocks(int M, int d_model, int d_ff, int reduce) {
 // into whole 64-row steps of the down kernel, if there is one that is not much smaller (five eighths; where that makes splits of
 // more than 1024 rows three quarters, up to 128 tokens seven eighths).  More splits only add partial blocks; fewer leave CUs
 // without a workgroup; a split with a partial last step takes the form with clamped addresses and a step more, which costs the
-// most with three or four token tiles per group. Whole call, us: 1920 x 3072 at 253 tokens 44.8 with 17 splits, 41.4 with 12, 40.6
-// with 8; 1024 x 2816 at 80 24.2 with 32, 20.5 with 12, 20.0 with 11; 2304 x 9216 at 256 68.7 with 14, 64.8 with 12; 2432 x 6656
-// at 256 60.6 with 12, 58.5 with 8; 1536 x 8960 at 256 53.4 with 12, 49.9 with 14, 52.1 with 20; 3584 x 18944 at 256 170 with 9,
-// 147 with 8; 6912 x 20352 at 212 266 with 4, 273 with 3; 4480 x 23040 at 68 139.9 with 7, 142.5 with 6; a long d_ff: 512 x 28672
-// at 256 83.9 with 12, 59.4 with 32, 60.0 with 64; 256 x 8192 at 1 18.8 with 8, 17.4 with 12; 1024 x 14336 at 256 57.4 with 12,
+// most with three or four token tiles per group. Whole call, us: 1920 x 3072 at 253 tokens 44.8 with 17 splits, 41.4 with 12,
+// 40.6 with 8; 1024 x 2816 at 80 24.2 with 32, 20.5 with 12, 20.0 with 11; 2304 x 9216 at 256 68.7 with 14, 64.8 with 12; 2432 x
+// 6656 at 256 60.6 with 12, 58.5 with 8; 1536 x 8960 at 256 53.4 with 12, 49.9 with 14, 52.1 with 20; 3584 x 18944 at 256 170
+// with 9, 147 with 8; 6912 x 20352 at 212 266 with 4, 273 with 3; 4480 x 23040 at 68 139.9 with 7, 142.5 with 6; a long d_ff: 512
+// x 28672 at 256 83.9 with 12, 59.4 with 32, 60.0 with 64; 256 x 8192 at 1 18.8 with 8, 17.4 with 12; 1024 x 14336 at 256 57.4
+// with 12,
 // 50.3 with 16, 52.3 with 32; no whole steps: 1920 x 10496 at 96 46.5 with 12 or 17, 45.5 with 16; few column blocks: 1152 x 5504
 // at 200 38.8 with 12, 37.6 with 16, 38.3 with 28, and at 128 30.7 with 12, 30.8 with 16; 2048 x 5504 at 200 46.9 with 12, 47.7
 // with 16.
@@ -291,11 +297,11 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             push(make_cfg(DFK_VARIANT_FUSED, DFK_PATH_VALU, clamp_splits(splits, d_ff), waves, 0, 0, 0,
                           a2dt));
     const int nchunk = d_model / (dtype == DFK_FP32 ? 4 : 8);
-    // The first of these is the untuned two-kernel form: the fewest d_ff splits (a power of two, 8 to 64) whose down kernel has at
-    // least 160 workgroups, or 64 splits where no count up to that has: with one or two column blocks (half inputs below a d_model of
-    // 1536, fp32 below 768).  A workgroup's loads in flight are what paces it, so too few leave most of the chip waiting; beyond, the
-    // sum of the splits' blocks costs more (down kernel, us, with 8, 16, 32 and 64 splits: half inputs, 8 tokens of 2888 x 7688, five column
-    // blocks: 105, 60.6, 41.4, 56.1; fp32, 4 tokens, eleven: 37.6, 26.8, 35.1, 40.2).
+    // The first of these is the untuned two-kernel form: the fewest d_ff splits (a power of two, 8 to 64) whose down kernel has
+    // at least 160 workgroups, or 64 splits where no count up to that has: with one or two column blocks (half inputs below a
+    // d_model of 1536, fp32 below 768).  A workgroup's loads in flight are what paces it, so too few leave most of the chip
+    // waiting; beyond, the sum of the splits' blocks costs more (down kernel, us, with 8, 16, 32 and 64 splits: half inputs, 8
+    // tokens of 2888 x 7688, five column blocks: 105, 60.6, 41.4, 56.1; fp32, 4 tokens, eleven: 37.6, 26.8, 35.1, 40.2).
     const int max_cb = std::max(1, nchunk / 64);
     int k2_first = 8;
     while (k2_first < 64 && k2_first * std::min(max_cb, 512 / k2_first) < 160) k2_first *= 2;
@@ -311,12 +317,13 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
 
 // W_down given as [d_model, d_ff]: whether the down projection is split over d_ff (kmajor = 5 with column blocks) or its
 // workgroups own rows of W_down^T whole, with nothing to sum across them.  Beyond 64 tokens always: whole rows take 64 tokens per
-// launch and stream the weights again for each (256 tokens, us: 4096 x 14336 345 whole rows, 108 split; 896 x 4864 136, 34; 12288 x
-// 12288 665, 265).  Up to 64, whole rows read all of A_2 in every workgroup; that costs more than a split's sum where it is at least
-// twice the workgroup's weights (tokens against rows) and at least 450 KB, or 180 KB where narrow widths leave four wavefronts.
-// Whole rows / split, us: 4096 x 14336 at 20 tokens 66.5 / 65.4, at 32 70.8 / 67.3, at 64 87.5 / 75.1; 2304 x 9216 at 32 38.7 / 37.4;
-// 6144 x 8064 at 48 67.5 / 65.3; 8192 x 7168 at 64 78.5 / 77.3; 896 x 4864 at 20 22.8 / 18.6; 512 x 2048 at 48 14.9 / 13.7.  On the
-// other side: 8192 x 7168 at 48 71.9 / 73.1; 6144 x 8064 at 32 62.5 / 62.7; 12288 x 12288 at 64 166 / 179; 1024 x 2816 at 32 13.8 /
+// launch and stream the weights again for each (256 tokens, us: 4096 x 14336 345 whole rows, 108 split; 896 x 4864 136, 34; 12288
+// x 12288 665, 265).  Up to 64, whole rows read all of A_2 in every workgroup; that costs more than a split's sum where it is at
+// least twice the workgroup's weights (tokens against rows) and at least 450 KB, or 180 KB where narrow widths leave four
+// wavefronts. Whole rows / split, us: 4096 x 14336 at 20 tokens 66.5 / 65.4, at 32 70.8 / 67.3, at 64 87.5 / 75.1; 2304 x 9216 at
+// 32 38.7 / 37.4; 6144 x 8064 at 48 67.5 / 65.3; 8192 x 7168 at 64 78.5 / 77.3; 896 x 4864 at 20 22.8 / 18.6; 512 x 2048 at 48
+// 14.9 / 13.7.  On the other side: 8192 x 7168 at 48 71.9 / 73.1; 6144 x 8064 at 32 62.5 / 62.7; 12288 x 12288 at 64 166 / 179;
+// 1024 x 2816 at 32 13.8 /
 // 15.1, at 64 18.3 / 18.3; 512 x 2048 at 32 12.1 / 12.5.
 bool wdt_split_pays(int M, int d_model, int d_ff) {
     if (M > 64) return true;
@@ -325,8 +332,8 @@ bool wdt_split_pays(int M, int d_model, int d_ff) {
     return M > 16 && tokens >= 2 * rows && a2 >= (size_t)(d_model < 1024 ? 180 : 450) << 10;
 }
 
-// The candidates of that layout: the 64-token pair's gate/up kernel, then the down kernel whose workgroups own slices of d_model; and
-// the form that splits d_ff.  First in the list = the untuned default.
+// The candidates of that layout: the 64-token pair's gate/up kernel, then the down kernel whose workgroups own slices of d_model;
+// and the form that splits d_ff.  First in the list = the untuned default.
 std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     std::vector<dfk_config_t> out;
     // plain fp32-FMA kernels for every shape and type (after the MFMA pair in the list, where there is one)
@@ -358,20 +365,24 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     auto split_form = [&]() {
         const int nblk = d_model / 128;
         if (nblk < 2) return;
-        for (int wd : M > 64 ? std::vector<int>{84} : std::vector<int>{84, 83, 48})   // (beyond 64 tokens waves and depth do not change its kernels)
+        // (beyond 64 tokens waves and depth do not change its kernels)
+        for (int wd : M > 64 ? std::vector<int>{84} : std::vector<int>{84, 83, 48})
             for (int splits : {256, more_splits})
                 for (int k2s : {big_splits(M, d_ff, nblk), 256 / nblk, std::min(12, 256 / nblk)})
                     push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_MFMA, clamp_splits(splits, d_ff), wd / 10, wd % 10,
                                   std::max(1, std::min(k2s, d_ff / 64)), nblk, (int)dtype, DFK_REDUCE_TICKET, 0, 5));
     };
-    // Half inputs where the whole-rows form does not exist (it needs four 128-wide chunks each way): the plain-FMA pair, which keeps A_2 in
-    // fp32, comes first at every token count.  The split form would round A_2 to half, and overflow beyond 65504: only for a caller who asks.
+    // Half inputs where the whole-rows form does not exist (it needs four 128-wide chunks each way): the plain-FMA pair, which
+    // keeps A_2 in fp32, comes first at every token count.  The split form would round A_2 to half, and overflow beyond 65504:
+    // only for a caller who asks.
     if (dtype == DFK_FP16 && (d_model < 512 || d_ff < 512)) valu();
     if (wdt_split_pays(M, d_model, d_ff)) split_form();
-    // Wavefronts, ring depth: three slots where the down kernel has workgroups (a 16-row tile each) for no more than three quarters of the CUs, so
-    // that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 32 tokens: 1536 x 4096 14.6 / 13.9, 15.2 / 14.8, 18.8 /
-    // 18.0; 2304 x 9216 30.3 / 29.5, 31.7 / 31.6, 38.9 / 38.4; 3072 x 8192 32.1 / 31.0, 32.5 / 32.0, 38.5 / 37.9; the most it loses there
-    // is 1.3 % (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216 37.7 / 37.9, 39.0 / 39.3, 46.5 / 46.9, 3584 x 18944 68.4 /
+    // Wavefronts, ring depth: three slots where the down kernel has workgroups (a 16-row tile each) for no more than three
+    // quarters of the CUs, so that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 32 tokens: 1536 x
+    // 4096 14.6 / 13.9, 15.2 / 14.8, 18.8 /
+    // 18.0; 2304 x 9216 30.3 / 29.5, 31.7 / 31.6, 38.9 / 38.4; 3072 x 8192 32.1 / 31.0, 32.5 / 32.0, 38.5 / 37.9; the most it
+    // loses there is 1.3 % (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216 37.7 / 37.9, 39.0 / 39.3, 46.5 /
+    // 46.9, 3584 x 18944 68.4 /
     // 69.9, 72.0 / 74.4, 89.7 / 90.6; 4096 x 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3.
     const std::vector<int> rings = 4 * t16 <= 3 * 256 ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
     for (int wd : rings)
@@ -385,26 +396,28 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     return out;
 }
 
-// One token: whether the single launch that keeps A_2 in LDS is the untuned choice, or the one that holds both kernels' workgroups.
-// The former has nothing to wait for, but 256 partial sums of all of Y, a second round of workgroups from d_ff = 16384 on (a
-// slice is at most 64 rows), and wavefronts that each own an eighth of the chunks and column blocks, which only widths that are
-// multiples of 1024 divide evenly.  us, A_2 in LDS / both kernels' workgroups: 2048 x 5504 20.2 / 21.1, 3072 x 12288 43.1 / 43.7, 4096 x
-// 8192 40.4 / 41.1, 4096 x 14336 59.4 / 60.1, 4096 x 16384 66.6 / 67.8.  On the other side: 4096 x 20480 88.5 / 83.2, 4096 x 4096 30.1 /
-// 23.7, 1024 x 2816 13.2 / 11.4, 1536 x 4096 20.2 / 15.1, 2304 x 9216 31.1 / 27.9, 3584 x 9216 40.8 / 37.1, 7168 x 20480 146 / 135,
-// 8192 x 14336 113 / 111, 8192 x 28672 222 / 213, 16384 x 16384 277 / 246; 3072 x 8192 30.8 / 30.7.  Beyond a d_ff of 32768 the launch of both
-// kernels' workgroups is not listed (more than 512 slices of 64 rows), and what follows is the pair of launches with the counter reduction.  A_2 in
-// LDS / pair: 512 x 36864 37.1 / 33.6, 1024 x 33280 45.3 / 44.5, 4096 x 53248 215 / 209, 5120 x 40960 202 / 195, 8192 x 40960 321 / 307, 16384 x
-// 53248 923 / 789; 1024 x 53248 63.4 / 63.3, 3072 x 40960 124 / 124, 2048 x 40960 86.5 / 88.0.
+// One token: whether the single launch that keeps A_2 in LDS is the untuned choice, or the one that holds both kernels'
+// workgroups. The former has nothing to wait for, but 256 partial sums of all of Y, a second round of workgroups from d_ff =
+// 16384 on (a slice is at most 64 rows), and wavefronts that each own an eighth of the chunks and column blocks, which only
+// widths that are multiples of 1024 divide evenly.  us, A_2 in LDS / both kernels' workgroups: 2048 x 5504 20.2 / 21.1, 3072 x
+// 12288 43.1 / 43.7, 4096 x 8192 40.4 / 41.1, 4096 x 14336 59.4 / 60.1, 4096 x 16384 66.6 / 67.8.  On the other side: 4096 x
+// 20480 88.5 / 83.2, 4096 x 4096 30.1 /
+// 23.7, 1024 x 2816 13.2 / 11.4, 1536 x 4096 20.2 / 15.1, 2304 x 9216 31.1 / 27.9, 3584 x 9216 40.8 / 37.1, 7168 x 20480 146 /
+// 135, 8192 x 14336 113 / 111, 8192 x 28672 222 / 213, 16384 x 16384 277 / 246; 3072 x 8192 30.8 / 30.7.  Beyond a d_ff of 32768
+// the launch of both kernels' workgroups is not listed (more than 512 slices of 64 rows), and what follows is the pair of
+// launches with the counter reduction.  A_2 in LDS / pair: 512 x 36864 37.1 / 33.6, 1024 x 33280 45.3 / 44.5, 4096 x 53248 215 /
+// 209, 5120 x 40960 202 / 195, 8192 x 40960 321 / 307, 16384 x 53248 923 / 789; 1024 x 53248 63.4 / 63.3, 3072 x 40960 124 / 124,
+// 2048 x 40960 86.5 / 88.0.
 bool local_pays(int d_model, int d_ff) {
     return d_model % 1024 == 0 && d_model >= 2048 && d_model <= 4096 && d_ff >= 2 * d_model && d_ff <= 16384;
 }
 
-// Untuned default, from measurements on MI355X.  One token of some sizes (local_pays): the single launch that keeps A_2 in LDS, with
-// the atomic reduction (no boundary between two kernels, and its 256 full-width partial sums are still cheap).  Else, up to
+// Untuned default, from measurements on MI355X.  One token of some sizes (local_pays): the single launch that keeps A_2 in LDS,
+// with the atomic reduction (no boundary between two kernels, and its 256 full-width partial sums are still cheap).  Else, up to
 // 64 tokens and a d_ff of 32768: the single launch that holds both kernels' workgroups (atomic reduction), which saves the launch
-// boundary at every token count.  Of the two-kernel forms: beyond 64 tokens the pair that takes up to 256 per
-// launch, else the pair for up to 64 tokens, then the rows-split down kernel, then the rest.  Within a form of the
-// 64-token pair: splits and column blocks as few_splits and two_blocks say.
+// boundary at every token count.  Of the two-kernel forms: beyond 64 tokens the pair that takes up to 256 per launch, else the
+// pair for up to 64 tokens, then the rows-split down kernel, then the rest.  Within a form of the 64-token pair: splits and
+// column blocks as few_splits and two_blocks say.
 // `fits`: which candidates the caller can run (all of them, or those within its scratch).
 template <typename F>
 bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant, dfk_config_t* out, F fits) {
@@ -443,19 +456,23 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
     return true;
 }
 
-// The pair for up to 64 tokens as the single launch of both kernels' workgroups: same splits, same reduction, so the same bits with the
-// counter reduction, and no boundary between two launches.  What a block runs where it pays, and a width off 128 without a tuned
-// entry (whose candidates are the pair and not this form of it; dfk_tune times it beside them).  Up to 16 tokens from 48 MB of weights
-// on: below, the down workgroups' wait costs what the boundary does.  us, pair / single launch:
-//   blocks, layers replayed from a graph: 2304 x 9216 at 1, 8 and 33 tokens 32.0 / 30.2, 32.6 / 31.1, 43.6 / 41.5; 4096 x 14336 at 1 and 64
-//   62.3 / 61.2, 83.3 / 81.7; 5120 x 40960 at 64 271 / 257; 1792 x 4864 (52 MB) at 8 and 33 20.4 / 20.2, 29.9 / 28.6; 1536 x 8960 at 17 30.2 /
+// The pair for up to 64 tokens as the single launch of both kernels' workgroups: same splits, same reduction, so the same bits
+// with the counter reduction, and no boundary between two launches.  What a block runs where it pays, and a width off 128 without
+// a tuned entry (whose candidates are the pair and not this form of it; dfk_tune times it beside them).  Up to 16 tokens from 48
+// MB of weights on: below, the down workgroups' wait costs what the boundary does.  us, pair / single launch:
+//   blocks, layers replayed from a graph: 2304 x 9216 at 1, 8 and 33 tokens 32.0 / 30.2, 32.6 / 31.1, 43.6 / 41.5; 4096 x 14336
+//   at 1 and 64
+//   62.3 / 61.2, 83.3 / 81.7; 5120 x 40960 at 64 271 / 257; 1792 x 4864 (52 MB) at 8 and 33 20.4 / 20.2, 29.9 / 28.6; 1536 x 8960
+//   at 17 30.2 /
 //   29.4.  On the other side: 1024 x 4096 (25 MB) at 17 and 64 18.5 / 19.8, 27.3 / 28.2; 1536 x 4096 (38 MB) at 32 22.3 / 23.4;
-//   1280 x 5120 (39 MB) at 17 23.0 / 23.6.  A width that is a multiple of 1024 gives the eight wavefronts equal runs of k, so the gate/up
-//   kernel ends evenly and there is less to gain: from 100 MB on.  2048 x 5504 (68 MB) at 8 and 17 22.7 / 23.2, 25.9 / 26.3; 1024 x 8192
-//   (50 MB) at 8 20.1 / 20.8; 2048 x 8192 (101 MB) at 17 and 40 31.1 / 31.2, 37.5 / 36.9.
-//   off 128, whole call: 2888 x 7688 at 1, 12 and 64 tokens 37.5 / 35.1, 39.1 / 37.3, 54.5 / 53.5; 1800 x 5000 at 16 and 33 25.0 / 23.9,
-//   30.9 / 29.7.  Beyond 16 tokens at every size: 2008 x 2400 (29 MB) at 17 and 33 22.1 / 20.6, 26.6 / 24.5; 904 x 1024 (6 MB) at 33 18.2 /
-//   17.5; 1416 x 3776 at 17 22.2 / 22.6, at 64 31.1 / 31.0.  Not where d_ff is no larger than d_model: 8200 x 1000 at 1 and 17 22.8 / 24.7,
+//   1280 x 5120 (39 MB) at 17 23.0 / 23.6.  A width that is a multiple of 1024 gives the eight wavefronts equal runs of k, so the
+//   gate/up kernel ends evenly and there is less to gain: from 100 MB on.  2048 x 5504 (68 MB) at 8 and 17 22.7 / 23.2, 25.9 /
+//   26.3; 1024 x 8192 (50 MB) at 8 20.1 / 20.8; 2048 x 8192 (101 MB) at 17 and 40 31.1 / 31.2, 37.5 / 36.9. off 128, whole call:
+//   2888 x 7688 at 1, 12 and 64 tokens 37.5 / 35.1, 39.1 / 37.3, 54.5 / 53.5; 1800 x 5000 at 16 and 33 25.0 / 23.9,
+//   30.9 / 29.7.  Beyond 16 tokens at every size: 2008 x 2400 (29 MB) at 17 and 33 22.1 / 20.6, 26.6 / 24.5; 904 x 1024 (6 MB) at
+//   33 18.2 /
+//   17.5; 1416 x 3776 at 17 22.2 / 22.6, at 64 31.1 / 31.0.  Not where d_ff is no larger than d_model: 8200 x 1000 at 1 and 17
+//   22.8 / 24.7,
 //   30.9 / 31.9 (2888 x 2888 at 12 24.5 / 23.4).
 bool single_launch_pays(int M, int d_model, int d_ff) {
     const size_t bytes = (size_t)6 * d_model * d_ff;
@@ -468,7 +485,8 @@ bool single_launch_of(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_d
     if (M > 64 || c.kmajor != 1 || c.path != DFK_PATH_MFMA || c.variant != DFK_VARIANT_TWO_KERNEL) return false;
     dfk_config_t r = c;
     r.variant = DFK_VARIANT_FUSED; r.kmajor = 4; r.depth = 4;
-    if (block ? !mfma_km_block_config_valid(r, M, d_model, d_ff, dtype) : !mfma_km_roles_config_valid(r, M, d_model, d_ff, dtype)) return false;
+    const auto fits = block ? mfma_km_block_config_valid : mfma_km_roles_config_valid;
+    if (!fits(r, M, d_model, d_ff, dtype)) return false;
     *out = r;
     return true;
 }
@@ -492,7 +510,8 @@ bool heuristic(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want_variant
         } else if (!enumerate_default(M, d_model, d_ff, dtype, want_variant, &c, [](const dfk_config_t&) { return true; })) {
             return false;
         }
-        if (want_variant == DFK_VARIANT_AUTO && d_model % 128 && single_launch_pays(M, d_model, d_ff)) single_launch_of(c, M, d_model, d_ff, dtype, false, &c);
+        if (want_variant == DFK_VARIANT_AUTO && d_model % 128 && single_launch_pays(M, d_model, d_ff))
+            single_launch_of(c, M, d_model, d_ff, dtype, false, &c);
         s.M = M; s.d_model = d_model; s.d_ff = d_ff; s.dtype = (int)dtype; s.variant = want_variant; s.cfg = c;
     }
     *out = s.cfg;
@@ -514,7 +533,8 @@ void table_put(int M, int d_model, int d_ff, int dtype, const Entry& e, bool cho
         g_table[Key(M, d_model, d_ff, dtype, kSlotWdt)] = e;
         return;
     }
-    // off 128 the single launch of both kernels' workgroups is a form of the pair, not an entry of the fused variant (that one keeps A_2 in fp32)
+    // off 128 the single launch of both kernels' workgroups is a form of the pair, not an entry of the fused variant (that one
+    // keeps A_2 in fp32)
     if (!(d_model % 128 && roles_launch(e.cfg))) g_table[Key(M, d_model, d_ff, dtype, e.cfg.variant)] = e;
     if (chosen) g_table[Key(M, d_model, d_ff, dtype, 0)] = e;
 }
@@ -870,11 +890,12 @@ bool block_carries(const dfk_config_t& k, int M, int d_model, int d_ff, dfk_dtyp
     if (k.variant == DFK_VARIANT_FUSED) return k.kmajor == 4 && mfma_km_block_config_valid(k, M, d_model, d_ff, dtype);
     return k.kmajor == 1 && d_model % 128 == 0 && mfma_km_config_valid(k, M, d_model, d_ff, dtype);
 }
-// The block's configuration without one from the caller: the choice of its layout (of the two-kernel variant), else the first candidate that
-// carries it; the pair for up to 64 tokens, tuned or not, in the form of a single launch where that pays.
+// The block's configuration without one from the caller: the choice of its layout (of the two-kernel variant), else the first
+// candidate that carries it; the pair for up to 64 tokens, tuned or not, in the form of a single launch where that pays.
 bool choose_block(int M, int d_model, int d_ff, dfk_dtype_t dtype, bool wd_t, dfk_config_t* out, int* tuned) {
     dfk_config_t c;
-    if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, tuned) : !choose(M, d_model, d_ff, dtype, DFK_VARIANT_TWO_KERNEL, &c, tuned)) return false;
+    if (wd_t ? !choose_wdt(M, d_model, d_ff, dtype, &c, tuned)
+             : !choose(M, d_model, d_ff, dtype, DFK_VARIANT_TWO_KERNEL, &c, tuned)) return false;
     if (!block_carries(c, M, d_model, d_ff, dtype)) {
         if (tuned) *tuned = 0;
         bool found = false;
@@ -986,7 +1007,8 @@ dfk_status_t dfk_get_choice_wdt(int M, int d_model, int d_ff, dfk_dtype_t dtype,
     return choose_wdt(M, d_model, d_ff, dtype, out, tuned_out) ? DFK_OK : DFK_ERR_UNSUPPORTED_SHAPE;
 }
 
-dfk_status_t dfk_get_choice_block(int M, int d_model, int d_ff, dfk_dtype_t dtype, int w_down_t, dfk_config_t* out, int* tuned_out) {
+dfk_status_t dfk_get_choice_block(int M, int d_model, int d_ff, dfk_dtype_t dtype, int w_down_t, dfk_config_t* out,
+                                  int* tuned_out) {
     if (!out) return DFK_ERR_INVALID_ARG;
     if (M < 1 || d_model < 1 || d_ff < 1) return DFK_ERR_INVALID_ARG;
     if (dtype != DFK_BF16 && dtype != DFK_FP16) return dtype == DFK_FP32 ? DFK_ERR_UNSUPPORTED_SHAPE : DFK_ERR_INVALID_ARG;
@@ -1068,7 +1090,8 @@ dfk_status_t dfk_tune(const int* M_list, int nM, int d_model, int d_ff, dfk_dtyp
         for (size_t k = 0; d_model % 128 && k < listed; ++k) {   // the pair's other form, which is not listed there
             dfk_config_t one;
             if (!single_launch_of(cands[k], M, d_model, d_ff, dtype, false, &one)) continue;
-            if (std::none_of(cands.begin(), cands.end(), [&](const dfk_config_t& o) { return same_cfg(o, one); })) cands.push_back(one);
+            auto same = [&](const dfk_config_t& o) { return same_cfg(o, one); };
+            if (std::none_of(cands.begin(), cands.end(), same)) cands.push_back(one);
         }
         Entry best, best_of[3];
         best.usec = best_of[1].usec = best_of[2].usec = -1.0;

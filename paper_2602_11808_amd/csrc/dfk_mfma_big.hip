@@ -15,7 +15,8 @@
 //
 // Data movement is the asynchronous global->LDS tile load of the other MFMA kernels,
 // organised as a workgroup pipeline:
-//   * a step is 64 k (or two such pieces in the gate/up kernel): tiles of 16 rows x 128 bytes (one cache line per row), 2 KB.  In LDS the eight
+//   * a step is 64 k (or two such pieces in the gate/up kernel): tiles of 16 rows x 128 bytes (one cache line per row), 2 KB.  In
+//   LDS the eight
 //     16-byte pieces of row i sit XOR-swizzled by i / 2, so that the operand reads of 16 rows
 //     cover all banks once.
 //   * wavefronts 0..3 request the weights, 4..7 the activations.  Loads complete in issue order
@@ -56,8 +57,8 @@ constexpr int big_w_bufs(int x_step, int w_step) {
 }
 // 64-k pieces per step of the gate/up kernel.  A step costs about 0.4 us before any multiplication; with few row tiles per slice
 // and few token tiles per group that is most of it, so two pieces share one, where LDS still holds three buffers of it (whole
-// call: 2432 x 3968 at 65 tokens 36.6 -> 32.8 us, 2560 x 3712 at 107 39.6 -> 37.0, 2304 x 8192 at 104 45.9 -> 43.1).  With one token
-// tile per group it gained 10 % at five row tiles (2304 x 9216) and lost 5 % at four (8192 x 7168), so not beyond three.
+// call: 2432 x 3968 at 65 tokens 36.6 -> 32.8 us, 2560 x 3712 at 107 39.6 -> 37.0, 2304 x 8192 at 104 45.9 -> 43.1).  With one
+// token tile per group it gained 10 % at five row tiles (2304 x 9216) and lost 5 % at four (8192 x 7168), so not beyond three.
 constexpr int big_gateup_pieces(int TT, int NTC) { return (TT == 1 && NTC <= 3) || (TT == 2 && NTC <= 5) ? 2 : 1; }
 
 // s_waitcnt vmcnt(n) for a run-time n (uniform); more than 63 waits for 63.
@@ -92,16 +93,17 @@ __device__ __forceinline__ unsigned keep32(unsigned o) {
 // This lane's byte offset of its MFMA operand within a tile: row q, the 16-byte piece of k group g of half kh.
 __device__ __forceinline__ int big_operand_off(int q, int g, int kh) { return q * 128 + (((4 * kh + g) ^ (q >> 1)) & 7) * 16; }
 
-// Step at which a workgroup of the gate/up kernel starts its walk through the k range.  All of them read the same X: in
-// lock-step they would ask the same few L2 channels for the same lines at the same moment, so starts differ, as a rule over the whole
+// Step at which a workgroup of the gate/up kernel starts its walk through the k range.  All of them read the same X: in lock-step
+// they would ask the same few L2 channels for the same lines at the same moment, so starts differ, as a rule over the whole
 // range.  But what is live of X is what lies between the first and the last of an XCD's workgroups (b, b + 8, ...), and that has
-// to stay in its 4 MB L2 beside the weights passing through.  Where X is larger than 3 MB the starts are spread over a window of 64
-// steps (2 MB at 256 tokens and 64 k a step) instead: otherwise X came from beyond the L2 again for every workgroup.  The same
-// where rows are a multiple of 16 KB apart: there a step's rows lie in the same memory channels, and XCDs that walk in step spread the
-// weights better.  Whole call, us, whole range / window / all at step 0: 16384 x 8192 at 256 tokens 455 / 269 / 274, 16384 x 16384 at 128
-// 364 / 319 / 352, 12288 x 12288 at 200 285 / 261 / 267, 12288 x 20480 at 200 482 / 444, 8192 x 28672 at 256 387 / 376, 8192 x 14336
-// at 100 148 / 142 / 150, 8192 x 28672 at 80 267 / 264.  On the other side of the line: 9856 x 28032 at 111 (2.2 MB) 326 / 332, 5504 x
-// 25216 at 105 193 / 196, 5760 x 29568 at 227 (2.6 MB) 305 / 305, 4096 x 14336 at 128 85.5 / 86.2 / 90.1.
+// to stay in its 4 MB L2 beside the weights passing through.  Where X is larger than 3 MB the starts are spread over a window of
+// 64 steps (2 MB at 256 tokens and 64 k a step) instead: otherwise X came from beyond the L2 again for every workgroup.  The same
+// where rows are a multiple of 16 KB apart: there a step's rows lie in the same memory channels, and XCDs that walk in step
+// spread the weights better.  Whole call, us, whole range / window / all at step 0: 16384 x 8192 at 256 tokens 455 / 269 / 274,
+// 16384 x 16384 at 128 364 / 319 / 352, 12288 x 12288 at 200 285 / 261 / 267, 12288 x 20480 at 200 482 / 444, 8192 x 28672 at 256
+// 387 / 376, 8192 x 14336 at 100 148 / 142 / 150, 8192 x 28672 at 80 267 / 264.  On the other side of the line: 9856 x 28032 at
+// 111 (2.2 MB) 326 / 332, 5504 x 25216 at 105 193 / 196, 5760 x 29568 at 227 (2.6 MB) 305 / 305, 4096 x 14336 at 128 85.5 / 86.2
+// / 90.1.
 __device__ __forceinline__ int big_k_start(const MlpArgs& a, int nsteps) {
     const unsigned b = blockIdx.x;
     const size_t row = (size_t)a.d_model * 2;
@@ -135,10 +137,10 @@ __device__ __forceinline__ void down_tile_of(int b, int S, int C, bool by_xcd, i
     }
 }
 
-// Step at which a workgroup of the down kernels starts its split.  In step with the split's other column blocks, so that what
-// is live of their A_2 rows stays small and XCDs spread W_down over the memory channels; only where a whole split sits on one XCD
-// (down_tile_of, a multiple of 8 splits), in a start of its own, against the lock-step on the L2 channels.  Down kernel with
-// its sum, us, own start / in step: 16384 x 16384 at 128 tokens 142 / 117, 9856 x 28032 at 111 148 / 110, 5760 x 29568 at 227 146 /
+// Step at which a workgroup of the down kernels starts its split.  In step with the split's other column blocks, so that what is
+// live of their A_2 rows stays small and XCDs spread W_down over the memory channels; only where a whole split sits on one XCD
+// (down_tile_of, a multiple of 8 splits), in a start of its own, against the lock-step on the L2 channels.  Down kernel with its
+// sum, us, own start / in step: 16384 x 16384 at 128 tokens 142 / 117, 9856 x 28032 at 111 148 / 110, 5760 x 29568 at 227 146 /
 // 126, 2304 x 9216 at 200 28.1 / 27.4, 4096 x 14336 at 128 (not placed by XCD) 37.8 / 36.3; at 256 (placed) 51.9 / 53.0.
 __device__ __forceinline__ int big_down_start(const MlpArgs& a, bool by_xcd, int cb, int nsteps) {
     return by_xcd && (a.k2_splits & 7) == 0 ? (int)(cb * 5u % (unsigned)nsteps) : 0;
@@ -148,9 +150,9 @@ __device__ __forceinline__ int big_down_start(const MlpArgs& a, bool by_xcd, int
 // NTC: the largest row-tile count of a d_ff slice of the launch (a compile-time constant so that
 // a step is straight-line code); every slice has NTC or NTC - 1 row tiles (the missing one's sums are never stored).
 //
-// DOWN_T: the same pipeline computes the down projection from W_down given as [d_model, d_ff]: Y^T = W_down^T A_2^T has the
-// shape of stage one with d_ff as the k range and A_2 in X's place.  Workgroup (js, cb) owns 128 rows of W_down^T (NTC = 8 tiles of
-// 16 rows of the one matrix) over d_ff split js in whole 64-row steps; the end stores the partial block of the split.
+// DOWN_T: the same pipeline computes the down projection from W_down given as [d_model, d_ff]: Y^T = W_down^T A_2^T has the shape
+// of stage one with d_ff as the k range and A_2 in X's place.  Workgroup (js, cb) owns 128 rows of W_down^T (NTC = 8 tiles of 16
+// rows of the one matrix) over d_ff split js in whole 64-row steps; the end stores the partial block of the split.
 template <int TT, typename E, int NTC, bool DOWN_T = false>
 __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char* lds, const bool by_xcd = false) {
     const int tid = threadIdx.x;
@@ -189,9 +191,9 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     DFK_STAMP(DOWN_T ? 3 : 0);
     constexpr int x_piece = 4 * TT * kBigTile, w_piece = NTC * kBigTile, x_step = KS * x_piece, w_step = KS * w_piece;
     constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
-    // The steps of a wavefront that requests N weight loads per 64-k piece or (N = -1) activations: of the slice's 2 nt weight loads
-    // (half n & 1 of row tile n / 2: the gate rows or the up rows) n = wave, wave + 4, ...; or the two loads of each token tile
-    // of its group.
+    // The steps of a wavefront that requests N weight loads per 64-k piece or (N = -1) activations: of the slice's 2 nt weight
+    // loads (half n & 1 of row tile n / 2: the gate rows or the up rows) n = wave, wave + 4, ...; or the two loads of each token
+    // tile of its group.
     auto steps = [&](auto n_) {
         constexpr int N = decltype(n_)::value;
         constexpr bool W = N >= 0;
@@ -200,8 +202,9 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         const char* const src = (W && DOWN_T ? (const char*)a.Wd + (size_t)(j0 + wave * 8) * row_bytes
                                  : W         ? (const char*)(wave & 1 ? a.Wu : a.Wg) + (size_t)(j0 + (wave >> 1) * 8) * row_bytes
                                              : (const char*)(DOWN_T ? a.a2 : a.X) + (size_t)a.m_base * row_bytes) + (size_t)k0 * 2;
-        // Byte offset of load i: row 16 i (gate and up rows; 32 i of the one matrix) or 8 i (tokens, the last one for those that do not
-        // exist) further on than load 0's; the piece's place changes by half a row (64 bytes) from a tile's rows 0..7 to its rows 8..15.
+        // Byte offset of load i: row 16 i (gate and up rows; 32 i of the one matrix) or 8 i (tokens, the last one for those that
+        // do not exist) further on than load 0's; the piece's place changes by half a row (64 bytes) from a tile's rows 0..7 to
+        // its rows 8..15.
         const unsigned rb = (unsigned)row_bytes;
         const unsigned off = (unsigned)(W ? prow : tile0 * 16 + prow) * rb, off_last = (unsigned)(a.m_count - 1) * rb;
         const unsigned place = (unsigned)(((piece ^ (prow >> 1)) & 7) * 16) ^ (W && (wave & 1) ? 64u : 0u);
@@ -522,11 +525,11 @@ __global__ __launch_bounds__(kBigWaves * 64) void k_down_big(MlpArgs a, int by_x
     down_big_body<TT, E>(a, by_xcd != 0, lds);
 }
 
-// Down projection from W_down given as [d_model, d_ff], 65 tokens and more (and fewer, see wdt_split_pays): the pipeline of
-// the gate/up kernel over (d_ff splits) x (blocks of 128 rows of W_down^T).  Its sibling for a few tokens, whose workgroups own rows
-// whole so that nothing is summed across them, takes 64 tokens per launch and streams all three weights again for each 64: that, not
-// its own pace, bounded it.  Whole call, 4096 x 14336, us: 80 tokens 149 -> 77, 128 173 -> 85, 256 345 -> 108 (the other layout,
-// whose weights are regrouped in registers, 115).
+// Down projection from W_down given as [d_model, d_ff], 65 tokens and more (and fewer, see wdt_split_pays): the pipeline of the
+// gate/up kernel over (d_ff splits) x (blocks of 128 rows of W_down^T).  Its sibling for a few tokens, whose workgroups own rows
+// whole so that nothing is summed across them, takes 64 tokens per launch and streams all three weights again for each 64: that,
+// not its own pace, bounded it.  Whole call, 4096 x 14336, us: 80 tokens 149 -> 77, 128 173 -> 85, 256 345 -> 108 (the other
+// layout, whose weights are regrouped in registers, 115).
 template <int TT, typename E>
 __global__ __launch_bounds__(kBigWaves * 64) void k_down_t_big(MlpArgs a, int by_xcd) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];

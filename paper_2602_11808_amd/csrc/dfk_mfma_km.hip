@@ -53,11 +53,18 @@ struct KmGeom {
     int down_first;          // tests: the down workgroups are at the head of the grid
 };
 
-static_assert(kRoleCount0 > kTicketLevel2 && kRolePassed < kMaxTickets - 1, "the words of the single launch lie between the reductions' counters");
+static_assert(kRoleCount0 > kTicketLevel2 && kRolePassed < kMaxTickets - 1,
+              "the words of the single launch lie between the reductions' counters");
 struct DeviceMem {
-    static __device__ __forceinline__ unsigned load(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    static __device__ __forceinline__ void store(unsigned* p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    static __device__ __forceinline__ unsigned fetch_add(unsigned* p, unsigned v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    static __device__ __forceinline__ unsigned load(const unsigned* p) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ void store(unsigned* p, unsigned v) {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ unsigned fetch_add(unsigned* p, unsigned v) {
+        return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     static __device__ __forceinline__ void settle() { drain_own_memory_ops(); }
     static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(8); }
 };
@@ -72,15 +79,15 @@ __host__ __device__ inline int km_norm_stride(int d_model, int waves) {
     return (((nchunks + waves - 1) / waves) * (kKC * 2) + 1023) & ~1023;
 }
 
-// ---------------------------------------------------------------- gate/up kernel
-// TAIL: the rows' length is no whole number of chunks (kdim any multiple of 8).  The last chunk's 16-byte pieces past
-// the row's end are fetched from its last 16 bytes instead and the operands zeroed at use.  A form of its own,
-// because the clamps cost a few VALU instructions per tile, in every chunk although only the last needs them: with it a 2888 x 7688
-// layer takes the matrix cores, 429 -> 39.7 us at 12 tokens in bf16 against the plain-FMA pair, which re-reads X for every weight row.
-// Rows then start anywhere in a cache line, and a 256-byte piece shares its first or last line with its neighbours: no
-// non-temporal hint here and in the down kernel of these widths, so that such a line is still in the L2 when the
-// neighbour asks for it: 2888 x 7688 at 1, 12 and 64 tokens 38.1 -> 37.1, 40.0 -> 38.9, 55.5 -> 54.4 us, 1000 x 3000 at 4 14.7 -> 14.0.
-// (Clamping only in the last chunk and column block, a branch per tile: 40.1 -> 40.4.)
+// ---------------------------------------------------------------- gate/up kernel TAIL: the rows' length is no whole number of
+// chunks (kdim any multiple of 8).  The last chunk's 16-byte pieces past the row's end are fetched from its last 16 bytes instead
+// and the operands zeroed at use.  A form of its own, because the clamps cost a few VALU instructions per tile, in every chunk
+// although only the last needs them: with it a 2888 x 7688 layer takes the matrix cores, 429 -> 39.7 us at 12 tokens in bf16
+// against the plain-FMA pair, which re-reads X for every weight row. Rows then start anywhere in a cache line, and a 256-byte
+// piece shares its first or last line with its neighbours: no non-temporal hint here and in the down kernel of these widths, so
+// that such a line is still in the L2 when the neighbour asks for it: 2888 x 7688 at 1, 12 and 64 tokens 38.1 -> 37.1, 40.0 ->
+// 38.9, 55.5 -> 54.4 us, 1000 x 3000 at 4 14.7 -> 14.0. (Clamping only in the last chunk and column block, a branch per tile:
+// 40.1 -> 40.4.)
 template <int NW, int TT, bool TAIL, bool ROT>
 struct KmStream1 {
     const char *Wg, *Wu, *X;
@@ -115,7 +122,8 @@ struct KmStream1 {
             for (int u = 0; u < 4; ++u) {
                 const int i = 4 * u + g;
                 const unsigned ko = min((unsigned)p_kc * (kKC * 2) + (q ^ i) * 16, k_last);
-                __builtin_amdgcn_global_load_lds((u < 2 ? Wg : Wu) + tb + (size_t)(i & 7) * row_bytes + ko, DFK_LDS_PTR(slot + u * 1024), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((u < 2 ? Wg : Wu) + tb + (size_t)(i & 7) * row_bytes + ko, DFK_LDS_PTR(slot + u * 1024),
+                                                 16, 0, 0);
             }
         } else {               // weight tile of row tile p_idx - TT: 8 rows of W_gate, the same 8 of W_up
             const size_t tb = w_base + (size_t)(p_idx - TT) * tile_rows * row_bytes + (size_t)p_kc * (kKC * 2);
@@ -508,23 +516,25 @@ struct KmStream2 {
 __host__ __device__ constexpr int km_col_blocks(int tt) { return tt >= 3 ? 1 : 2; }   // accumulator budget
 
 //
-// WAIT (the single launch of both kernels' workgroups): the stream carries the A tile of a 32-row block behind the
-// first column block's weight tiles and starts with those alone; then the workgroup waits until every gate/up
-// workgroup of its rows has counted itself done, or parks if that takes long (dfk_roles.h says why), and goes on as the kernel
-// does, but with A_2 loads of device scope: workgroups of other XCDs wrote parts of the lines this XCD's caches may hold.  (The writers store with device scope and
-// count themselves once the stores are acknowledged.)  With one invalidation of the caches per workgroup after the wait
+// WAIT (the single launch of both kernels' workgroups): the stream carries the A tile of a 32-row block behind the first column
+// block's weight tiles and starts with those alone; then the workgroup waits until every gate/up workgroup of its rows has
+// counted itself done, or parks if that takes long (dfk_roles.h says why), and goes on as the kernel does, but with A_2 loads of
+// device scope: workgroups of other XCDs wrote parts of the lines this XCD's caches may hold.  (The writers store with device
+// scope and count themselves once the stores are acknowledged.)  With one invalidation of the caches per workgroup after the wait
 // instead, and plain loads: 60.7 us where this takes 60.0 at one token of 4096 x 14336, 28.9 / 28.3 at 8 of 2304 x 9216, 71.1 /
 // 70.3 at 33 of 8192 x 7168; equal at 64 tokens of 8192 x 28672, where the 64 column blocks re-read the most.
 //
-// stand_in: this workgroup does the work of a parked one.  Returns whether there are notes of parked workgroups for the caller to go through.
+// stand_in: this workgroup does the work of a parked one.  Returns whether there are notes of parked workgroups for the caller to
+// go through.
 template <int NW, int TT, typename E, bool WAIT, bool TAIL = false>
-__device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds, const bool stand_in = false) {
+__device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds,
+                                             const bool stand_in = false) {
     __shared__ int flag;
     __shared__ unsigned passed;
     constexpr int NTHREADS = NW * 64;
     constexpr int CBM = km_col_blocks(TT);
     int tid = threadIdx.x;
-    if (WAIT) asm volatile("" : "+v"(tid));    // (the caller's loop: nothing that depends on the thread is kept from one round to the next)
+    if (WAIT) asm volatile("" : "+v"(tid));    // (for the caller's loop: nothing that depends on the thread is kept between its rounds)
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane & 15, g = lane >> 4;
@@ -565,7 +575,8 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
             if (tid == 0) {
                 const int ng = a.d_ff / 8;
                 const unsigned expected = (unsigned)(slice_of_group(ng, a.splits, j1 / 8 - 1) - slice_of_group(ng, a.splits, j0 / 8) + 1);
-                flag = role_wait<DeviceMem>(a.tickets, geo.role, js, expected, geo.role_spin_limit, stand_in ? nullptr : (unsigned*)a.Q, wg);
+                flag = role_wait<DeviceMem>(a.tickets, geo.role, js, expected, geo.role_spin_limit,
+                                            stand_in ? nullptr : (unsigned*)a.Q, wg);
             }
             __syncthreads();
             const int got = flag;
@@ -734,8 +745,8 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
     const int width = TAIL ? min(CB * 128, a.d_model - blk_lo * 128) : CB * 128;
     bool notes = false;
     if (WAIT && geo.role_wait > 0 && !stand_in) {
-        // every other down workgroup is past its wait, or parked, once the last one has said so: if none has parked, that one clears the
-        // words for the next launch here
+        // every other down workgroup is past its wait, or parked, once the last one has said so: if none has parked, that one
+        // clears the words for the next launch here
         const unsigned before = __builtin_amdgcn_readfirstlane(passed);
         if (role_left(geo.role, before) == 1u) {
             notes = before >> 16 != 0;
@@ -760,16 +771,15 @@ __global__ __launch_bounds__(NW * 64) void k_down_km(MlpArgs a, KmGeom geo) {
     down_km_body<NW, TT, E, false, TAIL>(a, geo, blockIdx.x, lds);
 }
 
-// ---------------------------------------------------------------- both kernels' workgroups in one launch
-// Grid = the gate/up kernel's workgroups followed by the down kernel's.  Workgroups of a grid are dispatched in index
-// order on each XCD, so a down workgroup as a rule waits for workgroups that run; where launches of other streams hold their CUs it
-// may park (dfk_roles.h): the wait ends in any order of dispatch.  What the single launch buys over
-// two: no launch boundary (drain, dispatch and ramp with HBM idle), and the down workgroups request their first
-// W_down tiles while the last gate/up workgroups are still streaming.  A_2 crosses between workgroups through
-// device memory (2 bytes per token and d_ff row), as between the two kernels.
+// ---------------------------------------------------------------- both kernels' workgroups in one launch Grid = the gate/up
+// kernel's workgroups followed by the down kernel's.  Workgroups of a grid are dispatched in index order on each XCD, so a down
+// workgroup as a rule waits for workgroups that run; where launches of other streams hold their CUs it may park (dfk_roles.h):
+// the wait ends in any order of dispatch.  What the single launch buys over two: no launch boundary (drain, dispatch and ramp
+// with HBM idle), and the down workgroups request their first W_down tiles while the last gate/up workgroups are still streaming.
+// A_2 crosses between workgroups through device memory (2 bytes per token and d_ff row), as between the two kernels.
 // NORM: with the normalisation in front and the residual added (dfk_mlp_block).  The output may be the input there: a column
-// block is stored once every d_ff split has arrived, so after every gate/up workgroup has read the input and published.
-// The notes of parked workgroups are in the group sums' place in the workspace, which a reduction over column blocks does not use.
+// block is stored once every d_ff split has arrived, so after every gate/up workgroup has read the input and published. The notes
+// of parked workgroups are in the group sums' place in the workspace, which a reduction over column blocks does not use.
 struct RolesArgs { MlpArgs a; KmGeom geo; };
 // The launch's arguments, read again: to the compiler other values each time.
 __device__ __forceinline__ RolesArgs roles_args_again() {
@@ -797,10 +807,11 @@ __global__ __launch_bounds__(NW * 64) void k_roles_km(RolesArgs r) {
         return;
     }
     if (__builtin_expect(!down_km_body<NW, TT, E, true, TAIL>(r.a, r.geo, wg - r.geo.n_gateup, lds), 1)) return;
-    // Others have parked: their work, one after the other.  Code apart from the call above and with arguments of its own for each round, so
-    // that nothing is kept in registers for it (as one loop around a single call it cost every launch 0.5 to 0.9 us).
-    const int n = __builtin_amdgcn_readfirstlane((int)DeviceMem::load(r.a.tickets + kRoleNotes));   // final, and by every wavefront read before it is cleared:
-    for (int i = 0; i < n; ++i) {                                                                   // at least one note is another's, whose work has barriers
+    // Others have parked: their work, one after the other.  Code apart from the call above and with arguments of its own for each
+    // round, so that nothing is kept in registers for it (as one loop around a single call it cost every launch 0.5 to 0.9 us).
+    // (The count is final, and every wavefront reads it before it is cleared: at least one note is another's, whose work has barriers.)
+    const int n = __builtin_amdgcn_readfirstlane((int)DeviceMem::load(r.a.tickets + kRoleNotes));
+    for (int i = 0; i < n; ++i) {
         RolesArgs k = roles_args_again();
         k.a.trace = nullptr;               // (the stamps of this workgroup are those of its own work)
         const int parked = __builtin_amdgcn_readfirstlane((int)DeviceMem::load((const unsigned*)k.a.Q + i));
@@ -852,9 +863,10 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
     return std::max(ring, (size_t)geo->pass * per_tile);
 }
 
-// Wavefronts of the pair's down kernel: as configured, but eight where the gate/up kernel runs four (narrow widths: few 128-k chunks
-// of d_model, which say nothing about the down kernel's d_ff rows) and there is more than one token tile.  Four there had twice the
-// tiles each and the same stages to add at the end: 896 x 4864 at 40 tokens 26.8 -> 24.4 us per call, 640 x 2560 at 64 27.5 -> 24.9, 512 x 1536 at 24
+// Wavefronts of the pair's down kernel: as configured, but eight where the gate/up kernel runs four (narrow widths: few 128-k
+// chunks of d_model, which say nothing about the down kernel's d_ff rows) and there is more than one token tile.  Four there had
+// twice the tiles each and the same stages to add at the end: 896 x 4864 at 40 tokens 26.8 -> 24.4 us per call, 640 x 2560 at 64
+// 27.5 -> 24.9, 512 x 1536 at 24
 // 15.2 -> 14.6; up to 16 tokens equal or worse (7.5 ->
 // 8.1 at one token of 1024 x 2816).
 constexpr int km_down_waves(int waves, int tt) { return waves == 4 && tt >= 2 ? 8 : waves; }
@@ -957,9 +969,11 @@ hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream
 }
 template <int NW, int TT>
 hipError_t launch_km_roles_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    if (a.d_model % kKC) return a.norm_w || a.dtype != DFK_BF16 ? hipErrorInvalidValue : launch_km_roles_te<NW, TT, BF16, false, true>(a, c, st);
-    if (a.norm_w) return a.dtype == DFK_FP16 ? launch_km_roles_te<NW, TT, FP16, true>(a, c, st) : launch_km_roles_te<NW, TT, BF16, true>(a, c, st);
-    return a.dtype == DFK_FP16 ? launch_km_roles_te<NW, TT, FP16, false>(a, c, st) : launch_km_roles_te<NW, TT, BF16, false>(a, c, st);
+    const bool half = a.dtype == DFK_FP16;
+    if (a.d_model % kKC)
+        return a.norm_w || a.dtype != DFK_BF16 ? hipErrorInvalidValue : launch_km_roles_te<NW, TT, BF16, false, true>(a, c, st);
+    if (a.norm_w) return half ? launch_km_roles_te<NW, TT, FP16, true>(a, c, st) : launch_km_roles_te<NW, TT, BF16, true>(a, c, st);
+    return half ? launch_km_roles_te<NW, TT, FP16, false>(a, c, st) : launch_km_roles_te<NW, TT, BF16, false>(a, c, st);
 }
 
 }  // namespace
@@ -1029,7 +1043,8 @@ bool mfma_km_roles_config_valid(const dfk_config_t& c, int M, int d_model, int d
     if (c.variant != DFK_VARIANT_FUSED || c.kmajor != 4 || c.waves != 8) return false;
     if ((long long)c.splits + (long long)c.k2_splits * c.k2_col_blocks > 65535) return false;
     if (c.k2_splits > kRoleCountEnd - kRoleCount0) return false;   // one counter per d_ff split of the down projection
-    // (the notes of parked workgroups, a word each, fit the group sums: at least 512 bytes per column, and 8 wavefronts need 904 columns)
+    // (the notes of parked workgroups, a word each, fit the group sums: at least 512 bytes per column, and 8 wavefronts need 904
+    // columns)
     static_assert((size_t)512 * 904 >= (size_t)4 * 65535, "room for a note of every down workgroup");
     return mfma_km_config_valid(roles_as_pair(c), M, d_model, d_ff, dtype);
 }

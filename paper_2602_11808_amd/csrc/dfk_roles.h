@@ -1,13 +1,14 @@
-// How the down workgroups of the launch that holds both kernels' workgroups (dfk_mfma_km.hip) wait for its gate/up workgroups.  Free of
-// device code, so that a host program can run it too: `Mem` supplies relaxed memory operations of device scope.
+// How the down workgroups of the launch that holds both kernels' workgroups (dfk_mfma_km.hip) wait for its gate/up workgroups.
+// Free of device code, so that a host program can run it too: `Mem` supplies relaxed memory operations of device scope.
 //
 // A gate/up workgroup waits for nobody.  A down workgroup waits until the slices of its d_ff split have been published.  Alone on
 // the device that wait ends by itself: each XCD takes a grid's workgroups in index order, gate/up first.  Two launches on two
-// streams could block each other: one XCD takes the workgroups of the first launch first, another those of the second, and both fill up with
-// down workgroups that wait for gate/up workgroups which find no room on the other XCD.  So a down workgroup that has waited for long
-// parks: it leaves a note and ends, and makes room.  One per launch may not, the last that has neither passed its wait nor
-// parked; it does the work of those that have when its own is done.  What waits for good is then one workgroup per launch in flight, and as long
-// as these are fewer than the CUs of an XCD (a process has 4 hardware queues, 32 at most), every gate/up workgroup gets its turn.
+// streams could block each other: one XCD takes the workgroups of the first launch first, another those of the second, and both
+// fill up with down workgroups that wait for gate/up workgroups which find no room on the other XCD.  So a down workgroup that
+// has waited for long parks: it leaves a note and ends, and makes room.  One per launch may not, the last that has neither passed
+// its wait nor parked; it does the work of those that have when its own is done.  What waits for good is then one workgroup per
+// launch in flight, and as long as these are fewer than the CUs of an XCD (a process has 4 hardware queues, 32 at most), every
+// gate/up workgroup gets its turn.
 #pragma once
 
 #if defined(__HIPCC__)
@@ -31,12 +32,17 @@ struct RoleShape {
     int stride;
 };
 
-// Polls after which a down workgroup parks: far more than a healthy wait takes (tens of microseconds; a poll is about a third of one).
+// Polls after which a down workgroup parks: far more than a healthy wait takes (tens of microseconds; a poll is about a third of
+// one).
 constexpr int kRoleParkPolls = 1024;
 
-DFK_HD unsigned role_left(const RoleShape& s, unsigned passed_word) { return (unsigned)s.n_down - (passed_word & 0xffffu) - (passed_word >> 16); }
+// Down workgroups that have neither passed nor parked.
+DFK_HD unsigned role_left(const RoleShape& s, unsigned passed_word) {
+    return (unsigned)s.n_down - (passed_word & 0xffffu) - (passed_word >> 16);
+}
 
-// True if workgroup `wg` has parked; false if all the others have passed or parked.  `list` has room for every down workgroup; each tries once.
+// True if workgroup `wg` has parked; false if all the others have passed or parked.  `list` has room for every down workgroup;
+// each tries once.
 template <typename Mem>
 DFK_HD bool role_park(unsigned* t, const RoleShape& s, unsigned* list, int wg) {
     Mem::store(list + Mem::fetch_add(t + kRoleNotes, 1u), (unsigned)wg);

@@ -1,6 +1,7 @@
-// Two launches that hold gate/up and down workgroups, on a model device: XCDs with a few places for workgroups each, every XCD taking the
-// two launches' workgroups in an order of its own.  Runs the waiting protocol that the kernels run (dfk_roles.h) and prints, per launch,
-// how many down workgroups gave up, how many parked, and whether work was done once each and the words are zero again.
+// Two launches that hold gate/up and down workgroups, on a model device: XCDs with a few places for workgroups each, every XCD
+// taking the two launches' workgroups in an order of its own.  Runs the waiting protocol that the kernels run (dfk_roles.h) and
+// prints, per launch, how many down workgroups gave up, how many parked, and whether work was done once each and the words are
+// zero again.
 //   roles_model <may park: 0 or 1> <order: 0 same, 1 opposite, 2 down workgroups first> <seed> <poll limit>
 #include <atomic>
 #include <cstdio>
@@ -38,11 +39,13 @@ struct Launch {
     }
     // as down_km_body: what the last one to pass has to go through is the caller's business
     bool down(int wg, bool stand_in) {
-        const int js = wg / kBlocks, got = dfk::role_wait<HostMem>(words.data(), shape, js, kSlices / kSplits, limit, may_park && !stand_in ? list.data() : nullptr, wg);
+        const int js = wg / kBlocks, per = kSlices / kSplits;
+        unsigned* const notes = may_park && !stand_in ? list.data() : nullptr;
+        const int got = dfk::role_wait<HostMem>(words.data(), shape, js, per, limit, notes, wg);
         if (got == dfk::kRoleParked) { ++parked; return false; }
         if (got == dfk::kRoleGaveUp) ++gave_up;
         const unsigned before = stand_in ? 0u : dfk::role_pass<HostMem>(words.data());
-        for (int s = js * (kSlices / kSplits); s < (js + 1) * (kSlices / kSplits); ++s) early += !stand_in && got == dfk::kRoleReady && !published[s];
+        for (int s = js * per; s < (js + 1) * per; ++s) early += got == dfk::kRoleReady && !published[s];
         ++done[wg];
         if (stand_in || dfk::role_left(shape, before) != 1u) return false;
         if (before >> 16) return true;
@@ -73,7 +76,8 @@ int main(int argc, char** argv) {
     for (int x = 0; x < kXcds; ++x)
         for (int k = 0; k < 2; ++k) {
             Launch* l = &launches[order == 1 ? k ^ x : k];
-            for (int i = x; i < kSlices + kDown; i += kXcds) queue[x].push_back({l, order == 2 ? (i + kSlices) % (kSlices + kDown) : i});
+            for (int i = x; i < kSlices + kDown; i += kXcds)
+                queue[x].push_back({l, order == 2 ? (i + kSlices) % (kSlices + kDown) : i});
         }
     std::vector<std::thread> places;
     for (int x = 0; x < kXcds; ++x)
