@@ -296,9 +296,9 @@ dfk_status_t dfk_mlp_block(const void* H, const void* norm_weight, float eps,
 
 /* The same with the down projection's weights given as W_down_t [d_model, d_ff] (see dfk_swiglu_mlp_wdt):
  * cfg == NULL or a kmajor = 5 configuration; the normalisation is folded into the gate/up kernel as with
- * kmajor = 1 (beyond 64 tokens with k2_col_blocks > 1 a small launch of its own, as with kmajor = 2:
- * the normalised input is rounded to dtype there, instead of the product H[m,k] * w[k]), the
- * residual is added where Y is stored. */
+ * kmajor = 1 (beyond 64 tokens with k2_col_blocks > 1 a small launch of its own rounds H[m,k] * w[k],
+ * and the per-token factor is applied to the fp32 sums as there), the residual is added where Y is
+ * stored. */
 dfk_status_t dfk_mlp_block_wdt(const void* H, const void* norm_weight, float eps,
                                const void* W_gate, const void* W_up, const void* W_down_t,
                                void* H_out, int M, int d_model, int d_ff, dfk_dtype_t dtype,

@@ -602,9 +602,12 @@ dfk_status_t run_in(const WsLayout& l, const void* X, const void* Wg, const void
         // costs more there than one small launch that writes the normalised input once.  The
         // 64-token pair folds the normalisation into its gate/up kernel unless the slices of the
         // normalisation weight do not fit its LDS beside the rings (very wide d_model): then it
-        // takes the same small launch.
+        // takes the same small launch.  The transposed layout rounds the product with the weight alone at every token count, as that
+        // kernel does, and scales its sums: rounding the normalised value instead was 0.5 % further from 64 bits with weights
+        // near one (100 tokens of 2048 x 5504, 2.231e-3 / 2.241e-3).  (The factors: in the group sums' place, which it does not use.)
         void* xn = (char*)ws + l.xn_off;
-        hipError_t e = launch_rmsnorm_weighted(X, norm_w, xn, M, d_model, eps, dtype, st);
+        if (wdt_split(c)) a.row_scale = a.Q;
+        hipError_t e = launch_rmsnorm_weighted(X, norm_w, xn, wdt_split(c) ? a.Q : nullptr, M, d_model, eps, dtype, st);
         if (e != hipSuccess) return hip_fail(e);
         a.X = xn;
         a.norm_w = nullptr;

@@ -86,6 +86,7 @@ struct MlpArgs {
     const void* norm_w;  // [d_model] weight of the RMS normalisation applied to X on the way in
     float eps;           // added to the mean square under the root
     const void* resid;   // [M, d_model] added to the result at the final store (may be Y itself)
+    const float* row_scale;  // [M] factor of a token's gate and up sums (pair for up to 256 tokens; NULL: none)
 };
 
 // d_ff is cut into slices at multiples of 8 rows: slice s of S covers the
@@ -182,8 +183,8 @@ hipError_t launch_stream_read(const void* src, size_t bytes, void* sink, hipStre
 hipError_t launch_read_gateup_pattern(const void* Wg, const void* Wu, int d_model, int d_ff, int splits, int waves,
                                       void* sink, hipStream_t st);
 hipError_t launch_rms_normalize(const void* in, void* out, int M, int d_model, hipStream_t st);
-hipError_t launch_rmsnorm_weighted(const void* in, const void* w, void* out, int M, int d_model, float eps, dfk_dtype_t dtype,
-                                   hipStream_t st);
+hipError_t launch_rmsnorm_weighted(const void* in, const void* w, void* out, float* scale_out, int M, int d_model, float eps,
+                                   dfk_dtype_t dtype, hipStream_t st);
 hipError_t launch_fill(void* dst, size_t elems, dfk_dtype_t dtype, float scale, unsigned seed,
                        hipStream_t st);
 

@@ -277,6 +277,11 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     else steps(std::integral_constant<int, NMAX - 1>{});
     DFK_STAMP(DOWN_T ? 4 : 2);
 
+    float scale[TT];                               // of the lane's tokens (requested here, used behind the barriers)
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+        scale[tt] = !DOWN_T && a.row_scale ? a.row_scale[a.m_base + min((tile0 + tt) * 16 + q, a.m_count - 1)] : 1.f;
+
     // The halves of the k range meet: wavefront (tg, 0) finishes row tiles [0, H), (tg, 1) the others.
     constexpr int H = (NTC + 1) / 2;
     lds_barrier();                                 // nothing in flight and nothing read any more: the buffers are free
@@ -311,7 +316,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         if ((rt < H) == (kh == 0) && rt < nt) {
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
-                const f32x4 v = acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64];
+                const f32x4 v = (acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64]) * scale[tt];
                 float o[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) o[i] = __shfl_xor(v[i], 32);

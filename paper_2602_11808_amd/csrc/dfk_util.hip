@@ -79,10 +79,11 @@ __global__ __launch_bounds__(256) void k_rms_normalize(const uint16_t* in, uint1
 
 // out[m,:] = round16(in[m,:] * w * rsqrt(mean(in[m,:]^2) + eps)), 16-bit element type E, fp32 arithmetic;
 // one workgroup per token, 16-byte accesses.  The normalisation ahead of the 256-token kernel pair in
-// dfk_mlp_block (there the in-kernel form costs more than this pass).
+// dfk_mlp_block (there the in-kernel form costs more than this pass).  With scale_out: out[m,:] = round16(in[m,:] * w) and
+// scale_out[m] = the factor, for a kernel that scales its sums by it.
 template <typename E>
 __global__ __launch_bounds__(256) void k_rmsnorm_weighted(const void* __restrict__ in, const void* __restrict__ w,
-                                                          void* __restrict__ out, int d_model, float eps) {
+                                                          void* __restrict__ out, float* __restrict__ scale_out, int d_model, float eps) {
     __shared__ float part[4];
     const u32x4* x = (const u32x4*)((const uint16_t*)in + (size_t)blockIdx.x * d_model);
     const u32x4* wv = (const u32x4*)w;
@@ -98,7 +99,11 @@ __global__ __launch_bounds__(256) void k_rmsnorm_weighted(const void* __restrict
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    const float scale = __builtin_amdgcn_rsqf((part[0] + part[1] + part[2] + part[3]) / (float)d_model + eps);
+    float scale = __builtin_amdgcn_rsqf((part[0] + part[1] + part[2] + part[3]) / (float)d_model + eps);
+    if (scale_out) {
+        if (threadIdx.x == 0) scale_out[blockIdx.x] = scale;
+        scale = 1.f;
+    }
     for (int i = threadIdx.x; i < nv; i += 256) {
         float f[8], g[8];
         E::widen(x[i], f);
@@ -135,12 +140,12 @@ hipError_t launch_transpose(const void* in, void* out, int rows, int cols, dfk_d
     return hipGetLastError();
 }
 
-hipError_t launch_rmsnorm_weighted(const void* in, const void* w, void* out, int M, int d_model, float eps, dfk_dtype_t dtype,
-                                   hipStream_t st) {
+hipError_t launch_rmsnorm_weighted(const void* in, const void* w, void* out, float* scale_out, int M, int d_model, float eps,
+                                   dfk_dtype_t dtype, hipStream_t st) {
     if (dtype == DFK_FP16)
-        hipLaunchKernelGGL(k_rmsnorm_weighted<FP16>, dim3((unsigned)M), dim3(256), 0, st, in, w, out, d_model, eps);
+        hipLaunchKernelGGL(k_rmsnorm_weighted<FP16>, dim3((unsigned)M), dim3(256), 0, st, in, w, out, scale_out, d_model, eps);
     else
-        hipLaunchKernelGGL(k_rmsnorm_weighted<BF16>, dim3((unsigned)M), dim3(256), 0, st, in, w, out, d_model, eps);
+        hipLaunchKernelGGL(k_rmsnorm_weighted<BF16>, dim3((unsigned)M), dim3(256), 0, st, in, w, out, scale_out, d_model, eps);
     return hipGetLastError();
 }
 
