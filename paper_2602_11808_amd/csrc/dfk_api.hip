@@ -317,19 +317,25 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
 
 // W_down given as [d_model, d_ff]: whether the down projection is split over d_ff (kmajor = 5 with column blocks) or its
 // workgroups own rows of W_down^T whole, with nothing to sum across them.  Beyond 64 tokens always: whole rows take 64 tokens per
-// launch and stream the weights again for each (256 tokens, us: 4096 x 14336 345 whole rows, 108 split; 896 x 4864 136, 34; 12288
-// x 12288 665, 265).  Up to 64, whole rows read all of A_2 in every workgroup; that costs more than a split's sum where it is at
-// least twice the workgroup's weights (tokens against rows) and at least 450 KB, or 180 KB where narrow widths leave four
-// wavefronts. Whole rows / split, us: 4096 x 14336 at 20 tokens 66.5 / 65.4, at 32 70.8 / 67.3, at 64 87.5 / 75.1; 2304 x 9216 at
-// 32 38.7 / 37.4; 6144 x 8064 at 48 67.5 / 65.3; 8192 x 7168 at 64 78.5 / 77.3; 896 x 4864 at 20 22.8 / 18.6; 512 x 2048 at 48
-// 14.9 / 13.7.  On the other side: 8192 x 7168 at 48 71.9 / 73.1; 6144 x 8064 at 32 62.5 / 62.7; 12288 x 12288 at 64 166 / 179;
-// 1024 x 2816 at 32 13.8 /
-// 15.1, at 64 18.3 / 18.3; 512 x 2048 at 32 12.1 / 12.5.
+// launch and stream the weights again for each (256 tokens, us: 4096 x 14336 345 whole rows, 108 split; 896 x 4864 136, 34; 12288 x
+// 12288 665, 265).  Up to 64, whole rows read all of A_2 in every workgroup, which costs with tokens x d_ff where tokens are at
+// least twice the workgroup's rows; the split's partial sums cost a launch and with tokens x d_model, the less of it the more tokens
+// the other form has to fetch beside the same weights.  Split over whole rows, time, 1024 to 4096 wide: at 17 to 32 tokens 1536 x 8960
+// 0.90 to 0.93, 2304 x 9216 0.98 to 0.99, 2816 x 9600 0.96 to 0.99, 3072 x 12288 0.95 to 0.98, 4096 x 14336 0.96 to 0.99, 3584 x
+// 18944 0.92 to 0.96; other side: 1024 x 5632 1.02, 2048 x 5504 1.05, 2560 x 6912 1.02 to 1.03, 3584 x 9216 1.02 to 1.04; at 33 to 48
+// 1280 x 5120 0.99, 2048 x 5504 0.98 to 0.99, 3584 x 9216 0.97 to 0.98; other side: 1024 x 2816 1.04 to 1.07, 1536 x 4096 1.04, 1792 x
+// 4864 1.00; at 49 to 64 1536 x 4096 0.98 to 0.99; other side: 1024 x 2816 1.00 to 1.01.  Where rows of W_down^T are a multiple of
+// 16 KB apart a step's rows share memory channels: 4096 x 8192 1.08 to 1.09, 1.04 and 0.98 to 0.99 at those counts, 3072 x 8192 1.03 to
+// 1.05 and 0.97, 2048 x 8192 1.00 to 1.02 and 0.94.  Beyond 4096 the whole rows are uneven shares as a rule: 6144 x 8064 1.01 to 1.03
+// up to 32 tokens, 0.97 to 0.98 at 48, 8192 x 7168 1.02 to 1.04 at 48, 0.98 at 64 (12288 x 12288 166 / 179 us at 64: tokens below twice
+// the rows).  Below 1024, where four wavefronts own the whole rows: 512 x 2048 1.04 to 1.06 up to 32 tokens, 0.93 at 48, 768 x 3072 0.94.
 bool wdt_split_pays(int M, int d_model, int d_ff) {
     if (M > 64) return true;
-    const int tokens = (M + 15) / 16 * 16, rows = d_model / std::max(1, std::min(256, d_model / 16));
-    const size_t a2 = (size_t)tokens * d_ff * 2;
-    return M > 16 && tokens >= 2 * rows && a2 >= (size_t)(d_model < 1024 ? 180 : 450) << 10;
+    const long long tokens = (M + 15) / 16 * 16, rows = d_model / std::max(1, std::min(256, d_model / 16)), a2 = tokens * d_ff;
+    if (M <= 16 || tokens < 2 * rows) return false;
+    if (d_model < 1024) return a2 >= 180 * 512;
+    if (d_model > 4096) return a2 >= 450 * 512;
+    return a2 >= (d_ff % 8192 ? 155000 : 200000) + 35 * (80 - tokens) * tokens * d_model / 1000;
 }
 
 // The candidates of that layout: the 64-token pair's gate/up kernel, then the down kernel whose workgroups own slices of d_model;

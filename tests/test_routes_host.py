@@ -137,7 +137,10 @@ def test_the_remembered_choice_is_what_a_new_thread_finds():
 
 @pytest.mark.parametrize("M,d,ff,split", [(16, 4096, 14336, False), (17, 4096, 14336, True), (64, 4096, 14336, True), (65, 12288, 12288, True),
                                           (64, 12288, 12288, False), (48, 8192, 7168, False), (64, 8192, 7168, True), (64, 1024, 2816, False),
-                                          (32, 896, 4864, True), (32, 512, 2048, False), (48, 512, 2048, True), (256, 512, 1024, True)])
+                                          (32, 896, 4864, True), (32, 512, 2048, False), (48, 512, 2048, True), (256, 512, 1024, True),
+                                          (20, 3072, 7680, False), (32, 3584, 9216, False), (33, 3584, 9216, True), (17, 2304, 9216, True), (32, 4096, 8192, False),
+                                          (48, 4096, 8192, False), (64, 4096, 8192, True), (48, 3072, 8192, True), (48, 1536, 4096, False), (64, 1536, 4096, True),
+                                          (48, 6144, 8064, True), (32, 6144, 8064, False)])
 def test_which_down_kernel_the_transposed_layout_gets(M, d, ff, split):
     for dt in (dfk.DFK_BF16, dfk.DFK_FP16):
         pick, tuned = dfk.dfk_get_choice_wdt(M, d, ff, dt)
