@@ -137,13 +137,19 @@ __device__ __forceinline__ void down_tile_of(int b, int S, int C, bool by_xcd, i
     }
 }
 
-// Step at which a workgroup of the down kernels starts its split.  In step with the split's other column blocks, so that what is
-// live of their A_2 rows stays small and XCDs spread W_down over the memory channels; only where a whole split sits on one XCD
-// (down_tile_of, a multiple of 8 splits), in a start of its own, against the lock-step on the L2 channels.  Down kernel with its
-// sum, us, own start / in step: 16384 x 16384 at 128 tokens 142 / 117, 9856 x 28032 at 111 148 / 110, 5760 x 29568 at 227 146 /
-// 126, 2304 x 9216 at 200 28.1 / 27.4, 4096 x 14336 at 128 (not placed by XCD) 37.8 / 36.3; at 256 (placed) 51.9 / 53.0.
+// Step at which a workgroup of the down kernels starts its split: in step with the split's other column blocks, or (own) in a start of
+// its own, against the lock-step on the L2 channels.  In step, what is live of the A_2 rows stays small and XCDs spread W_down over the
+// memory channels, which is what counts where A_2 is larger than an L2 and a split's workgroups are on several XCDs, and with wide
+// rows of W_down.  Own where a whole split sits on one XCD (down_tile_of, a multiple of 8 splits), or where all of A_2 fits one L2 and
+// rows of W_down are below 8 KB or W_down is given as [d_model, d_ff].  Down kernel with its sum, us, own / in step: 16384 x 16384 at 128
+// tokens 142 / 117, 9856 x 28032 at 111 148 / 110, 5760 x 29568 at 227 146 / 126; 4096 x 14336 at 256 (on one XCD) 51.9 / 53.0.
+// Whole call, own over in step, A_2 below 4 MB, at 80, 128 and 200 tokens: 1792 x 9344 0.988, 0.993, 0.986, 2560 x 6912 0.997, 0.986,
+// 1.006, 3072 x 7936 0.987, 0.987, 0.995, 2816 x 9600 0.994, 0.994, 1.011; 4096 x 8192 1.003, 1.002, 1.010, 12288 x 4096 1.012, 1.010,
+// 1.003; W_down as [d_model, d_ff]: 2304 x 9216 0.982, 0.986, 0.996, 12288 x 4096 0.977, 0.985, 0.985, 16384 x 4096 0.944, 0.957, 0.988.
+template <bool DOWN_T>
 __device__ __forceinline__ int big_down_start(const MlpArgs& a, bool by_xcd, int cb, int nsteps) {
-    return by_xcd && (a.k2_splits & 7) == 0 ? (int)(cb * 5u % (unsigned)nsteps) : 0;
+    const bool own = by_xcd ? (a.k2_splits & 7) == 0 : DOWN_T || a.d_model < 4096;
+    return own ? (int)(cb * 5u % (unsigned)nsteps) : 0;
 }
 
 // ---------------------------------------------------------------- gate/up kernel
@@ -178,7 +184,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     const size_t row_bytes = (size_t)(DOWN_T ? a.d_ff : a.d_model) * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
 
-    const int rot = DOWN_T ? big_down_start(a, by_xcd, cb, nsteps) : big_k_start(a, nsteps);
+    const int rot = DOWN_T ? big_down_start<true>(a, by_xcd, cb, nsteps) : big_k_start(a, nsteps);
     const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
     const int lo = big_operand_off(q, g, kh);
 
@@ -358,7 +364,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
     const size_t row_bytes = (size_t)a.d_model * 2;
     const int tile0 = tg * TT;
 
-    const int rot = big_down_start(a, by_xcd, cb, nsteps);
+    const int rot = big_down_start<false>(a, by_xcd, cb, nsteps);
     const int prow = lane >> 3, piece = lane & 7;
     const int lo = big_operand_off(q, g, kh);
 
