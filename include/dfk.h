@@ -153,10 +153,9 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  fields it uses.  Such launches may overlap on several streams (a workspace each): a
  *                  down workgroup whose wait takes long makes room for others and is made up for later
  *                  in the launch, so every wait ends as long as fewer such launches run at a time than
- *                  an XCD has CUs.  The bound is a last
- *                  resort, about two million polls (seconds); a workgroup whose wait runs out turns its
- *                  share of Y into NaN (in place, dfk_mlp_block's input is lost with it), and the
- *                  workspace has to be initialised again.  (Tests force these paths from the host with
+ *                  an XCD has CUs.  The bound is a last resort, about two million polls (seconds); a
+ *                  workgroup whose wait runs out turns its share of Y into NaN (in place, dfk_mlp_block's
+ *                  input is lost with it), and the workspace has to be initialised again.  (Tests force these paths from the host with
  *                  the environment variables DFK_DEBUG_SPIN_LIMIT = number of polls and
  *                  DFK_DEBUG_DOWN_FIRST; leave them unset otherwise.);
  *                  0 = the first single-launch kernel (bf16 only).

@@ -113,12 +113,10 @@ bool roles_launch(const dfk_config_t& c) { return c.variant == DFK_VARIANT_FUSED
 // the last workgroup of a column block reads all its splits' blocks alone.  16 / 12 splits, us: 512 x 1536 at 8 tokens 11.6 /
 // 11.1, 768 x 4224 at 8 15.9 / 15.4, 896 x 4864 at 33 23.4 / 22.8, 1024 x 5632 at 16 18.5 / 17.8, 2048 x 6144 at 64 38.5 / 36.1.
 // Where it gives more, the stream is longer by whole blocks: 512 x 4096 at 8 (two blocks of four wavefronts, three) 13.3 / 13.9,
-// 896 x 7168 at 33 25.1 / 26.2, 1024 x 8192 at 3 and 64 18.2 /
-// 19.2, 31.3 / 32.2, 896 x 4864 at 8 16.8 / 17.1.  From a width of 1536 on 16 splits are 192 workgroups and more, and up to four
-// blocks 12 are the better in any case: 1536 x 12288 at 8 and 64 29.6 / 29.4, 46.3 / 44.5, 2048 x 11264 34.4 / 33.6, 50.9 / 49.6;
-// beyond, 1536 x 18176 at 8
-// 40.5 / 41.3, 2048 x 24320 60.2 / 61.5, 2048 x 16384 42.9 / 42.6, at 33 54.0 / 54.8.  At two tokens equal: 896 x 4864 15.4 /
-// 15.8.
+// 896 x 7168 at 33 25.1 / 26.2, 1024 x 8192 at 3 and 64 18.2 / 19.2, 31.3 / 32.2, 896 x 4864 at 8 16.8 / 17.1.  From a width of
+// 1536 on 16 splits are 192 workgroups and more, and up to four blocks 12 are the better in any case: 1536 x 12288 at 8 and 64
+// 29.6 / 29.4, 46.3 / 44.5, 2048 x 11264 34.4 / 33.6, 50.9 / 49.6; beyond, 1536 x 18176 at 8 40.5 / 41.3, 2048 x 24320 60.2 /
+// 61.5, 2048 x 16384 42.9 / 42.6, at 33 54.0 / 54.8.  At two tokens equal: 896 x 4864 15.4 / 15.8.
 constexpr int kFewSplits = 16;
 int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
     const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
@@ -135,13 +133,12 @@ int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
 // splits, whose sum has to be paid for by the reading.  Time with two blocks over time with one, atomic reduction (single
 // launch), 2 to 16 tokens: 298 rows (5120 x 3584) 1.07 to 1.10, 614 (6144 x 6144) 1.00 to 1.02, 796 (7168 x 7168) 0.99 to 1.00,
 // 930 (5888 x 10240) 1.00 to 1.02, 938 (5120 x 11264) 0.96 to 0.98, 1109 (7168 x 9984) 0.98 to 0.99, 2201 (11008 x 11008) 0.96;
-// 32 tokens: 938
-// 1.01, 1109 1.01, 1194 (10240 x 7168) 1.00, 1424 (8192 x 11392) 1.00, 2201 0.96.  Counter reduction (pair of launches, the
-// block), 1 to 16 tokens: 938 1.00 to 1.03, 1175 (5888 x 12928) 1.00 to 1.02, 1393 (7168 x 12544) 0.98 to 1.00, 2201 0.98 to
-// 0.99, 2304 (5120 x 27648, 4 tokens, whole call) 138.6 -> 137.1 us; 32 tokens: 1424 1.02, 1792 (8192 x 14336) 1.02, 2389 (10240
-// x 14336) 1.00, 2848 (16384 x 11392) 1.00, 3584 (8192 x 28672, whole call) 235.3 -> 238.5 us, 4096 (16384 x 16384) 0.99, and
-// where splits of one block each make few workgroups 1536 (11008 x 7680, 172 of them) 0.99, 2457 (12288 x 12288, 192) 0.99.
-// Below a d_model of 5120 it gained at most 2 % and lost as much (4608 x 10112, 722 rows: 0.99 to 1.02).
+// 32 tokens: 938 1.01, 1109 1.01, 1194 (10240 x 7168) 1.00, 1424 (8192 x 11392) 1.00, 2201 0.96.  Counter reduction (pair of
+// launches, the block), 1 to 16 tokens: 938 1.00 to 1.03, 1175 (5888 x 12928) 1.00 to 1.02, 1393 (7168 x 12544) 0.98 to 1.00,
+// 2201 0.98 to 0.99, 2304 (5120 x 27648, 4 tokens, whole call) 138.6 -> 137.1 us; 32 tokens: 1424 1.02, 1792 (8192 x 14336) 1.02,
+// 2389 (10240 x 14336) 1.00, 2848 (16384 x 11392) 1.00, 3584 (8192 x 28672, whole call) 235.3 -> 238.5 us, 4096 (16384 x 16384)
+// 0.99, and where splits of one block each make few workgroups 1536 (11008 x 7680, 172 of them) 0.99, 2457 (12288 x 12288, 192)
+// 0.99. Below a d_model of 5120 it gained at most 2 % and lost as much (4608 x 10112, 722 rows: 0.99 to 1.02).
 bool two_blocks(int M, int d_model, int d_ff, int reduce) {
     if (d_model < 5120) return false;
     const int nblk = (d_model + 127) / 128, rows = d_ff / few_splits(M, d_model, d_ff, nblk / 2, reduce);
@@ -159,10 +156,9 @@ bool two_blocks(int M, int d_model, int d_ff, int reduce) {
 // 6656 at 256 60.6 with 12, 58.5 with 8; 1536 x 8960 at 256 53.4 with 12, 49.9 with 14, 52.1 with 20; 3584 x 18944 at 256 170
 // with 9, 147 with 8; 6912 x 20352 at 212 266 with 4, 273 with 3; 4480 x 23040 at 68 139.9 with 7, 142.5 with 6; a long d_ff: 512
 // x 28672 at 256 83.9 with 12, 59.4 with 32, 60.0 with 64; 256 x 8192 at 1 18.8 with 8, 17.4 with 12; 1024 x 14336 at 256 57.4
-// with 12,
-// 50.3 with 16, 52.3 with 32; no whole steps: 1920 x 10496 at 96 46.5 with 12 or 17, 45.5 with 16; few column blocks: 1152 x 5504
-// at 200 38.8 with 12, 37.6 with 16, 38.3 with 28, and at 128 30.7 with 12, 30.8 with 16; 2048 x 5504 at 200 46.9 with 12, 47.7
-// with 16.
+// with 12, 50.3 with 16, 52.3 with 32; no whole steps: 1920 x 10496 at 96 46.5 with 12 or 17, 45.5 with 16; few column blocks:
+// 1152 x 5504 at 200 38.8 with 12, 37.6 with 16, 38.3 with 28, and at 128 30.7 with 12, 30.8 with 16; 2048 x 5504 at 200 46.9
+// with 12, 47.7 with 16.
 int big_splits(int M, int d_ff, int k2c) {
     const int most = 256 / k2c, narrow = M > 128 && k2c < 10 ? std::min(16, d_ff / 320) : 0;
     const int want = std::min(most, std::max({12, d_ff / (k2c < 8 ? 512 : 640), narrow}));
@@ -385,11 +381,10 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     if (wdt_split_pays(M, d_model, d_ff)) split_form();
     // Wavefronts, ring depth: three slots where the down kernel has workgroups (a 16-row tile each) for no more than three
     // quarters of the CUs, so that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 32 tokens: 1536 x
-    // 4096 14.6 / 13.9, 15.2 / 14.8, 18.8 /
-    // 18.0; 2304 x 9216 30.3 / 29.5, 31.7 / 31.6, 38.9 / 38.4; 3072 x 8192 32.1 / 31.0, 32.5 / 32.0, 38.5 / 37.9; the most it
-    // loses there is 1.3 % (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216 37.7 / 37.9, 39.0 / 39.3, 46.5 /
-    // 46.9, 3584 x 18944 68.4 /
-    // 69.9, 72.0 / 74.4, 89.7 / 90.6; 4096 x 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3.
+    // 4096 14.6 / 13.9, 15.2 / 14.8, 18.8 / 18.0; 2304 x 9216 30.3 / 29.5, 31.7 / 31.6, 38.9 / 38.4; 3072 x 8192 32.1 / 31.0,
+    // 32.5 / 32.0, 38.5 / 37.9; the most it loses there is 1.3 % (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216
+    // 37.7 / 37.9, 39.0 / 39.3, 46.5 / 46.9, 3584 x 18944 68.4 / 69.9, 72.0 / 74.4, 89.7 / 90.6; 4096 x 14336 at 8 59.7 / 60.7,
+    // 8192 x 7168 at 24 64.3 / 65.3.
     const std::vector<int> rings = 4 * t16 <= 3 * 256 ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
     for (int wd : rings)
         for (int splits : {256, 512, more_splits})
@@ -407,13 +402,12 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
 // 16384 on (a slice is at most 64 rows), and wavefronts that each own an eighth of the chunks and column blocks, which only
 // widths that are multiples of 1024 divide evenly.  us, A_2 in LDS / both kernels' workgroups: 2048 x 5504 20.2 / 21.1, 3072 x
 // 12288 43.1 / 43.7, 4096 x 8192 40.4 / 41.1, 4096 x 14336 59.4 / 60.1, 4096 x 16384 66.6 / 67.8.  On the other side: 4096 x
-// 20480 88.5 / 83.2, 4096 x 4096 30.1 /
-// 23.7, 1024 x 2816 13.2 / 11.4, 1536 x 4096 20.2 / 15.1, 2304 x 9216 31.1 / 27.9, 3584 x 9216 40.8 / 37.1, 7168 x 20480 146 /
-// 135, 8192 x 14336 113 / 111, 8192 x 28672 222 / 213, 16384 x 16384 277 / 246; 3072 x 8192 30.8 / 30.7.  Beyond a d_ff of 32768
-// the launch of both kernels' workgroups is not listed (more than 512 slices of 64 rows), and what follows is the pair of
-// launches with the counter reduction.  A_2 in LDS / pair: 512 x 36864 37.1 / 33.6, 1024 x 33280 45.3 / 44.5, 4096 x 53248 215 /
-// 209, 5120 x 40960 202 / 195, 8192 x 40960 321 / 307, 16384 x 53248 923 / 789; 1024 x 53248 63.4 / 63.3, 3072 x 40960 124 / 124,
-// 2048 x 40960 86.5 / 88.0.
+// 20480 88.5 / 83.2, 4096 x 4096 30.1 / 23.7, 1024 x 2816 13.2 / 11.4, 1536 x 4096 20.2 / 15.1, 2304 x 9216 31.1 / 27.9, 3584 x
+// 9216 40.8 / 37.1, 7168 x 20480 146 / 135, 8192 x 14336 113 / 111, 8192 x 28672 222 / 213, 16384 x 16384 277 / 246; 3072 x 8192
+// 30.8 / 30.7.  Beyond a d_ff of 32768 the launch of both kernels' workgroups is not listed (more than 512 slices of 64 rows),
+// and what follows is the pair of launches with the counter reduction.  A_2 in LDS / pair: 512 x 36864 37.1 / 33.6, 1024 x 33280
+// 45.3 / 44.5, 4096 x 53248 215 / 209, 5120 x 40960 202 / 195, 8192 x 40960 321 / 307, 16384 x 53248 923 / 789; 1024 x 53248 63.4
+// / 63.3, 3072 x 40960 124 / 124, 2048 x 40960 86.5 / 88.0.
 bool local_pays(int d_model, int d_ff) {
     return d_model % 1024 == 0 && d_model >= 2048 && d_model <= 4096 && d_ff >= 2 * d_model && d_ff <= 16384;
 }
@@ -464,22 +458,20 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
 
 // The pair for up to 64 tokens as the single launch of both kernels' workgroups: same splits, same reduction, so the same bits
 // with the counter reduction, and no boundary between two launches.  What a block runs where it pays, and a width off 128 without
-// a tuned entry (whose candidates are the pair and not this form of it; dfk_tune times it beside them).  Up to 16 tokens from 48
-// MB of weights on: below, the down workgroups' wait costs what the boundary does.  us, pair / single launch:
-//   blocks, layers replayed from a graph: 2304 x 9216 at 1, 8 and 33 tokens 32.0 / 30.2, 32.6 / 31.1, 43.6 / 41.5; 4096 x 14336
-//   at 1 and 64
-//   62.3 / 61.2, 83.3 / 81.7; 5120 x 40960 at 64 271 / 257; 1792 x 4864 (52 MB) at 8 and 33 20.4 / 20.2, 29.9 / 28.6; 1536 x 8960
-//   at 17 30.2 /
-//   29.4.  On the other side: 1024 x 4096 (25 MB) at 17 and 64 18.5 / 19.8, 27.3 / 28.2; 1536 x 4096 (38 MB) at 32 22.3 / 23.4;
-//   1280 x 5120 (39 MB) at 17 23.0 / 23.6.  A width that is a multiple of 1024 gives the eight wavefronts equal runs of k, so the
-//   gate/up kernel ends evenly and there is less to gain: from 100 MB on.  2048 x 5504 (68 MB) at 8 and 17 22.7 / 23.2, 25.9 /
-//   26.3; 1024 x 8192 (50 MB) at 8 20.1 / 20.8; 2048 x 8192 (101 MB) at 17 and 40 31.1 / 31.2, 37.5 / 36.9. off 128, whole call:
-//   2888 x 7688 at 1, 12 and 64 tokens 37.5 / 35.1, 39.1 / 37.3, 54.5 / 53.5; 1800 x 5000 at 16 and 33 25.0 / 23.9,
-//   30.9 / 29.7.  Beyond 16 tokens at every size: 2008 x 2400 (29 MB) at 17 and 33 22.1 / 20.6, 26.6 / 24.5; 904 x 1024 (6 MB) at
-//   33 18.2 /
-//   17.5; 1416 x 3776 at 17 22.2 / 22.6, at 64 31.1 / 31.0.  Not where d_ff is no larger than d_model: 8200 x 1000 at 1 and 17
-//   22.8 / 24.7,
-//   30.9 / 31.9 (2888 x 2888 at 12 24.5 / 23.4).
+// a tuned entry (whose candidates are the pair and not this form of it; dfk_tune times it beside them).  us, pair / single launch:
+//
+// Blocks (layers replayed from a graph) from 48 MB of weights on; below, the down workgroups' wait costs what the boundary does.
+// 2304 x 9216 at 1, 8 and 33 tokens 32.0 / 30.2, 32.6 / 31.1, 43.6 / 41.5; 4096 x 14336 at 1 and 64 62.3 / 61.2, 83.3 / 81.7; 5120
+// x 40960 at 64 271 / 257; 1792 x 4864 (52 MB) at 8 and 33 20.4 / 20.2, 29.9 / 28.6; 1536 x 8960 at 17 30.2 / 29.4.  On the other
+// side: 1024 x 4096 (25 MB) at 17 and 64 18.5 / 19.8, 27.3 / 28.2; 1536 x 4096 (38 MB) at 32 22.3 / 23.4; 1280 x 5120 (39 MB) at 17
+// 23.0 / 23.6.  A width that is a multiple of 1024 gives the eight wavefronts equal runs of k, so the gate/up kernel ends evenly and
+// there is less to gain: from 100 MB on.  2048 x 5504 (68 MB) at 8 and 17 22.7 / 23.2, 25.9 / 26.3; 1024 x 8192 (50 MB) at 8 20.1 /
+// 20.8; 2048 x 8192 (101 MB) at 17 and 40 31.1 / 31.2, 37.5 / 36.9.
+//
+// Off 128 (whole call) from 48 MB on, beyond 16 tokens at every size.  2888 x 7688 at 1, 12 and 64 tokens 37.5 / 35.1, 39.1 / 37.3,
+// 54.5 / 53.5; 1800 x 5000 at 16 and 33 25.0 / 23.9, 30.9 / 29.7; 2008 x 2400 (29 MB) at 17 and 33 22.1 / 20.6, 26.6 / 24.5; 904 x
+// 1024 (6 MB) at 33 18.2 / 17.5; 1416 x 3776 at 17 22.2 / 22.6, at 64 31.1 / 31.0.  Not where d_ff is no larger than d_model: 8200 x
+// 1000 at 1 and 17 22.8 / 24.7, 30.9 / 31.9 (2888 x 2888 at 12 24.5 / 23.4).
 bool single_launch_pays(int M, int d_model, int d_ff) {
     const size_t bytes = (size_t)6 * d_model * d_ff;
     if (M > 64) return false;

@@ -16,9 +16,7 @@
 // Data movement is the asynchronous global->LDS tile load of the other MFMA kernels,
 // organised as a workgroup pipeline:
 //   * a step is 64 k (or two such pieces in the gate/up kernel): tiles of 16 rows x 128 bytes (one cache line per row), 2 KB.  In
-//   LDS the eight
-//     16-byte pieces of row i sit XOR-swizzled by i / 2, so that the operand reads of 16 rows
-//     cover all banks once.
+//     LDS the eight 16-byte pieces of row i sit XOR-swizzled by i / 2, so that the operand reads of 16 rows cover all banks once.
 //   * wavefronts 0..3 request the weights, 4..7 the activations.  Loads complete in issue order
 //     per wavefront, so a wavefront that requested both would have to wait for its newest
 //     activations (one or two steps ahead, out of L2) and with them for every older weight load (several

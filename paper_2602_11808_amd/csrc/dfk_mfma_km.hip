@@ -771,12 +771,13 @@ __global__ __launch_bounds__(NW * 64) void k_down_km(MlpArgs a, KmGeom geo) {
     down_km_body<NW, TT, E, false, TAIL>(a, geo, blockIdx.x, lds);
 }
 
-// ---------------------------------------------------------------- both kernels' workgroups in one launch Grid = the gate/up
-// kernel's workgroups followed by the down kernel's.  Workgroups of a grid are dispatched in index order on each XCD, so a down
-// workgroup as a rule waits for workgroups that run; where launches of other streams hold their CUs it may park (dfk_roles.h):
-// the wait ends in any order of dispatch.  What the single launch buys over two: no launch boundary (drain, dispatch and ramp
-// with HBM idle), and the down workgroups request their first W_down tiles while the last gate/up workgroups are still streaming.
-// A_2 crosses between workgroups through device memory (2 bytes per token and d_ff row), as between the two kernels.
+// ---------------------------------------------------------------- both kernels' workgroups in one launch
+// Grid = the gate/up kernel's workgroups followed by the down kernel's.  Workgroups of a grid are dispatched in index order on
+// each XCD, so a down workgroup as a rule waits for workgroups that run; where launches of other streams hold their CUs it may
+// park (dfk_roles.h): the wait ends in any order of dispatch.  What the single launch buys over two: no launch boundary (drain,
+// dispatch and ramp with HBM idle), and the down workgroups request their first W_down tiles while the last gate/up workgroups
+// are still streaming. A_2 crosses between workgroups through device memory (2 bytes per token and d_ff row), as between the two
+// kernels.
 // NORM: with the normalisation in front and the residual added (dfk_mlp_block).  The output may be the input there: a column
 // block is stored once every d_ff split has arrived, so after every gate/up workgroup has read the input and published. The notes
 // of parked workgroups are in the group sums' place in the workspace, which a reduction over column blocks does not use.
@@ -866,9 +867,7 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
 // Wavefronts of the pair's down kernel: as configured, but eight where the gate/up kernel runs four (narrow widths: few 128-k
 // chunks of d_model, which say nothing about the down kernel's d_ff rows) and there is more than one token tile.  Four there had
 // twice the tiles each and the same stages to add at the end: 896 x 4864 at 40 tokens 26.8 -> 24.4 us per call, 640 x 2560 at 64
-// 27.5 -> 24.9, 512 x 1536 at 24
-// 15.2 -> 14.6; up to 16 tokens equal or worse (7.5 ->
-// 8.1 at one token of 1024 x 2816).
+// 27.5 -> 24.9, 512 x 1536 at 24 15.2 -> 14.6; up to 16 tokens equal or worse (7.5 -> 8.1 at one token of 1024 x 2816).
 constexpr int km_down_waves(int waves, int tt) { return waves == 4 && tt >= 2 ? 8 : waves; }
 inline dfk_config_t km_down_cfg(const dfk_config_t& c, int tt) {
     dfk_config_t d = c;
