@@ -379,13 +379,13 @@ std::vector<dfk_config_t> candidates_wdt(int M, int d_model, int d_ff, dfk_dtype
     // only for a caller who asks.
     if (dtype == DFK_FP16 && (d_model < 512 || d_ff < 512)) valu();
     if (wdt_split_pays(M, d_model, d_ff)) split_form();
-    // Wavefronts, ring depth: three slots where the down kernel has workgroups (a 16-row tile each) for no more than three
-    // quarters of the CUs, so that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 32 tokens: 1536 x
-    // 4096 14.6 / 13.9, 15.2 / 14.8, 18.8 / 18.0; 2304 x 9216 30.3 / 29.5, 31.7 / 31.6, 38.9 / 38.4; 3072 x 8192 32.1 / 31.0,
-    // 32.5 / 32.0, 38.5 / 37.9; the most it loses there is 1.3 % (2048 x 8192 at 9 to 16 tokens).  On the other side: 3584 x 9216
-    // 37.7 / 37.9, 39.0 / 39.3, 46.5 / 46.9, 3584 x 18944 68.4 / 69.9, 72.0 / 74.4, 89.7 / 90.6; 4096 x 14336 at 8 59.7 / 60.7,
-    // 8192 x 7168 at 24 64.3 / 65.3.
-    const std::vector<int> rings = 4 * t16 <= 3 * 256 ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
+    // Wavefronts, ring depth: three slots where the down kernel has workgroups (a 16-row tile each) for less than seven eighths of
+    // the CUs, so that each needs more in flight, else two.  Two / three slots, us, at 1, 12 and 29 to 32 tokens: 1536 x 4096 14.6 /
+    // 13.9, 15.2 / 14.8, 18.8 / 18.0; 2304 x 9216 30.3 / 29.5, 31.7 / 31.6, 38.9 / 38.4; 3200 x 4352 25.0 / 24.2, 24.7 / 24.4, 29.7 /
+    // 28.7; 3456 x 8320 38.1 / 37.3, 37.9 / 37.6, 44.9 / 44.5; the most it loses there is 1.3 % (2048 x 8192 at 9 to 16 tokens).  On
+    // the other side: 3584 x 4352 25.6 / 25.5, 25.4 / 25.8, 30.1 / 30.3; 3584 x 18944 68.4 / 69.9, 72.0 / 74.4, 89.7 / 90.6; 4096 x
+    // 14336 at 8 59.7 / 60.7, 8192 x 7168 at 24 64.3 / 65.3.
+    const std::vector<int> rings = 8 * t16 < 7 * 256 ? std::vector<int>{83, 82, 84, 46} : std::vector<int>{82, 83, 84, 46};
     for (int wd : rings)
         for (int splits : {256, 512, more_splits})
             for (int k2s : {256, 512, 128}) {
