@@ -466,7 +466,11 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
 // side: 1024 x 4096 (25 MB) at 17 and 64 18.5 / 19.8, 27.3 / 28.2; 1536 x 4096 (38 MB) at 32 22.3 / 23.4; 1280 x 5120 (39 MB) at 17
 // 23.0 / 23.6.  A width that is a multiple of 1024 gives the eight wavefronts equal runs of k, so the gate/up kernel ends evenly and
 // there is less to gain: from 100 MB on.  2048 x 5504 (68 MB) at 8 and 17 22.7 / 23.2, 25.9 / 26.3; 1024 x 8192 (50 MB) at 8 20.1 /
-// 20.8; 2048 x 8192 (101 MB) at 17 and 40 31.1 / 31.2, 37.5 / 36.9.
+// 20.8; 2048 x 8192 (101 MB) at 17 and 40 31.1 / 31.2, 37.5 / 36.9.  Not where the 256 slices of d_ff have two row tiles each and
+// hardly one has fewer: no gate/up workgroup ends ahead of the others then, and their streams are short against the wait.  2816 x
+// 3456 at 2, 17 and 64 20.9 / 21.5, 25.5 / 26.6, 38.8 / 40.0; 3456 x 3712 23.8 / 24.0, 28.3 / 29.6, 42.6 / 43.6; 3584 x 3968 25.3 /
+// 25.7, 29.4 / 30.7, 43.2 / 44.5.  On the other side: 4352 x 4352 32.8 / 32.5, 37.8 / 36.6, 52.9 / 52.3; 3584 x 5376 30.9 / 29.9,
+// 35.0 / 34.5, 48.8 / 48.5; 2304 x 3328 (46 MB) 20.4 / 19.9, 24.9 / 25.4, 38.1 / 37.9.
 //
 // Off 128 (whole call) from 48 MB on, beyond 16 tokens at every size.  2888 x 7688 at 1, 12 and 64 tokens 37.5 / 35.1, 39.1 / 37.3,
 // 54.5 / 53.5; 1800 x 5000 at 16 and 33 25.0 / 23.9, 30.9 / 29.7; 2008 x 2400 (29 MB) at 17 and 33 22.1 / 20.6, 26.6 / 24.5; 904 x
@@ -476,6 +480,8 @@ bool single_launch_pays(int M, int d_model, int d_ff) {
     const size_t bytes = (size_t)6 * d_model * d_ff;
     if (M > 64) return false;
     if (d_model % 128) return d_ff > d_model && (M > 16 || bytes >= 48000000u);
+    const int tiles = d_ff / 8;
+    if (tiles > 2 * 256 * 13 / 16 && tiles <= 2 * 256) return false;
     return bytes >= (d_model % 1024 ? 48000000u : 100000000u);
 }
 // That form of a configuration, if it is of the pair and the form fits.

@@ -192,10 +192,12 @@ def _is_launch_form_of(c, pair):
     return c.as_dict() == dict(pair.as_dict(), variant=FUSED, kmajor=4, depth=4)
 
 
-# 48 MB of weights, 100 MB where the width is a multiple of 1024, whatever the token count up to 64; eight wavefronts
+# 48 MB of weights, 100 MB where the width is a multiple of 1024, whatever the token count up to 64; eight wavefronts; not where nearly
+# every slice of d_ff has two row tiles
 @pytest.mark.parametrize("dt", [dfk.DFK_BF16, dfk.DFK_FP16])
 @pytest.mark.parametrize("d,ff,single", [(1536, 5248, True), (1536, 5120, False), (2048, 8192, True), (2048, 8064, False), (1152, 8192, True), (1152, 4096, False),
-                                         (896, 28672, False), (2304, 9216, True), (4096, 14336, True), (5120, 40960, True)])
+                                         (896, 28672, False), (2304, 9216, True), (4096, 14336, True), (5120, 40960, True),
+                                         (2816, 3328, True), (2816, 3336, False), (3584, 3968, False), (4224, 4096, False), (4224, 4104, True)])
 def test_the_form_in_which_a_block_runs_the_pair(d, ff, single, dt):
     for M in (1, 16, 17, 64):
         c, tuned = dfk.dfk_get_choice_block(M, d, ff, dt)
