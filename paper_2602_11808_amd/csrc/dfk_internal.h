@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "dfk.h"
+#include "dfk_share.h"
 
 namespace dfk {
 
@@ -92,6 +93,12 @@ struct MlpArgs {
 // d_ff is cut into slices at multiples of 8 rows: slice s of S covers the
 // 8-row groups [s*NG/S, (s+1)*NG/S), NG = d_ff/8.
 __host__ __device__ inline void slice_rows(int d_ff, int S, int s, int& j0, int& j1) {
+    share_of((unsigned)d_ff / 8u, (unsigned)S, (unsigned)s, j0, j1);
+    j0 *= 8;
+    j1 *= 8;
+}
+// The same for any number of slices: kernels that take as many as there are groups.
+__host__ __device__ inline void slice_rows_any(int d_ff, int S, int s, int& j0, int& j1) {
     const long long ng = d_ff / 8;
     j0 = (int)(ng * s / S) * 8;
     j1 = (int)(ng * (s + 1) / S) * 8;

@@ -212,7 +212,7 @@ __global__ __launch_bounds__(NW * 64) void k_mfma(MlpArgs a, Geom geo) {
         blk_cnt = blk_cnt / a.k2_col_blocks;
         blk_lo = cb * blk_cnt;
     } else {
-        slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
+        slice_rows_any(a.d_ff, a.splits, blockIdx.x, j0, j1);
     }
     const int rows = j1 - j0;
     const int nt = rows / 8;

@@ -170,8 +170,9 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     if (DOWN_T) {
         down_tile_of((int)blockIdx.x, a.k2_splits, a.k2_col_blocks, by_xcd, js, cb);
         const int steps = a.d_ff / kBigStepK;
-        k0 = (int)((long long)steps * js / a.k2_splits);
-        nsteps = (int)((long long)steps * (js + 1) / a.k2_splits) - k0;
+        int k1;
+        share_of((unsigned)steps, (unsigned)a.k2_splits, (unsigned)js, k0, k1);
+        nsteps = k1 - k0;
         k0 *= kBigStepK;
         j0 = cb * 128; j1 = j0 + 128;
     } else {

@@ -69,9 +69,6 @@ struct DeviceMem {
     static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(8); }
 };
 
-// the slice (of S) that holds 8-row group gidx of ng: the inverse of slice_rows
-__device__ __forceinline__ int slice_of_group(int ng, int S, int gidx) { return (int)((((long long)gidx + 1) * S - 1) / ng); }
-
 // Bytes between the wavefronts' slices of the normalisation weight in LDS: the longest run of
 // chunks a wavefront can own, 1 KB-aligned (one load instruction writes 1 KB).
 __host__ __device__ inline int km_norm_stride(int d_model, int waves) {
@@ -190,9 +187,8 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     const int q = lane & 15, g = lane >> 4;
     int j0, j1;
     if (DOWN_T) {            // slices of d_model, in whole 16-row tiles
-        const long long t16 = a.d_model / 16;
-        j0 = (int)(t16 * wg / a.k2_splits) * 16;
-        j1 = (int)(t16 * (wg + 1) / a.k2_splits) * 16;
+        share_of((unsigned)a.d_model / 16u, (unsigned)a.k2_splits, (unsigned)wg, j0, j1);
+        j0 *= 16; j1 *= 16;
     } else {
         slice_rows(a.d_ff, a.splits, wg, j0, j1);
     }
@@ -202,7 +198,7 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     const int kdim = DOWN_T ? a.d_ff : a.d_model;
     static_assert(!TAIL || (!NORM && !DOWN_T), "a partial last chunk is built for the plain gate/up kernel");
     const int nchunks = TAIL ? (kdim + kKC - 1) / kKC : kdim / kKC;
-    const int c0 = wave * nchunks / NW, c1 = (wave + 1) * nchunks / NW;
+    const int c0 = (int)((unsigned)(wave * nchunks) / NW), c1 = (int)((unsigned)((wave + 1) * nchunks) / NW);
     const size_t kbase = (size_t)c0 * (kKC * 2);          // bytes into a row
 
     KmStream1<NW, TT, TAIL, !DOWN_T> ts;
@@ -391,7 +387,7 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
         __syncthreads();
         if (tid == 0) {                          // one count on every split of the down projection these rows belong to
             const int ng = a.d_ff / 8;
-            const int lo = slice_of_group(ng, a.k2_splits, j0 / 8), hi = slice_of_group(ng, a.k2_splits, j1 / 8 - 1);
+            const int lo = share_with(ng, a.k2_splits, j0 / 8), hi = share_with(ng, a.k2_splits, j1 / 8 - 1);
             for (int js = lo; js <= hi; ++js)
                 __hip_atomic_fetch_add(a.tickets + kRoleCount0 + js * geo.role.stride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -546,8 +542,8 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
     const int CB = (TAIL ? (a.d_model + 127) / 128 : a.d_model / 128) / a.k2_col_blocks;      // <= CBM, checked on the host
     const int blk_lo = cb * CB;
     const int njb_all = (rows + 31) / 32;
-    const int jb_lo = (int)((long long)njb_all * wave / NW);
-    const int njb = (int)((long long)njb_all * (wave + 1) / NW) - jb_lo;
+    const int jb_lo = (int)((unsigned)njb_all * (unsigned)wave / NW);
+    const int njb = (int)((unsigned)njb_all * (unsigned)(wave + 1) / NW) - jb_lo;
 
     KmStream2<NW, TT, TAIL, WAIT> ts;
     ts.Wd = (const char*)a.Wd; ts.A2 = (const char*)a.a2;
@@ -574,7 +570,7 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
         if (geo.role_wait > 0) {
             if (tid == 0) {
                 const int ng = a.d_ff / 8;
-                const unsigned expected = (unsigned)(slice_of_group(ng, a.splits, j1 / 8 - 1) - slice_of_group(ng, a.splits, j0 / 8) + 1);
+                const unsigned expected = (unsigned)(share_with(ng, a.splits, j1 / 8 - 1) - share_with(ng, a.splits, j0 / 8) + 1);
                 flag = role_wait<DeviceMem>(a.tickets, geo.role, js, expected, geo.role_spin_limit,
                                             stand_in ? nullptr : (unsigned*)a.Q, wg);
             }

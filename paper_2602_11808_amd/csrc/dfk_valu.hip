@@ -161,7 +161,7 @@ __global__ __launch_bounds__(512) void k_fused_valu(MlpArgs a, int a2_stride) {
     extern __shared__ __attribute__((aligned(16))) float a2s[];
     __shared__ int flag;
     int j0, j1;
-    slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
+    slice_rows_any(a.d_ff, a.splits, blockIdx.x, j0, j1);
     const int rows = j1 - j0;
     const int nchunk = a.d_model / E::VEC;
     stage1_valu<E, MT>(a, j0, rows, a.m_base, a.m_count, a2s, a2_stride);
@@ -175,7 +175,7 @@ template <typename E, int MT>
 __global__ __launch_bounds__(512) void k_gateup_valu(MlpArgs a, int a2_stride) {
     extern __shared__ __attribute__((aligned(16))) float a2s[];
     int j0, j1;
-    slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
+    slice_rows_any(a.d_ff, a.splits, blockIdx.x, j0, j1);
     const int rows = j1 - j0;
     stage1_valu<E, MT>(a, j0, rows, a.m_base, a.m_count, a2s, a2_stride);
     __syncthreads();
