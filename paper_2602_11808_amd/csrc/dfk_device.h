@@ -335,6 +335,15 @@ __device__ __forceinline__ void drain_accumulator(const MlpArgs& a, int c_lo, in
     else drain_accumulator_by<E, NTHREADS, 8>(a, c_lo, width);
 }
 
+// Partial sums per output in which the n blocks are added up (partial sum k: blocks k, k + ways, ...; the partial sums then in order): a
+// power of two up to 16, so that `outputs` (float4s) times it are no more than the workgroup's threads; 1: block after block.  The launch
+// that adds blocks up takes the same, so that the bits do not depend on who does it.
+__host__ __device__ inline int sum_ways(int outputs, int threads, int n) {
+    int w = 1;
+    while (w < 16 && 2 * w * outputs <= threads && 2 * w <= n) w *= 2;
+    return w;
+}
+
 // Last step of a one-level reduction with at most half as many outputs (float4s) as threads: the blocks are divided among
 // `ways` threads per output, whose sums meet in LDS (`scratch`: one float4 per thread), all in a fixed order.  One or two loads
 // per thread and a few dozen instructions, where the form below has every thread issue the loads of 16 blocks for
@@ -342,9 +351,8 @@ __device__ __forceinline__ void drain_accumulator(const MlpArgs& a, int c_lo, in
 // step is made of.  Down kernel, counter reduction, 12 to 16 splits: 512 x 1536 at 1 token 6.8 -> 5.8 us, 896 x 4864 9.4
 // -> 8.6.  (With batches of 8 loads and up to as many outputs as threads: 6.1 and 8.9, and 8.4 -> 8.2 at 8 tokens of 1024 x 2816.)
 template <typename E>
-__device__ __forceinline__ void sum_blocks_wide(const ReducePlan& r, void* Y, int m_base, const void* resid, int w4, float4* scratch) {
+__device__ __forceinline__ void sum_blocks_wide(const ReducePlan& r, void* Y, int m_base, const void* resid, int w4, float4* scratch, int ways) {
     const int tid = threadIdx.x, total = r.m_count * w4;
-    const int ways = min((int)blockDim.x / total, r.n1);
     const int way = tid / total, idx = tid - way * total;
     const int m = idx / w4, c4 = idx - m * w4;
     const size_t blk = (size_t)r.m_count * r.d_model, off = (size_t)m * r.d_model + r.c_lo + 4 * c4;
@@ -369,10 +377,10 @@ __device__ __forceinline__ void sum_blocks_wide(const ReducePlan& r, void* Y, in
     }
 }
 
-// scratch: LDS for one float4 per thread, or nullptr (then one thread per output always).
+// ways: of sum_ways; more than one need LDS for a float4 per thread (scratch).
 template <typename E>
 __device__ __forceinline__ void reduce_store(const ReducePlan& r, void* Y, int m_base, int* flag,
-                                             unsigned long long* trace = nullptr, const void* resid = nullptr, float4* scratch = nullptr) {
+                                             unsigned long long* trace = nullptr, const void* resid = nullptr, float4* scratch = nullptr, int ways = 1) {
     const int tid = threadIdx.x, nth = blockDim.x;
     const int w4 = (r.c_hi - r.c_lo) >> 2;
     const size_t blk = (size_t)r.m_count * r.d_model;
@@ -384,8 +392,8 @@ __device__ __forceinline__ void reduce_store(const ReducePlan& r, void* Y, int m
     if (tid == 0) *flag = arrive_last_acquire(r.tickets + r.t1, (unsigned)r.n1);
     __syncthreads();
     if (!*flag) { if (trace && tid == 0) trace[(size_t)blockIdx.x * 8 + 6] = wall_clock64(); return; }
-    if (scratch && r.n2 == 1 && 2 * r.m_count * w4 <= nth) {
-        sum_blocks_wide<E>(r, Y, m_base, resid, w4, scratch);
+    if (ways > 1) {
+        sum_blocks_wide<E>(r, Y, m_base, resid, w4, scratch, ways);
         if (trace && tid == 0) trace[(size_t)blockIdx.x * 8 + 6] = wall_clock64();
         return;
     }

@@ -546,28 +546,35 @@ __global__ __launch_bounds__(kBigWaves * 64) void k_down_t_big(MlpArgs a, int by
     gateup_big_body<TT, E, 8, true>(a, lds, by_xcd != 0);
 }
 
-// Sum of the splits' partial blocks (counter reduction mode of the down kernel above): with
-// hundreds of tokens the blocks are tens of MB, too much for the last workgroup of a column
-// block to add up alone, so a launch of its own spreads the sum over the whole chip.  Fixed
-// order (split 0, 1, ...): bitwise reproducible.  One thread per four consecutive outputs.
-template <typename E>
-__global__ __launch_bounds__(256) void k_sum_partials_big(MlpArgs a) {
-    const int w4 = a.d_model >> 2;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (size_t)a.m_count * w4) return;
-    const int m = (int)(idx / w4), c4 = (int)(idx - (size_t)m * w4);
+// Sum of the splits' partial blocks (counter reduction of the down kernels, this file's and the 64-token pair's): a launch of
+// its own spreads it over the whole chip, where the last workgroup of a column block would read them all alone (tens of MB with
+// hundreds of tokens; a chain of round trips with a few).  Fixed order (split 0, 1, ...): bitwise reproducible.  One thread per four
+// consecutive outputs; all loads of up to BATCH splits are requested before the first is added.  With few outputs it is nothing but
+// one round trip, so each CU gets one wavefront and 16 splits one batch: block of 896 x 4864 at 1 and 16 tokens 15.9 -> 15.3, 16.9 -> 16.1
+// us against 256 threads a workgroup and batches of 8.
+template <typename E, int BATCH, int WAYS>
+__global__ __launch_bounds__(256) void k_sum_partials(MlpArgs a) {
+    const unsigned w4 = (unsigned)a.d_model >> 2;
+    const unsigned idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= (unsigned)a.m_count * w4) return;
     const size_t blk = (size_t)a.m_count * a.d_model;
-    const float* src = a.P + (size_t)m * a.d_model + 4 * c4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int js0 = 0; js0 < a.k2_splits; js0 += 8) {
-        float4 t[8];
+    const float* src = a.P + (size_t)4 * idx;
+    float4 s[WAYS];
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
+    for (int w = 0; w < WAYS; ++w) s[w] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+    for (int js0 = 0; js0 < a.k2_splits; js0 += BATCH) {
+        float4 t[BATCH];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k)
             t[k] = js0 + k < a.k2_splits ? *(const float4*)(src + (size_t)(js0 + k) * blk) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) { v.x += t[k].x; v.y += t[k].y; v.z += t[k].z; v.w += t[k].w; }
+        for (int k = 0; k < BATCH; ++k) { s[k % WAYS].x += t[k].x; s[k % WAYS].y += t[k].y; s[k % WAYS].z += t[k].z; s[k % WAYS].w += t[k].w; }
     }
-    store4_plus<E>(a.Y, a.resid, (size_t)(a.m_base + m) * a.d_model + 4 * c4, v);
+    float4 v = s[0];
+#pragma unroll
+    for (int w = 1; w < WAYS; ++w) { v.x += s[w].x; v.y += s[w].y; v.z += s[w].z; v.w += s[w].w; }
+    store4_plus<E>(a.Y, a.resid, (size_t)a.m_base * a.d_model + (size_t)4 * idx, v);
 }
 
 // Every instantiation the launcher uses, spelled out (the host pass otherwise emitted the launch
@@ -584,8 +591,11 @@ __global__ __launch_bounds__(256) void k_sum_partials_big(MlpArgs a) {
 DFK_INST_GATEUP(1) DFK_INST_GATEUP(2) DFK_INST_GATEUP(3) DFK_INST_GATEUP(4)
 DFK_INST_GATEUP(5) DFK_INST_GATEUP(6) DFK_INST_GATEUP(7) DFK_INST_GATEUP(8)
 #undef DFK_INST_GATEUP
-template __global__ void k_sum_partials_big<BF16>(MlpArgs);
-template __global__ void k_sum_partials_big<FP16>(MlpArgs);
+#define DFK_INST_SUM(BATCH, WAYS)                                          \
+    template __global__ void k_sum_partials<BF16, BATCH, WAYS>(MlpArgs);  \
+    template __global__ void k_sum_partials<FP16, BATCH, WAYS>(MlpArgs);
+DFK_INST_SUM(8, 1) DFK_INST_SUM(16, 1) DFK_INST_SUM(16, 2) DFK_INST_SUM(16, 4) DFK_INST_SUM(16, 8) DFK_INST_SUM(16, 16)
+#undef DFK_INST_SUM
 #define DFK_INST_DOWN(TT)                                              \
     template __global__ void k_down_big<TT, BF16>(MlpArgs, int);   \
     template __global__ void k_down_big<TT, FP16>(MlpArgs, int);
@@ -645,13 +655,6 @@ hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStrea
     }
 }
 
-hipError_t launch_sum_partials(const MlpArgs& a, hipStream_t st) {
-    const size_t n4 = (size_t)a.m_count * (a.d_model / 4);
-    if (a.dtype == DFK_FP16) hipLaunchKernelGGL((k_sum_partials_big<FP16>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((k_sum_partials_big<BF16>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
 template <int TT, typename E>
 hipError_t launch_big_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     static LdsAllowance allowed2;   // of the down kernel of this instantiation, per device
@@ -665,7 +668,7 @@ hipError_t launch_big_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st
         hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigWaves * 64), lds, st, a, by_xcd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || a.reduce_mode == DFK_REDUCE_ATOMIC) return e;
-        return launch_sum_partials(a, st);
+        return launch_sum_partials(a, 1, st);
     }
     return hipSuccess;
 }
@@ -678,7 +681,7 @@ hipError_t launch_down_t_te(const MlpArgs& a, hipStream_t st) {
     if (hipError_t e = allow_lds(allowed, (const void*)k_down_t_big<TT, E>, lds); e != hipSuccess) return e;
     hipLaunchKernelGGL((k_down_t_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigWaves * 64), lds, st, a, by_xcd);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    return launch_sum_partials(a, st);
+    return launch_sum_partials(a, 1, st);
 }
 template <int TT>
 hipError_t launch_down_t(const MlpArgs& a, hipStream_t st) {
@@ -690,7 +693,27 @@ hipError_t launch_big_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st)
     return a.dtype == DFK_FP16 ? launch_big_te<TT, FP16>(a, c, st) : launch_big_te<TT, BF16>(a, c, st);
 }
 
+template <typename E>
+hipError_t launch_sum_e(const MlpArgs& a, int ways, hipStream_t st) {
+    const unsigned n4 = (unsigned)a.m_count * (unsigned)(a.d_model / 4);
+    const unsigned threads = n4 < 65536 ? 64 : 256;
+    const dim3 grid((n4 + threads - 1) / threads), block(threads);
+    switch (ways) {
+        case 16: hipLaunchKernelGGL((k_sum_partials<E, 16, 16>), grid, block, 0, st, a); break;
+        case 8: hipLaunchKernelGGL((k_sum_partials<E, 16, 8>), grid, block, 0, st, a); break;
+        case 4: hipLaunchKernelGGL((k_sum_partials<E, 16, 4>), grid, block, 0, st, a); break;
+        case 2: hipLaunchKernelGGL((k_sum_partials<E, 16, 2>), grid, block, 0, st, a); break;
+        default:
+            if (a.k2_splits <= 8) hipLaunchKernelGGL((k_sum_partials<E, 8, 1>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((k_sum_partials<E, 16, 1>), grid, block, 0, st, a);
+    }
+    return hipGetLastError();
+}
 }  // namespace
+
+hipError_t launch_sum_partials(const MlpArgs& a, int ways, hipStream_t st) {
+    return a.dtype == DFK_FP16 ? launch_sum_e<FP16>(a, ways, st) : launch_sum_e<BF16>(a, ways, st);
+}
 
 int mfma_big_tokens_per_launch() { return kBigTokensPerLaunch; }
 

@@ -23,8 +23,8 @@
 // blocks the stream holds the A_2 tiles (64 rows x 32 tokens: whole 128-byte lines per token;
 // [token][8 rows] per lane is the MFMA A operand) and then two W_down tiles per block and
 // column block, regrouped per lane with v_perm_b32.
-// The end (per-wavefront LDS stages, ticket or atomic reduction) is that of
-// k_down_rows, one token tile at a time.
+// The end: per-wavefront LDS stages, one token tile at a time, as in k_down_rows; then float atomics, or the splits'
+// partial blocks, which a small launch or the last workgroup to arrive adds up in order.
 //
 // Rows of X / A_2 past the launch's tokens are fetched from the last real token:
 // they only feed output rows that are never stored.
@@ -42,6 +42,7 @@ constexpr int kKmTokensPerLaunch = 64;
 struct KmGeom {
     int depth;   // ring slots per wavefront
     int pass;    // gate/up kernel: row tiles whose partial sums LDS holds per pass at the end
+    int sum_launch;  // down kernel, counter reduction: the splits' blocks are left to a launch that adds them up
     int norm_off;  // gate/up kernel with the normalisation: byte offset in LDS of the weight slices, past rings and stage
     // the single launch of both kernels' workgroups:
     RoleShape role;
@@ -509,6 +510,9 @@ struct KmStream2 {
     }
 };
 
+// partial sums per output of the splits' sum, for a workgroup of `threads` that owns cb column blocks
+__host__ __device__ inline int km_sum_ways(const MlpArgs& a, int cb, int threads) { return sum_ways(a.m_count * cb * 32, threads, a.k2_splits); }
+
 __host__ __device__ constexpr int km_col_blocks(int tt) { return tt >= 3 ? 1 : 2; }   // accumulator budget
 
 //
@@ -730,7 +734,11 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
 #pragma unroll
                             for (int w = 0; w < NW; ++w) v += *(const f32x4*)(stage + w * 16 * 128 + 4 * idx);
                             const int m = tt * 16 + (idx >> 5), c4 = idx & 31;
-                            if (!TAIL || nb + 4 * c4 < a.d_model) store4_device(a.P + ((size_t)js * a.m_count + m) * a.d_model + nb + 4 * c4, v[0], v[1], v[2], v[3]);
+                            float* dst = a.P + ((size_t)js * a.m_count + m) * a.d_model + nb + 4 * c4;
+                            if (!TAIL || nb + 4 * c4 < a.d_model) {
+                                if (geo.sum_launch) *(f32x4*)dst = v;
+                                else store4_device(dst, v[0], v[1], v[2], v[3]);
+                            }
                         }
                     }
                     __syncthreads();
@@ -749,6 +757,7 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
             if (!notes && tid == 0) role_clear<DeviceMem>(a.tickets, geo.role);
         }
     }
+    if (geo.sum_launch) return notes;
     if (atomic_mode) {
         drain_own_memory_ops();
         __syncthreads();
@@ -756,7 +765,7 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
         __syncthreads();
         if (flag) drain_accumulator<E, NTHREADS>(a, blk_lo * 128, width);
     } else {
-        reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid, (float4*)lds);
+        reduce_store<E>(plan_column_block(a, cb, blk_lo * 128, blk_lo * 128 + width), a.Y, a.m_base, &flag, a.trace, a.resid, (float4*)lds, km_sum_ways(a, CB, NTHREADS));
     }
     return notes;
 }
@@ -860,6 +869,26 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
     return std::max(ring, (size_t)geo->pass * per_tile);
 }
 
+// Who adds the splits' blocks up in the counter reduction: a launch of its own (launch_sum_partials), or the last workgroup of each
+// column block to arrive, a chain (stores of device scope acknowledged, counter, 12 to 16 blocks read by one CU) that takes 2.7 us at
+// one token and 8 at 64, where a launch and one round trip of all CUs take 2.5 at any count.  The bits are the same.
+// Block, pair of launches, us in a replayed graph, last workgroup / launch, at 1, 16 and 64 tokens: 512 x 1536 10.2 / 10.1, 12.1 / 11.2,
+// 22.6 / 17.5; 896 x 4864 15.9 / 15.3, 18.4 / 16.1, 31.6 / 26.1; 1024 x 5632 16.0 / 14.8, 18.3 / 16.6, 29.4 / 25.1; 2048 x 5504 22.6 / 20.0,
+// 24.1 / 21.3, 37.2 / 33.2.
+// The single launch of both kernels' workgroups has no other boundary to pay for: from four tokens on.  2304 x 9216 at 1, 2, 4, 16 and
+// 64 30.9 / 30.9, 30.8 / 31.0, 31.2 / 31.1, 33.8 / 32.4, 49.8 / 46.3; 2888 x 7688 35.9 / 36.6, 35.9 / 36.3, 36.4 / 36.5, 38.8 / 37.3, 54.2 /
+// 50.6; 5120 x 27648 136.3 / 136.7, 137.2 / 136.8, 138.0 / 137.1, 142.7 / 140.3, 175.9 / 172.1.
+// A third launch also costs 2.5 to 4 us of host time, which a replayed graph does not pay: with up to 16 tokens and 12 MB of weights the
+// two kernels are done before the host has issued three (eager, 512 x 1536 at one token 9.5 / 12.1), so there it is taken under capture.
+bool km_sum_launch(const MlpArgs& a, bool single, hipStream_t st) {
+    if (a.reduce_mode != DFK_REDUCE_TICKET) return false;
+    if (single) return a.m_count >= 4;
+    if (a.m_count > 16 || (size_t)6 * a.d_model * a.d_ff >= 12000000u) return true;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
+    return status == hipStreamCaptureStatusActive;
+}
+
 // Wavefronts of the pair's down kernel: as configured, but eight where the gate/up kernel runs four (narrow widths: few 128-k
 // chunks of d_model, which say nothing about the down kernel's d_ff rows) and there is more than one token tile.  Four there had
 // twice the tiles each and the same stages to add at the end: 896 x 4864 at 40 tokens 26.8 -> 24.4 us per call, 640 x 2560 at 64
@@ -888,8 +917,10 @@ hipError_t launch_km_tail(const MlpArgs& a, const dfk_config_t& c, hipStream_t s
         constexpr int NWD = km_down_waves(NW, TT);
         const size_t lds = km_lds_down(km_down_cfg(c, TT), &geo);
         if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NWD, TT, BF16, true>, lds); e != hipSuccess) return e;
+        geo.sum_launch = km_sum_launch(a, false, st);
         hipLaunchKernelGGL((k_down_km<NWD, TT, BF16, true>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NWD * 64), lds, st, a, geo);
-        return hipGetLastError();
+        if (hipError_t e = hipGetLastError(); e != hipSuccess || !geo.sum_launch) return e;
+        return launch_sum_partials(a, km_sum_ways(a, (a.d_model + 127) / 128 / a.k2_col_blocks, NWD * 64), st);
     }
     return hipSuccess;
 }
@@ -926,8 +957,10 @@ hipError_t launch_km_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st)
         constexpr int NWD = km_down_waves(NW, TT);
         const size_t lds = km_lds_down(km_down_cfg(c, TT), &geo);
         if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NWD, TT, E>, lds); e != hipSuccess) return e;
+        geo.sum_launch = km_sum_launch(a, false, st);
         hipLaunchKernelGGL((k_down_km<NWD, TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NWD * 64), lds, st, a, geo);
-        return hipGetLastError();
+        if (hipError_t e = hipGetLastError(); e != hipSuccess || !geo.sum_launch) return e;
+        return launch_sum_partials(a, km_sum_ways(a, (a.d_model + 127) / 128 / a.k2_col_blocks, NWD * 64), st);
     }
     return hipSuccess;
 }
@@ -959,8 +992,10 @@ hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream
     const int grid = geo.n_gateup + geo.role.n_down;
     if (grid == 0) return hipSuccess;
     if (hipError_t e = allow_lds(allowed, (const void*)k_roles_km<NW, TT, E, NORM, TAIL>, lds); e != hipSuccess) return e;
+    geo.sum_launch = tail && km_sum_launch(a, true, st);
     hipLaunchKernelGGL((k_roles_km<NW, TT, E, NORM, TAIL>), dim3(grid), dim3(NW * 64), lds, st, RolesArgs{a, geo});
-    return hipGetLastError();
+    if (hipError_t e = hipGetLastError(); e != hipSuccess || !geo.sum_launch) return e;
+    return launch_sum_partials(a, 1, st);
 }
 template <int NW, int TT>
 hipError_t launch_km_roles_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
