@@ -87,7 +87,9 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  * One candidate kernel configuration (Method section: tiling / loop-order
  * variants and tile sizes; the scheduler chooses among these).
  *   variant        DFK_VARIANT_FUSED or DFK_VARIANT_TWO_KERNEL
- *   path           DFK_PATH_VALU (any supported shape, all three element types) or
+ *   path           DFK_PATH_VALU (any supported shape, all three element types; with half inputs, a
+ *                  d_model that is no multiple of 128 and k2_col_blocks = ceil(d_model / 128) the two
+ *                  kernels run on the matrix cores, up to 64 tokens per launch, A_2 in fp32 all the same) or
  *                  DFK_PATH_MFMA (bf16, and IEEE half with the kernel families kmajor >= 1;
  *                  shape constraints, see dfk_config_valid)
  *   splits         number of d_ff slices = workgroups of the fused kernel, or of

@@ -299,6 +299,24 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
     // waiting; beyond, the sum of the splits' blocks costs more (down kernel, us, with 8, 16, 32 and 64 splits: half inputs, 8
     // tokens of 2888 x 7688, five column blocks: 105, 60.6, 41.4, 56.1; fp32, 4 tokens, eleven: 37.6, 26.8, 35.1, 40.2).
     const int max_cb = std::max(1, nchunk / 64);
+    // Half inputs off 128 run on the matrix cores, with A_2 in fp32, where the down kernel has a 128-column block per workgroup
+    // (half_off_128).  The plain-FMA kernels take 8 tokens per launch and read X anew for every weight row.  Whole call, us, plain FMA /
+    // matrix cores: 736 x 3472 at 1, 8, 64 and 256 tokens 19.3 / 17.2, 49.5 / 17.5, 388 / 30.2, 1545 / 114; 1800 x 5000 at 1, 4, 16 and 110
+    // 30.8 / 25.9, 61.0 / 25.4, 172 / 26.5, 1188 / 85.4; 2888 x 7688 at 2, 16 and 64 45.6 / 41.1, 189 / 42.5, 756 / 73.4.  One token needs no
+    // tile of sixteen: from 45 MB of weights on plain FMA is first there, 1208 x 6600 (48 MB) 23.9 / 25.6, 2888 x 5000 (87 MB) 29.0 / 31.2, 2936
+    // x 9000 (159 MB) 41.4 / 49.2, 2296 x 4104 (57 MB) 28.9 / 27.7, 2008 x 2400 (29 MB) 22.5 / 19.5; at two tokens from 180 MB on, 8200 x 4000
+    // (197 MB) 55.1 / 55.9, 2936 x 9000 55.8 / 49.1.
+    auto on_matrix_cores = [&]() {
+        if (dtype != DFK_FP16 || d_model % 128 == 0) return;
+        const int k2c = (d_model + 127) / 128, more_splits = d_ff > 512 * 64 ? ((d_ff + 63) / 64 + 255) / 256 * 256 : 512;
+        for (int splits : {256, more_splits}) {
+            const dfk_config_t c = make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_VALU, clamp_splits(splits, d_ff), k2c >= 8 ? 8 : 4, 0,
+                                            clamp_splits(few_splits(M, d_model, d_ff, k2c, DFK_REDUCE_TICKET), d_ff), k2c, DFK_FP32);
+            if (half_off_128(c, M, d_model, d_ff, dtype, nullptr)) push(c);
+        }
+    };
+    const size_t weights = (size_t)6 * d_model * d_ff;
+    if (M > 2 || weights < (M == 1 ? 45000000u : 180000000u)) on_matrix_cores();
     int k2_first = 8;
     while (k2_first < 64 && k2_first * std::min(max_cb, 512 / k2_first) < 160) k2_first *= 2;
     for (int splits : {512, 1024})
@@ -308,6 +326,7 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_VALU, clamp_splits(splits, d_ff), 8, 0, k2,
                           cb, a2dt));
         }
+    on_matrix_cores();   // (nothing is listed twice)
     return out;
 }
 
@@ -625,7 +644,7 @@ dfk_status_t run_in(const WsLayout& l, const void* X, const void* Wg, const void
     }
     // Token chunking on the host: a launch handles at most `per` tokens; further
     // chunks are further launches on the same stream (they re-stream the weights).
-    const int per = c.path == DFK_PATH_MFMA ? mfma_max_tokens_per_launch(c, d_model) : valu_max_tokens_per_launch();
+    const int per = c.path == DFK_PATH_MFMA ? mfma_max_tokens_per_launch(c, d_model) : valu_max_tokens_per_launch(c, M, d_model, d_ff, dtype);
     for (int m0 = 0; m0 < M; m0 += per) {
         a.m_base = m0;
         a.m_count = std::min(per, M - m0);
@@ -711,9 +730,9 @@ bool static_layout(int M, int d_ff, WsLayout* l, size_t* p_bytes, size_t* q_byte
 }
 
 // The partial-sum blocks a configuration writes in one launch fit p_bytes / q_bytes.
-bool partials_fit_static(const dfk_config_t& c, int M, int d_model, size_t p_bytes, size_t q_bytes) {
+bool partials_fit_static(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype, size_t p_bytes, size_t q_bytes) {
     if (c.reduce == DFK_REDUCE_ATOMIC) return true;   // accumulator only, already checked against its fixed size
-    const int per = c.path == DFK_PATH_MFMA ? mfma_max_tokens_per_launch(c, d_model) : valu_max_tokens_per_launch();
+    const int per = c.path == DFK_PATH_MFMA ? mfma_max_tokens_per_launch(c, d_model) : valu_max_tokens_per_launch(c, M, d_model, d_ff, dtype);
     const size_t tokens = (size_t)std::min(M, per);
     const bool fused = c.variant == DFK_VARIANT_FUSED && !roles_launch(c);
     const size_t blocks = fused ? (size_t)c.splits : (size_t)c.k2_splits;
@@ -869,10 +888,10 @@ dfk_status_t dfk_swiglu_mlp_static(const void* X, const void* Wg, const void* Wu
     dfk_config_t c;
     if (cfg) {
         c = *cfg;
-        if (!partials_fit_static(c, M, d_model, p_bytes, q_bytes)) return DFK_ERR_WORKSPACE;
+        if (!partials_fit_static(c, M, d_model, d_ff, dtype, p_bytes, q_bytes)) return DFK_ERR_WORKSPACE;
     } else {
         if (!choose(M, d_model, d_ff, dtype, DFK_VARIANT_AUTO, &c, nullptr)) return DFK_ERR_UNSUPPORTED_SHAPE;
-        auto fits = [&](const dfk_config_t& k) { return partials_fit_static(k, M, d_model, p_bytes, q_bytes); };
+        auto fits = [&](const dfk_config_t& k) { return partials_fit_static(k, M, d_model, d_ff, dtype, p_bytes, q_bytes); };
         if (!fits(c) && !enumerate_default(M, d_model, d_ff, dtype, DFK_VARIANT_AUTO, &c, fits)) return DFK_ERR_WORKSPACE;
     }
     void* ws = nullptr;
@@ -1068,7 +1087,7 @@ dfk_status_t dfk_time_kernels(const dfk_config_t* cfg, int M, int d_model, int d
     if (M < 1 || d_model < 1 || d_ff < 1) return DFK_ERR_INVALID_ARG;
     if (!shape_supported(M, d_model, d_ff)) return DFK_ERR_UNSUPPORTED_SHAPE;
     if (!config_valid(*cfg, M, d_model, d_ff, dtype)) return DFK_ERR_UNSUPPORTED_SHAPE;
-    const int per = cfg->path == DFK_PATH_MFMA ? mfma_max_tokens_per_launch(*cfg, d_model) : valu_max_tokens_per_launch();
+    const int per = cfg->path == DFK_PATH_MFMA ? mfma_max_tokens_per_launch(*cfg, d_model) : valu_max_tokens_per_launch(*cfg, M, d_model, d_ff, dtype);
     if (M > per) return DFK_ERR_UNSUPPORTED_SHAPE;   // one set of launches per call only
     if ((uintptr_t)scratch % 256) return DFK_ERR_ALIGNMENT;
     if (scratch_bytes < scratch_layout(M, d_model, d_ff, dtype, sets).total) return DFK_ERR_WORKSPACE;

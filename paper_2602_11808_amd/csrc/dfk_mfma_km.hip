@@ -30,6 +30,7 @@
 // they only feed output rows that are never stored.
 #include <atomic>
 #include <cstdlib>
+#include <type_traits>
 #include "dfk_mfma_common.h"
 #include "dfk_roles.h"
 
@@ -177,7 +178,9 @@ struct KmStream1 {
 // (a linear layer's own [out, in] layout): Y^T = W_down^T A_2^T has the shape of stage one, with d_ff as the k
 // range, a row tile = 16 rows of one matrix, A_2 in X's place, and workgroup s owning a slice of d_model whole:
 // nothing is summed across workgroups, the end just adds the wavefronts' k-partial sums and stores Y.
-template <int NW, int TT, typename E, bool NORM, bool PUBLISH, bool DOWN_T = false, bool TAIL = false>
+//
+// A32: A_2 is stored in fp32 (half inputs at widths off 128).
+template <int NW, int TT, typename E, bool NORM, bool PUBLISH, bool DOWN_T = false, bool TAIL = false, bool A32 = false>
 __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds) {
     constexpr int TOK = 16 * TT;
     constexpr int NTHREADS = NW * 64;
@@ -375,6 +378,10 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
                     g0 *= sm; g1 *= sm; u0 *= sm; u1 *= sm;
                 }
                 const size_t o = (size_t)(a.m_base + m) * a.d_ff + j0 + (rt0 + r) * 8 + 2 * pr;
+                if (A32) {
+                    *(float2*)((float*)a.a2 + o) = make_float2(silu_mul(g0, u0), silu_mul(g1, u1));
+                    continue;
+                }
                 const uint32_t v = E::pack2(silu_mul_fast(g0, u0), silu_mul_fast(g1, u1));
                 if (PUBLISH) __hip_atomic_store((uint32_t*)((uint16_t*)a.a2 + o), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 else *(uint32_t*)((uint16_t*)a.a2 + o) = v;
@@ -395,10 +402,10 @@ __device__ __forceinline__ void gateup_km_body(const MlpArgs& a, const KmGeom& g
     }
 }
 
-template <int NW, int TT, typename E, bool NORM, bool TAIL = false>
+template <int NW, int TT, typename E, bool NORM, bool TAIL = false, bool A32 = false>
 __global__ __launch_bounds__(NW * 64) void k_gateup_km(MlpArgs a, KmGeom geo) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    gateup_km_body<NW, TT, E, NORM, false, false, TAIL>(a, geo, blockIdx.x, lds);
+    gateup_km_body<NW, TT, E, NORM, false, false, TAIL, A32>(a, geo, blockIdx.x, lds);
 }
 
 // Down projection from W_down given as [d_model, d_ff]: k2_splits workgroups, a slice of d_model each.
@@ -412,15 +419,17 @@ __global__ __launch_bounds__(NW * 64) void k_down_t_km(MlpArgs a, KmGeom geo) {
 // TAIL: d_model is no multiple of 128 (any multiple of 8).  The last column block's 16-byte pieces past the row's end
 // are fetched from its last 16 bytes: columns are independent of each other, and those are never stored.
 // COHERENT: A_2 is being written by workgroups of the same launch, on any XCD, while this one runs.
-template <int NW, int TT, bool TAIL, bool COHERENT>
+// A32: A_2 is fp32, so a tile of it holds 32 rows and serves one block: no pairs of blocks.
+template <int NW, int TT, bool TAIL, bool COHERENT, bool A32>
 struct KmStream2 {
     // A_2 travels in tiles of 64 d_ff rows x 32 tokens: per token 128 contiguous bytes, one whole cache line per
     // request (a 32-row tile would be 64-byte pieces, twice the requests for the same bytes).  One tile serves
     // two 32-row blocks; NA tiles cover the launch's token tiles.
     static constexpr int NA = TT > 2 ? 2 : 1;
+    static constexpr int GRP = A32 ? 1 : 2;      // 32-row blocks that share the A tiles
     const char *Wd, *A2;
     size_t row_bytes;          // d_model * 2
-    size_t a2_row_bytes;       // d_ff * 2
+    size_t a2_row_bytes;       // bytes of d_ff elements of A_2
     size_t a2_base;            // byte offset of (token m_base, row j0)
     int d_ff, j0, rows, m_count;
     int blk_first, CB;
@@ -434,8 +443,8 @@ struct KmStream2 {
 
     __device__ __forceinline__ void issue() {
         unsigned char* slot = ring + issue_slot * kTileBytes;
-        const int jb0 = jb_lo + 2 * p_grp;
-        const bool two = 2 * p_grp + 1 < njb;
+        const int jb0 = jb_lo + GRP * p_grp;
+        const bool two = !A32 && 2 * p_grp + 1 < njb;
         if (p_idx >= a_pos && p_idx < a_pos + NA) {
             // A tile `half`: instruction u = tokens 32 half + 8u .. +7; lanes 8t .. 8t+7 = the 128 bytes of token t,
             // the 16-byte chunks of odd tokens swapped by four so that the operand reads spread over the banks
@@ -446,8 +455,8 @@ struct KmStream2 {
                 const int tl = 32 * half + 8 * u + (lane >> 3);
                 const int chunk = (lane & 7) ^ ((tl & 1) << 2);
                 const int token = min(min(tl, 16 * TT - 1), m_count - 1);
-                const int j = min(jb0 * 32 + 8 * chunk, rows - 8);   // past the split: any valid address (masked at use)
-                const char* src = A2 + a2_base + (size_t)token * a2_row_bytes + (size_t)j * 2;
+                const int j = min(jb0 * 32 + (A32 ? 4 : 8) * chunk, rows - (A32 ? 4 : 8));   // past the split: any valid address (masked at use)
+                const char* src = A2 + a2_base + (size_t)token * a2_row_bytes + (size_t)j * (A32 ? 4 : 2);
                 __builtin_amdgcn_global_load_lds(src, DFK_LDS_PTR(slot + u * 1024), 16, 0, COHERENT ? kAuxDeviceScope : 0);
             }
         } else {
@@ -486,7 +495,7 @@ struct KmStream2 {
     // limit: most tiles to request now (the single launch holds back the first A tile until A_2 is complete)
     __device__ __forceinline__ void start(const int limit) {
         off2 = (unsigned)(8 * g * row_bytes + 16 * q);
-        T = ((njb + 1) / 2) * NA + njb * 2 * CB;
+        T = ((njb + GRP - 1) / GRP) * NA + njb * 2 * CB;
         issued = 0; issue_slot = 0; take_slot = 0; p_grp = 0; p_idx = 0;
         const int ahead = min(min(depth - 1, T), limit);
         for (int i = 0; i < ahead; ++i) issue();
@@ -526,7 +535,10 @@ __host__ __device__ constexpr int km_col_blocks(int tt) { return tt >= 3 ? 1 : 2
 //
 // stand_in: this workgroup does the work of a parked one.  Returns whether there are notes of parked workgroups for the caller to
 // go through.
-template <int NW, int TT, typename E, bool WAIT, bool TAIL = false>
+//
+// A32 (half inputs at widths off 128): A_2 is fp32 and stays so, on the fp32 matrix instructions (16 x 16 x 4: instruction r of a block takes
+// rows 8g + r, for which a lane of group g holds the weights in register r already); the weights are widened, which is exact.
+template <int NW, int TT, typename E, bool WAIT, bool TAIL = false, bool A32 = false>
 __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo, const int wg, unsigned char* lds,
                                              const bool stand_in = false) {
     __shared__ int flag;
@@ -549,11 +561,13 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
     const int jb_lo = (int)((unsigned)njb_all * (unsigned)wave / NW);
     const int njb = (int)((unsigned)njb_all * (unsigned)(wave + 1) / NW) - jb_lo;
 
-    KmStream2<NW, TT, TAIL, WAIT> ts;
+    static_assert(!A32 || (!WAIT && std::is_same<E, FP16>::value), "fp32 A_2 is built for the pair of launches with half inputs");
+    typedef KmStream2<NW, TT, TAIL, WAIT, A32> Stream;
+    Stream ts;
     ts.Wd = (const char*)a.Wd; ts.A2 = (const char*)a.a2;
     ts.row_bytes = (size_t)a.d_model * 2;
-    ts.a2_row_bytes = (size_t)a.d_ff * 2;
-    ts.a2_base = ((size_t)a.m_base * a.d_ff + j0) * 2;
+    ts.a2_row_bytes = (size_t)a.d_ff * (A32 ? 4 : 2);
+    ts.a2_base = ((size_t)a.m_base * a.d_ff + j0) * (A32 ? 4 : 2);
     ts.d_ff = a.d_ff; ts.j0 = j0; ts.rows = rows; ts.m_count = a.m_count;
     ts.blk_first = blk_lo; ts.CB = CB;
     ts.jb_lo = jb_lo; ts.njb = njb;
@@ -603,23 +617,23 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) acc2[b][c][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    for (int grp = 0; 2 * grp < njb; ++grp) {
-        const int jb0 = jb_lo + 2 * grp;
-        const bool two = 2 * grp + 1 < njb;
+    for (int grp = 0; Stream::GRP * grp < njb; ++grp) {
+        const int jb0 = jb_lo + Stream::GRP * grp;
+        const bool two = !A32 && 2 * grp + 1 < njb;
         u32x4 av[2][TT];       // A operands of the pair's two blocks: A_2[token q of tile tt][rows 8g .. 8g+7 of the block]
         auto take_a = [&]() {
 #pragma unroll
-            for (int half = 0; half < KmStream2<NW, TT, TAIL, WAIT>::NA; ++half) {
+            for (int half = 0; half < Stream::NA; ++half) {
                 const unsigned char* slot = ts.acquire();
 #pragma unroll
                 for (int t2 = 0; t2 < 2; ++t2) {
                     const int tt = 2 * half + t2;
                     if (tt < TT) {
 #pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            const int idx = (2 * t2 + (q >> 3)) * 64 + (q & 7) * 8 + ((4 * h + g) ^ ((q & 1) << 2));
+                        for (int h = 0; h < 2; ++h) {      // A32: rows 8g + 4h .. +3 of the block in fp32
+                            const int idx = (2 * t2 + (q >> 3)) * 64 + (q & 7) * 8 + ((A32 ? 2 * g + h : 4 * h + g) ^ ((q & 1) << 2));
                             const u32x4 v = *(const u32x4*)(slot + idx * 16);
-                            av[h][tt] = (jb0 + h) * 32 + 8 * g >= rows ? u32x4{0, 0, 0, 0} : v;
+                            av[h][tt] = (A32 ? jb0 : jb0 + h) * 32 + 8 * g >= rows ? u32x4{0, 0, 0, 0} : v;
                         }
                     }
                 }
@@ -639,6 +653,22 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
             }
         };
         auto multiply = [&](const int b, const int h, const u32x4 (&w)[8]) {
+            if (A32) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+#pragma unroll
+                    for (int c = 0; c < 8; c += 2) {
+                        float w0, w1;
+                        FP16::widen2(w[r][c >> 1], w0, w1);
+#pragma unroll
+                        for (int tt = 0; tt < TT; ++tt) {
+                            const float x = __uint_as_float(av[r >> 2][tt][r & 3]);
+                            acc2[b][c][tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, w0, acc2[b][c][tt], 0, 0, 0);
+                            acc2[b][c + 1][tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, w1, acc2[b][c + 1][tt], 0, 0, 0);
+                        }
+                    }
+                return;
+            }
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
@@ -770,10 +800,10 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
     return notes;
 }
 
-template <int NW, int TT, typename E, bool TAIL = false>
+template <int NW, int TT, typename E, bool TAIL = false, bool A32 = false>
 __global__ __launch_bounds__(NW * 64) void k_down_km(MlpArgs a, KmGeom geo) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    down_km_body<NW, TT, E, false, TAIL>(a, geo, blockIdx.x, lds);
+    down_km_body<NW, TT, E, false, TAIL, A32>(a, geo, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------- both kernels' workgroups in one launch
@@ -901,28 +931,33 @@ inline dfk_config_t km_down_cfg(const dfk_config_t& c, int tt) {
     return d;
 }
 
-// The pair for a d_model that is no multiple of 128 (bf16, plain block).
-template <int NW, int TT>
-hipError_t launch_km_tail(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+// The pair for a d_model that is no multiple of 128 (plain block): bf16, or half with A_2 in fp32.
+template <int NW, int TT, typename E>
+hipError_t launch_km_tail_e(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    constexpr bool A32 = std::is_same<E, FP16>::value;
     static LdsAllowance allowed1, allowed2;
-    if (a.norm_w || a.dtype != DFK_BF16 || c.kmajor != 1) return hipErrorInvalidValue;
     KmGeom geo{};
     if (g_stage_mask & 1) {
         const size_t lds = km_lds_gateup(c, TT, a.d_model, a.d_ff, false, &geo);
-        if (hipError_t e = allow_lds(allowed1, (const void*)k_gateup_km<NW, TT, BF16, false, true>, lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_gateup_km<NW, TT, BF16, false, true>), dim3(a.splits), dim3(NW * 64), lds, st, a, geo);
+        if (hipError_t e = allow_lds(allowed1, (const void*)k_gateup_km<NW, TT, E, false, true, A32>, lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_gateup_km<NW, TT, E, false, true, A32>), dim3(a.splits), dim3(NW * 64), lds, st, a, geo);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
     if (g_stage_mask & 2) {
         constexpr int NWD = km_down_waves(NW, TT);
         const size_t lds = km_lds_down(km_down_cfg(c, TT), &geo);
-        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NWD, TT, BF16, true>, lds); e != hipSuccess) return e;
+        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_km<NWD, TT, E, true, A32>, lds); e != hipSuccess) return e;
         geo.sum_launch = km_sum_launch(a, false, st);
-        hipLaunchKernelGGL((k_down_km<NWD, TT, BF16, true>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NWD * 64), lds, st, a, geo);
+        hipLaunchKernelGGL((k_down_km<NWD, TT, E, true, A32>), dim3(a.k2_splits * a.k2_col_blocks), dim3(NWD * 64), lds, st, a, geo);
         if (hipError_t e = hipGetLastError(); e != hipSuccess || !geo.sum_launch) return e;
         return launch_sum_partials(a, km_sum_ways(a, (a.d_model + 127) / 128 / a.k2_col_blocks, NWD * 64), st);
     }
     return hipSuccess;
+}
+template <int NW, int TT>
+hipError_t launch_km_tail(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    if (a.norm_w || c.kmajor != 1 || a.a2_is_fp32 != (a.dtype == DFK_FP16)) return hipErrorInvalidValue;
+    return a.dtype == DFK_FP16 ? launch_km_tail_e<NW, TT, FP16>(a, c, st) : launch_km_tail_e<NW, TT, BF16>(a, c, st);
 }
 
 template <int NW, int TT, typename E>
@@ -1009,6 +1044,20 @@ hipError_t launch_km_roles_t(const MlpArgs& a, const dfk_config_t& c, hipStream_
 }  // namespace
 
 int mfma_km_tokens_per_launch() { return kKmTokensPerLaunch; }
+
+// Half inputs at a width off 128, two launches of path VALU whose down kernel has a 128-column block per workgroup: this pair, with A_2 in
+// fp32 as those configurations promise (`pair`: the same as a configuration of the pair).  Ring slots: what the pair's own lists start with.
+bool half_off_128(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype, dfk_config_t* pair) {
+    if (dtype != DFK_FP16 || c.path != DFK_PATH_VALU || c.variant != DFK_VARIANT_TWO_KERNEL || c.kmajor != 0) return false;
+    if (d_model % kKC == 0 || c.k2_col_blocks != (d_model + 127) / 128 || c.a2_dtype != DFK_FP32) return false;
+    dfk_config_t p = c;
+    p.path = DFK_PATH_MFMA; p.kmajor = 1; p.depth = c.waves == 8 ? 3 : 6;
+    p.a2_dtype = DFK_BF16;                  // (the same question for bf16: of the types only A_2's differs)
+    if (!mfma_km_config_valid(p, M, d_model, d_ff, DFK_BF16)) return false;
+    p.a2_dtype = DFK_FP32;
+    if (pair) *pair = p;
+    return true;
+}
 
 bool mfma_km_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     if (c.path != DFK_PATH_MFMA || (dtype != DFK_BF16 && dtype != DFK_FP16) || c.variant != DFK_VARIANT_TWO_KERNEL) return false;

@@ -320,6 +320,7 @@ bool valu_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_
     if (M < 1 || d_model < 8 || d_ff < 8 || d_model % 8 || d_ff % 8) return false;
     const int ng = d_ff / 8;
     if (c.splits < 1 || c.splits > ng) return false;
+    if (half_off_128(c, M, d_model, d_ff, dtype, nullptr)) return true;    // (not these kernels)
     const int mt = pick_mt(M);
     const int tokens = M < 8 ? M : 8;
     if ((long long)mt * max_slice_rows(d_ff, c.splits) > kMaxLdsFloats) return false;
@@ -344,9 +345,12 @@ bool valu_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_
     return true;
 }
 
-int valu_max_tokens_per_launch() { return 8; }
+int valu_max_tokens_per_launch(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    return half_off_128(c, M, d_model, d_ff, dtype, nullptr) ? mfma_km_tokens_per_launch() : 8;
+}
 
 hipError_t launch_valu(const MlpArgs& a, const dfk_config_t& c, dfk_dtype_t dtype, hipStream_t st) {
+    if (dfk_config_t pair; half_off_128(c, a.M, a.d_model, a.d_ff, dtype, &pair)) return launch_mfma_km(a, pair, st);
     return dtype == DFK_BF16 ? launch_e<BF16>(a, c, st) : dtype == DFK_FP16 ? launch_e<FP16>(a, c, st) : launch_e<FP32>(a, c, st);
 }
 
