@@ -94,11 +94,14 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  shape constraints, see dfk_config_valid)
  *   splits         number of d_ff slices = workgroups of the fused kernel, or of
  *                  the first kernel of the two-kernel variant
+ *                  (kmajor = 2, up to 256 of them: half as many where the gate/up kernel divides the tokens
+ *                  among two groups of workgroups, on layers of few d_ff rows)
  *   waves          wavefronts (64 lanes) per workgroup (kmajor = 1 pair with 4: the down kernel runs 8
  *                  beyond 16 tokens)
  *   depth          software pipeline depth of the weight stream (tiles or loads in flight)
  *   reduce         dfk_reduce_t
- *   k2_splits      two-kernel variant: d_ff splits of the down projection
+ *   k2_splits      two-kernel variant: d_ff splits of the down projection (beyond 64 tokens at most 256 / (token
+ *                  groups x column blocks) of them where the down kernel divides the tokens among groups)
  *   k2_col_blocks  two-kernel variant: column blocks of the down projection
  *                  (grid of the second kernel = k2_splits * k2_col_blocks)
  *   a2_dtype       two-kernel variant: type A_2 is stored in between the

@@ -72,6 +72,7 @@ struct MlpArgs {
     int M, d_model, d_ff;
     int m_base;        // first token this launch handles (host-side token chunking)
     int m_count;       // tokens this launch handles (at most what the kernels of the configuration take)
+    int group_tokens;  // 256-token pair: tokens of a workgroup (grid y: token groups; a multiple of 64, or m_count)
     int splits;        // d_ff slices (grid of the fused kernel / first kernel)
     int k2_splits, k2_col_blocks;
     int dtype;         // dfk_dtype_t of X, the weights and Y

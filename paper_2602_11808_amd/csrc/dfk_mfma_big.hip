@@ -182,6 +182,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     const int nt = DOWN_T ? NTC : (j1 - j0) / 8;   // NTC or NTC - 1 (slices differ by at most one 8-row group)
     const size_t row_bytes = (size_t)(DOWN_T ? a.d_ff : a.d_model) * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
+    const int t0 = (int)blockIdx.y * a.group_tokens, count = min(a.group_tokens, a.m_count - t0);   // this workgroup's tokens
 
     const int rot = DOWN_T ? big_down_start<true>(a, by_xcd, cb, nsteps) : big_k_start(a, nsteps);
     const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
@@ -206,12 +207,12 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         constexpr int nb = W ? nbw : nbx;
         const char* const src = (W && DOWN_T ? (const char*)a.Wd + (size_t)(j0 + wave * 8) * row_bytes
                                  : W         ? (const char*)(wave & 1 ? a.Wu : a.Wg) + (size_t)(j0 + (wave >> 1) * 8) * row_bytes
-                                             : (const char*)(DOWN_T ? a.a2 : a.X) + (size_t)a.m_base * row_bytes) + (size_t)k0 * 2;
+                                             : (const char*)(DOWN_T ? a.a2 : a.X) + (size_t)(a.m_base + t0) * row_bytes) + (size_t)k0 * 2;
         // Byte offset of load i: row 16 i (gate and up rows; 32 i of the one matrix) or 8 i (tokens, the last one for those that
         // do not exist) further on than load 0's; the piece's place changes by half a row (64 bytes) from a tile's rows 0..7 to
         // its rows 8..15.
         const unsigned rb = (unsigned)row_bytes;
-        const unsigned off = (unsigned)(W ? prow : tile0 * 16 + prow) * rb, off_last = (unsigned)(a.m_count - 1) * rb;
+        const unsigned off = (unsigned)(W ? prow : tile0 * 16 + prow) * rb, off_last = (unsigned)(count - 1) * rb;
         const unsigned place = (unsigned)(((piece ^ (prow >> 1)) & 7) * 16) ^ (W && (wave & 1) ? 64u : 0u);
         unsigned char* const dst0 = W ? lds + w_off + (wave >> 1) * kBigTile + (wave & 1) * 1024 : lds + tile0 * kBigTile;
         constexpr int buf_bytes = W ? w_step : x_step;
@@ -285,7 +286,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     float scale[TT];                               // of the lane's tokens (requested here, used behind the barriers)
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
-        scale[tt] = !DOWN_T && a.row_scale ? a.row_scale[a.m_base + min((tile0 + tt) * 16 + q, a.m_count - 1)] : 1.f;
+        scale[tt] = !DOWN_T && a.row_scale ? a.row_scale[a.m_base + t0 + min((tile0 + tt) * 16 + q, count - 1)] : 1.f;
 
     // The halves of the k range meet: wavefront (tg, 0) finishes row tiles [0, H), (tg, 1) the others.
     constexpr int H = (NTC + 1) / 2;
@@ -307,7 +308,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
                 for (int tt = 0; tt < TT; ++tt) {
                     const f32x4 v = acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64];
                     const int m = (tile0 + tt) * 16 + q;
-                    if (m < a.m_count) *(f32x4*)(a.P + ((size_t)js * a.m_count + m) * a.d_model + j0 + rt * 16 + 4 * g) = v;
+                    if (m < count) *(f32x4*)(a.P + ((size_t)js * a.m_count + t0 + m) * a.d_model + j0 + rt * 16 + 4 * g) = v;
                 }
             }
         }
@@ -326,11 +327,11 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
 #pragma unroll
                 for (int i = 0; i < 4; ++i) o[i] = __shfl_xor(v[i], 32);
                 const int m = (tile0 + tt) * 16 + q;
-                if (g < 2 && m < a.m_count) {
+                if (g < 2 && m < count) {
                     uint2 pk;
                     pk.x = E::pack2(silu_mul_fast(v[0], o[0]), silu_mul_fast(v[1], o[1]));
                     pk.y = E::pack2(silu_mul_fast(v[2], o[2]), silu_mul_fast(v[3], o[3]));
-                    *(uint2*)((uint16_t*)a.a2 + (size_t)(a.m_base + m) * a.d_ff + j0 + rt * 8 + 4 * g) = pk;
+                    *(uint2*)((uint16_t*)a.a2 + (size_t)(a.m_base + t0 + m) * a.d_ff + j0 + rt * 8 + 4 * g) = pk;
                 }
             }
         }
@@ -362,6 +363,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
     const int nsteps = (rows + kBigStepK - 1) / kBigStepK;
     const size_t row_bytes = (size_t)a.d_model * 2;
     const int tile0 = tg * TT;
+    const int t0 = (int)blockIdx.y * a.group_tokens, count = min(a.group_tokens, a.m_count - t0);   // this workgroup's tokens
 
     const int rot = big_down_start<false>(a, by_xcd, cb, nsteps);
     const int prow = lane >> 3, piece = lane & 7;
@@ -383,10 +385,10 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
         constexpr bool W = decltype(is_w)::value, RAGGED = decltype(ragged_)::value;
         constexpr int SLOTS = W ? 4 : 2 * TT;
         constexpr int nb = W ? nbw : nbx;
-        const char* const src = W ? (const char*)a.Wd + (size_t)cb * 256 : (const char*)a.a2 + ((size_t)a.m_base * a.d_ff + j0) * 2;
+        const char* const src = W ? (const char*)a.Wd + (size_t)cb * 256 : (const char*)a.a2 + ((size_t)(a.m_base + t0) * a.d_ff + j0) * 2;
         // A_2: byte offsets of the first token's row and of the last that exists (256 tokens x 2 d_ff bytes: below 4 GiB)
         const unsigned a2_row = (unsigned)a.d_ff * 2u;
-        const unsigned off = (unsigned)(tile0 * 16 + prow) * a2_row, off_last = (unsigned)(a.m_count - 1) * a2_row;
+        const unsigned off = (unsigned)(tile0 * 16 + prow) * a2_row, off_last = (unsigned)(count - 1) * a2_row;
         unsigned char* const dst0 = W ? lds + w_off + wave * 1024 : lds + tile0 * kBigTile;
         constexpr int buf_bytes = W ? w_step : x_step;
         auto first_row = [&](int step) { return (step + rot < nsteps ? step + rot : step + rot - nsteps) * kBigStepK; };
@@ -506,13 +508,13 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
                 v1[e] += kh == 0 ? acc2[4 + e][tt][i] : acc2[4 + e][tt][2 + i];
             }
             const int m = (tile0 + tt) * 16 + 4 * g + 2 * kh + i;
-            if (m < a.m_count) {
+            if (m < count) {
                 if (atomic_mode) {
                     float* dst = a.yacc + (size_t)m * a.d_model + nb0 + 8 * q;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) { acc_add(dst + e, v0[e]); acc_add(dst + 4 + e, v1[e]); }
                 } else {       // partial block of the split: plain stores, summed by the launch that follows
-                    float* dst = a.P + ((size_t)js * a.m_count + m) * a.d_model + nb0 + 8 * q;
+                    float* dst = a.P + ((size_t)js * a.m_count + t0 + m) * a.d_model + nb0 + 8 * q;
                     *(f32x4*)dst = v0;
                     *(f32x4*)(dst + 4) = v1;
                 }
@@ -609,15 +611,18 @@ DFK_INST_DOWN_T(1) DFK_INST_DOWN_T(2) DFK_INST_DOWN_T(3) DFK_INST_DOWN_T(4)
 
 // ---------------------------------------------------------------- host side
 int big_token_tiles(int m_count) { return (m_count + 63) / 64; }   // per token group
+void set_groups(MlpArgs* a, int groups) { a->group_tokens = groups > 1 ? ((a->m_count + groups - 1) / groups + 63) / 64 * 64 : a->m_count; }
+unsigned big_groups(const MlpArgs& a) { return (unsigned)((a.m_count + a.group_tokens - 1) / a.group_tokens); }
 
 // LDS of the kernels: activation and weight buffers, or what the two halves of the k range exchange at the end.
 size_t big_lds(int x_step, int w_step, size_t end) {
     return std::max((size_t)kBigXBufs * x_step + (size_t)big_w_bufs(x_step, w_step) * w_step, end);
 }
-size_t big_lds_gateup(const dfk_config_t& c, int TT, int d_ff) {
-    const int nt_max = max_slice_rows(d_ff, c.splits) / 8, ks = big_gateup_pieces(TT, nt_max);
+size_t big_lds_gateup_nt(int TT, int nt_max) {
+    const int ks = big_gateup_pieces(TT, nt_max);
     return big_lds(ks * 4 * TT * kBigTile, ks * nt_max * kBigTile, (size_t)kBigWaves * ((nt_max + 1) / 2) * TT * 1024);
 }
+size_t big_lds_gateup(const dfk_config_t& c, int TT, int d_ff) { return big_lds_gateup_nt(TT, max_slice_rows(d_ff, c.splits) / 8); }
 size_t big_lds_down_t(int TT) { return big_lds(4 * TT * kBigTile, 8 * kBigTile, (size_t)kBigWaves * 4 * TT * 1024); }
 size_t big_lds_down(int TT) { return big_lds(4 * TT * kBigTile, 4 * kTileBytes, (size_t)kBigWaves * TT * 4 * 1024); }
 constexpr bool big_buffers_fit() {
@@ -635,14 +640,14 @@ static_assert(big_buffers_fit(), "weights at least two steps ahead");
 template <int TT, typename E, int NTC>
 hipError_t launch_big_gateup(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     static LdsAllowance allowed;   // of this instantiation, per device
-    const size_t lds = big_lds_gateup(c, TT, a.d_ff);
+    const size_t lds = big_lds_gateup_nt(TT, NTC);
     if (hipError_t e = allow_lds(allowed, (const void*)k_gateup_big<TT, E, NTC>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_gateup_big<TT, E, NTC>), dim3(a.splits), dim3(kBigWaves * 64), lds, st, a);
+    hipLaunchKernelGGL((k_gateup_big<TT, E, NTC>), dim3(a.splits, big_groups(a)), dim3(kBigWaves * 64), lds, st, a);
     return hipGetLastError();
 }
 template <int TT, typename E>
 hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    switch (max_slice_rows(a.d_ff, c.splits) / 8) {
+    switch (max_slice_rows(a.d_ff, a.splits) / 8) {
         case 1: return launch_big_gateup<TT, E, 1>(a, c, st);
         case 2: return launch_big_gateup<TT, E, 2>(a, c, st);
         case 3: return launch_big_gateup<TT, E, 3>(a, c, st);
@@ -665,7 +670,7 @@ hipError_t launch_big_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st
         const size_t lds = big_lds_down(TT);
         const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
         if (hipError_t e = allow_lds(allowed2, (const void*)k_down_big<TT, E>, lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigWaves * 64), lds, st, a, by_xcd);
+        hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || a.reduce_mode == DFK_REDUCE_ATOMIC) return e;
         return launch_sum_partials(a, 1, st);
@@ -679,7 +684,7 @@ hipError_t launch_down_t_te(const MlpArgs& a, hipStream_t st) {
     const size_t lds = big_lds_down_t(TT);
     const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
     if (hipError_t e = allow_lds(allowed, (const void*)k_down_t_big<TT, E>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_down_t_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks), dim3(kBigWaves * 64), lds, st, a, by_xcd);
+    hipLaunchKernelGGL((k_down_t_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     return launch_sum_partials(a, 1, st);
 }
@@ -723,7 +728,9 @@ int mfma_big_tokens_per_launch() { return kBigTokensPerLaunch; }
 // down kernel of this family does not yet.
 hipError_t launch_big_gateup_64(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     if (a.norm_w || a.m_count > 64) return hipErrorInvalidValue;
-    return a.dtype == DFK_FP16 ? launch_big_gateup_n<1, FP16>(a, c, st) : launch_big_gateup_n<1, BF16>(a, c, st);
+    MlpArgs b = a;
+    set_groups(&b, 1);
+    return a.dtype == DFK_FP16 ? launch_big_gateup_n<1, FP16>(b, c, st) : launch_big_gateup_n<1, BF16>(b, c, st);
 }
 bool big_gateup_64_fits(const dfk_config_t& c, int d_model, int d_ff) {
     if (d_model < 128 || d_model % kKC || d_model > kMaxDModel) return false;
@@ -751,15 +758,67 @@ bool mfma_big_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, 
     return big_lds_gateup(c, big_token_tiles(tokens), d_ff) <= (size_t)kLdsLimit && big_lds_down(big_token_tiles(tokens)) <= (size_t)kLdsLimit;
 }
 
-hipError_t launch_mfma_big(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    if (a.norm_w) return hipErrorInvalidValue;   // the normalisation is folded into the 64-token pair only
-    switch (big_token_tiles(a.m_count)) {
+// Token groups (grid y): workgroups that each take a part of the launch's tokens, over fewer slices or splits of the weights.  What a
+// gate/up workgroup reads per step is its tokens of X and its rows of the weights; one of 256 on a narrow layer has one to four row
+// tiles beside up to 256 tokens, so most of the bytes that pass through its CU are X.  Half the tokens over twice the rows are fewer; the weights come out of
+// L2 the second time.  It pays while the rows (at most eight tiles) stay few against the tokens saved.  Whole call, us, one group / two:
+// beyond 192 tokens, at 230 or 256, 2048 x 2048 38.4 / 33.1, 3072 x 3072 53.0 / 42.8, 4096 x 4096 64.8 / 55.5, 2048 x 5504 49.4 / 47.2, 2304 x 8192
+// 59.5 / 56.8, 8192 x 7168 142.7 / 128.9; up to 192 with four tiles, 160 tokens: 2048 x 2048 34.4 / 29.6, 1024 x 3840 29.5 / 27.8, 4096 x 4096 56.9 /
+// 52.9, other side, 150: 2560 x 5120 47.6 / 49.8, 3072 x 8192 60.7 / 63.6, 4096 x 8192 73.2 / 73.1; up to 128 with three (two 64-k pieces share a step
+// there), 114: 2048 x 2048 26.6 / 25.3, 3072 x 3072 37.8 / 35.8, other side: 1024 x 3840 23.9 / 24.9, 4096 x 4096 44.5 / 49.0.  Four groups are never the best.
+static int big_gateup_groups(int m_count, int d_ff) {
+    const int tiles = (d_ff / 8 + 127) / 128;          // of the longest of 128 slices
+    return m_count > 64 && tiles <= (m_count > 192 ? 8 : m_count > 128 ? 4 : 3) ? 2 : 1;
+}
+// The down kernels', where the partial blocks are summed by a launch: up to 2048 wide there are few column blocks, and groups make
+// workgroups of them without more partial sums; four groups beyond 128 tokens up to 1024 wide; two as well up to 4096 wide with a d_ff of at
+// most 4096, beyond 128 tokens or with W_down as [d_model, d_ff].  Whole call, us, one group / two / four, at 70, 114 and 230 tokens: 512 x 1536
+// 14.1 / 13.5, 15.2 / 14.5, 20.9 / 19.1 / 18.5; 1024 x 3840 21.6 / 21.0, 23.9 / 23.1, 33.9 / 31.9 / 30.8; 1280 x 7168 31.5 / 29.8, 35.3 / 33.6, 45.9 / 41.8 /
+// 44.2; 2048 x 5504 33.2 / 31.9, 38.4 / 35.8, 49.4 / 46.0 / 47.8; 4096 x 4096 47.0 / 47.1, 49.0 / 48.5, 55.5 / 51.2; W_down as [d_model, d_ff]: 512 x
+// 1536 13.9 / 13.4, 15.1 / 14.0, 20.4 / 17.7 / 16.5; 1024 x 3840 21.5 / 20.7, 24.0 / 22.6, 32.6 / 29.7 / 27.3; 4096 x 4096 41.2 / 39.9, 44.4 / 44.0, 53.6 /
+// 50.2.  On the other side, at 80, 128 and 256: 2304 x 9216 44.0 / 48.1, 47.6 / 51.8, 64.6 / 66.1; 2560 x 5120 37.9 / 38.3, 42.2 / 41.5, 56.4 / 55.7;
+// 4096 x 14336 82.0 / 88.1, 89.8 / 93.7, 115.0 / 116.2; W_down as [d_model, d_ff], 2304 x 8192 at 70 and 230 39.3 / 42.8, 56.5 / 56.5.
+static int big_down_groups(const MlpArgs& a, bool wdt) {
+    const int k2c = a.k2_col_blocks;
+    if (a.m_count <= 64 || k2c > 32) return 1;
+    if (k2c > 16) return a.d_ff <= 4096 && (wdt || a.m_count > 128) ? 2 : 1;
+    return a.m_count > 128 && k2c <= 8 ? 4 : 2;
+}
+// The launch's arguments for that many groups: at most 256 workgroups, so fewer splits than the configuration says where those were many.
+static void set_down_groups(MlpArgs* a, int groups) {
+    set_groups(a, groups);
+    if (groups > 1) a->k2_splits = std::min(a->k2_splits, 256 / (groups * a->k2_col_blocks));
+}
+
+static hipError_t launch_big(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+    switch (big_token_tiles(a.group_tokens)) {
         case 1: return launch_big_t<1>(a, c, st);
         case 2: return launch_big_t<2>(a, c, st);
         case 3: return launch_big_t<3>(a, c, st);
         case 4: return launch_big_t<4>(a, c, st);
         default: return hipErrorInvalidValue;
     }
+}
+hipError_t launch_mfma_big(const MlpArgs& args, const dfk_config_t& c, hipStream_t st) {
+    if (args.norm_w) return hipErrorInvalidValue;   // the normalisation is folded into the 64-token pair only
+    const int saved = g_stage_mask;
+    hipError_t e = hipSuccess;
+    if (saved & 1) {
+        MlpArgs a = args;
+        const int groups = c.splits <= 256 ? big_gateup_groups(a.m_count, a.d_ff) : 1;
+        set_groups(&a, groups);
+        if (groups > 1) a.splits = std::min(a.splits, 128);
+        g_stage_mask = 1;
+        e = launch_big(a, c, st);
+    }
+    if (e == hipSuccess && (saved & 2)) {
+        MlpArgs a = args;
+        set_down_groups(&a, a.reduce_mode == DFK_REDUCE_TICKET ? big_down_groups(a, false) : 1);   // (atomic: one counter per column block)
+        g_stage_mask = 2;
+        e = launch_big(a, c, st);
+    }
+    g_stage_mask = saved;
+    return e;
 }
 
 // W_down as [d_model, d_ff] with the down projection split over d_ff (kmajor = 5, k2_col_blocks = d_model / 128 > 1): up to 64
@@ -791,11 +850,13 @@ hipError_t launch_wdt_split(const MlpArgs& a, const dfk_config_t& c, hipStream_t
     hipError_t e = g.kmajor == 1 ? launch_mfma_km(a, g, st) : launch_mfma_big(a, g, st);
     g_stage_mask = saved;
     if (e != hipSuccess || !(saved & 2)) return e;
-    switch (big_token_tiles(a.m_count)) {
-        case 1: return launch_down_t<1>(a, st);
-        case 2: return launch_down_t<2>(a, st);
-        case 3: return launch_down_t<3>(a, st);
-        case 4: return launch_down_t<4>(a, st);
+    MlpArgs b = a;
+    set_down_groups(&b, big_down_groups(b, true));
+    switch (big_token_tiles(b.group_tokens)) {
+        case 1: return launch_down_t<1>(b, st);
+        case 2: return launch_down_t<2>(b, st);
+        case 3: return launch_down_t<3>(b, st);
+        case 4: return launch_down_t<4>(b, st);
         default: return hipErrorInvalidValue;
     }
 }
