@@ -95,7 +95,8 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *   splits         number of d_ff slices = workgroups of the fused kernel, or of
  *                  the first kernel of the two-kernel variant
  *                  (kmajor = 2, up to 256 of them: half as many where the gate/up kernel divides the tokens
- *                  among two groups of workgroups, on layers of few d_ff rows)
+ *                  among two groups of workgroups, on layers of few d_ff rows; more than 256: fewer rounds of 256 where
+ *                  slices of up to 16 tiles of 8 rows make that possible)
  *   waves          wavefronts (64 lanes) per workgroup (kmajor = 1 pair with 4: the down kernel runs 8
  *                  beyond 16 tokens)
  *   depth          software pipeline depth of the weight stream (tiles or loads in flight)

@@ -25,7 +25,7 @@
 //     loads of the step; after it the step's tiles are whole and the buffers of the step before are free to refill.
 //
 // Gate/up kernel: workgroup s owns a d_ff slice of at most 8 row tiles (8 rows of W_gate and
-// the same 8 of W_up per tile).  Down kernel: workgroup (js, cb) owns one 128-column block over
+// the same 8 of W_up per tile; up to 16 in its wide form).  Down kernel: workgroup (js, cb) owns one 128-column block over
 // d_ff split js; W_down is regrouped per lane with v_perm_b32 as in the other down kernels.
 // In both the two halves of the k range meet in LDS at the end, each wavefront finishing half of the
 // outputs.  The down kernel's sums over the splits are plain stores of partial blocks and a small third launch.
@@ -40,6 +40,8 @@ namespace {
 
 constexpr int kBigWaves = 8;          // 4 token groups x 2 halves of the k range
 constexpr int kBigMaxRowTiles = 8;
+// Row tiles of a slice in the gate/up kernel's wide form, by token tiles per group: what LDS holds beside three buffers of X.
+constexpr int big_wide_tiles(int TT) { return TT == 2 ? 16 : TT == 3 ? 14 : TT == 4 ? 10 : 0; }
 constexpr int kBigTokensPerLaunch = 256;
 constexpr int kBigStepK = 64;         // k (d_ff rows in the down kernel) of one pipeline step
 constexpr int kBigTile = 2048;        // 16 rows x 128 bytes
@@ -157,7 +159,14 @@ __device__ __forceinline__ int big_down_start(const MlpArgs& a, bool by_xcd, int
 // DOWN_T: the same pipeline computes the down projection from W_down given as [d_model, d_ff]: Y^T = W_down^T A_2^T has the shape
 // of stage one with d_ff as the k range and A_2 in X's place.  Workgroup (js, cb) owns 128 rows of W_down^T (NTC = 8 tiles of 16
 // rows of the one matrix) over d_ff split js in whole 64-row steps; the end stores the partial block of the split.
-template <int TT, typename E, int NTC, bool DOWN_T = false>
+//
+// WIDE: slices of up to 16 row tiles (NTC even; NTC to NTC - 2 of them), for layers whose slices of 8 take two or more rounds of
+// workgroups on the CUs.  What bounds those is the loads of the two streams: each round reads all of X out of L2 again, 24 KB beside 14 KB of
+// weights per step of a workgroup at 150 tokens of the 8192 x 28672 layer.  Sums of that many tiles times both halves of the k range do not fit the
+// registers, so wavefront (tg, kh) owns row tiles half kh over the whole k range instead: the same bytes of LDS reads per row tile, and no
+// exchange at the end.  It goes through a step's k range in two rounds and reads operands one round ahead (a whole step ahead did not fit
+// the registers at three token tiles and 14 row tiles).
+template <int TT, typename E, int NTC, bool DOWN_T = false, bool WIDE = false>
 __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char* lds, const bool by_xcd = false) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -165,7 +174,9 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     const int q = lane & 15, g = lane >> 4;
     const int tg = wave & 3, kh = wave >> 2;
     int j0, j1, js = 0, cb = 0, k0 = 0;            // rows of the weights; d_ff split, column block and first k (DOWN_T)
-    constexpr int KS = DOWN_T ? 1 : big_gateup_pieces(TT, NTC);
+    constexpr int KS = DOWN_T || WIDE ? 1 : big_gateup_pieces(TT, NTC);
+    constexpr int NR = WIDE ? NTC / 2 : NTC;       // row tiles of a wavefront
+    static_assert(!WIDE || (NTC % 2 == 0 && !DOWN_T), "halves of the row tiles");
     int nsteps;
     if (DOWN_T) {
         down_tile_of((int)blockIdx.x, a.k2_splits, a.k2_col_blocks, by_xcd, js, cb);
@@ -179,18 +190,19 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         slice_rows(a.d_ff, a.splits, blockIdx.x, j0, j1);
         nsteps = a.d_model / (kBigStepK * KS);
     }
-    const int nt = DOWN_T ? NTC : (j1 - j0) / 8;   // NTC or NTC - 1 (slices differ by at most one 8-row group)
+    const int nt = DOWN_T ? NTC : (j1 - j0) / 8;   // NTC or NTC - 1, with WIDE also NTC - 2 (slices differ by at most one 8-row group)
     const size_t row_bytes = (size_t)(DOWN_T ? a.d_ff : a.d_model) * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
     const int t0 = (int)blockIdx.y * a.group_tokens, count = min(a.group_tokens, a.m_count - t0);   // this workgroup's tokens
 
     const int rot = DOWN_T ? big_down_start<true>(a, by_xcd, cb, nsteps) : big_k_start(a, nsteps);
     const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
-    const int lo = big_operand_off(q, g, kh);
+    const int lo = big_operand_off(q, g, WIDE ? 0 : kh);
+    const int rt0 = WIDE ? kh * NR : 0;            // first row tile of this wavefront
 
-    f32x4 acc[NTC][TT];
+    f32x4 acc[NR][TT];
 #pragma unroll
-    for (int rt = 0; rt < NTC; ++rt)
+    for (int rt = 0; rt < NR; ++rt)
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -227,7 +239,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
 #pragma unroll
             for (int i = 0; i < SLOTS; ++i) load(source(s), dst0 + s * buf_bytes, i);
 
-        u32x4 xk[2][KS][TT], wv[2][KS][NTC];       // operands of this step and of the next
+        u32x4 xk[2][KS][TT], wv[2][KS][NR];        // operands of this step (WIDE: round) and of the next
         int xbuf = 0, wbuf = 0, freebuf = 0;
         wait_vm_exact(SLOTS * (min(nb, nsteps) - 1));
         lds_barrier();
@@ -236,17 +248,53 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) xk[0][u][tt] = *(const u32x4*)(lds + u * x_piece + (tile0 + tt) * kBigTile + lo);
 #pragma unroll
-            for (int rt = 0; rt < NTC; ++rt) wv[0][u][rt] = *(const u32x4*)(lds + w_off + u * w_piece + rt * kBigTile + lo);
+            for (int rt = 0; rt < NR; ++rt) wv[0][u][rt] = *(const u32x4*)(lds + w_off + u * w_piece + (rt0 + rt) * kBigTile + lo);
         }
-        auto step = [&](int s, auto cur_) {
-            constexpr int cur = decltype(cur_)::value, nxt = cur ^ 1;
-            // The loads of step s + 1 have landed (later ones may be in flight), and every wavefront has read step s:
-            // its buffers are free for the loads of step s + nb.
+        // The loads of step s + 1 have landed (later ones may be in flight), and every wavefront has read step s:
+        // its buffers are free for the loads of step s + nb.
+        auto wait_next = [&](int s) {
             if (s + nb <= nsteps) wait_vm_const<SLOTS * (nb - 2)>();
             else if (s + 1 < nsteps) wait_vm_exact(SLOTS * (nsteps - s - 2));
             lds_barrier();
             if (++xbuf == nbx) xbuf = 0;
             if (++wbuf == nbw) wbuf = 0;
+        };
+        if constexpr (WIDE) {
+            // MFMAs of round u of a step beside the operand reads of the round behind it, and loads [l0, l1) of step s + nb.
+            auto round = [&](auto u_, int s, int l0, int l1) {
+                constexpr int cur = decltype(u_)::value, nxt = cur ^ 1;
+                const unsigned char* xs = lds + xbuf * x_step + tile0 * kBigTile + (lo ^ (64 * nxt));
+                const unsigned char* ws = lds + w_off + wbuf * w_step + rt0 * kBigTile + (lo ^ (64 * nxt));
+                const char* p = source(s + nb < nsteps ? s + nb : 0);
+                unsigned char* dst = dst0 + freebuf * buf_bytes;
+                const bool more = s + nb < nsteps;
+#pragma unroll
+                for (int rt = 0; rt < NR; ++rt) {
+#pragma unroll
+                    for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma16<E>(wv[cur][0][rt], xk[cur][0][tt], acc[rt][tt]);
+                    wv[nxt][0][rt] = *(const u32x4*)(ws + rt * kBigTile);
+#pragma unroll
+                    for (int tt = rt * TT / NR; tt < (rt + 1) * TT / NR; ++tt) xk[nxt][0][tt] = *(const u32x4*)(xs + tt * kBigTile);
+                    if (more) {
+#pragma unroll
+                        for (int i = l0 + rt * (l1 - l0) / NR; i < l0 + (rt + 1) * (l1 - l0) / NR; ++i) load(p, dst, i);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            constexpr auto first = std::integral_constant<int, 0>{};
+            constexpr auto second = std::integral_constant<int, 1>{};
+            round(first, nsteps, 0, 0);
+            for (int s = 0; s < nsteps; ++s) {
+                wait_next(s);
+                round(second, s, 0, SLOTS / 2);    // (behind the last step it reads operands that nothing multiplies)
+                if (s + 1 < nsteps) round(first, s, SLOTS / 2, SLOTS);
+                if (++freebuf == nb) freebuf = 0;
+            }
+        } else {
+        auto step = [&](int s, auto cur_) {
+            constexpr int cur = decltype(cur_)::value, nxt = cur ^ 1;
+            wait_next(s);
             const unsigned char* xs = lds + xbuf * x_step + tile0 * kBigTile + lo;
             const unsigned char* ws = lds + w_off + wbuf * w_step + lo;
             const char* p = source(s + nb < nsteps ? s + nb : 0);
@@ -276,6 +324,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
             step(s + 1, std::integral_constant<int, 1>{});
         }
         if (s < nsteps) step(s, std::integral_constant<int, 0>{});
+        }
     };
     constexpr int NMAX = (2 * NTC + 3) / 4;        // a weight wavefront has NMAX loads per step or one less
     if (kh == 1) steps(std::integral_constant<int, -1>{});
@@ -288,6 +337,31 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     for (int tt = 0; tt < TT; ++tt)
         scale[tt] = !DOWN_T && a.row_scale ? a.row_scale[a.m_base + t0 + min((tile0 + tt) * 16 + q, count - 1)] : 1.f;
 
+    // D tile of (row tile, token tile): lane (q, g) holds token q, tile rows 4g .. 4g+3; rows 0..7
+    // are the gate rows, 8..15 the up rows of the same 8 d_ff rows: lanes 32 apart pair up.
+    auto store = [&](const f32x4 sum, int rt, int tt) {
+        const f32x4 v = sum * scale[tt];
+        float o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = __shfl_xor(v[i], 32);
+        const int m = (tile0 + tt) * 16 + q;
+        if (g < 2 && m < count) {
+            uint2 pk;
+            pk.x = E::pack2(silu_mul_fast(v[0], o[0]), silu_mul_fast(v[1], o[1]));
+            pk.y = E::pack2(silu_mul_fast(v[2], o[2]), silu_mul_fast(v[3], o[3]));
+            *(uint2*)((uint16_t*)a.a2 + (size_t)(a.m_base + t0 + m) * a.d_ff + j0 + rt * 8 + 4 * g) = pk;
+        }
+    };
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int rt = 0; rt < NR; ++rt)
+            if (rt0 + rt < nt) {
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) store(acc[rt][tt], rt0 + rt, tt);
+            }
+        DFK_STAMP(1);
+        return;
+    } else {
     // The halves of the k range meet: wavefront (tg, 0) finishes row tiles [0, H), (tg, 1) the others.
     constexpr int H = (NTC + 1) / 2;
     lds_barrier();                                 // nothing in flight and nothing read any more: the buffers are free
@@ -315,34 +389,26 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         DFK_STAMP(6);
         return;
     }
-    // D tile of (row tile, token tile): lane (q, g) holds token q, tile rows 4g .. 4g+3; rows 0..7
-    // are the gate rows, 8..15 the up rows of the same 8 d_ff rows: lanes 32 apart pair up.
 #pragma unroll
     for (int rt = 0; rt < NTC; ++rt) {
         if ((rt < H) == (kh == 0) && rt < nt) {
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                const f32x4 v = (acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64]) * scale[tt];
-                float o[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = __shfl_xor(v[i], 32);
-                const int m = (tile0 + tt) * 16 + q;
-                if (g < 2 && m < count) {
-                    uint2 pk;
-                    pk.x = E::pack2(silu_mul_fast(v[0], o[0]), silu_mul_fast(v[1], o[1]));
-                    pk.y = E::pack2(silu_mul_fast(v[2], o[2]), silu_mul_fast(v[3], o[3]));
-                    *(uint2*)((uint16_t*)a.a2 + (size_t)(a.m_base + t0 + m) * a.d_ff + j0 + rt * 8 + 4 * g) = pk;
-                }
-            }
+            for (int tt = 0; tt < TT; ++tt) store(acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64], rt, tt);
         }
     }
     DFK_STAMP(1);
+    }
 }
 
 template <int TT, typename E, int NTC>
 __global__ __launch_bounds__(kBigWaves * 64) void k_gateup_big(MlpArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     gateup_big_body<TT, E, NTC>(a, lds);
+}
+template <int TT, typename E, int NTC>
+__global__ __launch_bounds__(kBigWaves * 64) void k_gateup_wide(MlpArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    gateup_big_body<TT, E, NTC, false, true>(a, lds);
 }
 
 // ---------------------------------------------------------------- down kernel
@@ -593,6 +659,12 @@ __global__ __launch_bounds__(256) void k_sum_partials(MlpArgs a) {
 DFK_INST_GATEUP(1) DFK_INST_GATEUP(2) DFK_INST_GATEUP(3) DFK_INST_GATEUP(4)
 DFK_INST_GATEUP(5) DFK_INST_GATEUP(6) DFK_INST_GATEUP(7) DFK_INST_GATEUP(8)
 #undef DFK_INST_GATEUP
+#define DFK_INST_WIDE(TT, NTC)                                       \
+    template __global__ void k_gateup_wide<TT, BF16, NTC>(MlpArgs); \
+    template __global__ void k_gateup_wide<TT, FP16, NTC>(MlpArgs);
+DFK_INST_WIDE(2, 10) DFK_INST_WIDE(2, 12) DFK_INST_WIDE(2, 14) DFK_INST_WIDE(2, 16)
+DFK_INST_WIDE(3, 10) DFK_INST_WIDE(3, 12) DFK_INST_WIDE(3, 14) DFK_INST_WIDE(4, 10)
+#undef DFK_INST_WIDE
 #define DFK_INST_SUM(BATCH, WAYS)                                          \
     template __global__ void k_sum_partials<BF16, BATCH, WAYS>(MlpArgs);  \
     template __global__ void k_sum_partials<FP16, BATCH, WAYS>(MlpArgs);
@@ -632,6 +704,7 @@ constexpr bool big_buffers_fit() {
             const int ks = big_gateup_pieces(tt, n);
             if (big_w_bufs(ks * 4 * tt * kBigTile, ks * n * kBigTile) < 3) return false;
         }
+        if (big_wide_tiles(tt) && big_w_bufs(4 * tt * kBigTile, big_wide_tiles(tt) * kBigTile) < 3) return false;
     }
     return true;
 }
@@ -645,6 +718,18 @@ hipError_t launch_big_gateup(const MlpArgs& a, const dfk_config_t& c, hipStream_
     hipLaunchKernelGGL((k_gateup_big<TT, E, NTC>), dim3(a.splits, big_groups(a)), dim3(kBigWaves * 64), lds, st, a);
     return hipGetLastError();
 }
+template <int TT, typename E, int NTC>
+hipError_t launch_big_wide(const MlpArgs& a, hipStream_t st) {
+    if constexpr (NTC > big_wide_tiles(TT)) {
+        return hipErrorInvalidValue;
+    } else {
+        static LdsAllowance allowed;   // of this instantiation, per device
+        const size_t lds = big_lds(4 * TT * kBigTile, NTC * kBigTile, 0);
+        if (hipError_t e = allow_lds(allowed, (const void*)k_gateup_wide<TT, E, NTC>, lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_gateup_wide<TT, E, NTC>), dim3(a.splits), dim3(kBigWaves * 64), lds, st, a);
+        return hipGetLastError();
+    }
+}
 template <int TT, typename E>
 hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     switch (max_slice_rows(a.d_ff, a.splits) / 8) {
@@ -656,6 +741,10 @@ hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStrea
         case 6: return launch_big_gateup<TT, E, 6>(a, c, st);
         case 7: return launch_big_gateup<TT, E, 7>(a, c, st);
         case 8: return launch_big_gateup<TT, E, 8>(a, c, st);
+        case 9: case 10: return launch_big_wide<TT, E, 10>(a, st);
+        case 11: case 12: return launch_big_wide<TT, E, 12>(a, st);
+        case 13: case 14: return launch_big_wide<TT, E, 14>(a, st);
+        case 15: case 16: return launch_big_wide<TT, E, 16>(a, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -770,6 +859,18 @@ static int big_gateup_groups(int m_count, int d_ff) {
     const int tiles = (d_ff / 8 + 127) / 128;          // of the longest of 128 slices
     return m_count > 64 && tiles <= (m_count > 192 ? 8 : m_count > 128 ? 4 : 3) ? 2 : 1;
 }
+// Slices of the gate/up kernel: as many rounds of 256 workgroups as the wide form needs, where that is fewer than the given splits are.
+// Each round reads all of X anew; that outweighs whatever else differs at both ends of the range.  Whole call, us, slices of up to eight
+// tiles / wide: 4096 x 28672 at 70 tokens 144.1 / 129.0, 1024 x 20480 at 100 49.2 / 45.7 (W_down as [d_model, d_ff] 48.8 / 44.4), 5120 x 17408
+// (nine tiles) at 100, 150 and 256 144.2 / 125.4, 172.0 / 144.6, 208.0 / 180.1, 2048 x 28672 at 160 105.8 / 97.0, block 8192 x 28672 at 150
+// 336 / 311, 12288 x 22528 at 150 419 / 370, 4096 x 20480 at 230 164.8 / 145.4; two rounds where there were three or four: 8192 x 45056 at 120
+// and 180 431 / 398, 503 / 480.
+static int big_wide_splits(int m_count, int d_ff, int splits) {
+    const int max_tiles = big_wide_tiles(big_token_tiles(m_count)), groups = d_ff / 8;
+    if (!max_tiles || splits <= 256) return splits;
+    const int rounds = ((groups + max_tiles - 1) / max_tiles + 255) / 256, n = 256 * rounds;
+    return n < splits && (groups + n - 1) / n > kBigMaxRowTiles ? n : splits;
+}
 // The down kernels', where the partial blocks are summed by a launch: up to 2048 wide there are few column blocks, and groups make
 // workgroups of them without more partial sums; four groups beyond 128 tokens up to 1024 wide; two as well up to 4096 wide with a d_ff of at
 // most 4096, beyond 128 tokens or with W_down as [d_model, d_ff].  Whole call, us, one group / two / four, at 70, 114 and 230 tokens: 512 x 1536
@@ -808,6 +909,7 @@ hipError_t launch_mfma_big(const MlpArgs& args, const dfk_config_t& c, hipStream
         const int groups = c.splits <= 256 ? big_gateup_groups(a.m_count, a.d_ff) : 1;
         set_groups(&a, groups);
         if (groups > 1) a.splits = std::min(a.splits, 128);
+        else a.splits = big_wide_splits(a.m_count, a.d_ff, a.splits);
         g_stage_mask = 1;
         e = launch_big(a, c, st);
     }
