@@ -252,8 +252,8 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         }
         // The loads of step s + 1 have landed (later ones may be in flight), and every wavefront has read step s:
         // its buffers are free for the loads of step s + nb.
-        auto wait_next = [&](int s) {
-            if (s + nb <= nsteps) wait_vm_const<SLOTS * (nb - 2)>();
+        auto wait_next = [&](int s, auto whole_) {
+            if (decltype(whole_)::value || s + nb <= nsteps) wait_vm_const<SLOTS * (nb - 2)>();
             else if (s + 1 < nsteps) wait_vm_exact(SLOTS * (nsteps - s - 2));
             lds_barrier();
             if (++xbuf == nbx) xbuf = 0;
@@ -261,13 +261,13 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
         };
         if constexpr (WIDE) {
             // MFMAs of round u of a step beside the operand reads of the round behind it, and loads [l0, l1) of step s + nb.
-            auto round = [&](auto u_, int s, int l0, int l1) {
+            auto round = [&](auto u_, int s, int l0, int l1, auto whole_) {
                 constexpr int cur = decltype(u_)::value, nxt = cur ^ 1;
                 const unsigned char* xs = lds + xbuf * x_step + tile0 * kBigTile + (lo ^ (64 * nxt));
                 const unsigned char* ws = lds + w_off + wbuf * w_step + rt0 * kBigTile + (lo ^ (64 * nxt));
                 const char* p = source(s + nb < nsteps ? s + nb : 0);
                 unsigned char* dst = dst0 + freebuf * buf_bytes;
-                const bool more = s + nb < nsteps;
+                const bool more = decltype(whole_)::value || s + nb < nsteps;
 #pragma unroll
                 for (int rt = 0; rt < NR; ++rt) {
 #pragma unroll
@@ -284,22 +284,29 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
             };
             constexpr auto first = std::integral_constant<int, 0>{};
             constexpr auto second = std::integral_constant<int, 1>{};
-            round(first, nsteps, 0, 0);
-            for (int s = 0; s < nsteps; ++s) {
-                wait_next(s);
-                round(second, s, 0, SLOTS / 2);    // (behind the last step it reads operands that nothing multiplies)
-                if (s + 1 < nsteps) round(first, s, SLOTS / 2, SLOTS);
+            round(first, nsteps, 0, 0, std::false_type{});
+            int s = 0;
+            for (; s + nb < nsteps; ++s) {
+                wait_next(s, std::true_type{});
+                round(second, s, 0, SLOTS / 2, std::true_type{});
+                round(first, s, SLOTS / 2, SLOTS, std::true_type{});
+                if (++freebuf == nb) freebuf = 0;
+            }
+            for (; s < nsteps; ++s) {
+                wait_next(s, std::false_type{});
+                round(second, nsteps, 0, 0, std::false_type{});    // (behind the last step it reads operands that nothing multiplies)
+                if (s + 1 < nsteps) round(first, nsteps, 0, 0, std::false_type{});
                 if (++freebuf == nb) freebuf = 0;
             }
         } else {
-        auto step = [&](int s, auto cur_) {
+        auto step = [&](int s, auto cur_, auto whole_) {
             constexpr int cur = decltype(cur_)::value, nxt = cur ^ 1;
-            wait_next(s);
+            wait_next(s, whole_);
             const unsigned char* xs = lds + xbuf * x_step + tile0 * kBigTile + lo;
             const unsigned char* ws = lds + w_off + wbuf * w_step + lo;
             const char* p = source(s + nb < nsteps ? s + nb : 0);
             unsigned char* dst = dst0 + freebuf * buf_bytes;
-            const bool more = s + nb < nsteps;
+            const bool more = decltype(whole_)::value || s + nb < nsteps;
             // Loads, operand reads of step s + 1 and MFMAs of step s in turn: in three blocks one after the other, each of the
             // three units idles while the eight wavefronts queue for another (75 us at 256 tokens of the 4096 x 14336 layer).
 #pragma unroll
@@ -319,11 +326,17 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
             if (++freebuf == nb) freebuf = 0;
         };
         int s = 0;
-        for (; s + 1 < nsteps; s += 2) {
-            step(s, std::integral_constant<int, 0>{});
-            step(s + 1, std::integral_constant<int, 1>{});
+        // Steps that request another have a loop of their own: with a branch around each row tile's loads the call took, us, 141.9 where
+        // it takes 134.2 (4096 x 20480 at 230 tokens), 208.6 / 200.4 (8192 x 18432 at 180), 111.1 / 109.7 (4096 x 14336 at 256).
+        for (; s + 1 + nb < nsteps; s += 2) {
+            step(s, std::integral_constant<int, 0>{}, std::true_type{});
+            step(s + 1, std::integral_constant<int, 1>{}, std::true_type{});
         }
-        if (s < nsteps) step(s, std::integral_constant<int, 0>{});
+        for (; s + 1 < nsteps; s += 2) {
+            step(s, std::integral_constant<int, 0>{}, std::false_type{});
+            step(s + 1, std::integral_constant<int, 1>{}, std::false_type{});
+        }
+        if (s < nsteps) step(s, std::integral_constant<int, 0>{}, std::false_type{});
         }
     };
     constexpr int NMAX = (2 * NTC + 3) / 4;        // a weight wavefront has NMAX loads per step or one less
@@ -489,16 +502,16 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
         for (int r = 0; r < 8; ++r) w[0][r] = *(const u32x4*)(ws0 + (r >> 2) * kTileBytes + (r & 3) * 1024);
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) av[0][tt] = *(const u32x4*)(xs0 + tt * kBigTile);
-        auto step = [&](int s, auto cur_) {
+        auto step = [&](int s, auto cur_, auto whole_) {
             constexpr int cur = decltype(cur_)::value, nxt = cur ^ 1;
-            if (s + nb <= nsteps) wait_vm_const<SLOTS * (nb - 2)>();
+            if (decltype(whole_)::value || s + nb <= nsteps) wait_vm_const<SLOTS * (nb - 2)>();
             else if (s + 1 < nsteps) wait_vm_exact(SLOTS * (nsteps - s - 2));
             lds_barrier();
             if (++xbuf == nbx) xbuf = 0;
             if (++wbuf == nbw) wbuf = 0;
             const unsigned char* xs = xs0 + xbuf * x_step;
             const unsigned char* ws = ws0 + wbuf * w_step;
-            const bool more = s + nb < nsteps;
+            const bool more = decltype(whole_)::value || s + nb < nsteps;
             const int r0 = first_row(more ? s + nb : 0);
             unsigned char* dst = dst0 + freebuf * buf_bytes;
             const int here = first_row(s);
@@ -508,15 +521,18 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt) av[cur][tt] = u32x4{0, 0, 0, 0};
             }
+            u32x4 bb[2];                           // operands of a column tile and the next
+            auto regroup = [&](int c) {
+#pragma unroll
+                for (int p = 0; p < 4; ++p) bb[c & 1][p] = __builtin_amdgcn_perm(w[cur][2 * p + 1][c >> 1], w[cur][2 * p][c >> 1], c & 1 ? 0x07060302u : 0x05040100u);
+            };
+            regroup(0);
             // operand reads of step s + 1, loads and MFMAs of step s in turn, as in the gate/up kernel
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
-                u32x4 bb;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) bb[p] = __builtin_amdgcn_perm(w[cur][2 * p + 1][c >> 1], w[cur][2 * p][c >> 1], sel);
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt) acc2[c][tt] = mfma16<E>(av[cur][tt], bb, acc2[c][tt]);
+                for (int tt = 0; tt < TT; ++tt) acc2[c][tt] = mfma16<E>(av[cur][tt], bb[c & 1], acc2[c][tt]);
+                if (c < 7) regroup(c + 1);          // beside the MFMAs
                 w[nxt][c] = *(const u32x4*)(ws + (c >> 2) * kTileBytes + (c & 3) * 1024);
 #pragma unroll
                 for (int tt = c * TT / 8; tt < (c + 1) * TT / 8; ++tt) av[nxt][tt] = *(const u32x4*)(xs + tt * kBigTile);
@@ -529,11 +545,17 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
             if (++freebuf == nb) freebuf = 0;
         };
         int s = 0;
-        for (; s + 1 < nsteps; s += 2) {
-            step(s, std::integral_constant<int, 0>{});
-            step(s + 1, std::integral_constant<int, 1>{});
+        // As in the gate/up kernel (with the regrouping beside the MFMAs, not before them: 8192 x 28672 at 150 tokens, whole call, 306.6 us
+        // before, 298.9 with this loop there and here, 294.9 with both); the clamped addresses leave no registers for a second loop.
+        for (; !RAGGED && s + 1 + nb < nsteps; s += 2) {
+            step(s, std::integral_constant<int, 0>{}, std::true_type{});
+            step(s + 1, std::integral_constant<int, 1>{}, std::true_type{});
         }
-        if (s < nsteps) step(s, std::integral_constant<int, 0>{});
+        for (; s + 1 < nsteps; s += 2) {
+            step(s, std::integral_constant<int, 0>{}, std::false_type{});
+            step(s + 1, std::integral_constant<int, 1>{}, std::false_type{});
+        }
+        if (s < nsteps) step(s, std::integral_constant<int, 0>{}, std::false_type{});
     };
     if (rows % kBigStepK == 0) {       // whole steps only: no clamped addresses, nothing to zero
         if (kh == 0) steps(std::true_type{}, std::false_type{});
