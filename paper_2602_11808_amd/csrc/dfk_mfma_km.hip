@@ -901,7 +901,7 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
 
 // Who adds the splits' blocks up in the counter reduction: a launch of its own (launch_sum_partials), or the last workgroup of each
 // column block to arrive, a chain (stores of device scope acknowledged, counter, 12 to 16 blocks read by one CU) that takes 2.7 us at
-// one token and 8 at 64, where a launch and one round trip of all CUs take 2.5 at any count.  The bits are the same.
+// one token and 8 at 64, where a launch and one round trip of all CUs take 2.5 at any count.  The bits are the same (km_sum_ways).
 // Block, pair of launches, us in a replayed graph, last workgroup / launch, at 1, 16 and 64 tokens: 512 x 1536 10.2 / 10.1, 12.1 / 11.2,
 // 22.6 / 17.5; 896 x 4864 15.9 / 15.3, 18.4 / 16.1, 31.6 / 26.1; 1024 x 5632 16.0 / 14.8, 18.3 / 16.6, 29.4 / 25.1; 2048 x 5504 22.6 / 20.0,
 // 24.1 / 21.3, 37.2 / 33.2.
@@ -1030,7 +1030,7 @@ hipError_t launch_km_roles_te(const MlpArgs& a, const dfk_config_t& c, hipStream
     geo.sum_launch = tail && km_sum_launch(a, true, st);
     hipLaunchKernelGGL((k_roles_km<NW, TT, E, NORM, TAIL>), dim3(grid), dim3(NW * 64), lds, st, RolesArgs{a, geo});
     if (hipError_t e = hipGetLastError(); e != hipSuccess || !geo.sum_launch) return e;
-    return launch_sum_partials(a, 1, st);
+    return launch_sum_partials(a, km_sum_ways(a, (a.d_model + 127) / 128 / a.k2_col_blocks, NW * 64), st);   // the pair's order: its bits
 }
 template <int NW, int TT>
 hipError_t launch_km_roles_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {

@@ -98,3 +98,29 @@ def test_the_bits_do_not_depend_on_who_adds(M):
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(Y, eager), (M, splits)
+
+
+# fewest outputs per workgroup that a launch adds up, where its partial sums per output (4, 2, 1) differ with the tokens and the column blocks
+@pytest.mark.parametrize("M", [1, 3, 4, 5, 8, 9])
+@pytest.mark.parametrize("d,ff,dtype", [(1024, 1544, "bf16"), (1024, 1544, "fp16"), (1000, 1544, "bf16")])
+def test_the_single_launch_gives_the_bits_of_the_pair(M, d, ff, dtype):
+    dt = dfk.DFK_BF16 if dtype == "bf16" else dfk.DFK_FP16
+    t = di.mlp_inputs(M, d, ff, seed=95, dtype=dtype)
+    g = {k: di.to_torch(v, DEV) for k, v in t.items()}
+    ws = dfk.new_workspace(M, d, ff, DEV)
+    ran = 0
+    for k2c in (8, 4):
+        for splits in (1, 2, 3, 7, 12, 16):
+            pair = _cfg(M, d, ff, dt, k2_splits=splits, k2_col_blocks=k2c)
+            one = dfk.dfk_config_t(**dict(pair.as_dict(), variant=FUSED, kmajor=4, depth=4))
+            if not (dfk.dfk_config_valid(pair, M, d, ff, dt) and dfk.dfk_config_valid(one, M, d, ff, dt)):
+                continue
+            out = []
+            for cfg in (pair, one):
+                Y = torch.full_like(g["X"], float("nan"))
+                dfk.dfk_swiglu_mlp_ex(g["X"], g["Wg"], g["Wu"], g["Wd"], Y, cfg, ws)
+                torch.cuda.synchronize()
+                out.append(Y.view(torch.int16))
+            assert torch.equal(*out), (pair, int((out[0] != out[1]).sum()))
+            ran += 1
+    assert ran >= 6
