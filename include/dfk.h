@@ -87,9 +87,8 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  * One candidate kernel configuration (Method section: tiling / loop-order
  * variants and tile sizes; the scheduler chooses among these).
  *   variant        DFK_VARIANT_FUSED or DFK_VARIANT_TWO_KERNEL
- *   path           DFK_PATH_VALU (any supported shape, all three element types; with half inputs, a
- *                  d_model that is no multiple of 128 and k2_col_blocks = ceil(d_model / 128) the two
- *                  kernels run on the matrix cores, up to 64 tokens per launch, A_2 in fp32 all the same) or
+ *   path           DFK_PATH_VALU (any supported shape, all three element types; plain fp32 FMAs, but for
+ *                  kmajor = 1 below) or
  *                  DFK_PATH_MFMA (bf16, and IEEE half with the kernel families kmajor >= 1;
  *                  shape constraints, see dfk_config_valid)
  *   splits         number of d_ff slices = workgroups of the fused kernel, or of
@@ -113,7 +112,7 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  1 = the wavefronts share the workgroup's (at most 4) column blocks
  *                  and divide its d_ff rows (meant for few d_ff splits: a short
  *                  cross-workgroup sum whatever the token count)
- *   kmajor         MFMA path, kernel family.
+ *   kmajor         kernel family (MFMA path, and VALU path where it says so).
  *                  two-kernel variant:
  *                  1 = the pair of kernels that take up to 64 tokens per launch (the activations
  *                  travel through the same LDS rings as the weight tiles instead of sitting in
@@ -121,6 +120,9 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  registers); needs k2_rows_by_wave = 0 and d_model a multiple of 128 with at
  *                  least `waves` 128-k chunks (512 and up; in bf16 also any
  *                  other multiple of 8 from 392 on, the last chunk counting as one);
+ *                  with path = DFK_PATH_VALU: pair 1 for half inputs and a d_model that is no multiple of
+ *                  128, with A_2 in fp32 on the fp32 matrix instructions (a2_dtype = DFK_FP32, reduce =
+ *                  DFK_REDUCE_TICKET, otherwise the constraints of pair 1 in bf16);
  *                  0 = the first pair (activations in registers, row-tile-major);
  *                  2 = the pair that takes up to 256 tokens per launch (offered beyond 64
  *                  tokens, and at any token count where d_model rules out pair 1): the wavefronts

@@ -186,6 +186,17 @@ bool same_cfg(const dfk_config_t& a, const dfk_config_t& b) {
            a.k2_rows_by_wave == b.k2_rows_by_wave && a.kmajor == b.kmajor;
 }
 
+// Half inputs off 128, untuned: whether the pair on the matrix cores comes before the plain-FMA one, which keeps A_2 in fp32 as well but
+// takes 8 tokens per launch and reads X anew for every weight row.  Whole call, us, plain FMA / matrix cores: 736 x 3472 at 1, 8, 64 and 256
+// tokens 19.3 / 17.2, 49.5 / 17.5, 388 / 30.2, 1545 / 114; 1800 x 5000 at 1, 4, 16 and 110 30.8 / 25.9, 61.0 / 25.4, 172 / 26.5, 1188 /
+// 85.4; 2888 x 7688 at 2, 16 and 64 45.6 / 41.1, 189 / 42.5, 756 / 73.4.  One token needs no tile of sixteen: from 45 MB of weights on plain
+// FMA is first there, 1208 x 6600 (48 MB) 23.9 / 25.6, 2888 x 5000 (87 MB) 29.0 / 31.2, 2936 x 9000 (159 MB) 41.4 / 49.2, 2296 x 4104 (57
+// MB) 28.9 / 27.7, 2008 x 2400 (29 MB) 22.5 / 19.5; at two tokens from 180 MB on, 8200 x 4000 (197 MB) 55.1 / 55.9, 2936 x 9000 55.8 / 49.1.
+bool matrix_cores_pay(int M, int d_model, int d_ff) {
+    const size_t weights = (size_t)6 * d_model * d_ff;
+    return M > 2 || weights < (M == 1 ? 45000000u : 180000000u);
+}
+
 // The candidate set of the scheduler (Method: tiling variants x tile sizes).
 std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     std::vector<dfk_config_t> out;
@@ -299,24 +310,6 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
     // waiting; beyond, the sum of the splits' blocks costs more (down kernel, us, with 8, 16, 32 and 64 splits: half inputs, 8
     // tokens of 2888 x 7688, five column blocks: 105, 60.6, 41.4, 56.1; fp32, 4 tokens, eleven: 37.6, 26.8, 35.1, 40.2).
     const int max_cb = std::max(1, nchunk / 64);
-    // Half inputs off 128 run on the matrix cores, with A_2 in fp32, where the down kernel has a 128-column block per workgroup
-    // (half_off_128).  The plain-FMA kernels take 8 tokens per launch and read X anew for every weight row.  Whole call, us, plain FMA /
-    // matrix cores: 736 x 3472 at 1, 8, 64 and 256 tokens 19.3 / 17.2, 49.5 / 17.5, 388 / 30.2, 1545 / 114; 1800 x 5000 at 1, 4, 16 and 110
-    // 30.8 / 25.9, 61.0 / 25.4, 172 / 26.5, 1188 / 85.4; 2888 x 7688 at 2, 16 and 64 45.6 / 41.1, 189 / 42.5, 756 / 73.4.  One token needs no
-    // tile of sixteen: from 45 MB of weights on plain FMA is first there, 1208 x 6600 (48 MB) 23.9 / 25.6, 2888 x 5000 (87 MB) 29.0 / 31.2, 2936
-    // x 9000 (159 MB) 41.4 / 49.2, 2296 x 4104 (57 MB) 28.9 / 27.7, 2008 x 2400 (29 MB) 22.5 / 19.5; at two tokens from 180 MB on, 8200 x 4000
-    // (197 MB) 55.1 / 55.9, 2936 x 9000 55.8 / 49.1.
-    auto on_matrix_cores = [&]() {
-        if (dtype != DFK_FP16 || d_model % 128 == 0) return;
-        const int k2c = (d_model + 127) / 128, more_splits = d_ff > 512 * 64 ? ((d_ff + 63) / 64 + 255) / 256 * 256 : 512;
-        for (int splits : {256, more_splits}) {
-            const dfk_config_t c = make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_VALU, clamp_splits(splits, d_ff), k2c >= 8 ? 8 : 4, 0,
-                                            clamp_splits(few_splits(M, d_model, d_ff, k2c, DFK_REDUCE_TICKET), d_ff), k2c, DFK_FP32);
-            if (half_off_128(c, M, d_model, d_ff, dtype, nullptr)) push(c);
-        }
-    };
-    const size_t weights = (size_t)6 * d_model * d_ff;
-    if (M > 2 || weights < (M == 1 ? 45000000u : 180000000u)) on_matrix_cores();
     int k2_first = 8;
     while (k2_first < 64 && k2_first * std::min(max_cb, 512 / k2_first) < 160) k2_first *= 2;
     for (int splits : {512, 1024})
@@ -326,7 +319,12 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
             push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_VALU, clamp_splits(splits, d_ff), 8, 0, k2,
                           cb, a2dt));
         }
-    on_matrix_cores();   // (nothing is listed twice)
+    if (dtype == DFK_FP16 && d_model % 128) {   // (ranked by matrix_cores_pay, not by their place)
+        const int k2c = (d_model + 127) / 128, more_splits = d_ff > 512 * 64 ? ((d_ff + 63) / 64 + 255) / 256 * 256 : 512;
+        for (int splits : {256, more_splits})
+            push(make_cfg(DFK_VARIANT_TWO_KERNEL, DFK_PATH_VALU, clamp_splits(splits, d_ff), k2c >= 8 ? 8 : 4, k2c >= 8 ? 3 : 6,
+                          clamp_splits(few_splits(M, d_model, d_ff, k2c, DFK_REDUCE_TICKET), d_ff), k2c, DFK_FP32, DFK_REDUCE_TICKET, 0, 1));
+    }
     return out;
 }
 
@@ -443,6 +441,7 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
     auto cands = candidates(M, d_model, d_ff, dtype);
     auto rank = [&](const dfk_config_t& c) {
         if (c.variant == DFK_VARIANT_TWO_KERNEL) {
+            if (c.path == DFK_PATH_VALU) return c.kmajor == 0 ? 2 : matrix_cores_pay(M, d_model, d_ff) ? 1 : 3;
             if (c.kmajor == 2) return M > 64 ? -1 : 1;     // one launch for up to 256 tokens beats several of 64
             if (c.kmajor == 3) return 1;
             return c.kmajor ? 0 : c.k2_rows_by_wave ? 1 : 2;

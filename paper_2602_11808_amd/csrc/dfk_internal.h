@@ -185,7 +185,7 @@ hipError_t launch_sum_partials(const MlpArgs& a, int ways, hipStream_t st);
 hipError_t launch_big_gateup_64(const MlpArgs& a, const dfk_config_t& c, hipStream_t st);
 bool big_gateup_64_fits(const dfk_config_t& c, int d_model, int d_ff);
 int valu_max_tokens_per_launch(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);
-// half inputs at a width off 128 that run on the 64-token pair with A_2 in fp32
+// half inputs at a width off 128 on the 64-token pair with A_2 in fp32 (path VALU, kmajor = 1)
 bool half_off_128(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype, dfk_config_t* pair);
 
 // utility kernels

@@ -1045,13 +1045,13 @@ hipError_t launch_km_roles_t(const MlpArgs& a, const dfk_config_t& c, hipStream_
 
 int mfma_km_tokens_per_launch() { return kKmTokensPerLaunch; }
 
-// Half inputs at a width off 128, two launches of path VALU whose down kernel has a 128-column block per workgroup: this pair, with A_2 in
-// fp32 as those configurations promise (`pair`: the same as a configuration of the pair).  Ring slots: what the pair's own lists start with.
+// Half inputs at a width off 128, path VALU with kmajor = 1: this pair, with A_2 in fp32 as everything of that path (`pair`: the same as
+// a configuration of the pair).
 bool half_off_128(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype, dfk_config_t* pair) {
-    if (dtype != DFK_FP16 || c.path != DFK_PATH_VALU || c.variant != DFK_VARIANT_TWO_KERNEL || c.kmajor != 0) return false;
-    if (d_model % kKC == 0 || c.k2_col_blocks != (d_model + 127) / 128 || c.a2_dtype != DFK_FP32) return false;
+    if (dtype != DFK_FP16 || c.path != DFK_PATH_VALU || c.variant != DFK_VARIANT_TWO_KERNEL || c.kmajor != 1) return false;
+    if (d_model % kKC == 0 || c.a2_dtype != DFK_FP32) return false;
     dfk_config_t p = c;
-    p.path = DFK_PATH_MFMA; p.kmajor = 1; p.depth = c.waves == 8 ? 3 : 6;
+    p.path = DFK_PATH_MFMA;
     p.a2_dtype = DFK_BF16;                  // (the same question for bf16: of the types only A_2's differs)
     if (!mfma_km_config_valid(p, M, d_model, d_ff, DFK_BF16)) return false;
     p.a2_dtype = DFK_FP32;

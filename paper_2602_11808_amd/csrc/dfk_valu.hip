@@ -314,13 +314,13 @@ hipError_t launch_e(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
 bool valu_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
     if (c.path != DFK_PATH_VALU) return false;
     if (c.variant != DFK_VARIANT_FUSED && c.variant != DFK_VARIANT_TWO_KERNEL) return false;
-    if (c.kmajor != 0 && !(c.kmajor == 5 && c.variant == DFK_VARIANT_TWO_KERNEL)) return false;   // 5: W_down as [d_model, d_ff]
+    if (c.kmajor != 0 && !((c.kmajor == 5 || c.kmajor == 1) && c.variant == DFK_VARIANT_TWO_KERNEL)) return false;   // 5: W_down as [d_model, d_ff]
     if (c.reduce != DFK_REDUCE_TICKET || c.k2_rows_by_wave != 0) return false;
     if (c.waves < 1 || c.waves > 8) return false;  // kernels are built for <= 512 threads
     if (M < 1 || d_model < 8 || d_ff < 8 || d_model % 8 || d_ff % 8) return false;
     const int ng = d_ff / 8;
     if (c.splits < 1 || c.splits > ng) return false;
-    if (half_off_128(c, M, d_model, d_ff, dtype, nullptr)) return true;    // (not these kernels)
+    if (c.kmajor == 1) return half_off_128(c, M, d_model, d_ff, dtype, nullptr);    // (not these kernels)
     const int mt = pick_mt(M);
     const int tokens = M < 8 ? M : 8;
     if ((long long)mt * max_slice_rows(d_ff, c.splits) > kMaxLdsFloats) return false;

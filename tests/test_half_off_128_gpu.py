@@ -98,3 +98,34 @@ def test_weights_that_are_not_finite_stay_where_the_plain_kernels_keep_them():
 def test_one_token_of_a_large_layer_stays_on_the_plain_kernels():
     assert not _matrix(dfk.dfk_get_choice(1, 2888, 7688, HALF)[0], 2888)
     assert _matrix(dfk.dfk_get_choice(2, 2888, 7688, HALF)[0], 2888)
+
+
+def _plain(M, d, ff, **over):
+    c = next(c for c in _cands(M, d, ff) if c.variant == TWO and c.path == dfk.DFK_PATH_VALU and c.kmajor == 0)
+    return dfk.dfk_config_t(**dict(c.as_dict(), **over))
+
+
+def test_plain_fma_by_name_within_the_static_scratch():
+    """Eight tokens per launch: 160 splits of them fit the array, of 64 tokens they would not."""
+    M, d, ff = 64, 1000, 1536
+    t = di.mlp_inputs(M, d, ff, seed=63, dtype="fp16")
+    ref = oracle.swiglu_mlp(t["X"], t["Wg"], t["Wu"], t["Wd"])
+    g = {k: di.to_torch(v, DEV) for k, v in t.items()}
+    Y = torch.full_like(g["X"], float("nan"))
+    dfk.dfk_swiglu_mlp_static(g["X"], g["Wg"], g["Wu"], g["Wd"], Y, _plain(M, d, ff, k2_splits=160, k2_col_blocks=8))
+    torch.cuda.synchronize()
+    assert_parity(di.as_f64(di.to_numpy(Y)), ref, "fp16", "static")
+
+
+@pytest.mark.parametrize("M", [3, 40])
+def test_an_input_that_is_not_finite_stays_in_its_token(M):
+    d, ff = 1000, 1536
+    t = di.mlp_inputs(M, d, ff, seed=64, dtype="fp16")
+    g = {k: di.to_torch(v, DEV) for k, v in t.items()}
+    clean = [y.clone() for y in _both(M, d, ff, g)]
+    g["X"][1, d - 1] = float("inf")
+    g["X"][M - 1, 5] = float("nan")
+    for y, was in zip(_both(M, d, ff, g), clean):
+        assert bool(torch.isnan(y[M - 1]).all()) and not bool(torch.isfinite(y[1]).any())
+        rest = [m for m in range(M) if m not in (1, M - 1)]
+        assert torch.equal(y[rest], was[rest])

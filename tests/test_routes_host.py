@@ -1,5 +1,6 @@
 """Which kernels a problem is given to, on the host: widths that are no multiple of 128, the split counts of the untuned choice,
 and that the remembered choice is the one a fresh search finds.  No HIP call is made."""
+import ctypes
 import threading
 
 import pytest
@@ -304,3 +305,27 @@ def test_one_token_of_a_d_ff_that_no_single_launch_takes(d, ff):
             assert (pick.variant, pick.kmajor, pick.reduce) == (TWO, 1, dfk.DFK_REDUCE_TICKET), pick
         if d >= 1024:
             assert dfk.dfk_get_choice(1, d, 32768, dt)[0].kmajor == 4
+
+
+def test_half_off_128_on_the_matrix_cores_is_a_configuration_of_its_own():
+    """Path VALU with kmajor = 1: for half inputs off 128 alone, with A_2 in fp32 and the counter reduction; first where it pays."""
+    h = dfk.DFK_FP16
+    for M, d, ff in ((1, 736, 3472), (3, 2888, 7688), (64, 904, 1000)):
+        c, _ = dfk.dfk_get_choice(M, d, ff, h)
+        assert (c.path, c.variant, c.kmajor, c.a2_dtype, c.reduce) == (VALU, TWO, 1, dfk.DFK_FP32, dfk.DFK_REDUCE_TICKET), c
+        for over in (dict(a2_dtype=h), dict(reduce=dfk.DFK_REDUCE_ATOMIC), dict(variant=FUSED), dict(kmajor=2), dict(kmajor=4), dict(waves=2), dict(path=MFMA)):
+            assert not dfk.dfk_config_valid(dfk.dfk_config_t(**dict(c.as_dict(), **over)), M, d, ff, h), over
+        for dt in (dfk.DFK_BF16, dfk.DFK_FP32):
+            assert not dfk.dfk_config_valid(c, M, d, ff, dt)
+        assert not dfk.dfk_config_valid(c, M, (d + 127) // 128 * 128, ff, h)
+        plain = next(o for o in cands(M, d, ff, h) if o.variant == TWO and o.kmajor == 0)
+        plain = dfk.dfk_config_t(**dict(plain.as_dict(), k2_col_blocks=(d + 127) // 128))
+        assert dfk.dfk_config_valid(plain, M, d, ff, h)
+        # tokens of a launch: 64 there, 8 of plain FMA, whatever its column blocks (asked of the per-kernel timer, which stops at the scratch)
+        us = (ctypes.c_double * 2)()
+        timed = lambda cfg, m: dfk.lib().dfk_time_kernels(ctypes.byref(cfg), m, d, ff, h, A, 0, 1, 1, None, us)
+        assert (timed(plain, 8), timed(plain, 9)) == (dfk.DFK_ERR_WORKSPACE, dfk.DFK_ERR_UNSUPPORTED_SHAPE)
+        assert (timed(c, 64), timed(c, 65)) == (dfk.DFK_ERR_WORKSPACE, dfk.DFK_ERR_UNSUPPORTED_SHAPE)
+    for M, d, ff in ((1, 2888, 7688), (2, 8200, 4000), (1, 264, 1000)):
+        c, _ = dfk.dfk_get_choice(M, d, ff, h)
+        assert (c.path, c.kmajor) == (VALU, 0), c
