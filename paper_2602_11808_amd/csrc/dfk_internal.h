@@ -113,7 +113,8 @@ inline int max_slice_rows(int d_ff, int S) {
 // ---------------------------------------------------------------- per-launch timing
 // Which launches of a call the launchers issue on the calling thread: bit 0 the first
 // (fused kernel, or gate/up kernel), bit 1 the second (down kernel).  3 except inside
-// dfk_time_kernels, which times each launch on its own, back to back.
+// dfk_time_kernels, which times each launch on its own, back to back, and while a launcher
+// that takes one kernel of the 64-token pair asks that pair's launcher for it.
 extern thread_local int g_stage_mask;
 
 // ---------------------------------------------------------------- dynamic-LDS allowance of a kernel
@@ -176,13 +177,13 @@ hipError_t launch_mfma_fused_km(const MlpArgs& a, const dfk_config_t& c, hipStre
 bool mfma_fused_km_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);
 int mfma_fused_km_tokens_per_launch();
 // the pair of kernels for 65..256 tokens per launch (dfk_mfma_big.hip; config field kmajor = 2)
-hipError_t launch_mfma_big(const MlpArgs& a, const dfk_config_t& c, hipStream_t st);
+hipError_t launch_mfma_big(const MlpArgs& a, hipStream_t st);
 bool mfma_big_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);
 int mfma_big_tokens_per_launch();
 // adds the splits' partial blocks up in order (a launch of its own), in `ways` partial sums per output (sum_ways)
 hipError_t launch_sum_partials(const MlpArgs& a, int ways, hipStream_t st);
 // its gate/up kernel with one token tile per group (up to 64 tokens), for the mixed pair (kmajor = 3)
-hipError_t launch_big_gateup_64(const MlpArgs& a, const dfk_config_t& c, hipStream_t st);
+hipError_t launch_big_gateup_64(const MlpArgs& a, hipStream_t st);
 bool big_gateup_64_fits(const dfk_config_t& c, int d_model, int d_ff);
 int valu_max_tokens_per_launch(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);
 // half inputs at a width off 128 on the 64-token pair with A_2 in fp32 (path VALU, kmajor = 1)

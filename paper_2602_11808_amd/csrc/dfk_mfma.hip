@@ -785,7 +785,7 @@ bool mfma_mixed_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff
 
 hipError_t launch_mfma_mixed(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
     if (g_stage_mask & 1) {
-        if (hipError_t e = launch_big_gateup_64(a, mixed_gateup_cfg(c), st); e != hipSuccess) return e;
+        if (hipError_t e = launch_big_gateup_64(a, st); e != hipSuccess) return e;
     }
     if (!(g_stage_mask & 2)) return hipSuccess;
     const int saved = g_stage_mask;
@@ -852,7 +852,7 @@ hipError_t launch_mfma(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) 
     if (c.kmajor == 4) return launch_mfma_km_roles(a, c, st);
     if (wdt_split(c)) return launch_wdt_split(a, c, st);
     if (c.kmajor == 3) return launch_mfma_mixed(a, c, st);
-    if (c.kmajor == 2) return launch_mfma_big(a, c, st);
+    if (c.kmajor == 2) return launch_mfma_big(a, st);
     if (c.kmajor == 1 && c.variant == DFK_VARIANT_FUSED) return launch_mfma_fused_km(a, c, st);
     if (c.kmajor) return launch_mfma_km(a, c, st);
     const int TT = token_tiles(c, a.m_count);

@@ -33,15 +33,13 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "dfk_big_plan.h"
 #include "dfk_mfma_common.h"
 
 namespace dfk {
 namespace {
 
 constexpr int kBigWaves = 8;          // 4 token groups x 2 halves of the k range
-constexpr int kBigMaxRowTiles = 8;
-// Row tiles of a slice in the gate/up kernel's wide form, by token tiles per group: what LDS holds beside three buffers of X.
-constexpr int big_wide_tiles(int TT) { return TT == 2 ? 16 : TT == 3 ? 14 : TT == 4 ? 10 : 0; }
 constexpr int kBigTokensPerLaunch = 256;
 constexpr int kBigStepK = 64;         // k (d_ff rows in the down kernel) of one pipeline step
 constexpr int kBigTile = 2048;        // 16 rows x 128 bytes
@@ -704,8 +702,6 @@ DFK_INST_DOWN_T(1) DFK_INST_DOWN_T(2) DFK_INST_DOWN_T(3) DFK_INST_DOWN_T(4)
 #undef DFK_INST_DOWN_T
 
 // ---------------------------------------------------------------- host side
-int big_token_tiles(int m_count) { return (m_count + 63) / 64; }   // per token group
-void set_groups(MlpArgs* a, int groups) { a->group_tokens = groups > 1 ? ((a->m_count + groups - 1) / groups + 63) / 64 * 64 : a->m_count; }
 unsigned big_groups(const MlpArgs& a) { return (unsigned)((a.m_count + a.group_tokens - 1) / a.group_tokens); }
 
 // LDS of the kernels: activation and weight buffers, or what the two halves of the k range exchange at the end.
@@ -733,7 +729,7 @@ constexpr bool big_buffers_fit() {
 static_assert(big_buffers_fit(), "weights at least two steps ahead");
 
 template <int TT, typename E, int NTC>
-hipError_t launch_big_gateup(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+hipError_t launch_big_gateup(const MlpArgs& a, hipStream_t st) {
     static LdsAllowance allowed;   // of this instantiation, per device
     const size_t lds = big_lds_gateup_nt(TT, NTC);
     if (hipError_t e = allow_lds(allowed, (const void*)k_gateup_big<TT, E, NTC>, lds); e != hipSuccess) return e;
@@ -753,16 +749,16 @@ hipError_t launch_big_wide(const MlpArgs& a, hipStream_t st) {
     }
 }
 template <int TT, typename E>
-hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+hipError_t launch_big_gateup_n(const MlpArgs& a, hipStream_t st) {
     switch (max_slice_rows(a.d_ff, a.splits) / 8) {
-        case 1: return launch_big_gateup<TT, E, 1>(a, c, st);
-        case 2: return launch_big_gateup<TT, E, 2>(a, c, st);
-        case 3: return launch_big_gateup<TT, E, 3>(a, c, st);
-        case 4: return launch_big_gateup<TT, E, 4>(a, c, st);
-        case 5: return launch_big_gateup<TT, E, 5>(a, c, st);
-        case 6: return launch_big_gateup<TT, E, 6>(a, c, st);
-        case 7: return launch_big_gateup<TT, E, 7>(a, c, st);
-        case 8: return launch_big_gateup<TT, E, 8>(a, c, st);
+        case 1: return launch_big_gateup<TT, E, 1>(a, st);
+        case 2: return launch_big_gateup<TT, E, 2>(a, st);
+        case 3: return launch_big_gateup<TT, E, 3>(a, st);
+        case 4: return launch_big_gateup<TT, E, 4>(a, st);
+        case 5: return launch_big_gateup<TT, E, 5>(a, st);
+        case 6: return launch_big_gateup<TT, E, 6>(a, st);
+        case 7: return launch_big_gateup<TT, E, 7>(a, st);
+        case 8: return launch_big_gateup<TT, E, 8>(a, st);
         case 9: case 10: return launch_big_wide<TT, E, 10>(a, st);
         case 11: case 12: return launch_big_wide<TT, E, 12>(a, st);
         case 13: case 14: return launch_big_wide<TT, E, 14>(a, st);
@@ -772,21 +768,15 @@ hipError_t launch_big_gateup_n(const MlpArgs& a, const dfk_config_t& c, hipStrea
 }
 
 template <int TT, typename E>
-hipError_t launch_big_te(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    static LdsAllowance allowed2;   // of the down kernel of this instantiation, per device
-    if (g_stage_mask & 1) {
-        if (hipError_t e = launch_big_gateup_n<TT, E>(a, c, st); e != hipSuccess) return e;
-    }
-    if (g_stage_mask & 2) {
-        const size_t lds = big_lds_down(TT);
-        const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
-        if (hipError_t e = allow_lds(allowed2, (const void*)k_down_big<TT, E>, lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess || a.reduce_mode == DFK_REDUCE_ATOMIC) return e;
-        return launch_sum_partials(a, 1, st);
-    }
-    return hipSuccess;
+hipError_t launch_big_down(const MlpArgs& a, hipStream_t st) {
+    static LdsAllowance allowed;   // of this instantiation, per device
+    const size_t lds = big_lds_down(TT);
+    const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
+    if (hipError_t e = allow_lds(allowed, (const void*)k_down_big<TT, E>, lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.reduce_mode == DFK_REDUCE_ATOMIC) return e;
+    return launch_sum_partials(a, 1, st);
 }
 
 template <int TT, typename E>
@@ -799,16 +789,6 @@ hipError_t launch_down_t_te(const MlpArgs& a, hipStream_t st) {
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     return launch_sum_partials(a, 1, st);
 }
-template <int TT>
-hipError_t launch_down_t(const MlpArgs& a, hipStream_t st) {
-    return a.dtype == DFK_FP16 ? launch_down_t_te<TT, FP16>(a, st) : launch_down_t_te<TT, BF16>(a, st);
-}
-
-template <int TT>
-hipError_t launch_big_t(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    return a.dtype == DFK_FP16 ? launch_big_te<TT, FP16>(a, c, st) : launch_big_te<TT, BF16>(a, c, st);
-}
-
 template <typename E>
 hipError_t launch_sum_e(const MlpArgs& a, int ways, hipStream_t st) {
     const unsigned n4 = (unsigned)a.m_count * (unsigned)(a.d_model / 4);
@@ -837,11 +817,11 @@ int mfma_big_tokens_per_launch() { return kBigTokensPerLaunch; }
 // the down kernel of the 64-token pair for 33..64 tokens (config field kmajor = 3): with three or four token
 // tiles the shared weight tiles (read from L2 once per workgroup instead of once per wavefront) pay, while the
 // down kernel of this family does not yet.
-hipError_t launch_big_gateup_64(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+hipError_t launch_big_gateup_64(const MlpArgs& a, hipStream_t st) {
     if (a.norm_w || a.m_count > 64) return hipErrorInvalidValue;
     MlpArgs b = a;
-    set_groups(&b, 1);
-    return a.dtype == DFK_FP16 ? launch_big_gateup_n<1, FP16>(b, c, st) : launch_big_gateup_n<1, BF16>(b, c, st);
+    b.group_tokens = a.m_count;
+    return a.dtype == DFK_FP16 ? launch_big_gateup_n<1, FP16>(b, st) : launch_big_gateup_n<1, BF16>(b, st);
 }
 bool big_gateup_64_fits(const dfk_config_t& c, int d_model, int d_ff) {
     if (d_model < 128 || d_model % kKC || d_model > kMaxDModel) return false;
@@ -869,80 +849,36 @@ bool mfma_big_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, 
     return big_lds_gateup(c, big_token_tiles(tokens), d_ff) <= (size_t)kLdsLimit && big_lds_down(big_token_tiles(tokens)) <= (size_t)kLdsLimit;
 }
 
-// Token groups (grid y): workgroups that each take a part of the launch's tokens, over fewer slices or splits of the weights.  What a
-// gate/up workgroup reads per step is its tokens of X and its rows of the weights; one of 256 on a narrow layer has one to four row
-// tiles beside up to 256 tokens, so most of the bytes that pass through its CU are X.  Half the tokens over twice the rows are fewer; the weights come out of
-// L2 the second time.  It pays while the rows (at most eight tiles) stay few against the tokens saved.  Whole call, us, one group / two:
-// beyond 192 tokens, at 230 or 256, 2048 x 2048 38.4 / 33.1, 3072 x 3072 53.0 / 42.8, 4096 x 4096 64.8 / 55.5, 2048 x 5504 49.4 / 47.2, 2304 x 8192
-// 59.5 / 56.8, 8192 x 7168 142.7 / 128.9; up to 192 with four tiles, 160 tokens: 2048 x 2048 34.4 / 29.6, 1024 x 3840 29.5 / 27.8, 4096 x 4096 56.9 /
-// 52.9, other side, 150: 2560 x 5120 47.6 / 49.8, 3072 x 8192 60.7 / 63.6, 4096 x 8192 73.2 / 73.1; up to 128 with three (two 64-k pieces share a step
-// there), 114: 2048 x 2048 26.6 / 25.3, 3072 x 3072 37.8 / 35.8, other side: 1024 x 3840 23.9 / 24.9, 4096 x 4096 44.5 / 49.0.  Four groups are never the best.
-static int big_gateup_groups(int m_count, int d_ff) {
-    const int tiles = (d_ff / 8 + 127) / 128;          // of the longest of 128 slices
-    return m_count > 64 && tiles <= (m_count > 192 ? 8 : m_count > 128 ? 4 : 3) ? 2 : 1;
+// What the pair launches: the gate/up kernel, the down kernel, the down kernel for W_down as [d_model, d_ff].
+enum class BigKernel { GateUp, Down, DownT };
+template <int TT, typename E>
+static hipError_t launch_big_te(const MlpArgs& a, BigKernel k, hipStream_t st) {
+    return k == BigKernel::GateUp ? launch_big_gateup_n<TT, E>(a, st) : k == BigKernel::Down ? launch_big_down<TT, E>(a, st) : launch_down_t_te<TT, E>(a, st);
 }
-// Slices of the gate/up kernel: as many rounds of 256 workgroups as the wide form needs, where that is fewer than the given splits are.
-// Each round reads all of X anew; that outweighs whatever else differs at both ends of the range.  Whole call, us, slices of up to eight
-// tiles / wide: 4096 x 28672 at 70 tokens 144.1 / 129.0, 1024 x 20480 at 100 49.2 / 45.7 (W_down as [d_model, d_ff] 48.8 / 44.4), 5120 x 17408
-// (nine tiles) at 100, 150 and 256 144.2 / 125.4, 172.0 / 144.6, 208.0 / 180.1, 2048 x 28672 at 160 105.8 / 97.0, block 8192 x 28672 at 150
-// 336 / 311, 12288 x 22528 at 150 419 / 370, 4096 x 20480 at 230 164.8 / 145.4; two rounds where there were three or four: 8192 x 45056 at 120
-// and 180 431 / 398, 503 / 480.
-static int big_wide_splits(int m_count, int d_ff, int splits) {
-    const int max_tiles = big_wide_tiles(big_token_tiles(m_count)), groups = d_ff / 8;
-    if (!max_tiles || splits <= 256) return splits;
-    const int rounds = ((groups + max_tiles - 1) / max_tiles + 255) / 256, n = 256 * rounds;
-    return n < splits && (groups + n - 1) / n > kBigMaxRowTiles ? n : splits;
+template <int TT>
+static hipError_t launch_big_t(const MlpArgs& a, BigKernel k, hipStream_t st) {
+    return a.dtype == DFK_FP16 ? launch_big_te<TT, FP16>(a, k, st) : launch_big_te<TT, BF16>(a, k, st);
 }
-// The down kernels', where the partial blocks are summed by a launch: up to 2048 wide there are few column blocks, and groups make
-// workgroups of them without more partial sums; four groups beyond 128 tokens up to 1024 wide; two as well up to 4096 wide with a d_ff of at
-// most 4096, beyond 128 tokens or with W_down as [d_model, d_ff].  Whole call, us, one group / two / four, at 70, 114 and 230 tokens: 512 x 1536
-// 14.1 / 13.5, 15.2 / 14.5, 20.9 / 19.1 / 18.5; 1024 x 3840 21.6 / 21.0, 23.9 / 23.1, 33.9 / 31.9 / 30.8; 1280 x 7168 31.5 / 29.8, 35.3 / 33.6, 45.9 / 41.8 /
-// 44.2; 2048 x 5504 33.2 / 31.9, 38.4 / 35.8, 49.4 / 46.0 / 47.8; 4096 x 4096 47.0 / 47.1, 49.0 / 48.5, 55.5 / 51.2; W_down as [d_model, d_ff]: 512 x
-// 1536 13.9 / 13.4, 15.1 / 14.0, 20.4 / 17.7 / 16.5; 1024 x 3840 21.5 / 20.7, 24.0 / 22.6, 32.6 / 29.7 / 27.3; 4096 x 4096 41.2 / 39.9, 44.4 / 44.0, 53.6 /
-// 50.2.  On the other side, at 80, 128 and 256: 2304 x 9216 44.0 / 48.1, 47.6 / 51.8, 64.6 / 66.1; 2560 x 5120 37.9 / 38.3, 42.2 / 41.5, 56.4 / 55.7;
-// 4096 x 14336 82.0 / 88.1, 89.8 / 93.7, 115.0 / 116.2; W_down as [d_model, d_ff], 2304 x 8192 at 70 and 230 39.3 / 42.8, 56.5 / 56.5.
-static int big_down_groups(const MlpArgs& a, bool wdt) {
-    const int k2c = a.k2_col_blocks;
-    if (a.m_count <= 64 || k2c > 32) return 1;
-    if (k2c > 16) return a.d_ff <= 4096 && (wdt || a.m_count > 128) ? 2 : 1;
-    return a.m_count > 128 && k2c <= 8 ? 4 : 2;
-}
-// The launch's arguments for that many groups: at most 256 workgroups, so fewer splits than the configuration says where those were many.
-static void set_down_groups(MlpArgs* a, int groups) {
-    set_groups(a, groups);
-    if (groups > 1) a->k2_splits = std::min(a->k2_splits, 256 / (groups * a->k2_col_blocks));
-}
-
-static hipError_t launch_big(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
+static hipError_t launch_big(const MlpArgs& args, BigKernel k, hipStream_t st) {
+    MlpArgs a = args;
+    const BigLaunch l = k == BigKernel::GateUp ? big_gateup_launch(a.m_count, a.d_ff, a.splits)
+                                               : big_down_launch(a.m_count, a.d_ff, a.k2_splits, a.k2_col_blocks, k == BigKernel::DownT, a.reduce_mode == DFK_REDUCE_TICKET);
+    (k == BigKernel::GateUp ? a.splits : a.k2_splits) = l.splits;
+    a.group_tokens = l.tokens;
     switch (big_token_tiles(a.group_tokens)) {
-        case 1: return launch_big_t<1>(a, c, st);
-        case 2: return launch_big_t<2>(a, c, st);
-        case 3: return launch_big_t<3>(a, c, st);
-        case 4: return launch_big_t<4>(a, c, st);
+        case 1: return launch_big_t<1>(a, k, st);
+        case 2: return launch_big_t<2>(a, k, st);
+        case 3: return launch_big_t<3>(a, k, st);
+        case 4: return launch_big_t<4>(a, k, st);
         default: return hipErrorInvalidValue;
     }
 }
-hipError_t launch_mfma_big(const MlpArgs& args, const dfk_config_t& c, hipStream_t st) {
-    if (args.norm_w) return hipErrorInvalidValue;   // the normalisation is folded into the 64-token pair only
-    const int saved = g_stage_mask;
-    hipError_t e = hipSuccess;
-    if (saved & 1) {
-        MlpArgs a = args;
-        const int groups = c.splits <= 256 ? big_gateup_groups(a.m_count, a.d_ff) : 1;
-        set_groups(&a, groups);
-        if (groups > 1) a.splits = std::min(a.splits, 128);
-        else a.splits = big_wide_splits(a.m_count, a.d_ff, a.splits);
-        g_stage_mask = 1;
-        e = launch_big(a, c, st);
+hipError_t launch_mfma_big(const MlpArgs& a, hipStream_t st) {
+    if (a.norm_w) return hipErrorInvalidValue;   // the normalisation is folded into the 64-token pair only
+    if (g_stage_mask & 1) {
+        if (hipError_t e = launch_big(a, BigKernel::GateUp, st); e != hipSuccess) return e;
     }
-    if (e == hipSuccess && (saved & 2)) {
-        MlpArgs a = args;
-        set_down_groups(&a, a.reduce_mode == DFK_REDUCE_TICKET ? big_down_groups(a, false) : 1);   // (atomic: one counter per column block)
-        g_stage_mask = 2;
-        e = launch_big(a, c, st);
-    }
-    g_stage_mask = saved;
-    return e;
+    return g_stage_mask & 2 ? launch_big(a, BigKernel::Down, st) : hipSuccess;
 }
 
 // W_down as [d_model, d_ff] with the down projection split over d_ff (kmajor = 5, k2_col_blocks = d_model / 128 > 1): up to 64
@@ -967,22 +903,21 @@ bool mfma_wdt_split_valid(const dfk_config_t& c, int M, int d_model, int d_ff, d
 }
 
 hipError_t launch_wdt_split(const MlpArgs& a, const dfk_config_t& c, hipStream_t st) {
-    const int saved = g_stage_mask;
-    dfk_config_t g = c;
-    g.kmajor = a.M <= mfma_km_tokens_per_launch() ? 1 : 2;
-    g_stage_mask = saved & 1;                          // the gate/up kernel only
-    hipError_t e = g.kmajor == 1 ? launch_mfma_km(a, g, st) : launch_mfma_big(a, g, st);
-    g_stage_mask = saved;
-    if (e != hipSuccess || !(saved & 2)) return e;
-    MlpArgs b = a;
-    set_down_groups(&b, big_down_groups(b, true));
-    switch (big_token_tiles(b.group_tokens)) {
-        case 1: return launch_down_t<1>(b, st);
-        case 2: return launch_down_t<2>(b, st);
-        case 3: return launch_down_t<3>(b, st);
-        case 4: return launch_down_t<4>(b, st);
-        default: return hipErrorInvalidValue;
+    if (g_stage_mask & 1) {
+        hipError_t e;
+        if (a.M <= mfma_km_tokens_per_launch()) {
+            dfk_config_t g = c;
+            g.kmajor = 1;
+            const int saved = g_stage_mask;
+            g_stage_mask = 1;                          // the gate/up kernel only
+            e = launch_mfma_km(a, g, st);
+            g_stage_mask = saved;
+        } else {
+            e = a.norm_w ? hipErrorInvalidValue : launch_big(a, BigKernel::GateUp, st);
+        }
+        if (e != hipSuccess) return e;
     }
+    return g_stage_mask & 2 ? launch_big(a, BigKernel::DownT, st) : hipSuccess;
 }
 
 }  // namespace dfk
