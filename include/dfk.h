@@ -455,7 +455,10 @@ dfk_status_t dfk_rms_normalize(const void* in, void* out, int M, int d_model, vo
  * of at least 64 bytes per workgroup of the launch is registered, each workgroup
  * writes up to 8 wall-clock stamps (100 MHz counter): [0] start, [1] first tile
  * landed, [2] stage one streamed, [3] A_2 ready, [4] stage two streamed,
- * [5] partial published, [6] end of first reduction level (or exit), [7] Y written by the last group.
+ * [5] partial published (stored, where a further launch adds the partial blocks up), [6] end of first
+ * reduction level (or exit), [7] Y written by the last group.  A workgroup's row is its place in the grid; where
+ * the pair for 256 tokens divides the tokens among groups of workgroups (kmajor = 2 and 5), the groups' rows follow
+ * each other.  A buffer too small for every launch of a call is left alone by that call.
  * NULL unregisters.  Off by default. */
 dfk_status_t dfk_set_trace_buffer(void* buffer, size_t bytes);
 

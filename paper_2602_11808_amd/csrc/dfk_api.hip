@@ -636,7 +636,9 @@ dfk_status_t run_in(const WsLayout& l, const void* X, const void* Wg, const void
     }
     a.trace = nullptr;
     {
-        const size_t grid = (size_t)c.splits + (size_t)c.k2_splits * std::max(1, c.k2_col_blocks);   // covers every kernel's grid
+        size_t grid = (size_t)c.splits + (size_t)c.k2_splits * std::max(1, c.k2_col_blocks);   // covers every kernel's grid,
+        if (c.kmajor == 2 || (wdt_split(c) && M > mfma_km_tokens_per_launch()))                 // but for those of token groups
+            grid = std::max(grid, mfma_big_workgroups(c, M, d_ff));
         const Registered tr = snapshot(g_trace);
         if (tr.ptr && tr.bytes >= grid * 8 * sizeof(unsigned long long))
             a.trace = (unsigned long long*)tr.ptr;

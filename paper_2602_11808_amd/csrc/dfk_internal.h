@@ -180,6 +180,8 @@ int mfma_fused_km_tokens_per_launch();
 hipError_t launch_mfma_big(const MlpArgs& a, hipStream_t st);
 bool mfma_big_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, dfk_dtype_t dtype);
 int mfma_big_tokens_per_launch();
+// workgroups of the larger of its two launches for M tokens (W_down as [d_model, d_ff], split over d_ff: beyond 64)
+size_t mfma_big_workgroups(const dfk_config_t& c, int M, int d_ff);
 // adds the splits' partial blocks up in order (a launch of its own), in `ways` partial sums per output (sum_ways)
 hipError_t launch_sum_partials(const MlpArgs& a, int ways, hipStream_t st);
 // its gate/up kernel with one token tile per group (up to 64 tokens), for the mixed pair (kmajor = 3)

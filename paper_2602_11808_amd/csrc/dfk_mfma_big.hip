@@ -36,6 +36,9 @@
 #include "dfk_big_plan.h"
 #include "dfk_mfma_common.h"
 
+// (with token groups a workgroup's row of stamps is that of its place in the grid)
+#define DFK_STAMP_BIG(k) DFK_STAMP_OF(blockIdx.y * gridDim.x + blockIdx.x, k)
+
 namespace dfk {
 namespace {
 
@@ -204,7 +207,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    DFK_STAMP(DOWN_T ? 3 : 0);
+    DFK_STAMP_BIG(DOWN_T ? 3 : 0);
     constexpr int x_piece = 4 * TT * kBigTile, w_piece = NTC * kBigTile, x_step = KS * x_piece, w_step = KS * w_piece;
     constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
     // The steps of a wavefront that requests N weight loads per 64-k piece or (N = -1) activations: of the slice's 2 nt weight
@@ -341,7 +344,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     if (kh == 1) steps(std::integral_constant<int, -1>{});
     else if ((2 * nt - wave + 3) >> 2 == NMAX) steps(std::integral_constant<int, NMAX>{});
     else steps(std::integral_constant<int, NMAX - 1>{});
-    DFK_STAMP(DOWN_T ? 4 : 2);
+    DFK_STAMP_BIG(DOWN_T ? 4 : 2);
 
     float scale[TT];                               // of the lane's tokens (requested here, used behind the barriers)
 #pragma unroll
@@ -370,7 +373,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt) store(acc[rt][tt], rt0 + rt, tt);
             }
-        DFK_STAMP(1);
+        DFK_STAMP_BIG(1);
         return;
     } else {
     // The halves of the k range meet: wavefront (tg, 0) finishes row tiles [0, H), (tg, 1) the others.
@@ -397,7 +400,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
                 }
             }
         }
-        DFK_STAMP(6);
+        DFK_STAMP_BIG(6);
         return;
     }
 #pragma unroll
@@ -407,7 +410,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
             for (int tt = 0; tt < TT; ++tt) store(acc[rt][tt] + theirs[((rt < H ? rt : rt - H) * TT + tt) * 64], rt, tt);
         }
     }
-    DFK_STAMP(1);
+    DFK_STAMP_BIG(1);
     }
 }
 
@@ -452,7 +455,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc2[c][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    DFK_STAMP(3);
+    DFK_STAMP_BIG(3);
     constexpr int x_step = 4 * TT * kBigTile, w_step = 4 * kTileBytes;
     constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
     // Loads per step: wavefronts 0..3 take row u = wave of the four 4 KB tiles (32-row block b, half h) of W_down: rows
@@ -562,7 +565,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
         if (kh == 0) steps(std::true_type{}, std::true_type{});
         else steps(std::false_type{}, std::true_type{});
     }
-    DFK_STAMP(4);
+    DFK_STAMP_BIG(4);
 
     // D tile (column tile c, token tile tt): lane (q, g) holds tokens 4g .. 4g+3 of the tile, column
     // 8q + c of the block: the lane's 8 column tiles are 8 consecutive columns.  The halves of the k range meet:
@@ -812,6 +815,11 @@ hipError_t launch_sum_partials(const MlpArgs& a, int ways, hipStream_t st) {
 }
 
 int mfma_big_tokens_per_launch() { return kBigTokensPerLaunch; }
+
+size_t mfma_big_workgroups(const dfk_config_t& c, int M, int d_ff) {
+    const BigLaunch up = big_gateup_launch(M, d_ff, c.splits), down = big_down_launch(M, d_ff, c.k2_splits, c.k2_col_blocks, wdt_split(c), c.reduce == DFK_REDUCE_TICKET);
+    return std::max((size_t)up.splits * up.groups, (size_t)down.splits * c.k2_col_blocks * down.groups);
+}
 
 // The gate/up kernel alone with one token tile per group: up to 64 tokens per launch.  Paired with
 // the down kernel of the 64-token pair for 33..64 tokens (config field kmajor = 3): with three or four token

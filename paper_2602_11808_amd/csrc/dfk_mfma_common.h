@@ -24,7 +24,8 @@ constexpr int kAuxDeviceScope = 16; // cache-policy bit "sc1": a load of device 
 // s_waitcnt with only vmcnt constrained (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4]<<14)
 #define DFK_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | ((((n) >> 4) & 3) << 14))
 #define DFK_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(0xC07F)
-#define DFK_STAMP(k) do { if (a.trace && tid == 0) a.trace[(size_t)blockIdx.x * 8 + (k)] = wall_clock64(); } while (0)
+#define DFK_STAMP_OF(wg, k) do { if (a.trace && tid == 0) a.trace[(size_t)(wg) * 8 + (k)] = wall_clock64(); } while (0)
+#define DFK_STAMP(k) DFK_STAMP_OF(blockIdx.x, k)
 
 // Wait until at most `newer_ops` of this wavefront's vector-memory operations
 // are outstanding (loads complete in issue order); newer_ops is a multiple of 4.

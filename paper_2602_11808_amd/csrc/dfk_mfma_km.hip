@@ -787,7 +787,11 @@ __device__ __forceinline__ bool down_km_body(const MlpArgs& a, const KmGeom& geo
             if (!notes && tid == 0) role_clear<DeviceMem>(a.tickets, geo.role);
         }
     }
-    if (geo.sum_launch) return notes;
+    if (geo.sum_launch) {
+        DFK_STAMP(5);
+        DFK_STAMP(6);
+        return notes;
+    }
     if (atomic_mode) {
         drain_own_memory_ops();
         __syncthreads();
