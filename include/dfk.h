@@ -100,8 +100,8 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  beyond 16 tokens)
  *   depth          software pipeline depth of the weight stream (tiles or loads in flight)
  *   reduce         dfk_reduce_t
- *   k2_splits      two-kernel variant: d_ff splits of the down projection (beyond 64 tokens at most 256 / (token
- *                  groups x column blocks) of them where the down kernel divides the tokens among groups)
+ *   k2_splits      two-kernel variant: d_ff splits of the down projection (beyond 64 tokens fewer where the down
+ *                  kernel divides the tokens among groups and all of them would be more workgroups than CUs)
  *   k2_col_blocks  two-kernel variant: column blocks of the down projection
  *                  (grid of the second kernel = k2_splits * k2_col_blocks)
  *   a2_dtype       two-kernel variant: type A_2 is stored in between the
@@ -456,9 +456,9 @@ dfk_status_t dfk_rms_normalize(const void* in, void* out, int M, int d_model, vo
  * writes up to 8 wall-clock stamps (100 MHz counter): [0] start, [1] first tile
  * landed, [2] stage one streamed, [3] A_2 ready, [4] stage two streamed,
  * [5] partial published (stored, where a further launch adds the partial blocks up), [6] end of first
- * reduction level (or exit), [7] Y written by the last group.  A workgroup's row is its place in the grid; where
- * the pair for 256 tokens divides the tokens among groups of workgroups (kmajor = 2 and 5), the groups' rows follow
- * each other.  A buffer too small for every launch of a call is left alone by that call.
+ * reduction level (or exit), [7] Y written by the last group.  Where the pair for 256 tokens divides
+ * the tokens among groups of workgroups (kmajor = 2 and 5), the groups' rows follow each other.  A buffer
+ * too small for every launch of a call is left alone by that call.
  * NULL unregisters.  Off by default. */
 dfk_status_t dfk_set_trace_buffer(void* buffer, size_t bytes);
 

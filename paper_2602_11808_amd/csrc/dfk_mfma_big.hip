@@ -36,8 +36,8 @@
 #include "dfk_big_plan.h"
 #include "dfk_mfma_common.h"
 
-// (with token groups a workgroup's row of stamps is that of its place in the grid)
-#define DFK_STAMP_BIG(k) DFK_STAMP_OF(blockIdx.y * gridDim.x + blockIdx.x, k)
+// (the token groups' rows of stamps follow each other)
+#define DFK_STAMP_BIG(k) DFK_STAMP_OF(blockIdx.y * (unsigned)per_group + blockIdx.x, k)
 
 namespace dfk {
 namespace {
@@ -195,6 +195,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
     const size_t row_bytes = (size_t)(DOWN_T ? a.d_ff : a.d_model) * 2;
     const int tile0 = tg * TT;                     // first token tile of this wavefront's group
     const int t0 = (int)blockIdx.y * a.group_tokens, count = min(a.group_tokens, a.m_count - t0);   // this workgroup's tokens
+    const int per_group = DOWN_T ? a.k2_splits * a.k2_col_blocks : a.splits;
 
     const int rot = DOWN_T ? big_down_start<true>(a, by_xcd, cb, nsteps) : big_k_start(a, nsteps);
     const int prow = lane >> 3, piece = lane & 7;  // a load covers 8 rows: lane l takes row l / 8, and the piece that belongs to its place
@@ -444,6 +445,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
     const size_t row_bytes = (size_t)a.d_model * 2;
     const int tile0 = tg * TT;
     const int t0 = (int)blockIdx.y * a.group_tokens, count = min(a.group_tokens, a.m_count - t0);   // this workgroup's tokens
+    const int per_group = a.k2_splits * a.k2_col_blocks;
 
     const int rot = big_down_start<false>(a, by_xcd, cb, nsteps);
     const int prow = lane >> 3, piece = lane & 7;
@@ -623,6 +625,7 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
 template <int TT, typename E>
 __global__ __launch_bounds__(kBigWaves * 64) void k_down_big(MlpArgs a, int by_xcd) {   // by_xcd: place the workgroups of a d_ff split on one XCD (see down_tile_of)
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    if ((int)blockIdx.x >= a.k2_splits * a.k2_col_blocks) return;   // (a row of the grid with token groups is a multiple of 8: big_down_launch)
     down_big_body<TT, E>(a, by_xcd != 0, lds);
 }
 
@@ -634,6 +637,7 @@ __global__ __launch_bounds__(kBigWaves * 64) void k_down_big(MlpArgs a, int by_x
 template <int TT, typename E>
 __global__ __launch_bounds__(kBigWaves * 64) void k_down_t_big(MlpArgs a, int by_xcd) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    if ((int)blockIdx.x >= a.k2_splits * a.k2_col_blocks) return;
     gateup_big_body<TT, E, 8, true>(a, lds, by_xcd != 0);
 }
 
@@ -771,24 +775,24 @@ hipError_t launch_big_gateup_n(const MlpArgs& a, hipStream_t st) {
 }
 
 template <int TT, typename E>
-hipError_t launch_big_down(const MlpArgs& a, hipStream_t st) {
+hipError_t launch_big_down(const MlpArgs& a, int row, hipStream_t st) {
     static LdsAllowance allowed;   // of this instantiation, per device
     const size_t lds = big_lds_down(TT);
     const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
     if (hipError_t e = allow_lds(allowed, (const void*)k_down_big<TT, E>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_down_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
+    hipLaunchKernelGGL((k_down_big<TT, E>), dim3(row, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.reduce_mode == DFK_REDUCE_ATOMIC) return e;
     return launch_sum_partials(a, 1, st);
 }
 
 template <int TT, typename E>
-hipError_t launch_down_t_te(const MlpArgs& a, hipStream_t st) {
+hipError_t launch_down_t_te(const MlpArgs& a, int row, hipStream_t st) {
     static LdsAllowance allowed;
     const size_t lds = big_lds_down_t(TT);
     const int by_xcd = (size_t)a.m_count * a.d_ff * 2 > kL2BytesPerXcd;
     if (hipError_t e = allow_lds(allowed, (const void*)k_down_t_big<TT, E>, lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_down_t_big<TT, E>), dim3(a.k2_splits * a.k2_col_blocks, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
+    hipLaunchKernelGGL((k_down_t_big<TT, E>), dim3(row, big_groups(a)), dim3(kBigWaves * 64), lds, st, a, by_xcd);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     return launch_sum_partials(a, 1, st);
 }
@@ -860,12 +864,12 @@ bool mfma_big_config_valid(const dfk_config_t& c, int M, int d_model, int d_ff, 
 // What the pair launches: the gate/up kernel, the down kernel, the down kernel for W_down as [d_model, d_ff].
 enum class BigKernel { GateUp, Down, DownT };
 template <int TT, typename E>
-static hipError_t launch_big_te(const MlpArgs& a, BigKernel k, hipStream_t st) {
-    return k == BigKernel::GateUp ? launch_big_gateup_n<TT, E>(a, st) : k == BigKernel::Down ? launch_big_down<TT, E>(a, st) : launch_down_t_te<TT, E>(a, st);
+static hipError_t launch_big_te(const MlpArgs& a, BigKernel k, int row, hipStream_t st) {
+    return k == BigKernel::GateUp ? launch_big_gateup_n<TT, E>(a, st) : k == BigKernel::Down ? launch_big_down<TT, E>(a, row, st) : launch_down_t_te<TT, E>(a, row, st);
 }
 template <int TT>
-static hipError_t launch_big_t(const MlpArgs& a, BigKernel k, hipStream_t st) {
-    return a.dtype == DFK_FP16 ? launch_big_te<TT, FP16>(a, k, st) : launch_big_te<TT, BF16>(a, k, st);
+static hipError_t launch_big_t(const MlpArgs& a, BigKernel k, int row, hipStream_t st) {
+    return a.dtype == DFK_FP16 ? launch_big_te<TT, FP16>(a, k, row, st) : launch_big_te<TT, BF16>(a, k, row, st);
 }
 static hipError_t launch_big(const MlpArgs& args, BigKernel k, hipStream_t st) {
     MlpArgs a = args;
@@ -874,10 +878,10 @@ static hipError_t launch_big(const MlpArgs& args, BigKernel k, hipStream_t st) {
     (k == BigKernel::GateUp ? a.splits : a.k2_splits) = l.splits;
     a.group_tokens = l.tokens;
     switch (big_token_tiles(a.group_tokens)) {
-        case 1: return launch_big_t<1>(a, k, st);
-        case 2: return launch_big_t<2>(a, k, st);
-        case 3: return launch_big_t<3>(a, k, st);
-        case 4: return launch_big_t<4>(a, k, st);
+        case 1: return launch_big_t<1>(a, k, l.row, st);
+        case 2: return launch_big_t<2>(a, k, l.row, st);
+        case 3: return launch_big_t<3>(a, k, l.row, st);
+        case 4: return launch_big_t<4>(a, k, l.row, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -13,7 +13,7 @@ int main() {
     int what, m, ff, splits, k2c, wdt, summed;
     while (scanf("%d %d %d %d %d %d %d", &what, &m, &ff, &splits, &k2c, &wdt, &summed) == 7) {
         const dfk::BigLaunch l = what == 0 ? dfk::big_gateup_launch(m, ff, splits) : dfk::big_down_launch(m, ff, splits, k2c, wdt, summed);
-        printf("%d %d %d\\n", l.splits, l.groups, l.tokens);
+        printf("%d %d %d %d\\n", l.splits, l.groups, l.tokens, l.row);
     }
 }
 """
@@ -52,13 +52,19 @@ GATEUP = [(64, 1024, 128, (128, 1, 64)), (65, 3072, 256, (128, 2, 64)), (65, 308
 DOWN = [(64, 1024, 16, 4, 0, 1, (16, 1, 64)), (65, 1024, 16, 4, 0, 1, (16, 2, 64)), (128, 1024, 12, 8, 0, 1, (12, 2, 64)), (193, 1024, 8, 8, 0, 1, (8, 4, 64)),
         (256, 1024, 8, 8, 0, 1, (8, 4, 64)), (256, 1024, 8, 9, 0, 1, (8, 2, 128)), (256, 5376, 8, 16, 0, 1, (8, 2, 128)), (256, 5376, 8, 17, 0, 1, (8, 1, 256)),
         (129, 4096, 4, 32, 0, 1, (4, 2, 128)), (129, 4104, 4, 32, 0, 1, (4, 1, 129)), (128, 4096, 4, 32, 0, 1, (4, 1, 128)), (128, 4096, 4, 32, 1, 1, (4, 2, 64)),
-        (128, 4096, 4, 33, 1, 1, (4, 1, 128)), (256, 1024, 8, 8, 0, 0, (8, 1, 256))]
+        (128, 4096, 4, 33, 1, 1, (4, 1, 128)), (256, 1024, 8, 8, 0, 0, (8, 1, 256)),
+        # bytes of W_down: 20 MB and a little more, 32 and 64 MB and a little more
+        (129, 20480, 8, 4, 0, 1, (8, 3, 64)), (129, 20488, 8, 4, 0, 1, (8, 2, 128)), (192, 8192, 8, 16, 0, 1, (8, 2, 128)), (192, 8200, 8, 16, 0, 1, (8, 1, 192)),
+        (193, 8200, 8, 16, 0, 1, (8, 2, 128)), (193, 16384, 8, 16, 0, 1, (8, 2, 128)), (193, 16392, 8, 16, 0, 1, (8, 1, 193)),
+        # more splits than fit: as many as 128, 80 and 64 workgroups a group make, then the next that cuts d_ff into whole 64-row steps
+        (128, 5504, 16, 9, 0, 1, (14, 2, 64)), (128, 9216, 16, 13, 0, 1, (9, 2, 64)), (160, 12288, 24, 7, 0, 1, (16, 2, 128)), (160, 4864, 15, 7, 0, 1, (11, 3, 64)),
+        (160, 3840, 12, 8, 0, 1, (10, 3, 64)), (250, 3840, 12, 8, 0, 1, (6, 4, 64)), (250, 3840, 12, 8, 1, 1, (8, 4, 64)), (100, 2560, 14, 5, 0, 1, (14, 2, 64))]
 
 
 def test_lines_of_the_rules(ask):
     rows = [gateup(*c[:3]) for c in GATEUP] + [down(*c[:6]) for c in DOWN]
     for c, got in zip(GATEUP + DOWN, ask(rows)):
-        assert got == c[-1], (c, got)
+        assert got[:3] == c[-1], (c, got)
 
 
 def test_every_launch_covers_the_tokens_and_stays_within_its_limits(ask):
@@ -69,12 +75,14 @@ def test_every_launch_covers_the_tokens_and_stays_within_its_limits(ask):
         splits = min(ff // 8, rng.choice([1, 64, 128, 200, 256, 512, -(-ff // 64), 1024]))
         k2c = rng.randint(1, 256)
         rows += [gateup(m, ff, splits), down(m, ff, min(ff // 8, rng.randint(1, 512)), k2c, rng.randint(0, 1), rng.randint(0, 1))]
-    for r, (splits, groups, tokens) in zip(rows, ask(rows)):
+    for r, (splits, groups, tokens, row) in zip(rows, ask(rows)):
         assert 1 <= splits <= r[3] and groups * tokens >= r[1] > (groups - 1) * tokens, (r, splits, groups, tokens)
         assert groups == 1 and tokens == r[1] or tokens % 64 == 0, (r, tokens)
+        work = splits * r[4]
+        assert row == work if groups == 1 or r[0] == 0 else row == -(-work // 8) * 8, (r, splits, groups, row)
         if r[0] == 0:
             tiles = -(-(r[2] // 8) // splits)
             if -(-(r[2] // 8) // r[3]) <= 8:       # what a valid configuration has
                 assert tiles <= (8 if groups > 1 or splits == r[3] else (0, 0, 16, 14, 10)[-(-tokens // 64)]), (r, splits, groups)
-        elif groups > 1:
-            assert splits * groups * r[4] <= 256, (r, splits, groups)
+        elif groups > 1 and splits > 1:
+            assert splits == r[3] or row // 8 * groups <= 32, (r, splits, groups)      # workgroups of an XCD with 32 CUs
