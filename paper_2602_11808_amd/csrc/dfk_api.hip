@@ -8,6 +8,7 @@
 #include <tuple>
 #include <vector>
 
+#include "dfk_big_plan.h"
 #include "dfk_internal.h"
 
 namespace dfk {
@@ -1095,6 +1096,17 @@ dfk_status_t dfk_time_kernels(const dfk_config_t* cfg, int M, int d_model, int d
     return time_kernels(*cfg, M, d_model, d_ff, dtype, scratch, sets, iters, (hipStream_t)stream, usec_out);
 }
 
+// Whether two candidates of the 256-token pair make the same launches of M tokens: its rules (dfk_big_plan.h) can make one count of
+// slices or splits of several configured ones, and its kernels take neither waves nor depth.  Tuning times such a launch once, under the
+// first of its names in the list, which is the untuned one where that is among them.
+static bool same_big_launches(const dfk_config_t& a, const dfk_config_t& b, int M, int d_ff) {
+    auto of_pair = [&](const dfk_config_t& c) { return c.kmajor == 2 || (wdt_split(c) && M > mfma_km_tokens_per_launch()); };
+    if (!of_pair(a) || !of_pair(b) || a.kmajor != b.kmajor || a.reduce != b.reduce || a.k2_col_blocks != b.k2_col_blocks) return false;
+    auto up = [&](const dfk_config_t& c) { return big_gateup_launch(M, d_ff, c.splits); };
+    auto down = [&](const dfk_config_t& c) { return big_down_launch(M, d_ff, c.k2_splits, c.k2_col_blocks, wdt_split(c), c.reduce == DFK_REDUCE_TICKET); };
+    return up(a).splits == up(b).splits && up(a).groups == up(b).groups && down(a).splits == down(b).splits;
+}
+
 dfk_status_t dfk_tune(const int* M_list, int nM, int d_model, int d_ff, dfk_dtype_t dtype,
                       void* scratch, size_t scratch_bytes, int sets, int iters, void* stream) {
     if (!M_list || nM < 1 || !scratch || sets < 1 || iters < 1) return DFK_ERR_INVALID_ARG;
@@ -1125,6 +1137,7 @@ dfk_status_t dfk_tune(const int* M_list, int nM, int d_model, int d_ff, dfk_dtyp
         bool fill = true;  // scratch layout depends on M: refill once per M (until a candidate has run)
         for (size_t k = 0; k < cands.size(); ++k) {
             const dfk_config_t& c = cands[k];
+            if (std::any_of(cands.begin(), cands.begin() + k, [&](const dfk_config_t& o) { return same_big_launches(o, c, M, d_ff); })) continue;
             double us = 0.0;
             dfk_status_t s = time_config(c, M, d_model, d_ff, dtype, scratch, sets, iters,
                                          (hipStream_t)stream, fill, &us);
@@ -1144,7 +1157,9 @@ dfk_status_t dfk_tune(const int* M_list, int nM, int d_model, int d_ff, dfk_dtyp
         Entry best_t;
         best_t.usec = -1.0;
         const auto cands_t = candidates_wdt(M, d_model, d_ff, dtype);
-        for (const auto& c : cands_t) {
+        for (size_t k = 0; k < cands_t.size(); ++k) {
+            const dfk_config_t& c = cands_t[k];
+            if (std::any_of(cands_t.begin(), cands_t.begin() + k, [&](const dfk_config_t& o) { return same_big_launches(o, c, M, d_ff); })) continue;
             if (cands_t[0].a2_dtype == DFK_FP32 && c.a2_dtype != DFK_FP32) continue;   // being faster is no reason to round A_2
             double us = 0.0;
             dfk_status_t s = time_config(c, M, d_model, d_ff, dtype, scratch, sets, iters, (hipStream_t)stream, false, &us);

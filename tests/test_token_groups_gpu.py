@@ -67,3 +67,19 @@ def test_the_block_in_both_layouts(M, d, ff):
         fn(H, w, 1e-5, g["Wg"], g["Wu"], wd, H, None, ws)       # in place
         torch.cuda.synchronize()
         assert_parity(di.as_f64(di.to_numpy(H)), ref, "bf16", fn.__name__)
+
+
+@pytest.mark.parametrize("M", [193, 200, 230, 256])
+def test_tuning_names_a_launch_once(M):
+    """512 x 1536: 64 and 128 splits would be cut to the 12 that are listed too; the entry says what runs."""
+    d, ff, bf = 512, 1536, dfk.DFK_BF16
+    scratch = torch.empty(dfk.dfk_tune_scratch_bytes(M, d, ff, bf, 2), dtype=torch.uint8, device=DEV)
+    n = dfk.dfk_num_candidates(M, d, ff, bf)
+    offered = {c.k2_splits for c in (dfk.dfk_get_candidate(M, d, ff, bf, i) for i in range(n)) if c.kmajor == 2 and c.reduce == dfk.DFK_REDUCE_TICKET}
+    assert {12, 64, 128} <= offered
+    try:
+        dfk.dfk_tune([M], d, ff, bf, scratch, sets=2, iters=5)
+        c, tuned = dfk.dfk_get_choice(M, d, ff, bf)
+        assert tuned and (c.kmajor != 2 or c.reduce != dfk.DFK_REDUCE_TICKET or c.k2_splits not in (64, 128)), c
+    finally:
+        dfk.dfk_clear_tuning()
