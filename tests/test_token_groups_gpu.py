@@ -1,5 +1,5 @@
 """256-token pair with the tokens divided among groups of workgroups: both sides of every line of the rules, last groups of few tokens and of all but
-one, ragged d_ff, both layouts of W_down, with and without the normalisation."""
+one, ragged d_ff, both layouts of W_down, with and without the normalisation.  The rules themselves are checked on the host (test_big_plan_host.py)."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -15,7 +15,10 @@ DEV = "cuda:0"
 # tokens: two groups of 64 (the second of 1, 63 or 64), of 128 (65, 127, 128), four of 64; one group beyond the lines.  d_ff: three, four and
 # eight row tiles of 128 slices and one more than each; fewer rows than slices; whole steps of the down kernel or not
 CASES = [(65, 256, 3072), (127, 512, 3080), (128, 384, 1536), (129, 1024, 4096), (130, 512, 4104), (192, 640, 2048), (193, 2048, 1000), (200, 512, 8192),
-         (256, 512, 8200), (255, 1152, 520), (129, 2176, 4096), (256, 2304, 4104), (70, 4096, 512), (256, 4224, 768), (68, 128, 64)]
+         (256, 512, 8200), (255, 1152, 520), (129, 2176, 4096), (256, 2304, 4104), (70, 4096, 512), (256, 4224, 768), (68, 128, 64),
+         # d_ff beyond the gate/up kernel's groups: two and four groups of the down kernel alone, up to 20, 32 and 64 MB of W_down and beyond; rows of the
+         # grid that are filled up to a multiple of 8; splits cut to what fits, with whole 64-row steps and without
+         (100, 256, 20480), (200, 384, 16392), (160, 896, 12288), (65, 640, 14336), (250, 1152, 9224), (130, 128, 28672), (256, 512, 28672)]
 
 
 def _run(t, M, d, ff, dtype, cfg):

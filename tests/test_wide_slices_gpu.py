@@ -1,5 +1,6 @@
 """256-token pair, gate/up kernel with slices of 9 to 16 row tiles: every token-tile count it is built for, shortest and longest slices and two rounds
-of them, d_ff that leaves slices of two lengths, few and many steps of the k range, both layouts of W_down, with and without the normalisation."""
+of them, d_ff that leaves slices of two lengths, few and many steps of the k range, both layouts of W_down, with and without the normalisation.
+Which d_ff and tokens get it is checked on the host (test_big_plan_host.py)."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -33,6 +34,34 @@ def test_against_the_oracle(M, d, ff):
     torch.cuda.synchronize()
     assert bool((buf[M] == 7.0).all())
     assert_parity(di.as_f64(di.to_numpy(buf[:M])), ref, dtype, (M, d, ff))
+
+
+# more than 64 steps, which wrap every ring many times: starts of the k walk over the whole range (X up to 3 MB), and in the window of 64 steps
+# (X beyond), with steps that are no multiple of it
+@pytest.mark.parametrize("M,d,ff", [(66, 8192, 16392), (150, 8192, 16512), (255, 4224, 16448), (256, 8320, 16392)])
+def test_many_steps(M, d, ff):
+    """Every sixteenth token against plain torch in 64 bits (the oracle takes minutes at these sizes), all of them against repeats."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(104)
+    t = [(torch.randn(s, generator=g, device=DEV) * w).to(torch.bfloat16) for s, w in (((M, d), 1.0), ((ff, d), d ** -0.5), ((ff, d), d ** -0.5), ((ff, d), ff ** -0.5))]
+    assert dfk.dfk_get_choice(M, d, ff)[0].kmajor == 2
+    ws = dfk.new_workspace(M, d, ff, DEV)
+    first = None
+    for rep in range(3):
+        buf = torch.full((M + 1, d), 7.0, dtype=torch.bfloat16, device=DEV)
+        print("case", M, d, ff, rep, flush=True)
+        dfk.dfk_swiglu_mlp_ex(*t, buf[:M], None, ws)
+        torch.cuda.synchronize()
+        assert bool((buf[M] == 7.0).all())
+        first = buf.clone() if first is None else first
+        assert torch.equal(first.view(torch.int16), buf.view(torch.int16)), rep       # fixed order: the same bits every time
+    rows = sorted({0, 15, 16, 63, 64, M - 1} | set(range(3, M, 16)))
+    x = t[0][rows].double()
+    gate = torch.cat([x @ w.double().t() for w in t[1].split(2048)], 1)
+    up = torch.cat([x @ w.double().t() for w in t[2].split(2048)], 1)
+    a = gate / (1 + torch.exp(-gate)) * up
+    ref = sum(p @ w.double() for p, w in zip(a.split(2048, 1), t[3].split(2048)))
+    assert_parity(first[rows].double().cpu().numpy(), ref.cpu().numpy(), "bf16", (M, d, ff))
 
 
 @pytest.mark.parametrize("M,ff", [(100, 30720), (150, 24576), (200, 18432)])
