@@ -909,14 +909,16 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
 // Block, pair of launches, us in a replayed graph, last workgroup / launch, at 1, 16 and 64 tokens: 512 x 1536 10.2 / 10.1, 12.1 / 11.2,
 // 22.6 / 17.5; 896 x 4864 15.9 / 15.3, 18.4 / 16.1, 31.6 / 26.1; 1024 x 5632 16.0 / 14.8, 18.3 / 16.6, 29.4 / 25.1; 2048 x 5504 22.6 / 20.0,
 // 24.1 / 21.3, 37.2 / 33.2.
-// The single launch of both kernels' workgroups has no other boundary to pay for: from four tokens on.  2304 x 9216 at 1, 2, 4, 16 and
-// 64 30.9 / 30.9, 30.8 / 31.0, 31.2 / 31.1, 33.8 / 32.4, 49.8 / 46.3; 2888 x 7688 35.9 / 36.6, 35.9 / 36.3, 36.4 / 36.5, 38.8 / 37.3, 54.2 /
-// 50.6; 5120 x 27648 136.3 / 136.7, 137.2 / 136.8, 138.0 / 137.1, 142.7 / 140.3, 175.9 / 172.1.
+// The single launch of both kernels' workgroups has no other boundary to pay for, so there the last workgroup stays where it can divide the
+// blocks among several threads per output (km_sum_ways: up to 8 tokens of one column block, 4 of two).  Whole call, last workgroup / launch,
+// at 4, 8, 12 and 16 tokens: 1792 x 4864 18.5 / 18.9, 19.0 / 19.0, 19.9 / 19.2, 20.6 / 19.4; 2304 x 9216 29.5 / 30.1, 30.4 / 30.4, 31.4 / 30.8, 31.9
+// / 31.0; 3200 x 5248 26.9 / 27.5, 27.5 / 27.6, 28.5 / 28.0, 29.1 / 28.2; 4096 x 14336 60.9 / 61.6, 61.8 / 62.1, 63.2 / 62.4, 63.6 / 62.9; two column
+// blocks, at 4, 5 and 8: 5120 x 27648 134.0 / 133.7, 135.3 / 134.3, 136.6 / 135.1; 8192 x 28672 212.2 / 212.3, 213.7 / 212.4, 215.3 / 213.8.
 // A third launch also costs 2.5 to 4 us of host time, which a replayed graph does not pay: with up to 16 tokens and 12 MB of weights the
 // two kernels are done before the host has issued three (eager, 512 x 1536 at one token 9.5 / 12.1), so there it is taken under capture.
 bool km_sum_launch(const MlpArgs& a, bool single, hipStream_t st) {
     if (a.reduce_mode != DFK_REDUCE_TICKET) return false;
-    if (single) return a.m_count >= 4;
+    if (single) return 2 * a.m_count * ((a.d_model + 127) / 128 / a.k2_col_blocks) * 32 > 8 * 64;
     if (a.m_count > 16 || (size_t)6 * a.d_model * a.d_ff >= 12000000u) return true;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
