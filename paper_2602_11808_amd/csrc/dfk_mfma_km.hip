@@ -914,12 +914,17 @@ size_t km_lds_down_t(const dfk_config_t& c, int TT, int d_model, KmGeom* geo) {
 // at 4, 8, 12 and 16 tokens: 1792 x 4864 18.5 / 18.9, 19.0 / 19.0, 19.9 / 19.2, 20.6 / 19.4; 2304 x 9216 29.5 / 30.1, 30.4 / 30.4, 31.4 / 30.8, 31.9
 // / 31.0; 3200 x 5248 26.9 / 27.5, 27.5 / 27.6, 28.5 / 28.0, 29.1 / 28.2; 4096 x 14336 60.9 / 61.6, 61.8 / 62.1, 63.2 / 62.4, 63.6 / 62.9; two column
 // blocks, at 4, 5 and 8: 5120 x 27648 134.0 / 133.7, 135.3 / 134.3, 136.6 / 135.1; 8192 x 28672 212.2 / 212.3, 213.7 / 212.4, 215.3 / 213.8.
-// A third launch also costs 2.5 to 4 us of host time, which a replayed graph does not pay: with up to 16 tokens and 12 MB of weights the
-// two kernels are done before the host has issued three (eager, 512 x 1536 at one token 9.5 / 12.1), so there it is taken under capture.
+// A third launch also costs 2.5 to 4 us of host time, which a replayed graph does not pay: with up to 16 tokens and 12 MB of weights, and with
+// one to three tokens up to 19, 17 and 13.5 MB, the two kernels are done before the host has issued three, so there it is taken under
+// capture.  Eager calls from Python, us, last workgroup / launch, at 1, 2 and 3 tokens: 512 x 1536 (5 MB) 9.5 / 12.1 at one; 512 x 4096 (12.6 MB)
+// 11.2 / 12.4, 11.5 / 12.9, 12.1 / 13.0; 768 x 2816 (13.0) 12.2 / 12.9, 12.5 / 12.9, 12.7 / 13.0; 768 x 3584 (16.5) 12.6 / 13.0, 12.8 / 13.0, 13.5 /
+// 13.2; 896 x 3328 (17.9) 13.0 / 13.2, 13.3 / 13.1, 13.9 / 13.0; 640 x 5120 (19.7) 14.0 / 13.8, 14.3 / 13.9, 15.0 / 13.9; 640 x 3840 (14.7) at 4 13.4 /
+// 13.1, 768 x 3072 (14.2) at 8 13.5 / 12.9.  (A_2 in fp32: 736 x 3472 in half, 15.3 MB, at one token 15.6 / 15.3.)
 bool km_sum_launch(const MlpArgs& a, bool single, hipStream_t st) {
     if (a.reduce_mode != DFK_REDUCE_TICKET) return false;
     if (single) return 2 * a.m_count * ((a.d_model + 127) / 128 / a.k2_col_blocks) * 32 > 8 * 64;
-    if (a.m_count > 16 || (size_t)6 * a.d_model * a.d_ff >= 12000000u) return true;
+    const size_t eager = a.a2_is_fp32 || a.m_count > 3 ? 12000000u : a.m_count == 1 ? 19000000u : a.m_count == 2 ? 17000000u : 13500000u;
+    if (a.m_count > 16 || (size_t)6 * a.d_model * a.d_ff >= eager) return true;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
     return status == hipStreamCaptureStatusActive;
