@@ -325,13 +325,13 @@ def timeline(args, torch, di, dfk, dev):
         ("same, counter reduction",
          dict(variant=1, kmajor=4, splits=256, waves=8, depth=4, reduce=0, k2_splits=16, k2_col_blocks=16),
          ((0, "gate/up start"), (1, "A_2 stored"), (3, "down start"), (7, "down: wait over"), (4, "down streamed (wave 0)"),
-          (5, "partial sums published"), (6, "reduced / exit"))),
+          (5, "partial sums published, or stored for the sum launch"), (6, "reduced / exit"))),
         ("two kernels (k_gateup_km, k_down_km), atomic",
          dict(variant=2, kmajor=1, splits=256, waves=8, depth=4, reduce=1, k2_splits=8, k2_col_blocks=32),
          ((0, "gate/up start"), (2, "gate/up streamed (wave 0)"), (1, "A_2 stored"), (3, "down start"), (4, "down streamed (wave 0)"))),
         ("same, counter reduction",
          dict(variant=2, kmajor=1, splits=256, waves=8, depth=4, reduce=0, k2_splits=8, k2_col_blocks=32),
-         ((0, "gate/up start"), (1, "A_2 stored"), (3, "down start"), (4, "down streamed (wave 0)"), (5, "partial sums published"),
+         ((0, "gate/up start"), (1, "A_2 stored"), (3, "down start"), (4, "down streamed (wave 0)"), (5, "partial sums published, or stored for the sum launch"),
           (6, "reduced / exit"))),
     ]
     out = []

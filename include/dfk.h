@@ -72,9 +72,11 @@ typedef enum { DFK_VARIANT_AUTO = 0, DFK_VARIANT_FUSED = 1, DFK_VARIANT_TWO_KERN
 typedef enum { DFK_PATH_VALU = 0, DFK_PATH_MFMA = 1 } dfk_path_t;
 
 /* How the split-d_ff partial sums of the down projection are combined.
- * DFK_REDUCE_TICKET: partial blocks in the workspace, summed in a fixed order by
- * the last workgroup to arrive at each of two levels of arrival counters;
- * run-to-run bitwise deterministic.
+ * DFK_REDUCE_TICKET: partial blocks in the workspace, summed in a fixed order: by
+ * the last workgroup to arrive at each of two levels of arrival counters (fused kernels,
+ * the VALU path, the first pair), or, in the pairs for up to 64 and 256 tokens and in the
+ * single launch of both kernels' workgroups, by a further small launch or, in small calls,
+ * the last workgroup of a column block; run-to-run bitwise deterministic, whoever adds.
  * DFK_REDUCE_ATOMIC: device-wide fp32 atomic adds into an accumulator in the
  * workspace, drained per 128-column block by the last wavefront to arrive;
  * shorter tail, summation order (hence the last bits) varies from run to run.
@@ -93,9 +95,9 @@ typedef enum { DFK_REDUCE_TICKET = 0, DFK_REDUCE_ATOMIC = 1 } dfk_reduce_t;
  *                  shape constraints, see dfk_config_valid)
  *   splits         number of d_ff slices = workgroups of the fused kernel, or of
  *                  the first kernel of the two-kernel variant
- *                  (kmajor = 2, up to 256 of them: half as many where the gate/up kernel divides the tokens
- *                  among two groups of workgroups, on layers of few d_ff rows; more than 256: fewer rounds of 256 where
- *                  slices of up to 16 tiles of 8 rows make that possible)
+ *                  (kmajor = 2, and 5 beyond 64 tokens, up to 256 of them: at most 128 where the gate/up kernel
+ *                  divides the tokens among two groups of workgroups, on layers of few d_ff rows; more than 256:
+ *                  fewer rounds of 256 where slices of up to 16 tiles of 8 rows make that possible)
  *   waves          wavefronts (64 lanes) per workgroup (kmajor = 1 pair with 4: the down kernel runs 8
  *                  beyond 16 tokens)
  *   depth          software pipeline depth of the weight stream (tiles or loads in flight)
@@ -382,9 +384,9 @@ dfk_status_t dfk_time_config(const dfk_config_t* cfg, int M, int d_model, int d_
  * of the first kernel back to back between two HIP events on `stream`, then the same
  * for the second.  usec_out[0] = the fused kernel, or the gate/up kernel of the
  * two-kernel variant; usec_out[1] = its down-projection kernel (0 for the fused
- * variant; with kmajor = 2 and DFK_REDUCE_TICKET it includes the small launch that adds the
- * partial sums).  M must fit one launch of the configuration (16, 32, 64 or 256 tokens on the
- * MFMA path, 8 on the VALU path), else DFK_ERR_UNSUPPORTED_SHAPE; iters <= 1024. */
+ * variant; where a small launch adds the partial sums it includes that one).  M must fit one
+ * launch of the configuration (16, 32, 64 or 256 tokens on the MFMA path, 8 on the VALU path, 64
+ * there with kmajor = 1), else DFK_ERR_UNSUPPORTED_SHAPE; iters <= 1024. */
 dfk_status_t dfk_time_kernels(const dfk_config_t* cfg, int M, int d_model, int d_ff,
                               dfk_dtype_t dtype, void* scratch, size_t scratch_bytes,
                               int sets, int iters, void* stream, double* usec_out);

@@ -111,13 +111,17 @@ bool roles_launch(const dfk_config_t& c) { return c.variant == DFK_VARIANT_FUSED
 // with 24, 19.8 with 64, at 64 tokens 39.7, 41.6, 55.5; atomic, at 16 tokens, 1024 x 28672 42.2 with 16, 40.0 with 32, 1536 x
 // 28672 53.9 with 16, 54.4 with 18, 53.1 with 21.
 // The counter reduction of more than two tokens takes 12 where that gives the busiest wavefront no more 32-row blocks than 16 do:
-// the last workgroup of a column block reads all its splits' blocks alone.  16 / 12 splits, us: 512 x 1536 at 8 tokens 11.6 /
+// every split is a block to be added.  The line was drawn with the last workgroup of a column block adding them alone, as it still does
+// in small eager calls (km_sum_launch); 16 / 12 splits, us: 512 x 1536 at 8 tokens 11.6 /
 // 11.1, 768 x 4224 at 8 15.9 / 15.4, 896 x 4864 at 33 23.4 / 22.8, 1024 x 5632 at 16 18.5 / 17.8, 2048 x 6144 at 64 38.5 / 36.1.
 // Where it gives more, the stream is longer by whole blocks: 512 x 4096 at 8 (two blocks of four wavefronts, three) 13.3 / 13.9,
 // 896 x 7168 at 33 25.1 / 26.2, 1024 x 8192 at 3 and 64 18.2 / 19.2, 31.3 / 32.2, 896 x 4864 at 8 16.8 / 17.1.  From a width of
 // 1536 on 16 splits are 192 workgroups and more, and up to four blocks 12 are the better in any case: 1536 x 12288 at 8 and 64
 // 29.6 / 29.4, 46.3 / 44.5, 2048 x 11264 34.4 / 33.6, 50.9 / 49.6; beyond, 1536 x 18176 at 8 40.5 / 41.3, 2048 x 24320 60.2 /
-// 61.5, 2048 x 16384 42.9 / 42.6, at 33 54.0 / 54.8.  At two tokens equal: 896 x 4864 15.4 / 15.8.
+// 61.5, 2048 x 16384 42.9 / 42.6, at 33 54.0 / 54.8.  At two tokens equal: 896 x 4864 15.4 / 15.8.  Where a launch adds the blocks on all
+// CUs (blocks replayed from a graph) 16 gain on 12 at few tokens: 2048 x 6144 at 64 35.5 / 33.9, 896 x 4864 at 33 22.1 / 21.9, 768 x 4224
+// at 8 15.2 / 15.1; 1024 x 5632 at 16 16.1 / 16.6, 1536 x 12288 at 8 and 64 29.1 / 29.9, 44.2 / 44.5, 2048 x 11264 32.4 / 33.1, 47.8 / 48.5.  The
+// line has not been moved for that.
 constexpr int kFewSplits = 16;
 int few_splits(int M, int d_model, int d_ff, int k2c, int reduce) {
     const int rows = reduce == DFK_REDUCE_ATOMIC ? d_model - d_model / 4 : M > 16 ? 2 * d_model : d_model;
@@ -495,6 +499,12 @@ bool enumerate_default(int M, int d_model, int d_ff, dfk_dtype_t dtype, int want
 // 54.5 / 53.5; 1800 x 5000 at 16 and 33 25.0 / 23.9, 30.9 / 29.7; 2008 x 2400 (29 MB) at 17 and 33 22.1 / 20.6, 26.6 / 24.5; 904 x
 // 1024 (6 MB) at 33 18.2 / 17.5; 1416 x 3776 at 17 22.2 / 22.6, at 64 31.1 / 31.0.  Not where d_ff is no larger than d_model: 8200 x
 // 1000 at 1 and 17 22.8 / 24.7, 30.9 / 31.9 (2888 x 2888 at 12 24.5 / 23.4).
+//
+// These figures are from before a launch added the splits' blocks (km_sum_launch), which gave the pair more than the single launch.  Blocks
+// in a graph with it: 2304 x 9216 at 1, 8 and 33 30.8 / 30.7, 31.1 / 31.7, 40.5 / 40.0; 4096 x 14336 at 1 and 64 63.3 / 62.8, 80.6 / 79.6; 1792 x
+// 4864 at 8 and 33 19.1 / 20.3, 26.0 / 25.9; 1536 x 8960 at 17 28.2 / 28.2; 3584 x 5376 at 2, 17 and 64 28.5 / 28.6, 32.6 / 32.7, 46.2 / 44.6; 5120 x
+// 27648 at 4 and 64 136.8 / 140.7, 179.7 / 171.6; on the other side 1024 x 4096 at 17 15.9 / 17.8, 2048 x 5504 at 8 21.0 / 23.0.  The lines are
+// where they were: up to 16 tokens of 48 to 100 MB the pair would now be the faster by up to 6 %.
 bool single_launch_pays(int M, int d_model, int d_ff) {
     const size_t bytes = (size_t)6 * d_model * d_ff;
     if (M > 64) return false;
