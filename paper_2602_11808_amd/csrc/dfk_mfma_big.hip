@@ -208,6 +208,7 @@ __device__ __forceinline__ void gateup_big_body(const MlpArgs& a, unsigned char*
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    if (DOWN_T && js >= a.k2_splits) return;       // as in the down kernel below
     DFK_STAMP_BIG(DOWN_T ? 3 : 0);
     constexpr int x_piece = 4 * TT * kBigTile, w_piece = NTC * kBigTile, x_step = KS * x_piece, w_step = KS * w_piece;
     constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
@@ -457,6 +458,10 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) acc2[c][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // A workgroup that only fills up a row of the grid (big_down_launch; the order is plain there, so its split would be past the last).
+    // Asked here and not on entry, where every workgroup waited for two arguments before it requested the others.  Whole call, us, on entry /
+    // here: 896 x 1280 at 234 tokens 18.5 / 18.3; W_down as [d_model, d_ff], 512 x 1152 at 228 18.0 / 17.9, 896 x 1664 at 96 16.45 / 16.26.
+    if (js >= a.k2_splits) return;
     DFK_STAMP_BIG(3);
     constexpr int x_step = 4 * TT * kBigTile, w_step = 4 * kTileBytes;
     constexpr int nbx = kBigXBufs, nbw = big_w_bufs(x_step, w_step), w_off = nbx * x_step;
@@ -625,7 +630,6 @@ __device__ __forceinline__ void down_big_body(const MlpArgs& a, const bool by_xc
 template <int TT, typename E>
 __global__ __launch_bounds__(kBigWaves * 64) void k_down_big(MlpArgs a, int by_xcd) {   // by_xcd: place the workgroups of a d_ff split on one XCD (see down_tile_of)
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    if ((int)blockIdx.x >= a.k2_splits * a.k2_col_blocks) return;   // (a row of the grid with token groups is a multiple of 8: big_down_launch)
     down_big_body<TT, E>(a, by_xcd != 0, lds);
 }
 
@@ -637,7 +641,6 @@ __global__ __launch_bounds__(kBigWaves * 64) void k_down_big(MlpArgs a, int by_x
 template <int TT, typename E>
 __global__ __launch_bounds__(kBigWaves * 64) void k_down_t_big(MlpArgs a, int by_xcd) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    if ((int)blockIdx.x >= a.k2_splits * a.k2_col_blocks) return;
     gateup_big_body<TT, E, 8, true>(a, lds, by_xcd != 0);
 }
 
