@@ -420,7 +420,8 @@ dfk_status_t dfk_set_choice(int M, int d_model, int d_ff, dfk_dtype_t dtype,
 void dfk_clear_tuning(void);
 
 /* Persist / reload the table (plain text, one entry per line; where a problem has entries of both
- * variants the chosen one is written last, and a loader takes a problem's last line as its choice). */
+ * variants the chosen one is written last, and a loader takes a problem's last line as its choice;
+ * a line of a version 2 table is read as the configuration it named then). */
 dfk_status_t dfk_save_tuning(const char* path);
 dfk_status_t dfk_load_tuning(const char* path);
 

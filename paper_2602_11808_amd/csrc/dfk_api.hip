@@ -1226,7 +1226,7 @@ dfk_status_t dfk_save_tuning(const char* path) {
     std::lock_guard<std::mutex> lk(g_mu);
     FILE* f = std::fopen(path, "w");
     if (!f) return DFK_ERR_IO;
-    std::fprintf(f, "# dfk tuning table v2: M d_model d_ff dtype variant path splits waves depth reduce "
+    std::fprintf(f, "# dfk tuning table v3: M d_model d_ff dtype variant path splits waves depth reduce "
                     "k2_splits k2_col_blocks a2_dtype k2_rows_by_wave kmajor usec\n");
     // One line per entry; a problem's chosen configuration comes after its other variant's line, and the loader
     // takes the last line of a problem as the choice.
@@ -1251,6 +1251,13 @@ dfk_status_t dfk_save_tuning(const char* path) {
     return ok ? DFK_OK : DFK_ERR_IO;
 }
 
+// A line of a version 2 table: there path VALU with a column block per 128 columns was the name of what is path VALU with kmajor = 1 since.
+static void rename_v2(dfk_config_t* c, int M, int d_model, int d_ff, dfk_dtype_t dtype) {
+    dfk_config_t n = *c;
+    n.kmajor = 1; n.depth = c->waves == 8 ? 3 : 6;
+    if (c->kmajor == 0 && half_off_128(n, M, d_model, d_ff, dtype, nullptr) && c->k2_col_blocks == (d_model + 127) / 128) *c = n;
+}
+
 dfk_status_t dfk_load_tuning(const char* path) {
     if (!path) return DFK_ERR_INVALID_ARG;
     FILE* f = std::fopen(path, "r");
@@ -1258,9 +1265,11 @@ dfk_status_t dfk_load_tuning(const char* path) {
     std::vector<std::pair<Key, Entry>> fresh;   // in file order
     char line[512];
     dfk_status_t rc = DFK_OK;
+    int version = 0;
     while (std::fgets(line, sizeof line, f)) {
         const char* p = line;
         while (*p == ' ' || *p == '\t') ++p;
+        (void)std::sscanf(p, "# dfk tuning table v%d", &version);
         if (*p == '#' || *p == '\n' || *p == '\r' || *p == 0) continue;
         int M, dm, df, dt;
         Entry e;
@@ -1270,7 +1279,12 @@ dfk_status_t dfk_load_tuning(const char* path) {
                                   &e.cfg.reduce, &e.cfg.k2_splits, &e.cfg.k2_col_blocks, &e.cfg.a2_dtype,
                                   &e.cfg.k2_rows_by_wave, &e.cfg.kmajor, &e.usec);
         if (n != 16 || M < 1 || M > DFK_MAX_M || (dt != DFK_BF16 && dt != DFK_FP32 && dt != DFK_FP16) || dm < 8 ||
-            df < 8 || dm % 8 || df % 8 || !config_valid(e.cfg, M, dm, df, (dfk_dtype_t)dt)) {
+            df < 8 || dm % 8 || df % 8) {
+            rc = DFK_ERR_IO;
+            break;
+        }
+        if (version == 2) rename_v2(&e.cfg, M, dm, df, (dfk_dtype_t)dt);
+        if (!config_valid(e.cfg, M, dm, df, (dfk_dtype_t)dt)) {
             rc = DFK_ERR_IO;
             break;
         }

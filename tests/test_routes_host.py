@@ -329,3 +329,34 @@ def test_half_off_128_on_the_matrix_cores_is_a_configuration_of_its_own():
     for M, d, ff in ((1, 2888, 7688), (2, 8200, 4000), (1, 264, 1000)):
         c, _ = dfk.dfk_get_choice(M, d, ff, h)
         assert (c.path, c.kmajor) == (VALU, 0), c
+
+
+def test_tables_of_before_that_name_load_as_what_they_named(tmp_path):
+    """Version 2 tables say path VALU with a column block per 128 columns for it; the first two shapes have such lines that plain FMA does not take."""
+    h = dfk.DFK_FP16
+    path = str(tmp_path / "table.txt")
+    # M, d_model, d_ff, splits, waves, k2_splits, whether plain FMA takes the configuration too
+    for M, d, ff, splits, waves, k2, plain in ((100, 10208, 8376, 256, 8, 3, False), (4, 7632, 25432, 512, 8, 4, False), (16, 736, 3472, 256, 4, 16, True)):
+        nblk = (d + 127) // 128
+        line = f"{M} {d} {ff} {h} {TWO} {VALU} {splits} {waves} 0 0 {k2} {nblk} {dfk.DFK_FP32} 0 0 25.0\n"
+        try:
+            open(path, "w").write("# dfk tuning table v2: M d_model d_ff ...\n" + line)
+            dfk.dfk_load_tuning(path)
+            c, tuned = dfk.dfk_get_choice(M, d, ff, h)
+            assert tuned and (c.path, c.kmajor, c.depth, c.k2_splits, c.k2_col_blocks) == (VALU, 1, 3 if waves == 8 else 6, k2, nblk), c
+            dfk.dfk_save_tuning(path)
+            dfk.dfk_clear_tuning()
+            dfk.dfk_load_tuning(path)                                   # as written now: nothing to rename
+            assert dfk.dfk_get_choice(M, d, ff, h)[0].as_dict() == c.as_dict()
+            dfk.dfk_clear_tuning()
+            for head in ("# dfk tuning table v3: M d_model d_ff ...\n", ""):
+                open(path, "w").write(head + line)
+                if not plain:
+                    with pytest.raises(dfk.DfkError):
+                        dfk.dfk_load_tuning(path)
+                    continue
+                dfk.dfk_load_tuning(path)
+                assert dfk.dfk_get_choice(M, d, ff, h)[0].kmajor == 0
+                dfk.dfk_clear_tuning()
+        finally:
+            dfk.dfk_clear_tuning()
