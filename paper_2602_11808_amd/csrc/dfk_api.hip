@@ -163,7 +163,8 @@ bool two_blocks(int M, int d_model, int d_ff, int reduce) {
 // x 28672 at 256 83.9 with 12, 59.4 with 32, 60.0 with 64; 256 x 8192 at 1 18.8 with 8, 17.4 with 12; 1024 x 14336 at 256 57.4
 // with 12, 50.3 with 16, 52.3 with 32; no whole steps: 1920 x 10496 at 96 46.5 with 12 or 17, 45.5 with 16; few column blocks:
 // 1152 x 5504 at 200 38.8 with 12, 37.6 with 16, 38.3 with 28, and at 128 30.7 with 12, 30.8 with 16; 2048 x 5504 at 200 46.9
-// with 12, 47.7 with 16.
+// with 12, 47.7 with 16.  (All without token groups; where the launch divides the tokens it takes fewer of these splits,
+// big_down_launch: 512 x 28672 at 256 has 32 and two groups, 55.4.)
 int big_splits(int M, int d_ff, int k2c) {
     const int most = 256 / k2c, narrow = M > 128 && k2c < 10 ? std::min(16, d_ff / 320) : 0;
     const int want = std::min(most, std::max({12, d_ff / (k2c < 8 ? 512 : 640), narrow}));
@@ -347,6 +348,9 @@ std::vector<dfk_config_t> candidates(int M, int d_model, int d_ff, dfk_dtype_t d
 // 1.05 and 0.97, 2048 x 8192 1.00 to 1.02 and 0.94.  Beyond 4096 the whole rows are uneven shares as a rule: 6144 x 8064 1.01 to 1.03
 // up to 32 tokens, 0.97 to 0.98 at 48, 8192 x 7168 1.02 to 1.04 at 48, 0.98 at 64 (12288 x 12288 166 / 179 us at 64: tokens below twice
 // the rows).  Below 1024, where four wavefronts own the whole rows: 512 x 2048 1.04 to 1.06 up to 32 tokens, 0.93 at 48, 768 x 3072 0.94.
+// With the sum launch's present form (16 splits a batch) the lines hold, best candidate of either: at 24 tokens 1536 x 8960 0.91,
+// 2304 x 9216 0.99, 4096 x 14336 0.99, other side 1024 x 5632 0.98, 2048 x 5504 1.05, 3584 x 9216 1.03; at 40 2048 x 5504 0.98, 1792 x 4864
+// 1.00, 4096 x 8192 1.03; 8192 x 7168 at 48 1.03; 512 x 2048 at 24 and 48 1.01, 0.91.
 bool wdt_split_pays(int M, int d_model, int d_ff) {
     if (M > 64) return true;
     const long long tokens = (M + 15) / 16 * 16, rows = d_model / std::max(1, std::min(256, d_model / 16)), a2 = tokens * d_ff;
